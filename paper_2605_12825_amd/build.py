@@ -15,7 +15,7 @@ LIB = os.path.join(_HERE, "liborthrus.so")
 LIB_HOST_UBSAN = os.path.join(_HERE, "liborthrus_hostubsan.so")
 HOST_UBSAN_FLAGS = ["-Xarch_host", "-fsanitize=undefined", "-Xarch_host", "-fsanitize-trap=undefined",
                     "-Xarch_host", "-fno-omit-frame-pointer"]
-SOURCES = ["orthrus_api.hip", "orthrus_attn.hip", "orthrus_consensus.hip", "orthrus_sampling.hip",
+SOURCES = ["orthrus_api.hip", "orthrus_attn.hip", "orthrus_attn_wide.hip", "orthrus_consensus.hip", "orthrus_sampling.hip",
            "orthrus_prefill.hip"]
 
 HIPCC_FLAGS = [
@@ -24,6 +24,11 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wno-unused-value",
 ]
+
+# Per-source additions.  attn_wide: the matrix products of that kernel keep scores and accumulators in plain vector
+# registers (the default moves every product's result to the accumulation file and copies the scores back: 32 extra
+# instructions per tile).
+SOURCE_FLAGS = {"orthrus_attn_wide.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def hipcc_path() -> str:
@@ -37,6 +42,7 @@ def source_digest() -> str:
     """Digest of everything the library is compiled from: sources, headers and compiler flags."""
     h = hashlib.sha256()
     h.update(" ".join(HIPCC_FLAGS).encode())
+    h.update(repr(sorted(SOURCE_FLAGS.items())).encode())
     for path in sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC)) + [HEADER]:
         h.update(os.path.basename(path).encode())
         with open(path, "rb") as f:
@@ -54,7 +60,7 @@ def build_library(verbose: bool = False, host_ubsan: bool = False) -> str:
 
     def compile_one(pair):
         src, obj = pair
-        cmd = [hipcc_path()] + flags + ["-c", "-o", obj, os.path.join(CSRC, src)]
+        cmd = [hipcc_path()] + flags + SOURCE_FLAGS.get(src, []) + ["-c", "-o", obj, os.path.join(CSRC, src)]
         if verbose:
             print(" ".join(cmd), flush=True)
         return subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)

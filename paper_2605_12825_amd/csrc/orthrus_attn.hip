@@ -29,122 +29,14 @@
 //            it writes final bf16 rows (one split) or an fp32 partial in register order that
 //            attn_combine_kernel merges in a fixed split order (deterministic).
 //   other forms of the same kernel: the balanced partition of a ragged batch's tiles over the
-//            resident workgroups (template flag BALANCED) and the AR view's causal prefill (PREFILL);
+//            resident workgroups (MODE kItemsBalanced) and the AR view's causal prefill (kItemsPrefill);
 //            both are described at the kernel.
 //   caches = K/V tiles are read once per call.  When the model streams more K/V between two passes
 //            over the same cache than the last-level cache holds, the tile loads carry the
 //            non-temporal hint and the fp32 partials leave with non-temporal stores.
-#include "orthrus_internal.h"
-
-#include <hip/hip_ext.h>
-
-#include <type_traits>
-
-#pragma clang diagnostic ignored "-Winline-asm"  // the direct-to-LDS loads below name M0 as clobbered
+#include "orthrus_attn_dev.h"
 
 namespace orthrus {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) short s16x4;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
-typedef __attribute__((address_space(4))) int32_t const_i32;
-
-union Frag {
-    uint4 u;
-    bf16x8 v;
-    s16x4 h[2];
-    u32x4 n;
-};
-
-// LDS tile layout.  A wave-wide 16-byte direct load fills 1024 contiguous LDS bytes = one "group" of
-// RPI consecutive K/V rows; groups are GS = 1040 bytes apart (the 16 bytes of padding rotate the
-// banks from group to group).  Inside a group, row r keeps its 16-byte chunk c at slot c ^ xm(r),
-// xm(r) = (r << 2) mod chunks-per-row, i.e. each row of a group starts in a different 64-byte bank
-// window.  Both MFMA operand read patterns then spread over the banks: the K read (lanes = 32
-// consecutive rows, same chunk) and the V transpose read (16 lanes = 4 rows x 32 bytes).  The
-// permutation is applied on the global side (a lane fetches the chunk that belongs in its slot).
-constexpr int kGroupStride = 1040;
-constexpr float kLazy = 8.0f;  // log2 of the largest exponential the lazy softmax reference allows
-template <int CH>
-__device__ __forceinline__ int xm(int r)
-{
-    return (r << 2) & (CH - 1);
-}
-
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
-{
-    f32x2 v = {lo, hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));  // v_cvt_pk_bf16_f32, RNE
-}
-
-// Combine a value with the one held by lane ^ 32 (the other half-wave) without going through LDS:
-// v_permlane32_swap exchanges the upper half of one register with the lower half of another.
-__device__ __forceinline__ float max_with_other_half(float x)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float sum_with_other_half(float x)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// Plain workgroup barrier.  Tile loads are tracked by hand (vmcnt), LDS traffic of the compiler's own
-// instructions is complete once their results were consumed; the empty asm statements keep the
-// compiler from moving memory operations across the barrier.
-__device__ __forceinline__ void wg_barrier()
-{
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
-template <int N>
-__device__ __forceinline__ void wait_vmcnt()
-{
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
-// The tiles of one (sequence, KV head) unit, cache tiles of 32 tokens followed by the in-block tile, dealt
-// out to `splits` pieces as evenly as whole tiles allow: the first `rem` pieces get one tile more, pieces
-// past the tile count get nothing, and the in-block tile (the unit's last) lands in the last piece that
-// has any.  A launch ends with its longest piece and the others cannot make up for it (a lone CU streams
-// no faster when its neighbours are done), so one tile of imbalance costs a whole tile's time.
-struct SplitCut {
-    int first;  // first tile of the piece (tile index in the unit)
-    int count;  // tiles in it, the in-block tile included if it is the unit's last piece
-    int live;   // pieces of this unit that have any tile
-};
-__host__ __device__ __forceinline__ SplitCut split_cut(int L, int splits, int split)
-{
-    const int total = ((L + 31) >> 5) + 1;  // cache tiles + the in-block tile
-    const int per = total / splits, rem = total - per * splits;
-    SplitCut c;
-    c.first = split * per + (split < rem ? split : rem);
-    c.count = per + (split < rem ? 1 : 0);
-    c.live = total < splits ? total : splits;
-    return c;
-}
-
-template <int D>
-struct AttnGeom {
-    static constexpr int CH = D / 8;          // 16-byte chunks per K/V row
-    static constexpr int ROWB = D * 2;        // bytes per K/V row
-    static constexpr int RPI = 64 / CH;       // rows per group = rows fetched by one wave-wide 16-byte load
-    static constexpr int NI = 32 / RPI;       // groups (= such loads) per 32-token K (or V) tile
-    static constexpr int GS = kGroupStride;   // LDS bytes between groups
-    static constexpr int TILE_B = NI * GS;    // one 32-token K (or V) tile in LDS
-    static constexpr int STAGE_B = 2 * TILE_B;
-    static constexpr int KSTEPS = D / 16;     // MFMA steps along d for S
-    static constexpr int DBLK = D / 32;       // 32-wide output blocks along d
-};
 
 // D head_dim, W compute waves (= 32-row blocks) per workgroup, NS LDS stages.
 //
@@ -155,12 +47,12 @@ struct AttnGeom {
 // wave they overlap.  The register budget is 168 (three waves per SIMD), so W + 1 <= 9 waves fit a CU;
 // the balanced form spills a dozen values that live across segments, outside the tile loop.
 //
-// PREFILL = 1 turns the same kernel into the AR view's causal prefill attention (Section 3.1): the new
+// MODE kItemsPrefill turns the same kernel into the AR view's causal prefill attention (Section 3.1): the new
 // tokens' K/V rows are already in the cache, a work item is (sequence, chunk of 32 new tokens, KV head),
 // its R = 32*G rows are the chunk's tokens times the G query heads, row (token i) sees cache tokens
 // 0 .. L+i (its own position included), and there is no staged block tile and no split.
 //
-// BALANCED = 1 (decode only) replaces the fixed (sequence, split, head) grid by an even partition of
+// MODE kItemsBalanced (decode only) replaces the fixed (sequence, split, head) grid by an even partition of
 // the whole launch's tile sequence: the tiles of all (head, sequence) units, cache tiles then the
 // in-block tile, are laid end to end (head-major), and workgroup w of the N launched takes tiles
 // [w*T/N, (w+1)*T/N).  A workgroup's range is cut into segments at unit boundaries; a segment that
@@ -173,10 +65,10 @@ struct AttnGeom {
 // PROBE = 1 is the measurement form behind orthrus_kv_stream_probe: the loader wave streams exactly the
 // tiles of the call, the compute waves only keep the barriers (no queries, no arithmetic, nothing is
 // written), so the launch takes as long as this kernel's K/V stream alone.
-template <int D, int W, int NS, int PREFILL = 0, int BALANCED = 0, int PROBE = 0>
+template <int D, int W, int NS, int MODE = kItemsSplit, int PROBE = 0>
 __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(const AttnArgs a)
 {
-    static_assert(!(PREFILL && BALANCED), "the balanced partition is a decode mode");
+    constexpr bool PREFILL = MODE == kItemsPrefill, BALANCED = MODE == kItemsBalanced;
     static_assert(!PROBE || (W == 1 && !PREFILL), "the stream probe is a decode-mode kernel with one idle compute wave");
     using Gm = AttnGeom<D>;
     constexpr int CH = Gm::CH, ROWB = Gm::ROWB, RPI = Gm::RPI, NI = Gm::NI, GS = Gm::GS;
@@ -195,299 +87,109 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(const AttnA
     const int K = a.block_k, G = a.group;
     const int P = 1 << a.page_shift;
 
-    // The work item (balanced mode: the current segment) as every wave of the workgroup sees it.
-    // Lengths and the page table are read-only for the whole launch and every index used here is
-    // wave-uniform: reading them through the constant address space makes these scalar loads
-    // (s_load_dword), which keeps them off the vector-memory counter that paces the tile loads.
-    int b, g;
-    int t_begin, t_end, n_cache, n_tiles;  // cache tokens [t_begin, t_end) in n_cache tiles; n_tiles adds the in-block tile
-    bool final_out;                        // this item holds every tile of its unit: write finished rows
-    size_t part_slot = 0;                  // else: index of the partial it writes
-    int row0 = 0, rows_live = K;  // prefill: first new-token index of the chunk, tokens in it; pos0 below
-    int pos0 = 0;                 // prefill: cache position of the chunk's first token
-    const const_i32 *pt_row;
-    int64_t head_off;
-
-    // validated length of sequence x (scalar)
-    auto seq_len = [&](int x) __attribute__((always_inline)) {
-        int L = ((const const_i32 *)a.seq_lens)[x];
-        if (L < 0 || L > a.max_seq_len) {
-            if (tid == 0) atomicExch(a.err_word, -4);
-            L = L < 0 ? 0 : a.max_seq_len;
-        }
-        return __builtin_amdgcn_readfirstlane(L);  // wave-uniform by construction; keeps the loop control scalar
-    };
-
-    // balanced mode: position in the launch's tile sequence
-    int bal_b = 0, bal_g = 0, bal_o = 0, bal_left = 0;
-    if constexpr (BALANCED) {
-        // tiles of sequence x as a lane sees it (cache tiles + the in-block tile), 0 past the batch
-        auto lane_tiles = [&](int x) __attribute__((always_inline)) {
-            if (x >= a.batch) return 0;
-            int L = a.seq_lens[x];
-            L = L < 0 ? 0 : (L > a.max_seq_len ? a.max_seq_len : L);
-            return ((L + 31) >> 5) + 1;
-        };
-        int per_head = 0;  // tiles of one head's units
-        for (int x0 = 0; x0 < a.batch; x0 += 64) {
-            int n = lane_tiles(x0 + lane);
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) n += __shfl_xor(n, off);
-            per_head += n;
-        }
-        per_head = __builtin_amdgcn_readfirstlane(per_head);
-        const int64_t total = (int64_t)per_head * a.num_kv_heads;
-        const int64_t nwg = total < (int64_t)gridDim.x ? total : (int64_t)gridDim.x;
-        if ((int64_t)blockIdx.x >= nwg) return;
-        const int64_t c0 = (int64_t)blockIdx.x * total / nwg, c1 = ((int64_t)blockIdx.x + 1) * total / nwg;
-        bal_left = __builtin_amdgcn_readfirstlane((int)(c1 - c0));
-        bal_g = __builtin_amdgcn_readfirstlane((int)(c0 / per_head));
-        const int r = (int)(c0 - (int64_t)bal_g * per_head);
-        // the sequence whose tiles contain offset r of the head: inclusive scan over 64 sequences at a time
-        int base = 0;
-        for (int x0 = 0; x0 < a.batch; x0 += 64) {
-            const int n = lane_tiles(x0 + lane);
-            int incl = n;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const int up = __shfl_up(incl, off);
-                if (lane >= off) incl += up;
-            }
-            const bool hit = n > 0 && base + incl - n <= r && r < base + incl;
-            const uint64_t mask = __ballot(hit);
-            if (mask) {
-                const int src = __builtin_ctzll(mask);
-                bal_b = x0 + src;
-                bal_o = r - (base + __shfl(incl - n, src));
-                break;
-            }
-            base += __shfl(incl, 63);
-        }
-        bal_b = __builtin_amdgcn_readfirstlane(bal_b);
-        bal_o = __builtin_amdgcn_readfirstlane(bal_o);
-    }
-
-    // Opens the next work item; false when the workgroup has none (left).
-    auto open_item = [&]() __attribute__((always_inline)) -> bool {
-        if constexpr (BALANCED) {
-            if (bal_left <= 0) return false;
-            b = bal_b;
-            g = bal_g;
-            const int L = seq_len(b);
-            const int nc = (L + 31) >> 5;                    // cache tiles of the unit; the in-block tile is tile nc
-            const int take = min(nc + 1 - bal_o, bal_left);  // tiles of this segment
-            const bool has_blk = bal_o + take == nc + 1;
-            // (everything here is wave-uniform; readfirstlane keeps it in scalar registers)
-            n_tiles = __builtin_amdgcn_readfirstlane(take);
-            n_cache = has_blk ? n_tiles - 1 : n_tiles;
-            t_begin = __builtin_amdgcn_readfirstlane(bal_o * 32);
-            t_end = min(L, t_begin + n_cache * 32);
-            final_out = bal_o == 0 && has_blk;
-            part_slot = (size_t)(blockIdx.x * 2u + (bal_o == 0 ? 1u : 0u));
-            bal_left = __builtin_amdgcn_readfirstlane(bal_left - take);
-            bal_o = 0;
-            int nb = bal_b + 1, ng = bal_g;
-            if (nb == a.batch) {
-                nb = 0;
-                ++ng;
-            }
-            bal_b = __builtin_amdgcn_readfirstlane(nb);
-            bal_g = __builtin_amdgcn_readfirstlane(ng);
-        } else {
-            // Workgroup id -> (sequence, split, KV head) with the sequence index fastest and the head
-            // slowest.  Consecutive workgroup ids go to different XCDs; a head's rows sit at a fixed
-            // offset inside every page, so an order that ties XCD k to head k makes each XCD hammer its
-            // own subset of the HBM channels and the XCDs finish far apart.  (Prefill: the middle index
-            // is the chunk, longest first.)
-            b = (int)(blockIdx.x % (unsigned)a.batch);
-            const int split = (int)((blockIdx.x / (unsigned)a.batch) % (unsigned)a.num_splits);
-            g = (int)(blockIdx.x / ((unsigned)a.batch * (unsigned)a.num_splits));
-            if constexpr (PREFILL) {
-                // lengths as the planning kernel left them: validated, 0 new tokens on a capacity error
-                const int L0 = __builtin_amdgcn_readfirstlane(((const const_i32 *)a.old_lens)[b]);
-                const int n_new = __builtin_amdgcn_readfirstlane(((const const_i32 *)a.new_lens)[b]);
-                const int chunk = a.num_splits - 1 - split;  // the chunks with the most cache tokens start first
-                row0 = chunk * 32;
-                if (row0 >= n_new) return false;
-                rows_live = min(32, n_new - row0);
-                pos0 = L0 + row0;
-                t_begin = 0;
-                t_end = pos0 + rows_live;  // everything up to the chunk's last token
-                n_cache = (t_end + 31) >> 5;
-                n_tiles = n_cache;
-                final_out = true;
-            } else {
-                const int L = seq_len(b);
-                // The sequence's own length, not the host's bound on it, is cut into num_splits pieces:
-                // they stay equal however loose the bound is (it only sized the grid), e.g. when a
-                // decode loop bumps it by K per step without reading back.
-                const SplitCut cut = split_cut(L, a.num_splits, split);
-                if (cut.count == 0) return false;  // fewer tiles than splits: nothing falls in this one
-                n_tiles = __builtin_amdgcn_readfirstlane(cut.count);
-                n_cache = split == cut.live - 1 ? n_tiles - 1 : n_tiles;  // the last piece ends with the in-block tile
-                t_begin = __builtin_amdgcn_readfirstlane(cut.first * 32);
-                t_end = min(L, t_begin + n_cache * 32);
-                final_out = a.num_splits == 1;
-                part_slot = ((size_t)b * a.num_kv_heads + g) * a.num_splits + split;
-            }
-        }
-        pt_row = (const const_i32 *)(a.page_table + (int64_t)b * a.max_pages_per_seq);
-        head_off = (int64_t)g * a.stride_head;
-        return true;
-    };
-    if (!open_item()) return;
+    WorkItems<MODE> it;
+    it.start(a);
+    if (!it.open(a)) return;
 
     const uint32_t smem_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)smem;
-    const int ld_tok = lane / CH, ld_ch = lane % CH;  // this lane's (row, slot) inside one wave-wide load
-
-    // Direct global->LDS load of 64 x 16 bytes: lane's bytes land at lds_addr + lane*16.  Issued
-    // through inline assembly so that whole tiles can stay in flight while older ones are computed;
-    // completion is awaited explicitly with s_waitcnt vmcnt (loads return in order).  M0 carries the
-    // LDS destination and is declared clobbered, so the compiler never carries a value of its own in M0
-    // across one of these statements (M0 is a reserved register, which clang remarks on for any clobber
-    // list that names it; the remark is switched off for this file).  Two address forms: a 64-bit
-    // address per lane, or a wave-uniform 64-bit base plus a 32-bit byte offset per lane.
-    //
-    // a.kv_nt selects the non-temporal form of the loads: when one call streams more K/V than the
-    // last-level cache holds, nothing of it is there for the next call anyway, and loads that do not
-    // allocate on their way stream ~7 % faster (measured); a working set that fits keeps the plain
-    // form, so that the second view's pass over the same cache still finds it.
-    // The choice is made once per wave (two copies of the loader's loop), not per load.
-    auto dma16 = [&](auto nt, const uint16_t *gp, uint32_t lds_addr) __attribute__((always_inline)) {
-        if constexpr (decltype(nt)::value)
-            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt"
-                         :
-                         : "v"(gp), "s"(lds_addr)
-                         : "memory", "m0");
-        else
-            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-                         :
-                         : "v"(gp), "s"(lds_addr)
-                         : "memory", "m0");
-    };
-    auto dma16s = [&](auto nt, const uint16_t *base, uint32_t voff, uint32_t lds_addr) __attribute__((always_inline)) {
-        if constexpr (decltype(nt)::value)
-            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
-                         :
-                         : "v"(voff), "s"(base), "s"(lds_addr)
-                         : "memory", "m0");
-        else
-            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                         :
-                         : "v"(voff), "s"(base), "s"(lds_addr)
-                         : "memory", "m0");
-    };
-
-    // Page ids of the two 16-token halves of cache tile t (the second repeats the first when that
-    // half lies past the end).  They are fetched one tile ahead of their use, so that the scalar
-    // load's latency is never in front of a tile's loads.
-    auto fetch_pages = [&](int t, int &p0, int &p1) __attribute__((always_inline)) {
-        p0 = 0;
-        p1 = 0;
-        if (t < n_cache) {
-            const int ts = t_begin + t * 32;
-            p0 = pt_row[ts >> a.page_shift];
-            p1 = p0;
-            if (ts + 16 < t_end) p1 = pt_row[(ts + 16) >> a.page_shift];
-        }
-    };
-    // Start the loads of tile t (cache tile, or the in-block tile when
-    // t == n_cache) into ring stage t % NS.  A full cache tile takes the cheap address form: page, head
-    // and row group go into a wave-uniform base (scalar arithmetic), the lane adds one loop-invariant
-    // byte offset.  In the last, ragged cache tile rows past the end repeat the last valid row (finite
-    // data, masked later): nothing is fetched through an unmapped page and no LDS row is left
-    // undefined; that tile and the in-block tile compute an address per lane.
-    const uint32_t lane_off = (uint32_t)(ld_tok * (int)a.stride_tok + ((ld_ch ^ xm<CH>(ld_tok)) << 3)) * 2u;
-    auto issue_tile = [&](auto nt, int t, int p0, int p1) __attribute__((always_inline)) {
-        const uint32_t dst = smem_lds + (t % NS) * STAGE_B;
-        if (t < n_cache) {
-            const int ts = t_begin + t * 32;
-            if (p0 < 0 || p0 >= a.num_pages || p1 < 0 || p1 >= a.num_pages) {
-                if (lane == 0) atomicExch(a.err_word, -4);
-                if (p0 < 0 || p0 >= a.num_pages) p0 = 0;
-                if (p1 < 0 || p1 >= a.num_pages) p1 = 0;
-            }
-            if (ts + 32 <= t_end) {
-                const int tsp = ts & (P - 1);
-#pragma unroll
-                for (int e = 0; e < LPT; ++e) {
-                    const int id = e;               // 0..LPT-1: K groups, then V groups
-                    const int u = id % NI;
-                    const int page = (u * RPI < 16) ? p0 : p1;
-                    const int tin = (tsp + u * RPI) & (P - 1);
-                    const int64_t soff = (int64_t)page * a.stride_page + head_off + (int64_t)tin * a.stride_tok;
-                    dma16s(nt, (id < NI ? a.k_pool : a.v_pool) + soff, lane_off, dst + (id < NI ? 0 : TILE_B) + u * GS);
-                }
-            } else {
-#pragma unroll
-                for (int e = 0; e < LPT; ++e) {
-                    const int id = e;
-                    const int u = id % NI;
-                    const uint16_t *pool = id < NI ? a.k_pool : a.v_pool;
-                    const int tok = u * RPI + ld_tok;
-                    const int tg = min(ts + tok, t_end - 1);
-                    const int p = (u * RPI < 16) ? p0 : p1;
-                    const int64_t off = (int64_t)p * a.stride_page + (int64_t)g * a.stride_head +
-                                        (int64_t)(tg & (P - 1)) * a.stride_tok + ((ld_ch ^ xm<CH>(ld_tok)) << 3);
-                    dma16(nt, pool + off, dst + (id < NI ? 0 : TILE_B) + u * GS);
-                }
-            }
-        } else if constexpr (!PROBE) {  // (the stream probe has no block inputs: its in-block tile stays empty)
-#pragma unroll
-            for (int e = 0; e < LPT; ++e) {
-                const int id = e;
-                const int u = id % NI;
-                const uint16_t *blk = id < NI ? a.k_blk : a.v_blk;
-                const int tok = u * RPI + ld_tok;
-                const int64_t off = ((int64_t)b * K + min(tok, K - 1)) * a.blk_stride_row + (int64_t)g * a.blk_stride_head +
-                                    ((ld_ch ^ xm<CH>(ld_tok)) << 3);
-                dma16(nt, blk + off, dst + (id < NI ? 0 : TILE_B) + u * GS);
-            }
-        }
-    };
-
-    // One step of the load pipeline, run by the loader wave once per tile i, around the tile's workgroup
-    // barrier: before the barrier the loads of tile i are complete; after it every compute wave is done
-    // reading stage (i-1) % NS, which is refilled with tile i+NS-1 while tile i is computed.
-    int np0 = 0, np1 = 0;  // page ids of the next tile to be issued
-    auto pipeline_fill = [&](auto nt) __attribute__((always_inline)) {
-#pragma unroll
-        for (int t = 0; t < NS - 1; ++t) {
-            fetch_pages(t, np0, np1);
-            if (t < n_tiles) issue_tile(nt, t, np0, np1);
-        }
-        fetch_pages(NS - 1, np0, np1);
-    };
-    auto pipeline_step = [&](auto nt, int i) __attribute__((always_inline)) {
-        const int ahead = min(NS - 2, n_tiles - 1 - i);  // tiles issued after tile i so far
-        if (ahead >= 2) wait_vmcnt<2 * LPT>();
-        else if (ahead == 1) wait_vmcnt<LPT>();
-        else wait_vmcnt<0>();
-        wg_barrier();
-        if (i + NS - 1 < n_tiles) issue_tile(nt, i + NS - 1, np0, np1);
-        fetch_pages(i + NS, np0, np1);
-    };
+    const int ld_tok = lane / CH;  // this lane's row inside one wave-wide load, and the byte offset of its chunk in that row
+    const uint32_t ld_swz = (uint32_t)(((lane % CH) ^ xm<CH>(ld_tok)) << 4);
 
     if (loader) {
-        // the loader wave: nothing but the load pipeline; its last wait leaves no load outstanding
+        // The loader wave: nothing but the load pipeline, one step per tile around the tile's workgroup barrier.
+        // Before the barrier the loads of tile i are complete; after it every compute wave is done reading the stage
+        // of tile i-1, which is refilled with tile i+NS-1 while tile i is computed.
+        HalfLoads<D> half(a, lane);
         auto run = [&](auto nt) __attribute__((always_inline)) {
             for (;;) {
-                pipeline_fill(nt);
-                for (int i = 0; i < n_tiles; ++i) pipeline_step(nt, i);
-                if (!BALANCED || !open_item()) break;
+                const int n_whole = half.usable ? min(it.n_cache, (it.t_end - it.t_begin) >> 5) : 0;
+                const char *kp = half.lowered(a.k_pool + it.head_off), *vp = half.lowered(a.v_pool + it.head_off);
+                uint32_t dst = smem_lds;  // ring slot of the next tile to be issued
+                int p0 = 0, p1 = 0;       // page ids of its two halves (the second repeats the first past the end)
+                // fetched one tile ahead of their use, so that the scalar load's latency is never in front of a tile's loads
+                auto fetch_pages = [&](int t) __attribute__((always_inline)) {
+                    if (t < it.n_cache) {
+                        const int ts = it.t_begin + t * 32;
+                        p0 = it.pt_row[(uint32_t)ts >> a.page_shift];
+                        p1 = it.pt_row[(uint32_t)(ts + 16 < it.t_end ? ts + 16 : ts) >> a.page_shift];
+                    }
+                };
+                auto issue_tile = [&](int t) __attribute__((always_inline)) {
+                    if (t < n_whole) {
+                        const uint32_t ts = (uint32_t)(it.t_begin + t * 32);
+                        const uint64_t o0 = half.offset(p0, ts), o1 = half.offset(p1, ts + 16);
+                        half.issue(nt, kp + o0, dst);
+                        half.issue(nt, kp + o1, dst + half.GPH * GS);
+                        half.issue(nt, vp + o0, dst + TILE_B);
+                        half.issue(nt, vp + o1, dst + TILE_B + half.GPH * GS);
+                    } else if (half.usable && t < it.n_cache) {
+                        // the last, ragged cache tile: rows past the end repeat the last valid row (finite data, masked
+                        // later), so nothing is fetched through an unmapped page and no LDS row is left undefined
+                        const uint64_t o0 = half.offset(p0, 0) >> 1, o1 = half.offset(p1, 0) >> 1;
+                        const uint16_t *const kb[2] = {a.k_pool + it.head_off + o0, a.k_pool + it.head_off + o1};
+                        const uint16_t *const vb[2] = {a.v_pool + it.head_off + o0, a.v_pool + it.head_off + o1};
+                        issue_rows<D>(nt, kb, vb, dst, [&](int u) __attribute__((always_inline)) {
+                            const int tg = min(it.t_begin + t * 32 + u * RPI + ld_tok, it.t_end - 1);
+                            return ((uint32_t)tg & half.page_mask) * half.tok_bytes + ld_swz;
+                        });
+                    } else if (t < it.n_cache) {  // strides past 32-bit arithmetic: an address per lane and load
+                        half.worst = max(half.worst, max((uint32_t)p0, (uint32_t)p1));
+                        const int q0 = (uint32_t)p0 < half.num_pages ? p0 : 0, q1 = (uint32_t)p1 < half.num_pages ? p1 : 0;
+#pragma unroll 1
+                        for (int u = 0; u < NI; ++u) {
+                            const int tg = min(it.t_begin + t * 32 + u * RPI + ld_tok, it.t_end - 1);
+                            const int64_t off = (int64_t)(u * RPI < 16 ? q0 : q1) * a.stride_page + it.head_off +
+                                                (int64_t)(tg & (P - 1)) * a.stride_tok + (ld_swz >> 1);
+                            dma16(nt, a.k_pool + off, dst + u * GS);
+                            dma16(nt, a.v_pool + off, dst + TILE_B + u * GS);
+                        }
+                    } else if constexpr (!PROBE && !PREFILL) {  // (the stream probe has no block inputs: its in-block tile stays empty)
+                        // the in-block tile; rows past the block repeat its last row
+                        const int64_t off0 = (int64_t)it.b * K * a.blk_stride_row + (int64_t)it.g * a.blk_stride_head;
+                        if (a.blk_stride_row < (1ll << 25)) {
+                            const uint16_t *const kb[2] = {a.k_blk + off0, a.k_blk + off0}, *const vb[2] = {a.v_blk + off0, a.v_blk + off0};
+                            const uint32_t row_bytes = (uint32_t)a.blk_stride_row * 2u;
+                            issue_rows<D>(nt, kb, vb, dst, [&](int u) __attribute__((always_inline)) {
+                                return (uint32_t)min(u * RPI + ld_tok, K - 1) * row_bytes + ld_swz;
+                            });
+                        } else {
+#pragma unroll 1
+                            for (int u = 0; u < NI; ++u) {
+                                const int64_t off = off0 + (int64_t)min(u * RPI + ld_tok, K - 1) * a.blk_stride_row + (ld_swz >> 1);
+                                dma16(nt, a.k_blk + off, dst + u * GS);
+                                dma16(nt, a.v_blk + off, dst + TILE_B + u * GS);
+                            }
+                        }
+                    }
+                    dst = dst + STAGE_B == smem_lds + NS * STAGE_B ? smem_lds : dst + STAGE_B;
+                    fetch_pages(t + 1);
+                };
+                int t = 0;  // next tile to be issued
+                fetch_pages(0);
+                for (; t < min(NS - 1, it.n_tiles); ++t) issue_tile(t);
+                for (int i = 0; i < it.n_tiles; ++i) {
+                    const int ahead = min(NS - 2, it.n_tiles - 1 - i);  // tiles issued after tile i so far
+                    if (ahead >= 2) wait_vmcnt<2 * LPT>();
+                    else if (ahead == 1) wait_vmcnt<LPT>();
+                    else wait_vmcnt<0>();
+                    wg_barrier();
+                    if (t < it.n_tiles) issue_tile(t++);
+                }
+                if (!BALANCED || !it.open(a)) break;
                 wg_barrier();  // every compute wave is done with the previous segment's last tile
             }
         };
         if (a.kv_nt) run(std::true_type{});
         else run(std::false_type{});
+        if (half.worst >= half.num_pages && lane == 0) atomicExch(a.err_word, -4);
         return;
     }
 
     // ---- compute waves
     if constexpr (PROBE) {
         for (;;) {
-            for (int i = 0; i < n_tiles; ++i) wg_barrier();
-            if (!BALANCED || !open_item()) break;
+            for (int i = 0; i < it.n_tiles; ++i) wg_barrier();
+            if (!BALANCED || !it.open(a)) break;
             wg_barrier();
         }
         return;
@@ -519,13 +221,13 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(const AttnA
         int irow;
         const int ridx = wave * 32 + col;
         // the lane's row exists: inside the R rows and, for prefill, inside the chunk's live tokens
-        const bool row_ok = ridx < a.rows && (!PREFILL || ridx / G < rows_live);
+        const bool row_ok = ridx < a.rows && (!PREFILL || ridx / G < it.rows_live);
         // row of q / out that holds block row (or new token) i of this sequence
-        const int64_t row_base = PREFILL ? (int64_t)b * a.max_new + row0 : (int64_t)b * K;
+        const int64_t row_base = PREFILL ? (int64_t)it.b * a.max_new + it.row0 : (int64_t)it.b * K;
         if (row_ok) {
             const int i = ridx / G, hl = ridx - i * G;
             irow = i;
-            const uint16_t *qp = a.q + (row_base + i) * a.q_stride_row + ((int64_t)g * G + hl) * a.q_stride_head;
+            const uint16_t *qp = a.q + (row_base + i) * a.q_stride_row + ((int64_t)it.g * G + hl) * a.q_stride_head;
 #pragma unroll
             for (int kk = 0; kk < KSTEPS; ++kk) qf[kk].u = *(const uint4 *)(qp + kk * 16 + h * 8);
         } else {
@@ -544,7 +246,7 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(const AttnA
 
         // ---- main loop: one barrier per tile
         int stage = 0;  // ring slot of tile i (= i % NS)
-        for (int i = 0; i < n_tiles; ++i) {
+        for (int i = 0; i < it.n_tiles; ++i) {
             wg_barrier();
 
             // LDS addresses of this tile's operands: one add per base, the rest are instruction offsets
@@ -557,9 +259,9 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(const AttnA
             for (int db = 0; db < DBLK; ++db) va_[db] = st_addr + vb[db];
             // lim = number of leading tile tokens this lane's row may see
             int lim = 32;
-            if (i < n_cache) lim = t_end - (t_begin + i * 32);
+            if (i < it.n_cache) lim = it.t_end - (it.t_begin + i * 32);
             else lim = a.view == 0 ? K : min(K, irow + 1);  // in-block tile: K rows, causal for the AR view
-            if constexpr (PREFILL) lim = min(lim, pos0 + irow + 1 - i * 32);  // causal: tokens up to the row's own
+            if constexpr (PREFILL) lim = min(lim, it.pos0 + irow + 1 - i * 32);  // causal: tokens up to the row's own
 
             f32x16 s;
 #pragma unroll
@@ -634,11 +336,11 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(const AttnA
 
         // ---- write-out: this wave's 32 rows
         l_run = sum_with_other_half(l_run);
-        if (final_out) {
+        if (it.final_out) {
             if (row_ok) {
                 const int i = irow, hl = ridx - i * G;
                 const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
-                uint16_t *op = a.out + ((row_base + i) * a.num_q_heads + (int64_t)g * G + hl) * D;
+                uint16_t *op = a.out + ((row_base + i) * a.num_q_heads + (int64_t)it.g * G + hl) * D;
 #pragma unroll
                 for (int db = 0; db < DBLK; ++db)
 #pragma unroll
@@ -649,12 +351,12 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(const AttnA
                         *(uint2 *)(op + 32 * db + 8 * r4 + 4 * h) = pk;
                     }
                 if (a.lse && h == 0)
-                    a.lse[((int64_t)b * a.num_q_heads + (int64_t)g * G + hl) * K + i] =
+                    a.lse[((int64_t)it.b * a.num_q_heads + (int64_t)it.g * G + hl) * K + i] =
                         (m_run + __builtin_amdgcn_logf(l_run)) * 0.6931471805599453f;
             }
         } else {
             // partial in register order: [partial][wave][db][r4][lane] float4, then (m, l) per row
-            const size_t slot = part_slot * W + wave;
+            const size_t slot = it.part_slot * a.part_blocks + wave;
             f32x4 *po = (f32x4 *)a.part_o + slot * (DBLK * 4 * 64) + lane;
 #pragma unroll
             for (int db = 0; db < DBLK; ++db)
@@ -666,7 +368,7 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(const AttnA
                 }
             if (h == 0) ((float2 *)a.part_ml)[slot * 32 + col] = make_float2(m_run, l_run);
         }
-        if (!BALANCED || !open_item()) break;
+        if (!BALANCED || !it.open(a)) break;
         wg_barrier();  // matches the loader's barrier between segments
     }
 }
@@ -684,16 +386,19 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(const AttnA
 // CHUNK = partials merged per round of loads: 8 keeps the registers low for the bandwidth-bound merges
 // of many units with few pieces each; 16 or 32 make the latency-bound merge of few units with many
 // splits a single memory round trip (a second round costs it ~1 us).
-template <int D, int W, int BALANCED = 0, int CHUNK = 8>
+constexpr unsigned kUnitsPerZ = 32768;  // grid (row block x d block, unit modulo this, unit / this)
+template <int D, int BALANCED = 0, int CHUNK = 8>
 __global__ void __launch_bounds__(256) attn_combine_kernel(const AttnArgs a)
 {
+    const int PB = a.part_blocks;
     constexpr int DBLK = D / 32;
     constexpr int MCHUNK = 32;  // m values fetched per round when there are more than CHUNK partials
     const int lane = threadIdx.x & 63, r4 = threadIdx.x >> 6;
     const int col = lane & 31, h = lane >> 5;
     const int db = blockIdx.x % DBLK;
-    const int wave = (blockIdx.x / DBLK) % W;  // row block
-    const int unit = blockIdx.x / (DBLK * W);
+    const int wave = blockIdx.x / DBLK;  // row block
+    const int unit = (int)(blockIdx.z * kUnitsPerZ + blockIdx.y);
+    if (unit >= a.batch * a.num_kv_heads) return;
     const int b = unit / a.num_kv_heads, g = unit % a.num_kv_heads;
     const int ridx = wave * 32 + col;
     int live;           // number of partials of this unit
@@ -741,11 +446,11 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const AttnArgs a)
     }
     // partial `s` of this unit: (m, l) of the lane's row and the lane's float4 of the accumulator
     auto ml_at = [&](int s) __attribute__((always_inline)) {
-        const size_t slot = (s == 0 ? first_slot : rest_slot + (size_t)s * slot_step) * W + wave;
+        const size_t slot = (s == 0 ? first_slot : rest_slot + (size_t)s * slot_step) * PB + wave;
         return (const float2 *)a.part_ml + slot * 32 + col;
     };
     auto po_at = [&](int s) __attribute__((always_inline)) {
-        const size_t slot = (s == 0 ? first_slot : rest_slot + (size_t)s * slot_step) * W + wave;
+        const size_t slot = (s == 0 ? first_slot : rest_slot + (size_t)s * slot_step) * PB + wave;
         return (const float4 *)a.part_o + slot * (DBLK * 4 * 64) + (size_t)(db * 4 + r4) * 64 + lane;
     };
 
@@ -815,15 +520,19 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
 {
     const int R = group * block_k;
     plan->rows = R;
-    const int W = R > 32 ? (R + 31) / 32 : 1;
-    plan->waves = W;
-    plan->rows_padded = W * 32;
-    plan->lds_bytes = lds_need(head_dim);
+    const int blocks = R > 32 ? (R + 31) / 32 : 1;
     const int64_t units = (int64_t)batch * num_kv_heads;
+    plan->wide = requested_splits >= 0 && requested_splits <= 1 && attn_wide_pays(R, units, num_cus);
+    const int W = plan->wide ? (R > 128 ? 4 : 2) : blocks;
+    plan->waves = W;
+    plan->row_blocks = plan->wide ? 2 * W : W;
+    plan->rows_padded = plan->row_blocks * 32;
+    plan->lds_bytes = plan->wide ? attn_wide_lds(W, head_dim) : lds_need(head_dim);
     // workgroups resident per CU: LDS ring size, and 12 waves (3 per SIMD: the kernel stays below 168
     // registers) of W compute waves + the loader wave each
     int per_cu = (int)(160 * 1024 / plan->lds_bytes);
-    if (per_cu > 12 / (W + 1)) per_cu = 12 / (W + 1);
+    const int by_waves = plan->wide ? 4 / W : 12 / (W + 1);
+    if (per_cu > by_waves) per_cu = by_waves;
     if (per_cu < 1) per_cu = 1;
     plan->bal_wgs = 0;
     // K/V bytes the model streams at most between two passes over the same layer's cache (the other
@@ -853,7 +562,7 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
         // once and read once, and brings the merge launch with it.
         const double kRate = 7.0e6;      // K/V bytes per microsecond (measured ceiling of the paged stream)
         const double kPartRate = 6.0e6;  // bytes per microsecond for the partials
-        const double kTile = W <= 4 ? 0.56 : 1.3;  // more than four 32-row blocks: two per SIMD
+        const double kTile = plan->wide ? 0.66 : W <= 4 ? 0.56 : 1.3;  // more than four 32-row blocks: two per SIMD
         const double kRound = 5.0, kCombine = 4.0, kSplit = 0.12, kWg = 0.008;
         const int64_t slots = (int64_t)num_cus * per_cu;
         const double tile_bytes = 32.0 * 2.0 * head_dim * 2.0;  // K + V bytes of one tile of one KV head
@@ -894,37 +603,44 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
     return hipSuccess;
 }
 
-// One attention call: the split kernel, then the merge when units were cut into pieces.
 template <int D, int W, int BALANCED>
-static hipError_t launch_variant(const AttnArgs &a, const AttnPlan &plan, hipStream_t stream, AttnLaunchEvents *ev)
+static hipError_t launch_split(const AttnArgs &a, const AttnPlan &plan, dim3 grid, hipStream_t stream, AttnLaunchEvents *ev)
 {
-    auto kern = attn_split_kernel<D, W, kStages, 0, BALANCED>;
-    auto comb = attn_combine_kernel<D, W, BALANCED, 8>;
-    if constexpr (!BALANCED) {
-        if (plan.num_splits > 16) comb = attn_combine_kernel<D, W, 0, 32>;
-        else if (plan.num_splits > 8) comb = attn_combine_kernel<D, W, 0, 16>;
-    }
-    const bool timed = ev && ev->on;
+    return launch_timed(attn_split_kernel<D, W, kStages, BALANCED ? kItemsBalanced : kItemsSplit>, grid, dim3(64 * (W + 1)),
+                        plan.lds_bytes, a, stream, ev, 0);
+}
+
+// One attention call: the split kernel, then the merge when units were cut into pieces.
+template <int D, int BALANCED>
+static hipError_t launch_attn_d(const AttnArgs &a, const AttnPlan &plan, hipStream_t stream, AttnLaunchEvents *ev)
+{
     dim3 grid(BALANCED ? (unsigned)plan.bal_wgs
                        : (unsigned)plan.num_splits * (unsigned)a.num_kv_heads * (unsigned)a.batch);
-    dim3 block(64 * (W + 1));
-    if (timed) {
-        hipExtLaunchKernelGGL(kern, grid, block, plan.lds_bytes, stream, ev->start[0], ev->stop[0], 0, a);
-        ev->used[0] = true;
+    hipError_t e = hipErrorInvalidValue;
+    if (plan.wide) {
+        e = launch_attn_wide(a, plan, D, grid, stream, ev);
     } else {
-        hipLaunchKernelGGL(kern, grid, block, plan.lds_bytes, stream, a);
+        switch (plan.waves) {
+        case 1: e = launch_split<D, 1, BALANCED>(a, plan, grid, stream, ev); break;
+        case 2: e = launch_split<D, 2, BALANCED>(a, plan, grid, stream, ev); break;
+        case 3: e = launch_split<D, 3, BALANCED>(a, plan, grid, stream, ev); break;
+        case 4: e = launch_split<D, 4, BALANCED>(a, plan, grid, stream, ev); break;
+        case 5: e = launch_split<D, 5, BALANCED>(a, plan, grid, stream, ev); break;
+        case 6: e = launch_split<D, 6, BALANCED>(a, plan, grid, stream, ev); break;
+        case 7: e = launch_split<D, 7, BALANCED>(a, plan, grid, stream, ev); break;
+        case 8: e = launch_split<D, 8, BALANCED>(a, plan, grid, stream, ev); break;
+        }
     }
-    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (BALANCED || plan.num_splits > 1) {
-        dim3 cgrid((unsigned)(a.batch * a.num_kv_heads) * W * (D / 32));
-        if (timed) {
-            hipExtLaunchKernelGGL(comb, cgrid, dim3(256), 0, stream, ev->start[1], ev->stop[1], 0, a);
-            ev->used[1] = true;
-        } else {
-            hipLaunchKernelGGL(comb, cgrid, dim3(256), 0, stream, a);
+        auto comb = attn_combine_kernel<D, BALANCED, 8>;
+        if constexpr (!BALANCED) {
+            if (plan.num_splits > 16) comb = attn_combine_kernel<D, 0, 32>;
+            else if (plan.num_splits > 8) comb = attn_combine_kernel<D, 0, 16>;
         }
-        e = hipGetLastError();
+        const unsigned units = (unsigned)(a.batch * a.num_kv_heads);
+        dim3 cgrid((unsigned)((a.rows + 31) / 32) * (D / 32), units < kUnitsPerZ ? units : kUnitsPerZ, (units + kUnitsPerZ - 1) / kUnitsPerZ);
+        e = launch_timed(comb, cgrid, dim3(256), 0, a, stream, ev, 1);
     }
     return e;
 }
@@ -936,7 +652,7 @@ static hipError_t launch_probe_d(const AttnArgs &a, const AttnPlan &plan, hipStr
                                  hipEvent_t stop)
 {
     const bool bal = plan.bal_wgs > 0;
-    auto kern = bal ? attn_split_kernel<D, 1, kStages, 0, 1, 1> : attn_split_kernel<D, 1, kStages, 0, 0, 1>;
+    auto kern = bal ? attn_split_kernel<D, 1, kStages, kItemsBalanced, 1> : attn_split_kernel<D, 1, kStages, kItemsSplit, 1>;
     dim3 grid(bal ? (unsigned)plan.bal_wgs : (unsigned)plan.num_splits * (unsigned)a.num_kv_heads * (unsigned)a.batch);
     const size_t lds = lds_need(D);
     if (start && stop) hipExtLaunchKernelGGL(kern, grid, dim3(128), lds, stream, start, stop, 0, a);
@@ -953,53 +669,27 @@ hipError_t launch_kv_stream_probe(const AttnArgs &a, const AttnPlan &plan, int h
     return hipErrorInvalidValue;
 }
 
-template <int D, int W>
-static hipError_t launch_prefill_variant(const AttnArgs &a, size_t lds_bytes, hipStream_t stream)
+// The prefill form with a compute wave per query head of the group (see launch_prefill_attn).
+template <int D>
+static hipError_t launch_prefill_split_d(AttnArgs a, hipStream_t stream)
 {
+    a.chunk_tokens = 32;
+    a.rows = 32 * a.group;
+    a.num_splits = (a.max_new + 31) / 32;
     dim3 grid((unsigned)a.num_splits * (unsigned)a.num_kv_heads * (unsigned)a.batch);
-    hipLaunchKernelGGL((attn_split_kernel<D, W, kStages, 1>), grid, dim3(64 * (W + 1)), lds_bytes, stream, a);
+    auto kern = a.group == 1   ? attn_split_kernel<D, 1, kStages, kItemsPrefill>
+                : a.group == 2 ? attn_split_kernel<D, 2, kStages, kItemsPrefill>
+                : a.group == 3 ? attn_split_kernel<D, 3, kStages, kItemsPrefill>
+                               : attn_split_kernel<D, 4, kStages, kItemsPrefill>;
+    hipLaunchKernelGGL(kern, grid, dim3(64 * (a.group + 1)), lds_need(D), stream, a);
     return hipGetLastError();
 }
 
-// Prefill attention: a.num_splits carries the number of 32-token chunks per sequence, a.rows = 32 * group.
-template <int D>
-static hipError_t launch_prefill_d(const AttnArgs &a, size_t lds, hipStream_t stream)
+hipError_t launch_prefill_split(const AttnArgs &a, int head_dim, hipStream_t stream)
 {
-    switch (a.group) {  // one compute wave per query head of the group
-    case 1: return launch_prefill_variant<D, 1>(a, lds, stream);
-    case 2: return launch_prefill_variant<D, 2>(a, lds, stream);
-    case 3: return launch_prefill_variant<D, 3>(a, lds, stream);
-    case 4: return launch_prefill_variant<D, 4>(a, lds, stream);
-    case 5: return launch_prefill_variant<D, 5>(a, lds, stream);
-    case 6: return launch_prefill_variant<D, 6>(a, lds, stream);
-    case 7: return launch_prefill_variant<D, 7>(a, lds, stream);
-    case 8: return launch_prefill_variant<D, 8>(a, lds, stream);
-    }
-    return hipErrorInvalidValue;
-}
-
-hipError_t launch_prefill_attn(const AttnArgs &a, int head_dim, hipStream_t stream)
-{
-    if (a.batch == 0 || a.num_splits == 0) return hipSuccess;
-    const size_t lds = lds_need(head_dim);
-    if (head_dim == 128) return launch_prefill_d<128>(a, lds, stream);
-    if (head_dim == 64) return launch_prefill_d<64>(a, lds, stream);
-    return hipErrorInvalidValue;
-}
-
-template <int D, int BALANCED>
-static hipError_t launch_attn_d(const AttnArgs &a, const AttnPlan &plan, hipStream_t stream, AttnLaunchEvents *events)
-{
-    switch (plan.waves) {
-    case 1: return launch_variant<D, 1, BALANCED>(a, plan, stream, events);
-    case 2: return launch_variant<D, 2, BALANCED>(a, plan, stream, events);
-    case 3: return launch_variant<D, 3, BALANCED>(a, plan, stream, events);
-    case 4: return launch_variant<D, 4, BALANCED>(a, plan, stream, events);
-    case 5: return launch_variant<D, 5, BALANCED>(a, plan, stream, events);
-    case 6: return launch_variant<D, 6, BALANCED>(a, plan, stream, events);
-    case 7: return launch_variant<D, 7, BALANCED>(a, plan, stream, events);
-    case 8: return launch_variant<D, 8, BALANCED>(a, plan, stream, events);
-    }
+    if (a.group > 4) return hipErrorInvalidValue;
+    if (head_dim == 128) return launch_prefill_split_d<128>(a, stream);
+    if (head_dim == 64) return launch_prefill_split_d<64>(a, stream);
     return hipErrorInvalidValue;
 }
 

@@ -1,0 +1,437 @@
+// Device code shared by the attention kernels: operand types, the LDS tile layout, the direct-to-LDS loads and the
+// walk over a launch's work items.
+#pragma once
+#include "orthrus_internal.h"
+
+#include <hip/hip_ext.h>
+
+#include <type_traits>
+
+#pragma clang diagnostic ignored "-Winline-asm"  // the direct-to-LDS loads below name M0 as clobbered
+
+namespace orthrus {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+typedef __attribute__((address_space(4))) int32_t const_i32;
+
+union Frag {
+    uint4 u;
+    bf16x8 v;
+    s16x4 h[2];
+    u32x4 n;
+};
+
+// LDS tile layout.  A wave-wide 16-byte direct load fills 1024 contiguous LDS bytes = one "group" of
+// RPI consecutive K/V rows; groups are GS = 1040 bytes apart (the 16 bytes of padding rotate the
+// banks from group to group).  Inside a group, row r keeps its 16-byte chunk c at slot c ^ xm(r),
+// xm(r) = (r << 2) mod chunks-per-row, i.e. each row of a group starts in a different 64-byte bank
+// window.  Both MFMA operand read patterns then spread over the banks: the K read (lanes = 32
+// consecutive rows, same chunk) and the V transpose read (16 lanes = 4 rows x 32 bytes).  The
+// permutation is applied on the global side (a lane fetches the chunk that belongs in its slot).
+constexpr int kGroupStride = 1040;
+constexpr float kLazy = 8.0f;  // log2 of the largest exponential the lazy softmax reference allows
+template <int CH>
+__device__ __forceinline__ int xm(int r)
+{
+    return (r << 2) & (CH - 1);
+}
+
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
+{
+    f32x2 v = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));  // v_cvt_pk_bf16_f32, RNE
+}
+
+// Combine a value with the one held by lane ^ 32 (the other half-wave) without going through LDS:
+// v_permlane32_swap exchanges the upper half of one register with the lower half of another.
+__device__ __forceinline__ float max_with_other_half(float x)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float sum_with_other_half(float x)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Online softmax of one lane's 16 scores (half of a row; lane ^ 32 holds the rest) against a lazily updated
+// reference m in the log2 domain.  The weights are taken against the old reference first; only when their sum says
+// that one of them may have outgrown it by more than 2^8 (rarely, after a row's first tile) does the reference move
+// to the running maximum, and the caller scales what it has accumulated.  No maximum is taken on the common path
+// (about 15 of the 75 vector instructions a tile would cost), and the result is the same: numerator and denominator
+// always share a reference.  NaN and infinite scores end up as they would with an eager maximum.
+constexpr float kLazySum = 256.0f;
+__device__ __forceinline__ void row_weights(const f32x16 &s, float c, float m, float (&e)[16], float &sum)
+{
+#pragma unroll
+    for (int r = 0; r < 16; ++r) e[r] = __builtin_amdgcn_exp2f(s[r] * c - m);
+    sum = e[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) sum += e[r];
+}
+// Moves m to the running maximum of the row and takes the weights again; returns the factor for the sums so far.
+__device__ __forceinline__ float move_reference(const f32x16 &s, float c, float &m, float (&e)[16], float &sum)
+{
+    float mx = s[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+    const float m_new = fmaxf(m, max_with_other_half(mx) * c);
+    const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+    m = m_new;
+    row_weights(s, c, m, e, sum);
+    return alpha;
+}
+
+// Plain workgroup barrier.  Tile loads are tracked by hand (vmcnt), LDS traffic of the compiler's own
+// instructions is complete once their results were consumed; the empty asm statements keep the
+// compiler from moving memory operations across the barrier.
+__device__ __forceinline__ void wg_barrier()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+template <int N>
+__device__ __forceinline__ void wait_vmcnt()
+{
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// The tiles of one (sequence, KV head) unit, cache tiles of 32 tokens followed by the in-block tile, dealt
+// out to `splits` pieces as evenly as whole tiles allow: the first `rem` pieces get one tile more, pieces
+// past the tile count get nothing, and the in-block tile (the unit's last) lands in the last piece that
+// has any.  A launch ends with its longest piece and the others cannot make up for it (a lone CU streams
+// no faster when its neighbours are done), so one tile of imbalance costs a whole tile's time.
+struct SplitCut {
+    int first;  // first tile of the piece (tile index in the unit)
+    int count;  // tiles in it, the in-block tile included if it is the unit's last piece
+    int live;   // pieces of this unit that have any tile
+};
+__host__ __device__ __forceinline__ SplitCut split_cut(int L, int splits, int split)
+{
+    const int total = ((L + 31) >> 5) + 1;  // cache tiles + the in-block tile
+    const int per = total / splits, rem = total - per * splits;
+    SplitCut c;
+    c.first = split * per + (split < rem ? split : rem);
+    c.count = per + (split < rem ? 1 : 0);
+    c.live = total < splits ? total : splits;
+    return c;
+}
+
+template <int D>
+struct AttnGeom {
+    static constexpr int CH = D / 8;          // 16-byte chunks per K/V row
+    static constexpr int ROWB = D * 2;        // bytes per K/V row
+    static constexpr int RPI = 64 / CH;       // rows per group = rows fetched by one wave-wide 16-byte load
+    static constexpr int NI = 32 / RPI;       // groups (= such loads) per 32-token K (or V) tile
+    static constexpr int GS = kGroupStride;   // LDS bytes between groups
+    static constexpr int TILE_B = NI * GS;    // one 32-token K (or V) tile in LDS
+    static constexpr int STAGE_B = 2 * TILE_B;
+    static constexpr int KSTEPS = D / 16;     // MFMA steps along d for S
+    static constexpr int DBLK = D / 32;       // 32-wide output blocks along d
+};
+
+
+// A pointer that is uniform by construction; readfirstlane keeps the compiler from carrying it in vector registers.
+__device__ __forceinline__ const void *uniform_ptr(const void *p)
+{
+    return (const void *)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uint64_t)p) |
+                          (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)((uint64_t)p >> 32)) << 32);
+}
+
+// Direct global->LDS load of 64 x 16 bytes: lane's bytes land at lds_addr + lane*16.  Issued through inline assembly so
+// that whole tiles can stay in flight while older ones are computed; completion is awaited explicitly with s_waitcnt
+// vmcnt (loads return in order).  M0 carries the LDS destination and is declared clobbered, so the compiler never
+// carries a value of its own in M0 across one of these statements (M0 is a reserved register, which clang remarks on
+// for any clobber list that names it; the remark is switched off for these files).
+//
+// NT selects the non-temporal form of the loads: when one call streams more K/V than the last-level cache holds,
+// nothing of it is there for the next call anyway, and loads that do not allocate on their way stream ~7 % faster
+// (measured); a working set that fits keeps the plain form, so that the second view's pass over the same cache still
+// finds it.
+template <class NT>
+__device__ __forceinline__ void dma16(NT, const uint16_t *gp, uint32_t lds_addr)
+{
+    if constexpr (NT::value)
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" : : "v"(gp), "s"(lds_addr) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(gp), "s"(lds_addr) : "memory", "m0");
+}
+
+// The same with a wave-uniform base and a 32-bit byte offset per lane.
+template <class NT>
+__device__ __forceinline__ void dma16s(NT, const uint16_t *base, uint32_t voff, uint32_t lds_addr)
+{
+    base = (const uint16_t *)uniform_ptr(base);
+    if constexpr (NT::value)
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" : : "v"(voff), "s"(base), "s"(lds_addr) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(base), "s"(lds_addr) : "memory", "m0");
+}
+
+// The loads of whole 16-token halves of a K or V tile (a half lies inside one page): a wave-uniform base (page, head,
+// token: scalar arithmetic on 32-bit byte strides) plus a loop-invariant byte offset per lane.  A half is GPH wave-wide
+// loads into groups GS bytes apart.  The instruction offset e*GS moves the LDS side and the memory side of load e
+// alike, so one M0 value serves the half and the lane offsets take e*GS back (the base is lowered by kBias so that
+// they stay positive).  One load costs the issuing wave two instructions instead of the ~11 of 64-bit arithmetic per load.
+template <int D>
+struct HalfLoads {
+    using Gm = AttnGeom<D>;
+    static constexpr int GPH = Gm::NI / 2;                 // loads per half
+    static constexpr uint32_t kBias = (GPH - 1) * Gm::GS;
+    uint32_t voff[GPH];
+    uint32_t page_bytes, tok_bytes, page_mask, num_pages;
+    uint32_t worst = 0;  // largest page id seen (as unsigned); an id past num_pages was read as page 0
+    bool usable;         // the strides fit the 32-bit arithmetic
+
+    __device__ __forceinline__ HalfLoads(const AttnArgs &a, int lane)
+    {
+        usable = a.stride_page < (1ll << 31) && a.stride_tok < (1ll << 30) >> a.page_shift;
+        page_bytes = (uint32_t)a.stride_page * 2u;
+        tok_bytes = (uint32_t)a.stride_tok * 2u;
+        page_mask = (1u << a.page_shift) - 1u;
+        num_pages = (uint32_t)min(a.num_pages, (int64_t)0x7fffffff);
+        const int tok = lane / Gm::CH, ch = lane % Gm::CH;
+#pragma unroll
+        for (int e = 0; e < GPH; ++e)
+            voff[e] = kBias - e * Gm::GS + (uint32_t)(tok + e * Gm::RPI) * tok_bytes + (uint32_t)((ch ^ xm<Gm::CH>(tok)) << 4);
+    }
+    // byte offset of token position `tok` (a multiple of 16) behind page id `id`
+    __device__ __forceinline__ uint64_t offset(int id, uint32_t tok)
+    {
+        worst = max(worst, (uint32_t)id);
+        const uint32_t pg = (uint32_t)id < num_pages ? (uint32_t)id : 0u;
+        return (uint64_t)pg * page_bytes + (tok & page_mask) * tok_bytes;
+    }
+    static __device__ __forceinline__ const char *lowered(const uint16_t *pool) { return (const char *)pool - kBias; }
+    template <class NT>
+    __device__ __forceinline__ void issue(NT, const char *base, uint32_t lds_addr) const
+    {
+        base = (const char *)uniform_ptr(base);
+        static_assert(Gm::GS == 1040 && (GPH == 4 || GPH == 2), "the instruction offsets below");
+        if constexpr (GPH == 4 && NT::value)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                         "global_load_lds_dwordx4 %2, %1 nt\n\tglobal_load_lds_dwordx4 %3, %1 offset:1040 nt\n\t"
+                         "global_load_lds_dwordx4 %4, %1 offset:2080 nt\n\tglobal_load_lds_dwordx4 %5, %1 offset:3120 nt"
+                         : : "s"(lds_addr), "s"(base), "v"(voff[0]), "v"(voff[1]), "v"(voff[GPH - 2]), "v"(voff[GPH - 1]) : "memory", "m0");
+        else if constexpr (GPH == 4)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                         "global_load_lds_dwordx4 %2, %1\n\tglobal_load_lds_dwordx4 %3, %1 offset:1040\n\t"
+                         "global_load_lds_dwordx4 %4, %1 offset:2080\n\tglobal_load_lds_dwordx4 %5, %1 offset:3120"
+                         : : "s"(lds_addr), "s"(base), "v"(voff[0]), "v"(voff[1]), "v"(voff[GPH - 2]), "v"(voff[GPH - 1]) : "memory", "m0");
+        else if constexpr (NT::value)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                         "global_load_lds_dwordx4 %2, %1 nt\n\tglobal_load_lds_dwordx4 %3, %1 offset:1040 nt"
+                         : : "s"(lds_addr), "s"(base), "v"(voff[0]), "v"(voff[1]) : "memory", "m0");
+        else
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                         "global_load_lds_dwordx4 %2, %1\n\tglobal_load_lds_dwordx4 %3, %1 offset:1040"
+                         : : "s"(lds_addr), "s"(base), "v"(voff[0]), "v"(voff[1]) : "memory", "m0");
+    }
+};
+
+// The 2*NI loads of a whole K/V tile whose rows are addressed lane by lane: row_off(u) is the byte offset of the row
+// that the lane fetches for group u, behind a uniform base per operand and half (a row's K and V share the offset).
+template <int D, class NT, class RowOff>
+__device__ __forceinline__ void issue_rows(NT nt, const uint16_t *const (&k)[2], const uint16_t *const (&v)[2], uint32_t lds_addr,
+                                           RowOff row_off)
+{
+    using Gm = AttnGeom<D>;
+#pragma unroll
+    for (int u = 0; u < Gm::NI; ++u) {
+        const int hf = u * Gm::RPI / 16;
+        const uint32_t off = row_off(u);
+        dma16s(nt, k[hf], off, lds_addr + u * Gm::GS);
+        dma16s(nt, v[hf], off, lds_addr + Gm::TILE_B + u * Gm::GS);
+    }
+}
+
+// The walk over a launch's work items as every wave of a workgroup sees it; the three forms are described at
+// attn_split_kernel.  Lengths and the page table are read-only for the whole launch and every index used here
+// is wave-uniform: reading them through the constant address space makes these scalar loads (s_load_dword),
+// which keeps them off the vector-memory counter that paces the tile loads.
+enum { kItemsSplit = 0, kItemsPrefill = 1, kItemsBalanced = 2 };
+
+template <int MODE>
+struct WorkItems {
+    int b, g;
+    int t_begin, t_end, n_cache, n_tiles;  // cache tokens [t_begin, t_end) in n_cache tiles; n_tiles adds the in-block tile
+    bool final_out;                        // this item holds every tile of its unit: write finished rows
+    size_t part_slot;                      // else: index of the partial it writes
+    int row0, rows_live;  // block rows of the item (prefill: first new-token index of the chunk, tokens in it)
+    int pos0;             // prefill: cache position of the chunk's first token
+    const const_i32 *pt_row;
+    int64_t head_off;
+    int bal_b, bal_g, bal_o, bal_left;  // balanced form: position in the launch's tile sequence
+
+    // validated length of sequence x (scalar)
+    __device__ __forceinline__ int seq_len(const AttnArgs &a, int x)
+    {
+        int L = ((const const_i32 *)a.seq_lens)[x];
+        if (L < 0 || L > a.max_seq_len) {
+            if (threadIdx.x == 0) atomicExch(a.err_word, -4);
+            L = L < 0 ? 0 : a.max_seq_len;
+        }
+        return __builtin_amdgcn_readfirstlane(L);  // wave-uniform by construction; keeps the loop control scalar
+    }
+
+    // Finds the workgroup's share (balanced form); the others need nothing.
+    __device__ __forceinline__ void start(const AttnArgs &a)
+    {
+        part_slot = 0;
+        row0 = 0;
+        rows_live = a.block_k;
+        pos0 = 0;
+        bal_left = 0;
+        if constexpr (MODE == kItemsBalanced) {
+            const int lane = threadIdx.x & 63;
+            // tiles of sequence x as a lane sees it (cache tiles + the in-block tile), 0 past the batch
+            auto lane_tiles = [&](int x) __attribute__((always_inline)) {
+                if (x >= a.batch) return 0;
+                int L = a.seq_lens[x];
+                L = L < 0 ? 0 : (L > a.max_seq_len ? a.max_seq_len : L);
+                return ((L + 31) >> 5) + 1;
+            };
+            int per_head = 0;  // tiles of one head's units
+            for (int x0 = 0; x0 < a.batch; x0 += 64) {
+                int n = lane_tiles(x0 + lane);
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1) n += __shfl_xor(n, off);
+                per_head += n;
+            }
+            per_head = __builtin_amdgcn_readfirstlane(per_head);
+            const int64_t total = (int64_t)per_head * a.num_kv_heads;
+            const int64_t nwg = total < (int64_t)gridDim.x ? total : (int64_t)gridDim.x;
+            if ((int64_t)blockIdx.x >= nwg) return;
+            const int64_t c0 = (int64_t)blockIdx.x * total / nwg, c1 = ((int64_t)blockIdx.x + 1) * total / nwg;
+            bal_left = __builtin_amdgcn_readfirstlane((int)(c1 - c0));
+            bal_g = __builtin_amdgcn_readfirstlane((int)(c0 / per_head));
+            const int r = (int)(c0 - (int64_t)bal_g * per_head);
+            // the sequence whose tiles contain offset r of the head: inclusive scan over 64 sequences at a time
+            int base = 0;
+            for (int x0 = 0; x0 < a.batch; x0 += 64) {
+                const int n = lane_tiles(x0 + lane);
+                int incl = n;
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const int up = __shfl_up(incl, off);
+                    if (lane >= off) incl += up;
+                }
+                const bool hit = n > 0 && base + incl - n <= r && r < base + incl;
+                const uint64_t mask = __ballot(hit);
+                if (mask) {
+                    const int src = __builtin_ctzll(mask);
+                    bal_b = x0 + src;
+                    bal_o = r - (base + __shfl(incl - n, src));
+                    break;
+                }
+                base += __shfl(incl, 63);
+            }
+            bal_b = __builtin_amdgcn_readfirstlane(bal_b);
+            bal_o = __builtin_amdgcn_readfirstlane(bal_o);
+        }
+    }
+
+    // Opens the next work item; false when the workgroup has none (left).
+    __device__ __forceinline__ bool open(const AttnArgs &a)
+    {
+        if constexpr (MODE == kItemsBalanced) {
+            if (bal_left <= 0) return false;
+            b = bal_b;
+            g = bal_g;
+            const int L = seq_len(a, b);
+            const int nc = (L + 31) >> 5;                    // cache tiles of the unit; the in-block tile is tile nc
+            const int take = min(nc + 1 - bal_o, bal_left);  // tiles of this segment
+            const bool has_blk = bal_o + take == nc + 1;
+            // (everything here is wave-uniform; readfirstlane keeps it in scalar registers)
+            n_tiles = __builtin_amdgcn_readfirstlane(take);
+            n_cache = has_blk ? n_tiles - 1 : n_tiles;
+            t_begin = __builtin_amdgcn_readfirstlane(bal_o * 32);
+            t_end = min(L, t_begin + n_cache * 32);
+            final_out = bal_o == 0 && has_blk;
+            part_slot = (size_t)(blockIdx.x * 2u + (bal_o == 0 ? 1u : 0u));
+            bal_left = __builtin_amdgcn_readfirstlane(bal_left - take);
+            bal_o = 0;
+            int nb = bal_b + 1, ng = bal_g;
+            if (nb == a.batch) {
+                nb = 0;
+                ++ng;
+            }
+            bal_b = __builtin_amdgcn_readfirstlane(nb);
+            bal_g = __builtin_amdgcn_readfirstlane(ng);
+        } else {
+            // Workgroup id -> (sequence, split, KV head) with the sequence index fastest and the head
+            // slowest.  Consecutive workgroup ids go to different XCDs; a head's rows sit at a fixed
+            // offset inside every page, so an order that ties XCD k to head k makes each XCD hammer its
+            // own subset of the HBM channels and the XCDs finish far apart.  (Prefill: the middle index
+            // is the chunk, longest first.)
+            b = (int)(blockIdx.x % (unsigned)a.batch);
+            int split;
+            if constexpr (MODE == kItemsPrefill) {
+                g = (int)((blockIdx.x / (unsigned)a.batch) % (unsigned)a.num_kv_heads);
+                split = (int)(blockIdx.x / ((unsigned)a.batch * (unsigned)a.num_kv_heads));
+            } else {
+                split = (int)((blockIdx.x / (unsigned)a.batch) % (unsigned)a.num_splits);
+                g = (int)(blockIdx.x / ((unsigned)a.batch * (unsigned)a.num_splits));
+            }
+            if constexpr (MODE == kItemsPrefill) {
+                // lengths as the planning kernel left them: validated, 0 new tokens on a capacity error
+                const int L0 = __builtin_amdgcn_readfirstlane(((const const_i32 *)a.old_lens)[b]);
+                const int n_new = __builtin_amdgcn_readfirstlane(((const const_i32 *)a.new_lens)[b]);
+                // every sequence's last chunk (the one with the most cache tokens) starts first
+                const int chunk = (n_new + a.chunk_tokens - 1) / a.chunk_tokens - 1 - split;
+                if (chunk < 0) return false;
+                row0 = chunk * a.chunk_tokens;
+                rows_live = min(a.chunk_tokens, n_new - row0);
+                pos0 = L0 + row0;
+                t_begin = 0;
+                t_end = pos0 + rows_live;  // everything up to the chunk's last token
+                n_cache = (t_end + 31) >> 5;
+                n_tiles = n_cache;
+                final_out = true;
+            } else {
+                const int L = seq_len(a, b);
+                // The sequence's own length, not the host's bound on it, is cut into num_splits pieces:
+                // they stay equal however loose the bound is (it only sized the grid), e.g. when a
+                // decode loop bumps it by K per step without reading back.
+                const SplitCut cut = split_cut(L, a.num_splits, split);
+                if (cut.count == 0) return false;  // fewer tiles than splits: nothing falls in this one
+                n_tiles = __builtin_amdgcn_readfirstlane(cut.count);
+                n_cache = split == cut.live - 1 ? n_tiles - 1 : n_tiles;  // the last piece ends with the in-block tile
+                t_begin = __builtin_amdgcn_readfirstlane(cut.first * 32);
+                t_end = min(L, t_begin + n_cache * 32);
+                final_out = a.num_splits == 1;
+                part_slot = ((size_t)b * a.num_kv_heads + g) * a.num_splits + split;
+            }
+        }
+        pt_row = (const const_i32 *)(a.page_table + (int64_t)b * a.max_pages_per_seq);
+        head_off = (int64_t)g * a.stride_head;
+        return true;
+    }
+};
+
+// Launch of one of a call's two kernels (kind 0: split, 1: combine), with its timing events attached when wanted.
+template <class Kern>
+inline hipError_t launch_timed(Kern kern, dim3 grid, dim3 block, size_t lds, const AttnArgs &a, hipStream_t stream,
+                               AttnLaunchEvents *ev, int kind)
+{
+    if (ev && ev->on) {
+        hipExtLaunchKernelGGL(kern, grid, block, lds, stream, ev->start[kind], ev->stop[kind], 0, a);
+        ev->used[kind] = true;
+    } else {
+        hipLaunchKernelGGL(kern, grid, block, lds, stream, a);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace orthrus

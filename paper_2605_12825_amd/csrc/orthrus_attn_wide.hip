@@ -1,0 +1,428 @@
+// The attention kernel for launches that are bound by arithmetic: prefill, and decode-mode batches with enough query
+// rows and units to fill the chip (the training block mask above all).  Same problem, MFMA forms, LDS tile layout,
+// masks and partials as attn_split_kernel (orthrus_attn.hip); what differs is how a CU is filled.
+//
+// Why: with 32 query rows per wave every 32-token tile costs a wave 16 KB of LDS reads for 512 cycles of matrix
+// instructions, and a wave's own chain (operand reads, scores, softmax, values) leaves the matrix cores idle for most
+// of it: 37 % busy in an 8192-token prefill with two such waves on each SIMD.  Here a wave owns 64 rows as two blocks
+// (one wave per SIMD, up to 512 registers), so an operand read serves two products, and the two blocks are half a tile
+// apart: while block 0's scores of tile i and values of tile i-1 go through the matrix cores, the vector unit takes
+// block 1's softmax of tile i-1, and the other way round in the second half ("slots").  Inside a slot every matrix
+// instruction is followed by its share of the softmax and of the LDS reads and loads, in written order
+// (sched_barrier): the compiler's own order keeps them apart.
+// Every wave issues its own share of the tile loads (a loader wave would halve the registers), NS-1 tiles ahead.
+//
+// What bounds it: issue.  A slot is 16 MFMA (512 cycles) next to ~60 vector, 8-16 LDS and ~22 scalar instructions of
+// one wave; about 1470 cycles per 64x32 tile against 1024 of matrix work, and at full load the clock drops from 2.3 to
+// 1.95 GHz.  Measured (32/8 heads, d = 128, 8192 new tokens): 666 -> 480 us per call, 1.2 PFLOP/s in this kernel against
+// 1.36 for the library's bf16 matrix product; ragged prefill at 28/4 heads 432 -> 340 us; training mask 859 -> 697 us.
+// Without any tile load the same loop takes 458 us, and 5, 6 or 9 ring stages make no difference.
+#include "orthrus_attn_dev.h"
+
+namespace orthrus {
+
+// D head_dim, W waves of 64 query rows, NS LDS stages, MODE the work items (kItemsSplit or kItemsPrefill), NT the
+// non-temporal form of loads and partials.
+template <int D, int W, int NS, int MODE, int NT = 0>
+__global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(const AttnArgs a)
+{
+    using Gm = AttnGeom<D>;
+    constexpr int CH = Gm::CH, ROWB = Gm::ROWB, RPI = Gm::RPI, NI = Gm::NI, GS = Gm::GS;
+    constexpr int TILE_B = Gm::TILE_B, STAGE_B = Gm::STAGE_B, KSTEPS = Gm::KSTEPS, DBLK = Gm::DBLK;
+    constexpr int LPW = 2 * NI / W;  // load instructions per tile and wave
+    static_assert(2 * NI % W == 0, "the waves share a tile's loads evenly");
+    constexpr int PG = 4 / W;  // of a tile's four 16-token halves (K, K, V, V), how many a wave loads
+    static_assert(W == 2 || W == 4, "a wave's halves stay within one operand");
+    static_assert(NS >= 4 && (NS - 3) * LPW < 64, "stage count");
+    static_assert(MODE == kItemsSplit || MODE == kItemsPrefill, "one work item per workgroup");
+    constexpr bool PREFILL = MODE == kItemsPrefill;
+    using NtTag = std::integral_constant<bool, NT != 0>;
+
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, h = lane >> 5;
+    const int K = a.block_k, G = a.group;
+    const int P = 1 << a.page_shift;
+    const uint32_t smem_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)smem;
+
+    WorkItems<MODE> w;
+    w.start(a);
+    if (!w.open(a)) return;
+
+    // ---- tile loads: a tile is four 16-token halves (K, K, V, V) and a wave loads PG of them, both of one operand
+    const int ld_tok = lane / CH;  // this lane's row inside one wave-wide load, and the byte offset of its chunk in that row
+    const uint32_t ld_swz = (uint32_t)(((lane % CH) ^ xm<CH>(ld_tok)) << 4);
+    HalfLoads<D> half(a, lane);
+    const int my_half = wave * PG % 2;
+    const bool my_v = wave * PG >= 2;
+    const uint32_t my_dst = (my_v ? TILE_B : 0) + my_half * half.GPH * GS;
+    const uint32_t dst_first = smem_lds + my_dst, dst_end = dst_first + NS * STAGE_B;
+    const uint16_t *my_operand = (my_v ? a.v_pool : a.k_pool) + w.head_off;
+    const char *my_pool = half.lowered(my_operand);
+    const int n_whole = half.usable ? min(w.n_cache, (w.t_end - w.t_begin) >> 5) : 0;  // tiles loaded a half at a time
+    uint32_t dst = dst_first;                                     // where the next tile to be issued goes
+    uint32_t page_at = (uint32_t)(w.t_begin + my_half * 16);      // token position of this wave's first half of that tile
+    int page[PG];                                                 // page ids of its halves
+    auto load_pages = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < PG; ++u) page[u] = w.pt_row[(page_at + u * 16u) >> a.page_shift];
+    };
+    auto advance = [&]() __attribute__((always_inline)) {
+        dst = dst + STAGE_B == dst_end ? dst_first : dst + STAGE_B;
+        page_at += 32;
+    };
+    // any tile t, outside the main loop
+    auto issue_tile = [&](int t) __attribute__((always_inline)) {
+        if (t < n_whole) {
+            load_pages();
+#pragma unroll
+            for (int u = 0; u < PG; ++u)
+                half.issue(NtTag{}, my_pool + half.offset(page[u], page_at + u * 16u), dst + u * half.GPH * GS);
+        } else if (PREFILL || t < w.n_cache) {
+            // the last, ragged cache tile: rows past the end repeat the last valid row (finite data, masked later), so
+            // nothing is fetched through an unmapped page and no LDS row is left undefined
+#pragma unroll 1
+            for (int e = 0; e < PG * half.GPH; ++e) {
+                const int tg = min((int)page_at + e * RPI + ld_tok, w.t_end - 1);
+                const int first = min((int)page_at + e * RPI / 16 * 16, w.t_end - 1);
+                const uint32_t id = (uint32_t)w.pt_row[first >> a.page_shift];  // (a load's rows lie in one page)
+                half.worst = max(half.worst, id);
+                const int64_t off = (int64_t)(id < half.num_pages ? id : 0u) * a.stride_page + (int64_t)(tg & (P - 1)) * a.stride_tok;
+                dma16(NtTag{}, my_operand + off + (ld_swz >> 1), dst + e * GS);
+            }
+        } else {
+            // the in-block tile; rows past the block repeat its last row
+            const uint16_t *blk = (my_v ? a.v_blk : a.k_blk) + (int64_t)w.b * K * a.blk_stride_row + (int64_t)w.g * a.blk_stride_head;
+#pragma unroll 1
+            for (int e = 0; e < PG * half.GPH; ++e)
+                dma16(NtTag{}, blk + (int64_t)min(my_half * 16 + e * RPI + ld_tok, K - 1) * a.blk_stride_row + (ld_swz >> 1), dst + e * GS);
+        }
+        advance();
+    };
+
+    // ---- lane-invariant LDS read offsets inside one stage
+    int kb[KSTEPS / 2];
+    {
+        const int r = col % RPI;
+#pragma unroll
+        for (int q = 0; q < KSTEPS / 2; ++q)
+            kb[q] = (col / RPI) * GS + r * ROWB + ((q ^ (xm<CH>(r) >> 2)) << 6) + (h << 4);
+    }
+    int vb[DBLK];
+    {
+        const int tok0 = 4 * h + ((lane & 15) >> 2);
+        const int r = tok0 % RPI;
+        const int tr_ch = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+#pragma unroll
+        for (int db = 0; db < DBLK; ++db)
+            vb[db] = TILE_B + (tok0 / RPI) * GS + r * ROWB + ((db ^ (xm<CH>(r) >> 2)) << 6) + (tr_ch << 4) + ((lane & 1) << 3);
+    }
+    const float c = a.scale_log2e;
+    // ---- pipeline fill
+#pragma unroll 1
+    for (int t = 0; t < NS - 1; ++t)
+        if (t < w.n_tiles) issue_tile(t);
+
+    // ---- queries: block x holds rows wave*64 + 32*x + col
+    Frag qf[2][KSTEPS];
+    int irow[2];
+    bool row_ok[2];
+    const int64_t row_base = PREFILL ? (int64_t)w.b * a.max_new + w.row0 : (int64_t)w.b * K;
+    const int rows = w.rows_live * G;
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        const int ridx = wave * 64 + x * 32 + col;
+        row_ok[x] = ridx < rows;
+        const int i = ridx / G, hl = ridx - i * G;
+        irow[x] = row_ok[x] ? i : w.rows_live - 1;
+        if (row_ok[x]) {
+            const uint16_t *qp = a.q + (row_base + i) * a.q_stride_row + ((int64_t)w.g * G + hl) * a.q_stride_head;
+#pragma unroll
+            for (int kk = 0; kk < KSTEPS; ++kk) qf[x][kk].u = *(const uint4 *)(qp + kk * 16 + h * 8);
+        } else {
+#pragma unroll
+            for (int kk = 0; kk < KSTEPS; ++kk) qf[x][kk].u = make_uint4(0, 0, 0, 0);
+        }
+    }
+    // tiles of this wave: n_full that every row sees whole, n_mine that any row sees
+    int n_full, n_mine;
+    if constexpr (PREFILL) {
+        const int i0 = wave * 64 / G;
+        const int i1 = min((wave * 64 + 63) / G, w.rows_live - 1);
+        n_full = i0 < w.rows_live ? (w.pos0 + i0 + 1) >> 5 : 0;
+        n_mine = i0 < w.rows_live ? ((w.pos0 + i1) >> 5) + 1 : 0;
+    } else {
+        n_full = (w.t_end - w.t_begin) >> 5;
+        n_mine = w.n_tiles;
+    }
+    auto limit = [&](int x, int i) __attribute__((always_inline)) -> int {
+        if constexpr (PREFILL) return w.pos0 + irow[x] + 1 - i * 32;
+        if (i < w.n_cache) return w.t_end - (w.t_begin + i * 32);
+        return a.view == 0 ? K : min(K, irow[x] + 1);
+    };
+
+    f32x16 o[2][DBLK], s[2];
+    float m[2], l[2];
+    Frag kf[KSTEPS], vf[DBLK][2], p[2][2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        m[x] = kNegBig;
+        l[x] = 0.f;
+        p[x][0].u = p[x][1].u = make_uint4(0, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[x][r] = -INFINITY;
+#pragma unroll
+        for (int db = 0; db < DBLK; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[x][db][r] = 0.f;
+    }
+    // LDS reads: one add per operand base, the rest are instruction offsets (the empty asm keeps them so)
+    auto read_k = [&](uint32_t st, int kk) __attribute__((always_inline)) {
+        uint32_t ad = st + kb[kk >> 1];
+        asm("" : "+v"(ad));
+        kf[kk].n = *(const lds_u32x4 *)(uintptr_t)(ad + ((kk & 1) << 5));
+    };
+    auto read_v = [&](uint32_t st, int db, int q2) __attribute__((always_inline)) {
+        uint32_t ad = st + vb[db];
+        asm("" : "+v"(ad));
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            vf[db][q2].h[q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                (lds_s16x4 *)(uintptr_t)(ad + (2 * q2 + q) * (8 / RPI) * GS));
+    };
+    constexpr int NCH = KSTEPS + 2 * DBLK;  // products of a slot
+    constexpr int JD = NCH == 16 ? 6 : 3;        // the slot's first tile load goes out here
+    static_assert(JD + LPW <= NCH, "");
+    constexpr int VPC = 16 / NCH;           // softmax values handled next to each of them
+    // One slot: the matrix work of block C (scores of tile i, values of tile i-1) next to the softmax of the other
+    // block's last scores, one product and VPC values at a time.  `extra(j)` adds the loads that go next to product j.
+    auto slot = [&](auto cb, auto masked, int lim, auto &&extra) __attribute__((always_inline)) {
+        constexpr int C = decltype(cb)::value, X = 1 - C;
+        f32x16 z;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) z[r] = 0.f;
+        float e[16], sum = 0.f;
+        f32x16 t;
+        uint32_t pk[8];
+        const float mref = m[X];
+#pragma unroll
+        for (int j = 0; j < NCH; ++j) {
+            if (j < KSTEPS) {
+                z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[j].v, qf[C][j].v, z, 0, 0, 0);
+            } else {
+                const int db = (j - KSTEPS) % DBLK, q2 = (j - KSTEPS) / DBLK;
+                o[C][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db][q2].v, p[C][q2].v, o[C][db], 0, 0, 0);
+            }
+            extra(j);
+#pragma unroll
+            for (int v = 0; v < VPC; ++v) {
+                const int r = j * VPC + v;
+                t[r] = s[X][r];
+                if constexpr (decltype(masked)::value) {
+                    const int tok = 8 * (r >> 2) + 4 * h + (r & 3);
+                    t[r] = tok >= lim ? -INFINITY : t[r];
+                }
+                e[r] = __builtin_amdgcn_exp2f(t[r] * c - mref);
+                if (r == 1) sum = e[0];
+                else if (r > 1) sum += e[r - 1];
+                if ((r & 1) && r >= 3) pk[(r - 3) / 2] = pack_bf16(e[r - 3], e[r - 2]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        sum += e[15];
+        pk[7] = pack_bf16(e[14], e[15]);
+        asm volatile("" : "+v"(sum), "+v"(pk[0]), "+v"(pk[1]), "+v"(pk[2]), "+v"(pk[3]), "+v"(pk[4]), "+v"(pk[5]), "+v"(pk[6]), "+v"(pk[7]));
+        if (__builtin_expect(__any(sum > kLazySum), 0)) {
+            const float alpha = move_reference(t, c, m[X], e, sum);
+            l[X] *= alpha;
+#pragma unroll
+            for (int db = 0; db < DBLK; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[X][db][r] *= alpha;
+#pragma unroll
+            for (int r = 1; r < 16; r += 2) pk[r / 2] = pack_bf16(e[r - 1], e[r]);
+        }
+        l[X] += sum;
+        p[X][0].u = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+        p[X][1].u = make_uint4(pk[4], pk[5], pk[6], pk[7]);
+        s[C] = z;
+    };
+    // The barrier inside tile i's step: tile i+1 has landed, the stage of tile i-1 is free and takes tile i+NS-1.
+    auto step_barrier = [&](int i) __attribute__((always_inline)) {
+        const int ahead = min(NS - 3, w.n_tiles - 2 - i);
+        if (ahead >= 3) wait_vmcnt<3 * LPW>();
+        else if (ahead == 2) wait_vmcnt<2 * LPW>();
+        else if (ahead == 1) wait_vmcnt<LPW>();
+        else wait_vmcnt<0>();
+        wg_barrier();
+        if (i + NS - 1 < w.n_tiles) issue_tile(i + NS - 1);
+    };
+    // tile 0 has landed
+    {
+        const int ahead = min(NS - 2, w.n_tiles - 1);
+        if (ahead >= 3) wait_vmcnt<3 * LPW>();
+        else if (ahead == 2) wait_vmcnt<2 * LPW>();
+        else if (ahead == 1) wait_vmcnt<LPW>();
+        else wait_vmcnt<0>();
+        wg_barrier();
+    }
+    uint32_t st = smem_lds, sv = smem_lds;  // stages of tiles i and i-1 (first pass: of tile 0, against zero weights)
+    auto next = [&](uint32_t x) __attribute__((always_inline)) { return x + STAGE_B == smem_lds + NS * STAGE_B ? smem_lds : x + STAGE_B; };
+#pragma unroll
+    for (int kk = 0; kk < KSTEPS; ++kk) read_k(st, kk);
+    auto tile = [&](auto fast, auto masked, int i) __attribute__((always_inline)) {
+        slot(std::integral_constant<int, 0>{}, masked, limit(1, i - 1), [&](int j) __attribute__((always_inline)) {
+            if (j < KSTEPS) read_v(sv, j % DBLK, j / DBLK);
+            if constexpr (decltype(fast)::value) {
+                if (j == NCH - 1) load_pages();
+            }
+        });
+        sv = st;
+        uint64_t off[PG];
+        slot(std::integral_constant<int, 1>{}, masked, limit(0, i), [&](int j) __attribute__((always_inline)) {
+            if constexpr (decltype(fast)::value) {
+                if (j == 0) {
+                    wait_vmcnt<(NS - 3) * LPW>();
+                    wg_barrier();
+                }
+                if (j == 1) st = next(st);
+#pragma unroll
+                for (int u = 0; u < PG; ++u) {
+                    if (j == JD - 1 - u) {
+                        off[u] = half.offset(page[u], page_at + u * 16u);
+                    }
+                    if (j == JD + 2 * u) half.issue(NtTag{}, my_pool + off[u], dst + u * half.GPH * GS);
+                }
+                if (j == NCH - 1) advance();
+            } else {
+                if (j == 0) {
+                    step_barrier(i);
+                    st = next(st);
+                }
+            }
+            if (j >= KSTEPS) read_k(st, j - KSTEPS);
+        });
+    };
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the queries are in registers before the loop starts
+    int i = 0;
+    const int n_fast = min(n_full, n_whole - (NS - 1));  // tiles whose step issues a whole tile
+    for (; i < n_fast; ++i) tile(std::true_type{}, std::false_type{}, i);
+    for (; i < n_full; ++i) tile(std::false_type{}, std::false_type{}, i);
+    for (; i < n_mine; ++i) tile(std::false_type{}, std::true_type{}, i);
+    // drain: the last tile's value products (its second block's softmax in between)
+#pragma unroll
+    for (int kk = 0; kk < KSTEPS; ++kk) read_v(sv, kk / 2, kk % 2);
+    slot(std::integral_constant<int, 0>{}, std::true_type{}, limit(1, n_mine - 1), [](int) {});
+#pragma unroll
+    for (int q2 = 0; q2 < 2; ++q2)
+#pragma unroll
+        for (int db = 0; db < DBLK; ++db)
+            o[1][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db][q2].v, p[1][q2].v, o[1][db], 0, 0, 0);
+    for (; i < w.n_tiles; ++i) step_barrier(i);
+
+    // ---- write-out
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        const float lt = sum_with_other_half(l[x]);
+        if (w.final_out) {
+            if (row_ok[x]) {
+                const int hl = wave * 64 + x * 32 + col - irow[x] * G;
+                const float inv = lt > 0.f ? 1.f / lt : 0.f;
+                uint16_t *op = a.out + ((row_base + irow[x]) * a.num_q_heads + (int64_t)w.g * G + hl) * D;
+#pragma unroll
+                for (int db = 0; db < DBLK; ++db)
+#pragma unroll
+                    for (int r4 = 0; r4 < 4; ++r4) {
+                        uint2 pk;
+                        pk.x = pack_bf16(o[x][db][4 * r4] * inv, o[x][db][4 * r4 + 1] * inv);
+                        pk.y = pack_bf16(o[x][db][4 * r4 + 2] * inv, o[x][db][4 * r4 + 3] * inv);
+                        *(uint2 *)(op + 32 * db + 8 * r4 + 4 * h) = pk;
+                    }
+                if (!PREFILL && a.lse && h == 0)
+                    a.lse[((int64_t)w.b * a.num_q_heads + (int64_t)w.g * G + hl) * K + irow[x]] =
+                        (m[x] + __builtin_amdgcn_logf(lt)) * 0.6931471805599453f;
+            }
+        } else {
+            const size_t slot = w.part_slot * a.part_blocks + 2 * wave + x;
+            f32x4 *po = (f32x4 *)a.part_o + slot * (DBLK * 4 * 64) + lane;
+#pragma unroll
+            for (int db = 0; db < DBLK; ++db)
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4) {
+                    const f32x4 v = {o[x][db][4 * r4], o[x][db][4 * r4 + 1], o[x][db][4 * r4 + 2], o[x][db][4 * r4 + 3]};
+                    if (NT) __builtin_nontemporal_store(v, &po[(db * 4 + r4) * 64]);
+                    else po[(db * 4 + r4) * 64] = v;
+                }
+            if (h == 0) ((float2 *)a.part_ml)[slot * 32 + col] = make_float2(m[x], lt);
+        }
+    }
+    if (half.worst >= half.num_pages && lane == 0) atomicExch(a.err_word, -4);
+}
+
+// ---------------------------------------------------------------------------------------------
+// host side
+
+// LDS ring stages: four waves have the CU's LDS to themselves, two workgroups of two waves share it
+constexpr int wide_stages(int W) { return W == 4 ? 6 : 4; }
+
+size_t attn_wide_lds(int waves, int head_dim)
+{
+    return (size_t)wide_stages(waves) * (head_dim == 128 ? AttnGeom<128>::STAGE_B : AttnGeom<64>::STAGE_B);
+}
+
+// Decode mode: worth it when the waves' rows are nearly all real (7/8) and the units alone put a wave on every SIMD.
+// Both sides of the line, attn_split_kernel -> this kernel: training mask with 8192 units of 128 rows 857 -> 697 us, of
+// 96 rows 626 -> 640; 64 sequences of 2000 tokens, 512 units of 128 rows 102 -> 90; 32 of 4000, 256 units 93 -> 97;
+// 256 units of 256 rows 79 -> 74; 8 units cut into 32 splits each 45 -> 54.
+bool attn_wide_pays(int rows, int64_t units, int num_cus)
+{
+    const int waves = rows > 128 ? 4 : 2;
+    return 8 * rows >= 7 * 64 * waves && units * waves >= 4 * (int64_t)num_cus;
+}
+
+template <int D, int W>
+static auto wide_decode_kernel(int nt)
+{
+    return nt ? attn_wide_kernel<D, W, wide_stages(W), kItemsSplit, 1> : attn_wide_kernel<D, W, wide_stages(W), kItemsSplit, 0>;
+}
+
+hipError_t launch_attn_wide(const AttnArgs &a, const AttnPlan &plan, int head_dim, dim3 grid, hipStream_t stream, AttnLaunchEvents *ev)
+{
+    auto kern = head_dim == 128 ? (plan.waves == 4 ? wide_decode_kernel<128, 4>(plan.kv_nt) : wide_decode_kernel<128, 2>(plan.kv_nt))
+                                : (plan.waves == 4 ? wide_decode_kernel<64, 4>(plan.kv_nt) : wide_decode_kernel<64, 2>(plan.kv_nt));
+    return launch_timed(kern, grid, dim3(64 * plan.waves), plan.lds_bytes, a, stream, ev, 0);
+}
+
+template <int D, int W>
+static hipError_t launch_prefill_wide(AttnArgs a, hipStream_t stream)
+{
+    a.chunk_tokens = 64 * W / a.group;
+    a.rows = 64 * W;
+    a.num_splits = (a.max_new + a.chunk_tokens - 1) / a.chunk_tokens;
+    dim3 grid((unsigned)a.num_splits * (unsigned)a.num_kv_heads * (unsigned)a.batch);
+    hipLaunchKernelGGL((attn_wide_kernel<D, W, wide_stages(W), kItemsPrefill>), grid, dim3(64 * W), attn_wide_lds(W, D), stream, a);
+    return hipGetLastError();
+}
+
+// Prefill forms.  While the launch leaves SIMDs idle a 32-row wave with its own loader is the faster chain (0.55 us per
+// tile against 0.65 us for twice the rows): up to one such wave per SIMD, two workgroups per CU and four waves per
+// workgroup attn_split_kernel's prefill form stays (1024 new tokens, group 4: 38 against 45 us; 2048: 92 against 69).
+// Otherwise four waves per workgroup once every CU gets two of them, else two waves for the finer grain
+// (8 sequences of 333 tokens: 38 against 42 us; d = 64 is faster with four throughout, 40 against 47 us).
+hipError_t launch_prefill_attn(const AttnArgs &a, int head_dim, int num_cus, hipStream_t stream)
+{
+    if (a.batch == 0 || a.max_new == 0) return hipSuccess;
+    const int64_t units = (int64_t)a.batch * a.num_kv_heads;
+    const int64_t items32 = units * ((a.max_new + 31) / 32);
+    if (a.group <= 4 && items32 <= 2 * num_cus && items32 * a.group <= 4 * num_cus)
+        return launch_prefill_split(a, head_dim, stream);
+    const int chunk = 256 / a.group;
+    const int64_t items = units * ((a.max_new + chunk - 1) / chunk);
+    if (head_dim == 128)
+        return items < 2 * num_cus ? launch_prefill_wide<128, 2>(a, stream) : launch_prefill_wide<128, 4>(a, stream);
+    if (head_dim == 64) return launch_prefill_wide<64, 4>(a, stream);
+    return hipErrorInvalidValue;
+}
+
+}  // namespace orthrus

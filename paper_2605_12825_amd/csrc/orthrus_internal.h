@@ -10,8 +10,10 @@ constexpr float kNegBig = -1.0e30f;
 
 struct AttnPlan {
     int rows;          // R = G * K query rows per KV head
-    int waves;         // compute waves per workgroup = 32-row blocks (1 .. 8)
-    int rows_padded;   // waves * 32
+    bool wide;         // 64 rows per wave (attn_wide_kernel) instead of 32
+    int waves;         // compute waves per workgroup
+    int row_blocks;    // 32-row blocks a partial holds
+    int rows_padded;   // row_blocks * 32
     int chunk_tokens;  // cache tokens per split at the host bound (the kernels cut each sequence by its own length)
     int num_splits;    // splits per (sequence, KV head)
     int bal_wgs;       // > 0: balanced partition over this many workgroups instead of fixed splits
@@ -38,6 +40,7 @@ struct AttnArgs {
     int64_t q_stride_row, q_stride_head, blk_stride_row, blk_stride_head;
     int batch, num_q_heads, num_kv_heads, group, block_k, rows;
     int page_shift, max_pages_per_seq, max_seq_len, chunk_tokens, num_splits, view;
+    int part_blocks;  // 32-row blocks a partial holds
     int bal_wgs;  // balanced partition: workgroups of the split launch (0 otherwise)
     int kv_nt;    // non-temporal K/V tile loads (see AttnPlan)
     float scale_log2e;  // sm_scale * log2(e)
@@ -167,7 +170,12 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
                      int requested_splits, int num_cus, int num_layers, AttnPlan *plan);
 hipError_t launch_attn(const AttnArgs &a, const AttnPlan &plan, int head_dim, hipStream_t stream,
                        AttnLaunchEvents *events = nullptr);
-hipError_t launch_prefill_attn(const AttnArgs &a, int head_dim, hipStream_t stream);
+// The 64-rows-per-wave kernel: whether it is the better one for these rows, its LDS need, its launch (grid from the plan).
+bool attn_wide_pays(int rows, int64_t units, int num_cus);
+size_t attn_wide_lds(int waves, int head_dim);
+hipError_t launch_attn_wide(const AttnArgs &a, const AttnPlan &plan, int head_dim, dim3 grid, hipStream_t stream, AttnLaunchEvents *events);
+hipError_t launch_prefill_attn(const AttnArgs &a, int head_dim, int num_cus, hipStream_t stream);
+hipError_t launch_prefill_split(const AttnArgs &a, int head_dim, hipStream_t stream);
 hipError_t launch_consensus(const ConsensusArgs &a, hipStream_t stream);
 hipError_t launch_sampling_consensus(const SamplingArgs &a, hipStream_t stream);
 int consensus_chunk_elems();

@@ -1,0 +1,103 @@
+"""The 64-rows-per-wave attention kernel (the one for launches that fill the chip) against the oracle: decode-mode
+batches and prefill at the smallest launches that take it, with lengths on both sides of every tile and ring edge.
+Same bars as every other attention parity test."""
+import numpy as np
+import pytest
+
+import oracle
+from orthrus_inputs import Workload, make_block, make_cache
+
+from test_gpu_parity import AR, DIFF, GpuCase, _check_attn, _oracle_attn
+from test_gpu_prefill import Case, _check, _new_tokens
+
+pytestmark = pytest.mark.gpu
+
+# empty, inside / at / past a tile, and past the LDS ring (4 or 6 stages of 32 tokens)
+EDGES = [0, 1, 31, 32, 33, 63, 64, 96, 127, 128, 129, 160, 161, 191, 192, 193, 224, 255, 257, 300]
+
+
+def _lens(n, seed):
+    rng = np.random.default_rng(seed)
+    return rng.permutation(np.concatenate((EDGES, rng.integers(0, 301, size=n)))[:max(n, len(EDGES))])[:n].astype(np.int32)
+
+
+@pytest.mark.parametrize("view", [DIFF, AR])
+@pytest.mark.parametrize("g,K,hkv,batch,d,page", [
+    (4, 32, 8, 64, 128, 16),     # 128 rows, two waves, full
+    (7, 16, 8, 64, 128, 32),     # 112 rows: the second wave's last block ends in padding
+    (8, 32, 4, 64, 128, 16),     # 256 rows, four waves
+    (7, 32, 4, 64, 128, 64),     # 224 rows: a block of padding
+    (8, 16, 8, 64, 64, 16),
+    (8, 31, 4, 64, 64, 16),
+])
+def test_decode_batches_that_fill_the_chip(g, K, hkv, batch, d, page, view):
+    w = Workload(name="wide", seed=8100 + g * K + d, batch=batch, num_q_heads=g * hkv, num_kv_heads=hkv, head_dim=d,
+                 block_k=K, context=300, page_size=page, paging="scattered")
+    cache = make_cache(w, seq_lens=_lens(batch, 8200 + K))
+    blk = make_block(w, 8300 + K)
+    case = GpuCase(w, cache, max_seq_len=300)
+    got, lse = case.attn(view, blk)
+    want, want_lse = _oracle_attn(view, w, blk, cache, want_lse=True)
+    _check_attn(got, want)
+    np.testing.assert_allclose(lse, want_lse, rtol=0, atol=2e-3)
+    assert case.step.device_error() == 0
+    again, _ = case.attn(view, blk)
+    np.testing.assert_array_equal(again, got)
+    case.step.close()
+
+
+@pytest.mark.parametrize("g,hkv,batch,d,T", [
+    (4, 8, 64, 128, 70),         # 64 tokens x 4 heads per workgroup: one full and one short chunk
+    (1, 8, 70, 128, 40),
+    (7, 8, 40, 128, 75),         # 36 tokens x 7 heads: 252 of 256 rows
+    (5, 2, 3, 128, 90),          # two waves: 25 tokens x 5 heads
+    (8, 2, 3, 64, 90),
+])
+def test_prefill_that_fills_the_chip(g, hkv, batch, d, T):
+    w = Workload(name="widep", seed=8400 + g, batch=batch, num_q_heads=g * hkv, num_kv_heads=hkv, head_dim=d, block_k=8,
+                 context=300, page_size=16, paging="shuffled", steps=(T + 7) // 8 + 1)
+    cache = make_cache(w, seq_lens=_lens(batch, 8500 + g))
+    rng = np.random.default_rng(8600 + g)
+    new_lens = rng.integers(0, T + 1, size=batch).astype(np.int32)
+    new_lens[:3] = (T, 0, 1)
+    q, kn, vn = _new_tokens(w, T, 8700 + g)
+    ref_k, ref_v, ref_l = cache["k_pool"].copy(), cache["v_pool"].copy(), cache["seq_lens"].copy()
+    want, _ = oracle.prefill_attn(w.sm_scale, q, kn, vn, new_lens, ref_k, ref_v, cache["page_table"], ref_l)
+    case = Case(w, cache, max_seq_len=int(cache["seq_lens"].max()) + T)
+    got = case.prefill(q, kn, vn, new_lens)
+    _check(got, want, new_lens)
+    k, v, l = case.state()
+    np.testing.assert_array_equal(l, ref_l)
+    np.testing.assert_array_equal(k, ref_k)
+    np.testing.assert_array_equal(v, ref_v)
+    assert case.step.device_error() == 0
+    case.step.close()
+
+
+@pytest.mark.parametrize("batch,hkv,K", [(2, 2, 8), (64, 8, 32)])
+def test_pool_strides_past_32_bit_byte_arithmetic(batch, hkv, K):
+    """Pages of 2^23 tokens (only their first rows exist): an in-page offset no longer fits the kernels' 32-bit byte
+    arithmetic, which their general address form has to take over, in both attention kernels."""
+    d, rows, L = 128, 320, 290
+    w = Workload(name="huge", seed=8800 + batch, batch=batch, num_q_heads=4 * hkv, num_kv_heads=hkv, head_dim=d, block_k=K,
+                 context=L, page_size=rows, paging="contiguous", steps=0)
+    lens = _lens(batch, 8900)
+    rng = np.random.default_rng(8901)
+    mk = lambda *s: (rng.standard_normal(s, dtype=np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    k_pool, v_pool = mk(batch, hkv, rows, d), mk(batch, hkv, rows, d)
+    cache = dict(k_pool=k_pool, v_pool=v_pool, page_table=np.arange(batch, dtype=np.int32)[:, None], seq_lens=np.minimum(lens, L))
+    blk = make_block(w, 8902)
+    from paper_2605_12825_amd import runtime as rt
+    import torch
+    step = rt.DecodeStep(batch=batch, num_q_heads=4 * hkv, num_kv_heads=hkv, head_dim=d, block_k=K, page_size=1 << 23,
+                         max_pages_per_seq=1, max_seq_len=L, num_pages=batch, pool_strides=(0, hkv * rows * d, rows * d, d))
+    D = rt.to_device_bits
+    out = torch.zeros((batch, K, 4 * hkv, d), dtype=torch.int16, device="cuda")
+    step.attn(AR, D(blk["q"]), D(blk["k_blk"]), D(blk["v_blk"]), D(k_pool), D(v_pool), D(cache["page_table"]),
+              D(cache["seq_lens"]), out)
+    torch.cuda.synchronize()
+    from orthrus_inputs import bf16_bits_to_f32
+    got = bf16_bits_to_f32(rt.bits_to_numpy(out)).astype(np.float64)
+    _check_attn(got, _oracle_attn(AR, w, blk, cache))
+    assert step.device_error() == 0
+    step.close()
