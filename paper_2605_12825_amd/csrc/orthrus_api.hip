@@ -167,7 +167,6 @@ orthrus::AttnArgs decode_attn_args(const orthrus_ctx *ctx, const orthrus_params 
     a.group = p->num_q_heads / p->num_kv_heads; a.block_k = p->block_k; a.rows = plan.rows;
     a.page_shift = log2_exact(p->page_size); a.max_pages_per_seq = p->max_pages_per_seq;
     a.max_seq_len = p->max_seq_len; a.chunk_tokens = plan.chunk_tokens; a.num_splits = plan.num_splits;
-    a.part_blocks = plan.row_blocks;
     a.bal_wgs = plan.bal_wgs;
     a.kv_nt = plan.kv_nt;
     a.view = view;
@@ -410,7 +409,7 @@ orthrus_status orthrus_prefill_attn(orthrus_ctx *ctx, const orthrus_params *p, i
     a.group = group; a.block_k = 32; a.rows = 32 * group;
     a.page_shift = f.page_shift; a.max_pages_per_seq = p->max_pages_per_seq;
     a.max_seq_len = p->max_seq_len; a.chunk_tokens = 0; a.num_splits = 0;  // the launcher picks the chunks
-    a.part_blocks = 0; a.bal_wgs = 0;
+    a.bal_wgs = 0;
     a.kv_nt = 0;  // every chunk of a sequence re-reads the same cache rows: keep them cached
     a.view = (int)ORTHRUS_VIEW_AR_VERIFY;
     a.scale_log2e = p->sm_scale * 1.4426950408889634f;

@@ -1,6 +1,6 @@
 // The attention kernel for launches that are bound by arithmetic: prefill, and decode-mode batches with enough query
-// rows and units to fill the chip (the training block mask above all).  Same problem, MFMA forms, LDS tile layout,
-// masks and partials as attn_split_kernel (orthrus_attn.hip); what differs is how a CU is filled.
+// rows and units to fill the chip (the training block mask above all).  Same problem, MFMA forms, LDS tile layout
+// and masks as attn_split_kernel, never split along the keys (orthrus_attn.hip); what differs is how a CU is filled.
 //
 // Why: with 32 query rows per wave every 32-token tile costs a wave 16 KB of LDS reads for 512 cycles of matrix
 // instructions, and a wave's own chain (operand reads, scores, softmax, values) leaves the matrix cores idle for most
@@ -22,7 +22,7 @@
 namespace orthrus {
 
 // D head_dim, W waves of 64 query rows, NS LDS stages, MODE the work items (kItemsSplit or kItemsPrefill), NT the
-// non-temporal form of loads and partials.
+// non-temporal form of the tile loads.
 template <int D, int W, int NS, int MODE, int NT = 0>
 __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(const AttnArgs a)
 {
@@ -321,41 +321,26 @@ __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(const AttnArgs a)
             o[1][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db][q2].v, p[1][q2].v, o[1][db], 0, 0, 0);
     for (; i < w.n_tiles; ++i) step_barrier(i);
 
-    // ---- write-out
+    // ---- write-out (every workgroup holds all of its rows' keys)
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
         const float lt = sum_with_other_half(l[x]);
-        if (w.final_out) {
-            if (row_ok[x]) {
-                const int hl = wave * 64 + x * 32 + col - irow[x] * G;
-                const float inv = lt > 0.f ? 1.f / lt : 0.f;
-                uint16_t *op = a.out + ((row_base + irow[x]) * a.num_q_heads + (int64_t)w.g * G + hl) * D;
+        if (!row_ok[x]) continue;
+        const int hl = wave * 64 + x * 32 + col - irow[x] * G;
+        const float inv = lt > 0.f ? 1.f / lt : 0.f;
+        uint16_t *op = a.out + ((row_base + irow[x]) * a.num_q_heads + (int64_t)w.g * G + hl) * D;
 #pragma unroll
-                for (int db = 0; db < DBLK; ++db)
+        for (int db = 0; db < DBLK; ++db)
 #pragma unroll
-                    for (int r4 = 0; r4 < 4; ++r4) {
-                        uint2 pk;
-                        pk.x = pack_bf16(o[x][db][4 * r4] * inv, o[x][db][4 * r4 + 1] * inv);
-                        pk.y = pack_bf16(o[x][db][4 * r4 + 2] * inv, o[x][db][4 * r4 + 3] * inv);
-                        *(uint2 *)(op + 32 * db + 8 * r4 + 4 * h) = pk;
-                    }
-                if (!PREFILL && a.lse && h == 0)
-                    a.lse[((int64_t)w.b * a.num_q_heads + (int64_t)w.g * G + hl) * K + irow[x]] =
-                        (m[x] + __builtin_amdgcn_logf(lt)) * 0.6931471805599453f;
+            for (int r4 = 0; r4 < 4; ++r4) {
+                uint2 pk;
+                pk.x = pack_bf16(o[x][db][4 * r4] * inv, o[x][db][4 * r4 + 1] * inv);
+                pk.y = pack_bf16(o[x][db][4 * r4 + 2] * inv, o[x][db][4 * r4 + 3] * inv);
+                *(uint2 *)(op + 32 * db + 8 * r4 + 4 * h) = pk;
             }
-        } else {
-            const size_t slot = w.part_slot * a.part_blocks + 2 * wave + x;
-            f32x4 *po = (f32x4 *)a.part_o + slot * (DBLK * 4 * 64) + lane;
-#pragma unroll
-            for (int db = 0; db < DBLK; ++db)
-#pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    const f32x4 v = {o[x][db][4 * r4], o[x][db][4 * r4 + 1], o[x][db][4 * r4 + 2], o[x][db][4 * r4 + 3]};
-                    if (NT) __builtin_nontemporal_store(v, &po[(db * 4 + r4) * 64]);
-                    else po[(db * 4 + r4) * 64] = v;
-                }
-            if (h == 0) ((float2 *)a.part_ml)[slot * 32 + col] = make_float2(m[x], lt);
-        }
+        if (!PREFILL && a.lse && h == 0)
+            a.lse[((int64_t)w.b * a.num_q_heads + (int64_t)w.g * G + hl) * K + irow[x]] =
+                (m[x] + __builtin_amdgcn_logf(lt)) * 0.6931471805599453f;
     }
     if (half.worst >= half.num_pages && lane == 0) atomicExch(a.err_word, -4);
 }

@@ -12,8 +12,7 @@ struct AttnPlan {
     int rows;          // R = G * K query rows per KV head
     bool wide;         // 64 rows per wave (attn_wide_kernel) instead of 32
     int waves;         // compute waves per workgroup
-    int row_blocks;    // 32-row blocks a partial holds
-    int rows_padded;   // row_blocks * 32
+    int rows_padded;   // rows in whole 32-row blocks
     int chunk_tokens;  // cache tokens per split at the host bound (the kernels cut each sequence by its own length)
     int num_splits;    // splits per (sequence, KV head)
     int bal_wgs;       // > 0: balanced partition over this many workgroups instead of fixed splits
@@ -40,7 +39,6 @@ struct AttnArgs {
     int64_t q_stride_row, q_stride_head, blk_stride_row, blk_stride_head;
     int batch, num_q_heads, num_kv_heads, group, block_k, rows;
     int page_shift, max_pages_per_seq, max_seq_len, chunk_tokens, num_splits, view;
-    int part_blocks;  // 32-row blocks a partial holds
     int bal_wgs;  // balanced partition: workgroups of the split launch (0 otherwise)
     int kv_nt;    // non-temporal K/V tile loads (see AttnPlan)
     float scale_log2e;  // sm_scale * log2(e)
