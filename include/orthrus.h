@@ -266,7 +266,7 @@ orthrus_status orthrus_consensus_commit_noalloc(orthrus_ctx *ctx, const orthrus_
  *   remaining arguments as in orthrus_consensus_commit; workspace at least
  *   orthrus_sampling_workspace_bytes(p)
  *
- * Arithmetic is fp32 (log-sum-exp per 8192-element chunk, merged in chunk order); a decision whose
+ * Arithmetic is fp32 (log-sum-exp per 8192-element chunk, merged in a fixed order); a decision whose
  * two sides differ by less than fp32 rounding of the log-sum-exp may fall either way.
  */
 orthrus_status orthrus_sampling_consensus_commit(orthrus_ctx *ctx, const orthrus_params *p, float temperature,

@@ -5,13 +5,13 @@
 //   argmax_partial_kernel  grid (row * chunks + chunk): each workgroup scans one chunk of one logits
 //                          row with 16-byte loads and reduces (value, index) through wavefront
 //                          shuffles; one (value, index) pair per chunk goes to the workspace.
-//   accept_commit_kernel   grid (sequence): the four waves finish the K row argmaxes (chunk pairs spread
-//                          over the lanes, wavefront-shuffle reduction), the first wave finds the
-//                          accepted prefix with a wavefront ballot, writes tokens/lengths and checks
-//                          that the appended positions are mapped; then the whole workgroup copies
-//                          the appended K/V rows into their pages (up to kInlineLayers layers).
-//   commit_kernel          grid (sequence, layer): the same copy as its own launch when there are
-//                          more layers than one workgroup should copy.
+//   accept_commit_kernel   grid (sequence, layer): the four waves finish the K row argmaxes (chunk pairs
+//                          spread over the lanes, wavefront-shuffle reduction), the first wave finds the
+//                          accepted prefix with a wavefront ballot and checks that the appended positions
+//                          are mapped; then the workgroup copies its layer's appended K/V rows into their
+//                          pages.  The workgroup of layer 0 writes tokens and lengths.  (Every layer's
+//                          workgroup repeats the few microseconds of the decision: a third launch that copies
+//                          by it cost 4 to 7 us.)
 // (A single-launch variant in which the last-arriving workgroup of a sequence finishes the job was
 // measured and dropped: the device-scope release/acquire fences it needs per workgroup cost far
 // more than the two extra launches.)
@@ -89,8 +89,6 @@ __device__ __forceinline__ void wave_best(float &bv, int &bi)
     }
 }
 
-constexpr int kInlineLayers = 2;
-
 __global__ void __launch_bounds__(256) argmax_partial_kernel(const ConsensusArgs a)
 {
     const int row = blockIdx.x / a.chunks, chunk = blockIdx.x - row * a.chunks;
@@ -100,38 +98,36 @@ __global__ void __launch_bounds__(256) argmax_partial_kernel(const ConsensusArgs
     const int end = min(a.vocab, begin + a.chunk_elems);
     float bv = -INFINITY;
     int bi = 0x7fffffff;
-    // 16-byte loads need the row start aligned; rows are 4*vocab bytes apart
-    const bool vec_ok = ((a.vocab & 3) == 0) && ((((uintptr_t)a.ar_logits) & 15) == 0);
-    if (vec_ok) {
-        // begin is a multiple of 4 (chunk_elems is); end too since vocab is.  All of a thread's loads of
-        // the chunk go out before the first comparison (kChunkElems / 1024 = 8 loads of 16 bytes).
-        constexpr int NL = kChunkElems / (256 * 4);
-        float4 x[NL];
+    if (a.do_commit && tid == 0 && chunk == 0 && row % a.block_k == 0) commit_snapshot(a, row / a.block_k);
+    // The 16-byte aligned middle of the chunk, all of a thread's loads before the first comparison (kChunkElems / 1024
+    // = 8 of 16 bytes), and up to three elements on either side of it (a row starts anywhere when the vocabulary is
+    // not a multiple of four; element by element such a scan took three times as long).
+    const int head = min((int)((0 - ((uintptr_t)(base + begin) >> 2)) & 3), end - begin);
+    const int mid = begin + head, nvec = (end - mid) >> 2, tail = mid + 4 * nvec;
+    constexpr int NL = kChunkElems / (256 * 4);
+    float4 x[NL];
 #pragma unroll
-        for (int u = 0; u < NL; ++u) {
-            const int i = begin + (u * 256 + tid) * 4;
-            x[u] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-            if (i < end) {  // read once, never again: do not let the row displace anything in the caches
-                const f32x4 v = __builtin_nontemporal_load((const f32x4 *)(base + i));
-                x[u] = make_float4(v[0], v[1], v[2], v[3]);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < NL; ++u) {
-            const int i = begin + (u * 256 + tid) * 4;
-            if (i < end) {
-                if (bi == 0x7fffffff) { bv = x[u].x; bi = i; } else take_later(x[u].x, i, bv, bi);
-                take_later(x[u].y, i + 1, bv, bi);
-                take_later(x[u].z, i + 2, bv, bi);
-                take_later(x[u].w, i + 3, bv, bi);
-            }
-        }
-    } else {
-        for (int i = begin + tid; i < end; i += 256) {
-            const float x = base[i];
-            if (bi == 0x7fffffff) { bv = x; bi = i; } else take_later(x, i, bv, bi);
+    for (int u = 0; u < NL; ++u) {
+        const int v = u * 256 + tid;
+        x[u] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+        if (v < nvec) {  // read once, never again: do not let the row displace anything in the caches
+            const f32x4 t = __builtin_nontemporal_load((const f32x4 *)(base + mid) + v);
+            x[u] = make_float4(t[0], t[1], t[2], t[3]);
         }
     }
+    const int edge = tid < 4 ? (tid < head ? begin + tid : end) : tid < 8 ? tail + tid - 4 : end;
+    const float xe = edge < end ? base[edge] : -INFINITY;
+#pragma unroll
+    for (int u = 0; u < NL; ++u) {
+        const int i = mid + (u * 256 + tid) * 4;
+        if (u * 256 + tid < nvec) {
+            if (bi == 0x7fffffff) { bv = x[u].x; bi = i; } else take_later(x[u].x, i, bv, bi);
+            take_later(x[u].y, i + 1, bv, bi);
+            take_later(x[u].z, i + 2, bv, bi);
+            take_later(x[u].w, i + 3, bv, bi);
+        }
+    }
+    if (edge < end && outranks(xe, edge, bv, bi)) { bv = xe; bi = edge; }
     wave_best(bv, bi);
     __shared__ float sv[4];
     __shared__ int si[4];
@@ -148,7 +144,8 @@ __global__ void __launch_bounds__(256) argmax_partial_kernel(const ConsensusArgs
 
 __global__ void __launch_bounds__(256) accept_commit_kernel(const ConsensusArgs a)
 {
-    const int b = blockIdx.x, tid = threadIdx.x;
+    const int b = blockIdx.x, layer = blockIdx.y, tid = threadIdx.x;
+    const bool lead = layer == 0;
     const int K = a.block_k;
     __shared__ int s_L, s_m;
     __shared__ int s_am[32], s_pg[32];
@@ -204,33 +201,26 @@ __global__ void __launch_bounds__(256) accept_commit_kernel(const ConsensusArgs 
         const unsigned long long mism = ~__ballot(match);           // lanes >= K never match
         const int n_acc = mism ? __ffsll((long long)mism) - 1 : 64;  // first mismatching row (<= K)
         const int m = min(n_acc + 1, K);
-        if (lane < K) a.out_tokens[(int64_t)b * K + lane] = lane < m ? am : -1;
+        if (lead && lane < K) a.out_tokens[(int64_t)b * K + lane] = lane < m ? am : -1;
         const int anchor = __shfl(am, m - 1);
         int committed = m;
         if (a.do_commit) {
-            committed = commit_decide(a, b, lane, m, probe);
+            committed = commit_decide(a, b, lane, m, probe, lead);
             if (lane < K) s_pg[lane] = probe.pg;
         }
         if (lane == 0) {
-            a.accept_len[b] = n_acc;
-            a.num_committed[b] = committed;
-            a.next_anchor[b] = anchor;
+            if (lead) {
+                a.accept_len[b] = n_acc;
+                a.num_committed[b] = committed;
+                a.next_anchor[b] = anchor;
+            }
             s_L = probe.L;
             s_m = a.do_commit ? committed : 0;
         }
     }
     __syncthreads();
-    // ---- commit: the whole workgroup copies the appended rows when there are few layers
-    if (a.do_commit && a.num_layers <= kInlineLayers && s_m > 0)
-        for (int layer = 0; layer < a.num_layers; ++layer) append_rows(a, b, layer, s_L, s_m, tid, 256, s_pg);
-}
-
-// The same copy as its own launch: grid (sequence, layer).
-__global__ void __launch_bounds__(256) commit_kernel(const ConsensusArgs a)
-{
-    const int b = blockIdx.x, layer = blockIdx.y;
-    const int L = a.commit_info[b * 2], m = a.commit_info[b * 2 + 1];
-    if (m > 0) append_rows(a, b, layer, L, m, threadIdx.x, 256);
+    // ---- commit: this workgroup's layer
+    if (s_m > 0) append_rows(a, b, layer, s_L, s_m, tid, 256, s_pg);
 }
 
 hipError_t launch_consensus(const ConsensusArgs &a, hipStream_t stream)
@@ -240,14 +230,8 @@ hipError_t launch_consensus(const ConsensusArgs &a, hipStream_t stream)
     hipLaunchKernelGGL(argmax_partial_kernel, g1, dim3(256), 0, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(accept_commit_kernel, dim3(a.batch), dim3(256), 0, stream, a);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (a.do_commit && a.num_layers > kInlineLayers) {
-        hipLaunchKernelGGL(commit_kernel, dim3(a.batch, a.num_layers), dim3(256), 0, stream, a);
-        e = hipGetLastError();
-    }
-    return e;
+    hipLaunchKernelGGL(accept_commit_kernel, dim3(a.batch, a.do_commit ? a.num_layers : 1), dim3(256), 0, stream, a);
+    return hipGetLastError();
 }
 
 }  // namespace orthrus

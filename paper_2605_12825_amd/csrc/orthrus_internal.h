@@ -53,7 +53,7 @@ struct ConsensusArgs {
     int32_t *seq_lens, *accept_len, *num_committed, *out_tokens, *next_anchor;
     float *part_val;     // [B*K][chunks]
     int32_t *part_idx;   // [B*K][chunks]
-    int32_t *commit_info;  // [B][2]: length before the step, rows to append (0 = none)
+    int32_t *commit_info;  // [B]: length before the step (the scan's snapshot; seq_lens is bumped while others still read)
     int32_t *err_word;
     int64_t stride_layer, stride_page, stride_head, stride_tok, num_pages;
     int64_t blk_stride_layer, blk_stride_row, blk_stride_head;  // of k_blk_ar / v_blk_ar
@@ -67,8 +67,9 @@ struct SamplingArgs {
     const float *accept_u;    // [B][K]
     const float *gumbel;      // [B][V]
     float4 *lse_part;         // [B*K][chunks]: (max_p, sum_p, max_q, sum_q) of logits / T over the chunk
-    float4 *draw_part;        // [B][chunks]: (best score among p>q, its index, best score of log p + g, its index)
+    float4 *draw_part;        // [B][draw_chunks]: (best score among p>q, its index, best score of log p + g, its index)
     float inv_temperature;
+    int draw_chunks;          // draw_chunk_elems()-sized pieces of a row
 };
 
 // ---- commit helpers shared by the greedy and the sampling consensus kernels (device code)
@@ -116,7 +117,7 @@ __device__ __forceinline__ void append_rows(const ConsensusArgs &a, int b, int l
     static_assert(kBatch == 4, "the loop body above is written out for four chunks");
 }
 
-// What lane k < K of a sequence's first wave learns about token position L + k (L = seq_lens[b]) before
+// What lane k < K of a sequence's first wave learns about token position L + k (L = length before the step) before
 // the number of rows to append is known: fetched at the start of the kernel, so that these dependent
 // loads (length, then page id) run next to the argmax reductions instead of after them.
 struct CommitProbe {
@@ -126,7 +127,7 @@ struct CommitProbe {
 __device__ __forceinline__ CommitProbe commit_probe(const ConsensusArgs &a, int b, int lane)
 {
     CommitProbe p;
-    p.L = a.seq_lens[b];
+    p.L = a.commit_info[b];
     p.pg = -1;
     if (lane < a.block_k && p.L >= 0) {
         const int slot = (p.L + lane) >> a.page_shift;
@@ -135,22 +136,22 @@ __device__ __forceinline__ CommitProbe commit_probe(const ConsensusArgs &a, int 
     return p;
 }
 
-// Run by the first wave once it knows m, the number of rows to append: positions L..L+m-1 must be mapped;
-// then the length is bumped, else the capacity error is flagged and the sequence left alone.  Records
-// (L, rows to append) for a later copy launch.  Returns the rows that will be appended (m or 0).  Every
-// lane of the wave must call it.
-__device__ __forceinline__ int commit_decide(const ConsensusArgs &a, int b, int lane, int m, const CommitProbe &p)
+// Kept by the first kernel of a step: the lengths before it.  The second kernel runs one workgroup per (sequence,
+// layer), each of which needs the length, while the workgroup of layer 0 bumps seq_lens.
+__device__ __forceinline__ void commit_snapshot(const ConsensusArgs &a, int b) { a.commit_info[b] = a.seq_lens[b]; }
+
+// Run by the first wave once it knows m, the number of rows to append: positions L..L+m-1 must be mapped, else the
+// sequence is left alone.  With `lead` (one workgroup per sequence) the length is bumped or the capacity error flagged.
+// Returns the rows that will be appended (m or 0).  Every lane of the wave must call it.
+__device__ __forceinline__ int commit_decide(const ConsensusArgs &a, int b, int lane, int m, const CommitProbe &p, bool lead)
 {
     const bool bad = lane < m && (p.pg < 0 || p.pg >= a.num_pages);
     const bool any_bad = __ballot(bad) != 0ull;
-    const int committed = any_bad ? 0 : m;
-    if (lane == 0) {
-        a.commit_info[b * 2] = p.L;
-        a.commit_info[b * 2 + 1] = committed;
+    if (lead && lane == 0) {
         if (any_bad) atomicExch(a.err_word, -4);
         else a.seq_lens[b] = p.L + m;
     }
-    return committed;
+    return any_bad ? 0 : m;
 }
 #endif
 
@@ -177,6 +178,7 @@ hipError_t launch_prefill_split(const AttnArgs &a, int head_dim, hipStream_t str
 hipError_t launch_consensus(const ConsensusArgs &a, hipStream_t stream);
 hipError_t launch_sampling_consensus(const SamplingArgs &a, hipStream_t stream);
 int consensus_chunk_elems();
+int draw_chunk_elems();
 // Static device scratch of the allocation-free consensus entry point: looked up once per device (with
 // that device current), then used through the returned device address only.
 hipError_t consensus_scratch_init(int device);

@@ -7,12 +7,16 @@
 //
 //   lse_partial_kernel      grid (row * chunks + chunk): (max, sum of exp) of both scaled logit rows
 //                           over one 8192-element chunk, 16-byte loads, wavefront shuffles.
-//   draw_partial_kernel     grid (chunk, sequence): every workgroup re-derives the K keep decisions of
+//   draw_partial_kernel     grid (draw chunk, sequence): every workgroup re-derives the K keep decisions of
 //                           its sequence from the chunk pairs (same code, same order => same answer
-//                           everywhere), and if a row j < K was rejected scans its chunk of row j for the
-//                           two candidate maxima.
-//   sample_commit_kernel    grid (sequence): decisions again, final maximum over the chunks in chunk
-//                           order, outputs, page check and the in-place commit of the kept rows.
+//                           everywhere), and if a row j < K was rejected scans its 2048-element piece of row
+//                           j for the two candidate maxima.
+//   sample_commit_kernel    grid (sequence, layer): decisions again; the workgroup of layer 0 finishes the draw
+//                           (a total order: any order of merging gives the same token) and writes the
+//                           outputs, every layer's workgroup commits its layer's kept rows.
+// The two small kernels are chains of memory round trips and exponentials.  Eight threads share a row's chunk pairs
+// and the draw's pieces are small, so that a batch of one fills 63 workgroups instead of 16 with four times fewer
+// exponentials per thread (batch 1, K = 16, V = 128256: 14.2 + 9.0 us before; batch 8, K = 32, V = 151936: 16.9 + 11.3).
 #include "orthrus_internal.h"
 
 namespace orthrus {
@@ -20,7 +24,8 @@ namespace orthrus {
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int kSChunk = 8192;
-constexpr int kSInlineLayers = 2;
+constexpr int kDrawChunk = 2048;
+int draw_chunk_elems() { return kDrawChunk; }
 
 __device__ __forceinline__ void lse_merge(float &m, float &s, float m2, float s2)
 {
@@ -39,22 +44,32 @@ __global__ void __launch_bounds__(256) lse_partial_kernel(const SamplingArgs a)
     const float *qr = a.diff_logits + (int64_t)row * V;
     const int begin = chunk * kSChunk, end = min(V, begin + kSChunk);
     const float it = a.inv_temperature;
+    if (a.c.do_commit && tid == 0 && chunk == 0 && row % a.c.block_k == 0) commit_snapshot(a.c, row / a.c.block_k);
     constexpr int PER = kSChunk / 256;  // 32 values per thread and row
     float xp[PER], xq[PER];
-    const bool vec_ok = ((V & 3) == 0) && (((((uintptr_t)a.c.ar_logits) | ((uintptr_t)a.diff_logits)) & 15) == 0);
-    if (vec_ok) {
+    // 16-byte loads of the aligned middle, and up to three elements on either side of it (a row starts anywhere when
+    // the vocabulary is not a multiple of four), if both logit sets are aligned alike; else element by element.
+    float xpe = -INFINITY, xqe = -INFINITY;
+    const int skew = (int)((0 - ((uintptr_t)(pr + begin) >> 2)) & 3);
+    if (skew == (int)((0 - ((uintptr_t)(qr + begin) >> 2)) & 3)) {
+        const int head = min(skew, end - begin), mid = begin + head, nvec = (end - mid) >> 2, tail = mid + 4 * nvec;
 #pragma unroll
         for (int u = 0; u < PER / 4; ++u) {
-            const int i = begin + (u * 256 + tid) * 4;
+            const int v = u * 256 + tid;
             float4 vp = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY), vq = vp;
-            if (i < end) {  // one pass over both logit sets: loads that do not displace anything in the caches
-                const f32x4 tp = __builtin_nontemporal_load((const f32x4 *)(pr + i));
-                const f32x4 tq = __builtin_nontemporal_load((const f32x4 *)(qr + i));
+            if (v < nvec) {  // one pass over both logit sets: loads that do not displace anything in the caches
+                const f32x4 tp = __builtin_nontemporal_load((const f32x4 *)(pr + mid) + v);
+                const f32x4 tq = __builtin_nontemporal_load((const f32x4 *)(qr + mid) + v);
                 vp = make_float4(tp[0], tp[1], tp[2], tp[3]);
                 vq = make_float4(tq[0], tq[1], tq[2], tq[3]);
             }
             xp[4 * u] = vp.x; xp[4 * u + 1] = vp.y; xp[4 * u + 2] = vp.z; xp[4 * u + 3] = vp.w;
             xq[4 * u] = vq.x; xq[4 * u + 1] = vq.y; xq[4 * u + 2] = vq.z; xq[4 * u + 3] = vq.w;
+        }
+        const int edge = tid < 4 ? (tid < head ? begin + tid : end) : tid < 8 ? tail + tid - 4 : end;
+        if (edge < end) {
+            xpe = pr[edge];
+            xqe = qr[edge];
         }
     } else {
 #pragma unroll
@@ -67,12 +82,12 @@ __global__ void __launch_bounds__(256) lse_partial_kernel(const SamplingArgs a)
     // Per thread: maximum of the raw logits (1/T > 0 keeps the order), then the sum of
     // exp((x - max) / T) as exp2 of one fused multiply-add per element.  Entries past the end are
     // -inf and add exp2(-inf) = 0; a thread that saw nothing but -inf keeps (max, sum) = (-inf, 0).
-    float rp = -INFINITY, rq = -INFINITY;
+    float rp = xpe, rq = xqe;
 #pragma unroll
     for (int u = 0; u < PER; ++u) { rp = fmaxf(rp, xp[u]); rq = fmaxf(rq, xq[u]); }
     const float c2 = it * 1.4426950408889634f;  // log2(e) / T
     const float bp = rp == -INFINITY ? 0.f : -rp * c2, bq = rq == -INFINITY ? 0.f : -rq * c2;
-    float sp = 0.f, sq = 0.f;
+    float sp = __builtin_amdgcn_exp2f(__builtin_fmaf(xpe, c2, bp)), sq = __builtin_amdgcn_exp2f(__builtin_fmaf(xqe, c2, bq));
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
         sp += __builtin_amdgcn_exp2f(__builtin_fmaf(xp[u], c2, bp));
@@ -96,44 +111,56 @@ __global__ void __launch_bounds__(256) lse_partial_kernel(const SamplingArgs a)
     }
 }
 
-// Keep decisions of sequence b, made by the first wavefront (lane k < K owns row k).  Returns the first
-// row that is not kept (K if none) and, for that row, the two log-sum-exps.
-__device__ __forceinline__ int first_rejected(const SamplingArgs &a, int b, int lane, float &lsep_j, float &lseq_j)
+// Keep decisions of sequence b, made by the whole workgroup: eight threads per row merge its chunk pairs (a fixed tree:
+// every eighth chunk in order, then by shuffles).  Returns the first row that is not kept (K if none) and, for that
+// row, the two log-sum-exps.  Contains barriers.
+__device__ __forceinline__ int first_rejected(const SamplingArgs &a, int b, int tid, float &lsep_j, float &lseq_j)
 {
     const int K = a.c.block_k, V = a.c.vocab, chunks = a.c.chunks;
-    bool keep = true;  // lanes >= K do not stop the run
-    float lsep = 0.f, lseq = 0.f;
-    if (lane < K) {
-        const int64_t row = (int64_t)b * K + lane;
-        float4 r = a.lse_part[row * chunks];
-        // the row's chunk pairs, eight loads in flight at a time, merged in chunk order
-        for (int c0 = 1; c0 < chunks; c0 += 8) {
-            float4 t[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) t[u] = a.lse_part[row * chunks + min(c0 + u, chunks - 1)];
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (c0 + u < chunks) {
-                    lse_merge(r.x, r.y, t[u].x, t[u].y);
-                    lse_merge(r.z, r.w, t[u].z, t[u].w);
-                }
-        }
-        lsep = r.x + logf(r.y);
-        lseq = r.z + logf(r.w);
+    const int k = tid >> 3, sub = tid & 7;
+    __shared__ int s_keep[32];
+    __shared__ float2 s_lse[32];
+    if (k < K) {
+        const int64_t row = (int64_t)b * K + k;
         const int x = a.c.draft_tokens[row];
-        keep = false;
-        if (x >= 0 && x < V) {
-            const float px = expf(a.c.ar_logits[row * V + x] * a.inv_temperature - lsep);
-            const float qx = expf(a.diff_logits[row * V + x] * a.inv_temperature - lseq);
-            keep = a.accept_u[row] * qx < px;
+        const float4 *part = a.lse_part + row * chunks;
+        float4 r = make_float4(-INFINITY, 0.f, -INFINITY, 0.f);
+        for (int c0 = sub; c0 < chunks; c0 += 32) {  // four loads in flight
+            float4 t[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) t[u] = c0 + 8 * u < chunks ? part[c0 + 8 * u] : make_float4(-INFINITY, 0.f, -INFINITY, 0.f);
+            const float mp = fmaxf(fmaxf(fmaxf(t[0].x, t[1].x), fmaxf(t[2].x, t[3].x)), r.x);
+            const float mq = fmaxf(fmaxf(fmaxf(t[0].z, t[1].z), fmaxf(t[2].z, t[3].z)), r.z);
+            float sp = mp == -INFINITY ? 0.f : r.y * expf(r.x - mp), sq = mq == -INFINITY ? 0.f : r.w * expf(r.z - mq);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (mp != -INFINITY) sp += t[u].y * expf(t[u].x - mp);
+                if (mq != -INFINITY) sq += t[u].w * expf(t[u].z - mq);
+            }
+            r = make_float4(mp, sp, mq, sq);
+        }
+        const bool valid = x >= 0 && x < V;
+        const float ap = valid ? a.c.ar_logits[row * V + x] : 0.f, aq = valid ? a.diff_logits[row * V + x] : 0.f;
+        const float u01 = a.accept_u[row];
+#pragma unroll
+        for (int off = 1; off < 8; off <<= 1) {
+            lse_merge(r.x, r.y, __shfl_xor(r.x, off), __shfl_xor(r.y, off));
+            lse_merge(r.z, r.w, __shfl_xor(r.z, off), __shfl_xor(r.w, off));
+        }
+        const float lsep = r.x + logf(r.y), lseq = r.z + logf(r.w);
+        if (sub == 0) {
+            s_keep[k] = valid && u01 * expf(aq * a.inv_temperature - lseq) < expf(ap * a.inv_temperature - lsep);
+            s_lse[k] = make_float2(lsep, lseq);
         }
     }
-    const unsigned long long rej = ~__ballot(keep);
-    const int j = rej ? __ffsll((long long)rej) - 1 : 64;
-    const int jj = j < K ? j : K;
-    lsep_j = __shfl(lsep, jj < K ? jj : 0);
-    lseq_j = __shfl(lseq, jj < K ? jj : 0);
-    return jj;
+    __syncthreads();
+    const int lane = tid & 63;
+    const unsigned long long rej = ~__ballot(lane >= K || s_keep[lane < K ? lane : 0]);
+    const int j = rej ? __ffsll((long long)rej) - 1 : K;
+    const float2 l = s_lse[j < K ? j : 0];
+    lsep_j = l.x;
+    lseq_j = l.y;
+    return j;
 }
 
 __device__ __forceinline__ bool better_score(float v1, int i1, float v2, int i2)
@@ -144,22 +171,15 @@ __device__ __forceinline__ bool better_score(float v1, int i1, float v2, int i2)
 __global__ void __launch_bounds__(256) draw_partial_kernel(const SamplingArgs a)
 {
     const int chunk = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
-    const int K = a.c.block_k, V = a.c.vocab, chunks = a.c.chunks;
-    __shared__ int s_j;
-    __shared__ float s_lsep, s_lseq;
-    if (tid < 64) {
-        float lp, lq;
-        const int j = first_rejected(a, b, tid, lp, lq);
-        if (tid == 0) { s_j = j; s_lsep = lp; s_lseq = lq; }
-    }
-    __syncthreads();
-    const int j = s_j;
+    const int K = a.c.block_k, V = a.c.vocab;
+    float lsep, lseq;
+    const int j = first_rejected(a, b, tid, lsep, lseq);
     if (j >= K) return;  // every draft kept: nothing to draw
-    const float lsep = s_lsep, lseq = s_lseq, it = a.inv_temperature;
+    const float it = a.inv_temperature;
     const float *pr = a.c.ar_logits + ((int64_t)b * K + j) * V;
     const float *qr = a.diff_logits + ((int64_t)b * K + j) * V;
     const float *gr = a.gumbel + (int64_t)b * V;
-    const int begin = chunk * kSChunk, end = min(V, begin + kSChunk);
+    const int begin = chunk * kDrawChunk, end = min(V, begin + kDrawChunk);
     float bp = -INFINITY, ba = -INFINITY;   // best among p > q, best of log p + g
     int ip = 0x7fffffff, ia = 0x7fffffff;
     auto visit = [&](int i, float xp, float xq, float g) __attribute__((always_inline)) {
@@ -176,7 +196,7 @@ __global__ void __launch_bounds__(256) draw_partial_kernel(const SamplingArgs a)
                         (((((uintptr_t)a.c.ar_logits) | ((uintptr_t)a.diff_logits) | ((uintptr_t)a.gumbel)) & 15) == 0);
     if (vec_ok) {
         // all of a thread's loads of the chunk go out before the first score is formed
-        constexpr int NL = kSChunk / (256 * 4);
+        constexpr int NL = kDrawChunk / (256 * 4);
         float4 vp[NL], vq[NL], vg[NL];
 #pragma unroll
         for (int u = 0; u < NL; ++u) {
@@ -199,7 +219,17 @@ __global__ void __launch_bounds__(256) draw_partial_kernel(const SamplingArgs a)
             }
         }
     } else {
-        for (int i = begin + tid; i < end; i += 256) visit(i, pr[i], qr[i], gr[i]);
+        constexpr int NS = kDrawChunk / 256;
+        float vp[NS], vq[NS], vg[NS];
+#pragma unroll
+        for (int u = 0; u < NS; ++u) {
+            const int i = begin + u * 256 + tid;
+            vp[u] = vq[u] = vg[u] = 0.f;
+            if (i < end) { vp[u] = pr[i]; vq[u] = qr[i]; vg[u] = gr[i]; }
+        }
+#pragma unroll
+        for (int u = 0; u < NS; ++u)
+            if (begin + u * 256 + tid < end) visit(begin + u * 256 + tid, vp[u], vq[u], vg[u]);
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
@@ -217,75 +247,69 @@ __global__ void __launch_bounds__(256) draw_partial_kernel(const SamplingArgs a)
             if (better_score(sh[w].x, __float_as_int(sh[w].y), bp, ip)) { bp = sh[w].x; ip = __float_as_int(sh[w].y); }
             if (better_score(sh[w].z, __float_as_int(sh[w].w), ba, ia)) { ba = sh[w].z; ia = __float_as_int(sh[w].w); }
         }
-        a.draw_part[(int64_t)b * chunks + chunk] = make_float4(bp, __int_as_float(ip), ba, __int_as_float(ia));
+        a.draw_part[(int64_t)b * a.draw_chunks + chunk] = make_float4(bp, __int_as_float(ip), ba, __int_as_float(ia));
     }
 }
 
 __global__ void __launch_bounds__(256) sample_commit_kernel(const SamplingArgs a)
 {
     const ConsensusArgs &c = a.c;
-    const int b = blockIdx.x, tid = threadIdx.x;
-    const int K = c.block_k, chunks = c.chunks;
+    const int b = blockIdx.x, layer = blockIdx.y, tid = threadIdx.x;
+    const bool lead = layer == 0;
+    const int K = c.block_k;
     __shared__ int s_L, s_m;
     __shared__ int s_pg[32];
+    // the page ids of the K positions that may be appended do not depend on the decisions: their loads go out first
+    CommitProbe probe = {0, -1};
+    if (tid < 64 && c.do_commit) probe = commit_probe(c, b, tid);
+    float lp, lq;
+    const int j = first_rejected(a, b, tid, lp, lq);
     if (tid < 64) {
         const int lane = tid;
-        // the length and the page ids of the K positions that may be appended do not depend on the
-        // decisions: their loads go out first
-        CommitProbe probe = {0, -1};
-        if (c.do_commit) probe = commit_probe(c, b, lane);
-        float lp, lq;
-        const int j = first_rejected(a, b, lane, lp, lq);
-        int repl = -1;
-        if (j < K) {
-            float bp = -INFINITY, ba = -INFINITY;
-            int ip = 0x7fffffff, ia = 0x7fffffff;
-            // every lane walks the chunks in order (same result in all lanes), eight loads in flight at a time
-            for (int c0 = 0; c0 < chunks; c0 += 8) {
-                float4 t[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) t[u] = a.draw_part[(int64_t)b * chunks + min(c0 + u, chunks - 1)];
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (c0 + u < chunks) {
-                        if (better_score(t[u].x, __float_as_int(t[u].y), bp, ip)) { bp = t[u].x; ip = __float_as_int(t[u].y); }
-                        if (better_score(t[u].z, __float_as_int(t[u].w), ba, ia)) { ba = t[u].z; ia = __float_as_int(t[u].w); }
-                    }
-            }
-            repl = ip != 0x7fffffff ? ip : ia;
-        }
         const int m = min(j + 1, K);
-        if (lane < K) {
-            int t = -1;
-            if (lane < j) t = c.draft_tokens[(int64_t)b * K + lane];
-            else if (lane == j && lane < m) t = repl;
-            c.out_tokens[(int64_t)b * K + lane] = lane < m ? t : -1;
+        if (lead) {
+            int repl = -1;
+            if (j < K) {
+                float bp = -INFINITY, ba = -INFINITY;
+                int ip = 0x7fffffff, ia = 0x7fffffff;
+                for (int d = lane; d < a.draw_chunks; d += 64) {
+                    const float4 t = a.draw_part[(int64_t)b * a.draw_chunks + d];
+                    if (better_score(t.x, __float_as_int(t.y), bp, ip)) { bp = t.x; ip = __float_as_int(t.y); }
+                    if (better_score(t.z, __float_as_int(t.w), ba, ia)) { ba = t.z; ia = __float_as_int(t.w); }
+                }
+#pragma unroll
+                for (int off = 32; off >= 1; off >>= 1) {
+                    const float op = __shfl_xor(bp, off), oa = __shfl_xor(ba, off);
+                    const int jp = __shfl_xor(ip, off), ja = __shfl_xor(ia, off);
+                    if (better_score(op, jp, bp, ip)) { bp = op; ip = jp; }
+                    if (better_score(oa, ja, ba, ia)) { ba = oa; ia = ja; }
+                }
+                repl = ip != 0x7fffffff ? ip : ia;
+            }
+            if (lane < K) {
+                int t = -1;
+                if (lane < j) t = c.draft_tokens[(int64_t)b * K + lane];
+                else if (lane == j) t = repl;
+                c.out_tokens[(int64_t)b * K + lane] = t;
+            }
+            if (lane == 0) {
+                c.accept_len[b] = j;
+                c.next_anchor[b] = j < K ? repl : c.draft_tokens[(int64_t)b * K + K - 1];
+            }
         }
-        const int last_tok = (j < K) ? repl : c.draft_tokens[(int64_t)b * K + K - 1];
         int committed = m;
-        const int L = probe.L;
         if (c.do_commit) {
-            committed = commit_decide(c, b, lane, m, probe);
+            committed = commit_decide(c, b, lane, m, probe, lead);
             if (lane < K) s_pg[lane] = probe.pg;
         }
         if (lane == 0) {
-            c.accept_len[b] = j;
-            c.num_committed[b] = committed;
-            c.next_anchor[b] = last_tok;
-            s_L = L;
+            if (lead) c.num_committed[b] = committed;
+            s_L = probe.L;
             s_m = c.do_commit ? committed : 0;
         }
     }
     __syncthreads();
-    if (c.do_commit && c.num_layers <= kSInlineLayers && s_m > 0)
-        for (int layer = 0; layer < c.num_layers; ++layer) append_rows(c, b, layer, s_L, s_m, tid, 256, s_pg);
-}
-
-__global__ void __launch_bounds__(256) sample_commit_layers_kernel(const SamplingArgs a)
-{
-    const int b = blockIdx.x, layer = blockIdx.y;
-    const int L = a.c.commit_info[b * 2], m = a.c.commit_info[b * 2 + 1];
-    if (m > 0) append_rows(a.c, b, layer, L, m, threadIdx.x, 256);
+    if (s_m > 0) append_rows(c, b, layer, s_L, s_m, tid, 256, s_pg);
 }
 
 hipError_t launch_sampling_consensus(const SamplingArgs &a, hipStream_t stream)
@@ -296,17 +320,11 @@ hipError_t launch_sampling_consensus(const SamplingArgs &a, hipStream_t stream)
                        stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(draw_partial_kernel, dim3(c.chunks, c.batch), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(draw_partial_kernel, dim3(a.draw_chunks, c.batch), dim3(256), 0, stream, a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(sample_commit_kernel, dim3(c.batch), dim3(256), 0, stream, a);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (c.do_commit && c.num_layers > kSInlineLayers) {
-        hipLaunchKernelGGL(sample_commit_layers_kernel, dim3(c.batch, c.num_layers), dim3(256), 0, stream, a);
-        e = hipGetLastError();
-    }
-    return e;
+    hipLaunchKernelGGL(sample_commit_kernel, dim3(c.batch, c.do_commit ? c.num_layers : 1), dim3(256), 0, stream, a);
+    return hipGetLastError();
 }
 
 }  // namespace orthrus

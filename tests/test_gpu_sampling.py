@@ -162,3 +162,48 @@ def test_sampling_capacity_error_and_multi_layer():
     np.testing.assert_array_equal(got["seq_lens"], rl)
     np.testing.assert_array_equal(got["k_pool"], rk)
     np.testing.assert_array_equal(got["v_pool"], rv)
+
+
+@pytest.mark.parametrize("vocab", [1, 3, 5, 2047, 2048, 2049, 8191, 8194, 16387])
+@pytest.mark.parametrize("layers", [1, 5])
+def test_vocabularies_around_the_chunk_and_load_edges(vocab, layers):
+    """Rows that start off a 16-byte boundary (vocabulary not a multiple of four), pieces of the draw and of the
+    log-sum-exp that end inside, at and just past a boundary, and the commit into one and into several layers."""
+    w = Workload(name="edge", seed=9100 + vocab, batch=5, num_q_heads=4, num_kv_heads=2, head_dim=64, block_k=6,
+                 context_range=(0, 50), page_size=16, paging="shuffled", vocab=vocab, steps=1)
+    if vocab > 8:
+        c, _ = _clear_case(w, 9200 + 40 * vocab, temperature=0.9)
+    else:  # too few tokens for a clear margin: drafts outside the vocabulary are never kept, and one token is the draw
+        c = make_sampling_case(w, 9300 + vocab, temperature=0.9)
+        c["draft_tokens"][:] = vocab
+        c["ar_logits"][:] = np.float32(-50.0)
+        c["ar_logits"][:, :, vocab // 2] = 50.0
+    cache = make_cache(w)
+    ks = np.stack([make_cache(w, seed=9400 + l, seq_lens=cache["seq_lens"])["k_pool"] for l in range(layers)])
+    vs = np.stack([make_cache(w, seed=9500 + l, seq_lens=cache["seq_lens"])["v_pool"] for l in range(layers)])
+    blk = [make_block(w, 9600 + l) for l in range(layers)]
+    kb, vb = np.stack([x["k_blk"] for x in blk]), np.stack([x["v_blk"] for x in blk])
+    rk, rv, rl = ks.copy(), vs.copy(), cache["seq_lens"].copy()
+    want = oracle.sampling_consensus_commit(c["ar_logits"], c["diff_logits"], c["draft_tokens"], c["accept_u"], c["gumbel"],
+                                            0.9, kb, vb, rk, rv, cache["page_table"], rl)
+    from paper_2605_12825_amd import runtime as rt
+    D = rt.to_device_bits
+    step = rt.DecodeStep(batch=5, num_q_heads=4, num_kv_heads=2, head_dim=64, block_k=6, page_size=16,
+                         max_pages_per_seq=cache["page_table"].shape[1], max_seq_len=16 * cache["page_table"].shape[1],
+                         num_pages=ks.shape[1],
+                         vocab=vocab, num_layers=layers)
+    kp, vp, sl, pt = D(ks), D(vs), D(cache["seq_lens"]), D(cache["page_table"])
+    acc, ncm, anc = (torch.full((5,), -7, dtype=torch.int32, device="cuda") for _ in range(3))
+    tok = torch.full((5, 6), -7, dtype=torch.int32, device="cuda")
+    # the logits one element off their allocation's start: neither set is 16-byte aligned
+    off = lambda x: torch.cat((torch.zeros(1, device="cuda"), D(x).reshape(-1)))[1:]
+    step.sampling_consensus_commit(0.9, off(c["ar_logits"]), off(c["diff_logits"]), D(c["draft_tokens"]), D(c["accept_u"]),
+                                   D(c["gumbel"]), D(kb), D(vb), kp, vp, pt, sl, acc, ncm, tok, anc)
+    torch.cuda.synchronize()
+    assert step.device_error() == 0
+    for name, got in (("accept_len", acc), ("num_committed", ncm), ("out_tokens", tok), ("next_anchor", anc)):
+        np.testing.assert_array_equal(got.cpu().numpy(), want[name], err_msg=name)
+    np.testing.assert_array_equal(sl.cpu().numpy(), rl)
+    np.testing.assert_array_equal(rt.bits_to_numpy(kp), rk)
+    np.testing.assert_array_equal(rt.bits_to_numpy(vp), rv)
+    step.close()
