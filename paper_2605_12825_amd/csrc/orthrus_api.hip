@@ -162,7 +162,7 @@ orthrus::AttnArgs decode_attn_args(const orthrus_ctx *ctx, const orthrus_params 
     a.part_o = (float *)workspace;
     a.part_ml = workspace ? (float *)((char *)workspace + align_up(plan.part_o_bytes, 256)) : nullptr;
     a.err_word = ctx->err_word;
-    a.old_lens = nullptr; a.new_lens = nullptr; a.max_new = 0;
+    a.old_lens = nullptr; a.new_lens = nullptr; a.seq_lens_out = nullptr; a.max_new = 0;
     a.stride_page = p->pool_stride_page; a.stride_head = p->pool_stride_head; a.stride_tok = p->pool_stride_tok;
     a.num_pages = p->num_pages;
     a.q_stride_head = p->q_stride_head ? p->q_stride_head : p->head_dim;
@@ -406,7 +406,7 @@ orthrus_status orthrus_prefill_attn(orthrus_ctx *ctx, const orthrus_params *p, i
     a.page_table = page_table; a.seq_lens = seq_lens;
     a.out = (uint16_t *)out; a.lse = nullptr; a.part_o = nullptr; a.part_ml = nullptr;
     a.err_word = ctx->err_word;
-    a.old_lens = f.old_lens; a.new_lens = f.new_lens; a.max_new = max_new_tokens;
+    a.old_lens = f.old_lens; a.new_lens = f.new_lens; a.seq_lens_out = seq_lens; a.max_new = max_new_tokens;
     a.stride_page = p->pool_stride_page; a.stride_head = p->pool_stride_head; a.stride_tok = p->pool_stride_tok;
     a.num_pages = p->num_pages;
     a.q_stride_head = p->head_dim; a.q_stride_row = (int64_t)p->num_q_heads * p->head_dim;

@@ -385,12 +385,14 @@ struct WorkItems {
                 g = (int)(blockIdx.x / ((unsigned)a.batch * (unsigned)a.num_splits));
             }
             if constexpr (MODE == kItemsPrefill) {
-                // lengths as the planning kernel left them: validated, 0 new tokens on a capacity error
+                // lengths as the append kernel left them: validated, 0 new tokens on a capacity error
                 const int L0 = __builtin_amdgcn_readfirstlane(((const const_i32 *)a.old_lens)[b]);
                 const int n_new = __builtin_amdgcn_readfirstlane(((const const_i32 *)a.new_lens)[b]);
                 // every sequence's last chunk (the one with the most cache tokens) starts first
                 const int chunk = (n_new + a.chunk_tokens - 1) / a.chunk_tokens - 1 - split;
                 if (chunk < 0) return false;
+                // this launch reads the recorded lengths only, so the sequence's first chunk may bump the live one
+                if (chunk == 0 && g == 0 && threadIdx.x == 0) a.seq_lens_out[b] = L0 + n_new;
                 row0 = chunk * a.chunk_tokens;
                 rows_live = min(a.chunk_tokens, n_new - row0);
                 pos0 = L0 + row0;

@@ -119,10 +119,25 @@ __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(const AttnArgs a)
             vb[db] = TILE_B + (tok0 / RPI) * GS + r * ROWB + ((db ^ (xm<CH>(r) >> 2)) << 6) + (tr_ch << 4) + ((lane & 1) << 3);
     }
     const float c = a.scale_log2e;
-    // ---- pipeline fill
+    // ---- pipeline fill (the page ids of the whole fill in one round trip)
+    if (n_whole >= NS - 1) {
+        int ids[NS - 1][PG];
+#pragma unroll
+        for (int t = 0; t < NS - 1; ++t)
+#pragma unroll
+            for (int u = 0; u < PG; ++u) ids[t][u] = w.pt_row[(page_at + t * 32u + u * 16u) >> a.page_shift];
+#pragma unroll
+        for (int t = 0; t < NS - 1; ++t) {
+#pragma unroll
+            for (int u = 0; u < PG; ++u)
+                half.issue(NtTag{}, my_pool + half.offset(ids[t][u], page_at + u * 16u), dst + u * half.GPH * GS);
+            advance();
+        }
+    } else {
 #pragma unroll 1
-    for (int t = 0; t < NS - 1; ++t)
-        if (t < w.n_tiles) issue_tile(t);
+        for (int t = 0; t < NS - 1; ++t)
+            if (t < w.n_tiles) issue_tile(t);
+    }
 
     // ---- queries: block x holds rows wave*64 + 32*x + col
     Frag qf[2][KSTEPS];

@@ -30,8 +30,9 @@ struct AttnArgs {
     float *part_o;   // [p][wave][d block][4][lane] float4: unnormalised partial outputs, register order
     float *part_ml;  // [p][wave][32 rows] float2: running max (log2 domain) and sum
     int32_t *err_word;
-    // prefill only: lengths before the call and validated new-token counts [B] (workspace), row stride T
+    // prefill only: lengths before the call and validated new-token counts [B] (workspace), the lengths to bump, row stride T
     const int32_t *old_lens, *new_lens;
+    int32_t *seq_lens_out;
     int max_new;
     int64_t stride_page, stride_head, stride_tok, num_pages;
     // block inputs: elements between consecutive rows (b*K + i) and heads of q, and of k_blk / v_blk
@@ -189,8 +190,8 @@ size_t consensus_scratch_bytes();
 hipError_t launch_kv_stream_probe(const AttnArgs &a, const AttnPlan &plan, int head_dim, hipStream_t stream,
                                   hipEvent_t start, hipEvent_t stop);
 
-// Prefill front end (defined with the commit kernels): validates lengths and pages, records the lengths
-// before the call and the accepted new-token counts, bumps seq_lens, then copies the new K/V rows in.
+// Prefill front end: validates lengths and pages, records the lengths before the call and the accepted new-token
+// counts, copies the new K/V rows in (the attention bumps seq_lens).
 struct PrefillArgs {
     const uint16_t *k_new, *v_new;   // [B][T][H_kv][d]
     const int32_t *new_lens_in;      // [B] requested new tokens
