@@ -209,7 +209,7 @@ def run_prefill(args, torch, rt, w):
                    "page_size": w.page_size, "new_tokens": T},
         "roofline": {"bound": "mfma", "achieved": round(tf, 1), "peak": 2500.0, "unit": "TFLOP/s",
                      "frac": round(tf / 2500.0, 4), "traffic": None,
-                     "kernel": "orthrus_prefill_attn = plan + append + attn_split_kernel (prefill form); ordinary "
+                     "kernel": "orthrus_prefill_attn = append + attention kernel; ordinary "
                                "events around the whole call, so launch gaps are inside",
                      "avg_launch_us": round(ms * 1e3, 2), "algorithmic_flops_per_launch": int(flops)},
     }
