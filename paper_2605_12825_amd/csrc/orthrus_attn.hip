@@ -604,7 +604,7 @@ static size_t lds_need(int head_dim)
 }
 
 hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv_heads, int max_seq_len,
-                     int requested_splits, int num_cus, int num_layers, AttnPlan *plan)
+                     int requested_splits, int num_cus, int num_layers, double pool_tokens, AttnPlan *plan)
 {
     const int R = group * block_k;
     plan->rows = R;
@@ -623,8 +623,11 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
     if (per_cu < 1) per_cu = 1;
     plan->bal_wgs = 0;
     // K/V bytes the model streams at most between two passes over the same layer's cache (the other
-    // layers' caches come in between), against the 256 MB last-level cache (see the kernel's loads)
-    const double stream_bytes = (double)(num_layers > 1 ? num_layers : 1) * batch * max_seq_len * num_kv_heads * 4.0 * head_dim;
+    // layers' caches come in between), against the 256 MB last-level cache (see the kernel's loads).  Sequences
+    // may share pages: a layer holds no more tokens than its pool (the training mask's 1024 blocks read 32 MB
+    // between them: 685 us with non-temporal loads, 622 without; 64 caches of their own 89 against 99).
+    const double tokens = (double)batch * max_seq_len < pool_tokens ? (double)batch * max_seq_len : pool_tokens;
+    const double stream_bytes = (double)(num_layers > 1 ? num_layers : 1) * tokens * num_kv_heads * 4.0 * head_dim;
     plan->kv_nt = stream_bytes > 1.25 * 256.0 * 1024 * 1024 ? 1 : 0;
     if (requested_splits < 0) {
         // balanced partition: as many workgroups as are resident at once, two partial slots each

@@ -167,7 +167,7 @@ struct AttnLaunchEvents {
 
 // Host-side launchers (defined next to the kernels).  Return hipSuccess or the launch error.
 hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv_heads, int max_seq_len,
-                     int requested_splits, int num_cus, int num_layers, AttnPlan *plan);
+                     int requested_splits, int num_cus, int num_layers, double pool_tokens, AttnPlan *plan);
 hipError_t launch_attn(const AttnArgs &a, const AttnPlan &plan, int head_dim, hipStream_t stream,
                        AttnLaunchEvents *events = nullptr);
 // The 64-rows-per-wave kernel: whether it is the better one for these rows, its LDS need, its launch (grid from the plan).
