@@ -303,8 +303,7 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(const AttnA
             bool moved;
             if constexpr (kWeightsFirst) {
                 row_weights(s, c, m_run, p, sum);
-                moved = __any(sum > kLazySum);
-                if (__builtin_expect(moved, 0)) alpha = move_reference(s, c, m_run, p, sum);
+                moved = __builtin_expect(may_outgrow(sum), 0) && move_reference(s, c, m_run, p, sum, alpha);
             } else {
                 float mx = s[0];
 #pragma unroll
@@ -327,7 +326,7 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(const AttnA
                 sum = 0.f;
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    p[r] = __builtin_amdgcn_exp2f(s[r] * c - m_run);
+                    p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c, -m_run));
                     sum += p[r];
                 }
             }

@@ -64,31 +64,35 @@ __device__ __forceinline__ float sum_with_other_half(float x)
 }
 
 // Online softmax of one lane's 16 scores (half of a row; lane ^ 32 holds the rest) against a lazily updated
-// reference m in the log2 domain.  The weights are taken against the old reference first; only when their sum says
-// that one of them may have outgrown it by more than 2^8 (rarely, after a row's first tile) does the reference move
-// to the running maximum, and the caller scales what it has accumulated.  No maximum is taken on the common path
-// (about 15 of the 75 vector instructions a tile would cost), and the result is the same: numerator and denominator
-// always share a reference.  NaN and infinite scores end up as they would with an eager maximum.
-constexpr float kLazySum = 256.0f;
+// reference m in the log2 domain.  The weights are taken against the old reference first.  Only when their sum says
+// that one of them may have outgrown it by more than 2^kLazy (rarely, after a row's first tile) is the maximum taken,
+// and the reference moves to it by the same rule that a maximum in every tile would apply: no maximum on the common
+// path (about 15 of the 75 vector instructions a tile would cost) and the same bits.  A weight above 2^kLazy puts the
+// sum above kLazySum (a little below 2^kLazy, for the exponential's rounding); a sum that is NaN compares false.
+constexpr float kLazySum = 255.0f;
+static_assert(kLazy == 8.0f, "kLazySum follows it");
 __device__ __forceinline__ void row_weights(const f32x16 &s, float c, float m, float (&e)[16], float &sum)
 {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) e[r] = __builtin_amdgcn_exp2f(s[r] * c - m);
+    for (int r = 0; r < 16; ++r) e[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c, -m));
     sum = e[0];
 #pragma unroll
     for (int r = 1; r < 16; ++r) sum += e[r];
 }
-// Moves m to the running maximum of the row and takes the weights again; returns the factor for the sums so far.
-__device__ __forceinline__ float move_reference(const f32x16 &s, float c, float &m, float (&e)[16], float &sum)
+__device__ __forceinline__ bool may_outgrow(float sum) { return __any(!(sum <= kLazySum)); }
+// Moves m to the running maximum of the row if any of the wave's rows has outgrown its reference, and takes the weights
+// again; alpha is the factor for the sums so far.  False when nothing moved.
+__device__ __forceinline__ bool move_reference(const f32x16 &s, float c, float &m, float (&e)[16], float &sum, float &alpha)
 {
     float mx = s[0];
 #pragma unroll
     for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
-    const float m_new = fmaxf(m, max_with_other_half(mx) * c);
-    const float alpha = __builtin_amdgcn_exp2f(m - m_new);
-    m = m_new;
+    const float m_cand = fmaxf(m, max_with_other_half(mx) * c);
+    if (!__any(m_cand - m > kLazy)) return false;
+    alpha = __builtin_amdgcn_exp2f(m - m_cand);
+    m = m_cand;
     row_weights(s, c, m, e, sum);
-    return alpha;
+    return true;
 }
 
 // Plain workgroup barrier.  Tile loads are tracked by hand (vmcnt), LDS traffic of the compiler's own

@@ -238,7 +238,7 @@ __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(const AttnArgs a)
                     const int tok = 8 * (r >> 2) + 4 * h + (r & 3);
                     t[r] = tok >= lim ? -INFINITY : t[r];
                 }
-                e[r] = __builtin_amdgcn_exp2f(t[r] * c - mref);
+                e[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(t[r], c, -mref));
                 if (r == 1) sum = e[0];
                 else if (r > 1) sum += e[r - 1];
                 if ((r & 1) && r >= 3) pk[(r - 3) / 2] = pack_bf16(e[r - 3], e[r - 2]);
@@ -248,8 +248,8 @@ __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(const AttnArgs a)
         sum += e[15];
         pk[7] = pack_bf16(e[14], e[15]);
         asm volatile("" : "+v"(sum), "+v"(pk[0]), "+v"(pk[1]), "+v"(pk[2]), "+v"(pk[3]), "+v"(pk[4]), "+v"(pk[5]), "+v"(pk[6]), "+v"(pk[7]));
-        if (__builtin_expect(__any(sum > kLazySum), 0)) {
-            const float alpha = move_reference(t, c, m[X], e, sum);
+        float alpha;
+        if (__builtin_expect(may_outgrow(sum), 0) && move_reference(t, c, m[X], e, sum, alpha)) {
             l[X] *= alpha;
 #pragma unroll
             for (int db = 0; db < DBLK; ++db)

@@ -1,11 +1,13 @@
 """The 64-rows-per-wave attention kernel (the one for launches that fill the chip) against the oracle: decode-mode
 batches and prefill at the smallest launches that take it, with lengths on both sides of every tile and ring edge.
 Same bars as every other attention parity test."""
+from dataclasses import replace
+
 import numpy as np
 import pytest
 
 import oracle
-from orthrus_inputs import Workload, make_block, make_cache
+from orthrus_inputs import Workload, bf16_bits_to_f32, f32_to_bf16_bits, make_block, make_cache
 
 from test_gpu_parity import AR, DIFF, GpuCase, _check_attn, _oracle_attn
 from test_gpu_prefill import Case, _check, _new_tokens
@@ -96,8 +98,52 @@ def test_pool_strides_past_32_bit_byte_arithmetic(batch, hkv, K):
     step.attn(AR, D(blk["q"]), D(blk["k_blk"]), D(blk["v_blk"]), D(k_pool), D(v_pool), D(cache["page_table"]),
               D(cache["seq_lens"]), out)
     torch.cuda.synchronize()
-    from orthrus_inputs import bf16_bits_to_f32
     got = bf16_bits_to_f32(rt.bits_to_numpy(out)).astype(np.float64)
     _check_attn(got, _oracle_attn(AR, w, blk, cache))
     assert step.device_error() == 0
     step.close()
+
+
+def _wider(q):
+    return f32_to_bf16_bits(np.float32(2.0) * bf16_bits_to_f32(q))
+
+
+@pytest.mark.parametrize("g,K,hkv,batch,d", [(4, 32, 8, 64, 128), (8, 32, 4, 64, 128), (7, 32, 4, 64, 128), (8, 16, 8, 64, 64)])
+def test_decode_bits_do_not_depend_on_the_batch_size(g, K, hkv, batch, d):
+    """A sequence that is not split gets the same bits in a batch that fills the chip (64 rows per wave) and alone (32
+    rows): both kernels move a row's softmax reference by the same rule.  Scores of twice the usual size and
+    short first tiles, so that references move."""
+    w = Workload(name="bits", seed=9000 + g * K + d, batch=batch, num_q_heads=g * hkv, num_kv_heads=hkv, head_dim=d,
+                 block_k=K, context=300, page_size=16, paging="scattered")
+    cache, blk = make_cache(w, seq_lens=_lens(batch, 9001)), make_block(w, 9002)
+    blk["q"] = _wider(blk["q"])
+    case = GpuCase(w, cache, max_seq_len=300)
+    got = case.attn(DIFF, blk, want_lse=False)
+    _check_attn(got, _oracle_attn(DIFF, w, blk, cache))
+    case.step.close()
+    for b in range(0, batch, 2):
+        few = GpuCase(replace(w, batch=2), dict(cache, page_table=cache["page_table"][b:b + 2], seq_lens=cache["seq_lens"][b:b + 2]),
+                      num_splits=1, max_seq_len=300)
+        part = few.attn(DIFF, {x: blk[x][b:b + 2] for x in blk}, want_lse=False)
+        np.testing.assert_array_equal(part, got[b:b + 2], err_msg="sequences %d, %d" % (b, b + 1))
+        few.step.close()
+
+
+@pytest.mark.parametrize("g,batch,T", [(4, 64, 70), (1, 70, 40)])
+def test_prefill_bits_do_not_depend_on_the_batch_size(g, batch, T):
+    """The same for prefill, where the chunks of both forms start at whole 32-row blocks."""
+    w = Workload(name="bitsp", seed=9100 + g, batch=batch, num_q_heads=g * 8, num_kv_heads=8, head_dim=128, block_k=8,
+                 context=300, page_size=16, paging="shuffled", steps=(T + 7) // 8 + 1)
+    cache = make_cache(w, seq_lens=_lens(batch, 9101))
+    new_lens = np.random.default_rng(9102).integers(1, T + 1, size=batch).astype(np.int32)
+    q, kn, vn = _new_tokens(w, T, 9103)
+    q = _wider(q)
+    msl = int(cache["seq_lens"].max()) + T
+    case = Case(w, cache, max_seq_len=msl)
+    got = case.prefill(q, kn, vn, new_lens)
+    case.step.close()
+    for b in range(0, batch, 2):
+        few = Case(replace(w, batch=2), dict(cache, page_table=cache["page_table"][b:b + 2], seq_lens=cache["seq_lens"][b:b + 2]), msl)
+        part = few.prefill(q[b:b + 2], kn[b:b + 2], vn[b:b + 2], new_lens[b:b + 2])
+        np.testing.assert_array_equal(part, got[b:b + 2], err_msg="sequences %d, %d" % (b, b + 1))
+        few.step.close()
