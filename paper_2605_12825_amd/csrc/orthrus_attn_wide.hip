@@ -273,6 +273,11 @@ __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(const AttnArgs a)
         wg_barrier();
         if (i + NS - 1 < w.n_tiles) issue_tile(i + NS - 1);
     };
+    // The pipeline's first pass multiplies zero weights, where an infinite V would make NaN of the sums: it reads the V
+    // half of the last stage, which holds zeros until the barrier of the first step lets a tile into it.
+    const uint32_t last_v = smem_lds + (NS - 1) * STAGE_B + TILE_B;
+    for (int x = tid * 16; x < TILE_B; x += 64 * W * 16) *(lds_u32x4 *)(uintptr_t)(last_v + x) = u32x4{0, 0, 0, 0};
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     // tile 0 has landed
     {
         const int ahead = min(NS - 2, w.n_tiles - 1);
@@ -282,7 +287,7 @@ __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(const AttnArgs a)
         else wait_vmcnt<0>();
         wg_barrier();
     }
-    uint32_t st = smem_lds, sv = smem_lds;  // stages of tiles i and i-1 (first pass: of tile 0, against zero weights)
+    uint32_t st = smem_lds, sv = smem_lds + (NS - 1) * STAGE_B;  // stages of tiles i and i-1
     auto next = [&](uint32_t x) __attribute__((always_inline)) { return x + STAGE_B == smem_lds + NS * STAGE_B ? smem_lds : x + STAGE_B; };
 #pragma unroll
     for (int kk = 0; kk < KSTEPS; ++kk) read_k(st, kk);

@@ -147,3 +147,48 @@ def test_prefill_bits_do_not_depend_on_the_batch_size(g, batch, T):
         part = few.prefill(q[b:b + 2], kn[b:b + 2], vn[b:b + 2], new_lens[b:b + 2])
         np.testing.assert_array_equal(part, got[b:b + 2], err_msg="sequences %d, %d" % (b, b + 1))
         few.step.close()
+
+
+def _check_with_infinities(got, want):
+    """Infinities where the 64-bit result has them and nowhere else; everything finite within the usual bars."""
+    fin = np.isfinite(want)
+    assert not fin.all()
+    np.testing.assert_array_equal(got[~fin], want[~fin])
+    _check_attn(np.where(fin, got, 0.0), np.where(fin, want, 0.0))
+
+
+@pytest.mark.parametrize("batch", [2, 64])                        # the 32-row kernel, the 64-row kernel
+@pytest.mark.parametrize("g,K,hkv,d", [(4, 32, 8, 128), (8, 32, 4, 128), (8, 16, 8, 64)])
+def test_infinite_value_in_the_first_tile_stays_infinite(batch, g, K, hkv, d):
+    """An infinite V in a sequence's first 32 tokens, or in its block when the cache is empty, makes its column infinite
+    for every row that sees it: zero weights of a pipeline that is still filling must not meet it."""
+    lens = np.where(np.arange(batch) % 2, 32 + 37 * (np.arange(batch) % 8), 0).astype(np.int32)
+    w = Workload(name="inf", seed=9200 + d + g, batch=batch, num_q_heads=g * hkv, num_kv_heads=hkv, head_dim=d, block_k=K,
+                 context=300, page_size=16, paging="shuffled")
+    cache, blk = make_cache(w, seq_lens=lens), make_block(w, 9201)
+    for b in range(batch):
+        bits, head, col = (0x7F80, 0xFF80)[b // 2 % 2], b % hkv, (7 * b) % d
+        if lens[b]:
+            cache["v_pool"][cache["page_table"][b, b % 2], head, b % 16, col] = bits
+        else:
+            blk["v_blk"][b, 0, head, col] = bits
+    case = GpuCase(w, cache)
+    _check_with_infinities(case.attn(DIFF, blk, want_lse=False), _oracle_attn(DIFF, w, blk, cache))
+    case.step.close()
+
+
+@pytest.mark.parametrize("batch", [2, 64])
+def test_infinite_value_in_the_first_tile_stays_infinite_in_prefill(batch):
+    T, hkv, d = 70, 8, 128
+    w = Workload(name="infp", seed=9300, batch=batch, num_q_heads=4 * hkv, num_kv_heads=hkv, head_dim=d, block_k=8, context=300,
+                 page_size=16, paging="shuffled", steps=(T + 7) // 8 + 1)
+    cache = make_cache(w, seq_lens=(32 + 45 * (np.arange(batch) % 5)).astype(np.int32))
+    for b in range(batch):
+        cache["v_pool"][cache["page_table"][b, b % 2], b % hkv, b % 16, (7 * b) % d] = 0x7F80
+    q, kn, vn = _new_tokens(w, T, 9301)
+    new_lens = np.full(batch, T, np.int32)
+    ref = [cache[x].copy() for x in ("k_pool", "v_pool", "seq_lens")]
+    want, _ = oracle.prefill_attn(w.sm_scale, q, kn, vn, new_lens, ref[0], ref[1], cache["page_table"], ref[2])
+    case = Case(w, cache, max_seq_len=int(cache["seq_lens"].max()) + T)
+    _check_with_infinities(bf16_bits_to_f32(case.prefill(q, kn, vn, new_lens)).astype(np.float64), want)
+    case.step.close()
