@@ -204,7 +204,8 @@ orthrus_status orthrus_dual_view_attn(orthrus_ctx *ctx, const orthrus_params *p,
  *                                           (pools, page_table and seq_lens are then not touched)
  *   k_pool, v_pool [dev] bf16, updated in place; page_table [dev] as above
  *   seq_lens     [dev] int32 [B], updated in place
- *   accept_len, num_committed, next_anchor [dev] int32 [B]; out_tokens [dev] int32 [B, K]
+ *   accept_len, num_committed, next_anchor [dev] int32 [B]; out_tokens [dev] int32 [B, K], which may be
+ *                                           draft_tokens itself (tokens written over the drafts)
  *   workspace/workspace_bytes: at least orthrus_consensus_workspace_bytes(p)
  *
  * Device-side errors: if a position L..L+m-1 is not mapped (beyond max_pages_per_seq or page

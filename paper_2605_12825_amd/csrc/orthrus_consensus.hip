@@ -4,14 +4,16 @@
 //
 //   argmax_partial_kernel  grid (row * chunks + chunk): each workgroup scans one chunk of one logits
 //                          row with 16-byte loads and reduces (value, index) through wavefront
-//                          shuffles; one (value, index) pair per chunk goes to the workspace.
+//                          shuffles; one (value, index) pair per chunk goes to the workspace, with a mark when
+//                          the index is the row's draft.
 //   accept_commit_kernel   grid (sequence, layer): the four waves finish the K row argmaxes (chunk pairs
 //                          spread over the lanes, wavefront-shuffle reduction), the first wave finds the
-//                          accepted prefix with a wavefront ballot and checks that the appended positions
+//                          accepted prefix from the marks with a wavefront ballot and checks that the appended positions
 //                          are mapped; then the workgroup copies its layer's appended K/V rows into their
 //                          pages.  The workgroup of layer 0 writes tokens and lengths.  (Every layer's
 //                          workgroup repeats the few microseconds of the decision: a third launch that copies
-//                          by it cost 4 to 7 us.)
+//                          by it cost 4 to 7 us.  It reads nothing that layer 0's workgroup writes, drafts
+//                          included: out_tokens may be draft_tokens.)
 // (A single-launch variant in which the last-arriving workgroup of a sequence finishes the job was
 // measured and dropped: the device-scope release/acquire fences it needs per workgroup cost far
 // more than the two extra launches.)
@@ -66,7 +68,7 @@ constexpr int kChunkElems = 8192;  // floats per (row, chunk) workgroup: 32 KiB
 int consensus_chunk_elems() { return kChunkElems; }
 
 // true if candidate (v1, i1) outranks (v2, i2)
-__device__ __forceinline__ bool outranks(float v1, int i1, float v2, int i2)
+__device__ __forceinline__ bool outranks(float v1, uint32_t i1, float v2, uint32_t i2)
 {
     const bool n1 = v1 != v1, n2 = v2 != v2;
     if (n1 || n2) return (n1 && n2) ? (i1 < i2) : n1;
@@ -74,17 +76,17 @@ __device__ __forceinline__ bool outranks(float v1, int i1, float v2, int i2)
 }
 
 // update for a candidate known to sit at a larger index than the current best
-__device__ __forceinline__ void take_later(float v, int i, float &bv, int &bi)
+__device__ __forceinline__ void take_later(float v, uint32_t i, float &bv, uint32_t &bi)
 {
     if (!(bv != bv) && ((v != v) || v > bv)) { bv = v; bi = i; }
 }
 
-__device__ __forceinline__ void wave_best(float &bv, int &bi)
+__device__ __forceinline__ void wave_best(float &bv, uint32_t &bi)
 {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
         const float ov = __shfl_xor(bv, off);
-        const int oi = __shfl_xor(bi, off);
+        const uint32_t oi = (uint32_t)__shfl_xor((int)bi, off);
         if (outranks(ov, oi, bv, bi)) { bv = ov; bi = oi; }
     }
 }
@@ -97,7 +99,8 @@ __global__ void __launch_bounds__(256) argmax_partial_kernel(const ConsensusArgs
     const int begin = chunk * a.chunk_elems;
     const int end = min(a.vocab, begin + a.chunk_elems);
     float bv = -INFINITY;
-    int bi = 0x7fffffff;
+    uint32_t bi = 0x7fffffff;
+    const int draft = tid == 0 ? a.draft_tokens[row] : -1;
     if (a.do_commit && tid == 0 && chunk == 0 && row % a.block_k == 0) commit_snapshot(a, row / a.block_k);
     // The 16-byte aligned middle of the chunk, all of a thread's loads before the first comparison (kChunkElems / 1024
     // = 8 of 16 bytes), and up to three elements on either side of it (a row starts anywhere when the vocabulary is
@@ -130,7 +133,7 @@ __global__ void __launch_bounds__(256) argmax_partial_kernel(const ConsensusArgs
     if (edge < end && outranks(xe, edge, bv, bi)) { bv = xe; bi = edge; }
     wave_best(bv, bi);
     __shared__ float sv[4];
-    __shared__ int si[4];
+    __shared__ uint32_t si[4];
     if ((tid & 63) == 0) { sv[tid >> 6] = bv; si[tid >> 6] = bi; }
     __syncthreads();
     if (tid == 0) {
@@ -138,7 +141,7 @@ __global__ void __launch_bounds__(256) argmax_partial_kernel(const ConsensusArgs
         for (int w = 1; w < 4; ++w)
             if (outranks(sv[w], si[w], bv, bi)) { bv = sv[w]; bi = si[w]; }
         a.part_val[(int64_t)row * a.chunks + chunk] = bv;
-        a.part_idx[(int64_t)row * a.chunks + chunk] = bi;
+        a.part_idx[(int64_t)row * a.chunks + chunk] = bi << 1 | (bi == (uint32_t)draft ? 1u : 0u);
     }
 }
 
@@ -148,33 +151,30 @@ __global__ void __launch_bounds__(256) accept_commit_kernel(const ConsensusArgs 
     const bool lead = layer == 0;
     const int K = a.block_k;
     __shared__ int s_L, s_m;
-    __shared__ int s_am[32], s_pg[32];
+    __shared__ uint32_t s_am[32];  // index << 1 | mark
+    __shared__ int s_pg[32];
     const int wave = tid >> 6, lane = tid & 63;
-    // ---- loads that do not depend on the argmaxes go out first (first wave): the drafts, the length
-    // and the page ids of the K positions that may be appended
-    int draft = -1;
+    // ---- loads that do not depend on the argmaxes go out first (first wave): the length and the page ids of the K
+    // positions that may be appended
     CommitProbe probe = {0, -1};
-    if (wave == 0) {
-        if (lane < K) draft = a.draft_tokens[(int64_t)b * K + lane];
-        if (a.do_commit) probe = commit_probe(a, b, lane);
-    }
+    if (wave == 0 && a.do_commit) probe = commit_probe(a, b, lane);
     // ---- row argmaxes: wave w finishes rows w, w+4, ...; a lane takes the chunk pairs lane, lane+64, ...
     // All loads of a wave's rows go out before the first reduction, so the phase costs one memory round
-    // trip, not one per chunk.  A lane without a chunk holds (-inf, INT_MAX), which every real pair outranks.
+    // trip, not one per chunk.  A lane without a chunk holds (-inf, UINT_MAX), which every real pair outranks.
     {
         constexpr int kRowsPerWave = 8;  // block_k <= 32 rows over 4 waves
         float bv[kRowsPerWave];
-        int bi[kRowsPerWave];
+        uint32_t bi[kRowsPerWave];
 #pragma unroll
         for (int u = 0; u < kRowsPerWave; ++u) {
             const int k = wave + 4 * u;
             bv[u] = -INFINITY;
-            bi[u] = 0x7fffffff;
+            bi[u] = 0xffffffffu;
             if (k < K) {
                 const int64_t r = ((int64_t)b * K + k) * a.chunks;
                 for (int ch = lane; ch < a.chunks; ch += 64) {
                     const float v = a.part_val[r + ch];
-                    const int i = a.part_idx[r + ch];
+                    const uint32_t i = a.part_idx[r + ch];
                     if (outranks(v, i, bv[u], bi[u])) { bv[u] = v; bi[u] = i; }
                 }
             }
@@ -194,8 +194,8 @@ __global__ void __launch_bounds__(256) accept_commit_kernel(const ConsensusArgs 
         int am = -1;
         bool match = false;
         if (lane < K) {
-            am = s_am[lane];
-            match = draft == am;
+            am = (int)(s_am[lane] >> 1);
+            match = s_am[lane] & 1u;
         }
         // accepted prefix = run of matching rows starting at row 0
         const unsigned long long mism = ~__ballot(match);           // lanes >= K never match

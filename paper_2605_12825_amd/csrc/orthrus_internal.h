@@ -53,8 +53,9 @@ struct ConsensusArgs {
     const int32_t *page_table;
     int32_t *seq_lens, *accept_len, *num_committed, *out_tokens, *next_anchor;
     float *part_val;     // [B*K][chunks]
-    int32_t *part_idx;   // [B*K][chunks]
+    uint32_t *part_idx;  // [B*K][chunks]: index << 1, plus 1 if it is the row's draft
     int32_t *commit_info;  // [B]: length before the step (the scan's snapshot; seq_lens is bumped while others still read)
+    int32_t *first_rej;    // [B]: sampling: first row that is not kept, K if none (the draw kernel's decision)
     int32_t *err_word;
     int64_t stride_layer, stride_page, stride_head, stride_tok, num_pages;
     int64_t blk_stride_layer, blk_stride_row, blk_stride_head;  // of k_blk_ar / v_blk_ar

@@ -10,10 +10,11 @@
 //   draw_partial_kernel     grid (draw chunk, sequence): every workgroup re-derives the K keep decisions of
 //                           its sequence from the chunk pairs (same code, same order => same answer
 //                           everywhere), and if a row j < K was rejected scans its 2048-element piece of row
-//                           j for the two candidate maxima.
-//   sample_commit_kernel    grid (sequence, layer): decisions again; the workgroup of layer 0 finishes the draw
-//                           (a total order: any order of merging gives the same token) and writes the
-//                           outputs, every layer's workgroup commits its layer's kept rows.
+//                           j for the two candidate maxima.  The first one records j.
+//   sample_commit_kernel    grid (sequence, layer): the workgroup of layer 0 finishes the draw (a total order:
+//                           any order of merging gives the same token) and writes the outputs, every layer's
+//                           workgroup commits its layer's kept rows.  Only layer 0's reads the drafts, before
+//                           it writes the tokens: out_tokens may be draft_tokens.
 // The two small kernels are chains of memory round trips and exponentials.  Eight threads share a row's chunk pairs
 // and the draw's pieces are small, so that a batch of one fills 63 workgroups instead of 16 with four times fewer
 // exponentials per thread (batch 1, K = 16, V = 128256: 14.2 + 9.0 us before; batch 8, K = 32, V = 151936: 16.9 + 11.3).
@@ -174,6 +175,7 @@ __global__ void __launch_bounds__(256) draw_partial_kernel(const SamplingArgs a)
     const int K = a.c.block_k, V = a.c.vocab;
     float lsep, lseq;
     const int j = first_rejected(a, b, tid, lsep, lseq);
+    if (chunk == 0 && tid == 0) a.c.first_rej[b] = j;
     if (j >= K) return;  // every draft kept: nothing to draw
     const float it = a.inv_temperature;
     const float *pr = a.c.ar_logits + ((int64_t)b * K + j) * V;
@@ -259,13 +261,11 @@ __global__ void __launch_bounds__(256) sample_commit_kernel(const SamplingArgs a
     const int K = c.block_k;
     __shared__ int s_L, s_m;
     __shared__ int s_pg[32];
-    // the page ids of the K positions that may be appended do not depend on the decisions: their loads go out first
-    CommitProbe probe = {0, -1};
-    if (tid < 64 && c.do_commit) probe = commit_probe(c, b, tid);
-    float lp, lq;
-    const int j = first_rejected(a, b, tid, lp, lq);
     if (tid < 64) {
         const int lane = tid;
+        const int j = c.first_rej[b];
+        CommitProbe probe = {0, -1};
+        if (c.do_commit) probe = commit_probe(c, b, lane);
         const int m = min(j + 1, K);
         if (lead) {
             int repl = -1;
