@@ -109,12 +109,6 @@ orthrus_status make_plan(const orthrus_params *p, int num_cus, orthrus::AttnPlan
     return ORTHRUS_OK;
 }
 
-size_t draw_chunks(const orthrus_params *p)
-{
-    const int de = orthrus::draw_chunk_elems();
-    return ((size_t)p->vocab + de - 1) / de;
-}
-
 int consensus_chunks(const orthrus_params *p)
 {
     const int ce = orthrus::consensus_chunk_elems();
@@ -599,7 +593,7 @@ int64_t orthrus_sampling_workspace_bytes(const orthrus_params *p)
     if (s != ORTHRUS_OK) return (int64_t)s;
     const size_t rows = (size_t)p->batch * p->block_k;
     const size_t chunks = (size_t)consensus_chunks(p);
-    return (int64_t)(align_up(rows * chunks * 16, 256) + align_up((size_t)p->batch * draw_chunks(p) * 16, 256) +
+    return (int64_t)(align_up(rows * chunks * 16, 256) + align_up((size_t)p->batch * chunks * 16, 256) +
                      align_up((size_t)p->batch * 2 * sizeof(int32_t), 256));
 }
 
@@ -636,7 +630,7 @@ orthrus_status orthrus_sampling_consensus_commit(orthrus_ctx *ctx, const orthrus
     const size_t chunks = (size_t)consensus_chunks(p);
     if (rows * chunks > 0x7fffffffull || chunks > 65535) return ORTHRUS_EUNSUPPORTED;
     const size_t o1 = align_up(rows * chunks * 16, 256);
-    const size_t o2 = o1 + align_up((size_t)p->batch * draw_chunks(p) * 16, 256);
+    const size_t o2 = o1 + align_up((size_t)p->batch * chunks * 16, 256);
     const size_t need = o2 + align_up((size_t)p->batch * 2 * sizeof(int32_t), 256);
     if (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 255)) return ORTHRUS_EWORKSPACE;
 
@@ -661,9 +655,10 @@ orthrus_status orthrus_sampling_consensus_commit(orthrus_ctx *ctx, const orthrus
     c.chunks = (int)chunks; c.chunk_elems = orthrus::consensus_chunk_elems(); c.do_commit = do_commit ? 1 : 0;
     a.diff_logits = diff_logits; a.accept_u = accept_u; a.gumbel = gumbel;
     a.lse_part = (float4 *)workspace;
-    a.draw_part = (float4 *)((char *)workspace + o1);
+    a.draw_key = (unsigned long long *)((char *)workspace + o1);
     a.inv_temperature = 1.0f / temperature;
-    a.draw_chunks = (int)draw_chunks(p);
+    const int de = orthrus::draw_chunk_elems();
+    a.draw_chunks = p->vocab / de + (p->vocab % de ? 1 : 0);
     hipError_t e = orthrus::launch_sampling_consensus(a, (hipStream_t)stream);
     return e == hipSuccess ? ORTHRUS_OK : ORTHRUS_EHIP;
 }

@@ -69,7 +69,7 @@ struct SamplingArgs {
     const float *accept_u;    // [B][K]
     const float *gumbel;      // [B][V]
     float4 *lse_part;         // [B*K][chunks]: (max_p, sum_p, max_q, sum_q) of logits / T over the chunk
-    float4 *draw_part;        // [B][draw_chunks]: (best score among p>q, its index, best score of log p + g, its index)
+    unsigned long long *draw_key;  // [B][2 * chunks]: best candidates of the draw (draw_key_of), two pieces to a key
     float inv_temperature;
     int draw_chunks;          // draw_chunk_elems()-sized pieces of a row
 };

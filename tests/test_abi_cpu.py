@@ -112,6 +112,17 @@ def test_balanced_partition_plan_on_the_host():
         orthrus.orthrus_attn_num_splits(p)
 
 
+@pytest.mark.parametrize("batch,K,vocab,greedy,sampling", [(1, 16, 128256, 2304, 4608), (8, 32, 151936, 39168, 80640),
+                                                          (3, 5, 2049, 768, 768), (2, 4, 1, 768, 768)])
+def test_consensus_workspaces_do_not_grow(batch, K, vocab, greedy, sampling):
+    """Programs keep these buffers: one entry per (row, 8192-element chunk), one per (sequence, chunk) for the draw and two
+    words per sequence, each padded to 256 bytes."""
+    p = _good()
+    p.batch, p.block_k, p.vocab = batch, K, vocab
+    assert orthrus.orthrus_consensus_workspace_bytes(p) == greedy
+    assert orthrus.orthrus_sampling_workspace_bytes(p) == sampling
+
+
 def test_prefill_workspace_and_argument_checks_on_the_host():
     p = _good()
     assert orthrus.orthrus_prefill_workspace_bytes(p, 4096) >= 2 * 4 * p.batch

@@ -207,3 +207,35 @@ def test_vocabularies_around_the_chunk_and_load_edges(vocab, layers):
     np.testing.assert_array_equal(rt.bits_to_numpy(kp), rk)
     np.testing.assert_array_equal(rt.bits_to_numpy(vp), rv)
     step.close()
+
+
+@pytest.mark.parametrize("batch,K,vocab", [(1, 16, 128256), (8, 3, 40000), (3, 5, 2049)])
+def test_workspace_of_exactly_the_asked_size_and_full_of_rubbish(batch, K, vocab):
+    """Nothing is read that the call did not write, nothing is written behind the size that the query names, and one byte
+    less is refused."""
+    from paper_2605_12825_amd import binding as B
+    from paper_2605_12825_amd import runtime as rt
+    w = Workload(name="ws", seed=9800 + vocab, batch=batch, num_q_heads=4, num_kv_heads=2, head_dim=64, block_k=K,
+                 context_range=(0, 50), page_size=16, vocab=vocab)
+    c, _ = _clear_case(w, 9810, temperature=0.9)
+    want = oracle.sampling_consensus_commit(c["ar_logits"], c["diff_logits"], c["draft_tokens"], c["accept_u"], c["gumbel"], 0.9)
+    step = rt.DecodeStep(batch=batch, num_q_heads=4, num_kv_heads=2, head_dim=64, block_k=K, page_size=16, max_pages_per_seq=4,
+                         max_seq_len=64, num_pages=4, vocab=vocab)
+    n = B.orthrus_sampling_workspace_bytes(step.params)
+    dev = {x: rt.to_device_bits(v) for x, v in c.items() if isinstance(v, np.ndarray)}
+    for byte in (0xFF, 0x7F, 0x00):
+        room = torch.full((n + 4096,), byte, dtype=torch.uint8, device="cuda")
+        outs = [torch.full((batch,), -7, dtype=torch.int32, device="cuda") for _ in range(3)]
+        toks = torch.full((batch, K), -7, dtype=torch.int32, device="cuda")
+
+        def call(ws, check):
+            return B.orthrus_sampling_consensus_commit(step.ctx, step.params, 0.9, dev["ar_logits"], dev["diff_logits"],
+                                                       dev["draft_tokens"], dev["accept_u"], dev["gumbel"], None, None, None, None,
+                                                       None, None, outs[0], outs[1], toks, outs[2], ws, check=check)
+        assert call(room[:n - 1], False) == B.ORTHRUS_EWORKSPACE
+        call(room[:n], True)
+        torch.cuda.synchronize()
+        assert (room[n:] == byte).all()
+        got = dict(accept_len=outs[0], num_committed=outs[1], out_tokens=toks, next_anchor=outs[2])
+        _same({x: v.cpu().numpy() for x, v in got.items()}, want)
+    step.close()
