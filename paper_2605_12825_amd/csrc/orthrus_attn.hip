@@ -394,10 +394,14 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(const AttnA
 // float4 it would hold in the split kernel's accumulator, so every load is a contiguous 1 KB per wave
 // and all splits of a chunk are in flight together.
 //
+// BALANCED: the pieces of a unit are found from the split kernel's partition arithmetic: unit (g, b) covers
+// tiles [U0, U1) of the launch's tile sequence, its pieces belong to workgroups w_lo..w_hi, the first in its
+// slot 2w+1 and the others in slot 2w; a unit held by one workgroup was finished by the split kernel.
+//
 // CHUNK = partials merged per round of loads: 8 keeps the registers low for the bandwidth-bound merges
 // of many units with few pieces each; 16 or 32 make the latency-bound merge of few units with many
 // splits a single memory round trip (a second round costs it ~1 us).
-template <int D, int W, int CHUNK>
+template <int D, int W, int BALANCED, int CHUNK>
 __global__ void __launch_bounds__(256) attn_combine_kernel(const AttnArgs a)
 {
     constexpr int DBLK = D / 32;
@@ -409,17 +413,56 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const AttnArgs a)
     const int unit = blockIdx.x / (DBLK * W);
     const int b = unit / a.num_kv_heads, g = unit % a.num_kv_heads;
     const int ridx = wave * 32 + col;
-    int L = ((const const_i32 *)a.seq_lens)[b];
-    L = L < 0 ? 0 : (L > a.max_seq_len ? a.max_seq_len : L);
-    const int live = split_cut(L, a.num_splits, 0).live;  // the split kernel's pieces of this sequence
-    const size_t first_slot = (size_t)unit * a.num_splits;
+    int live;           // number of partials of this unit
+    size_t first_slot;  // partial index of piece 0; piece s > 0 sits at rest_slot + s * slot_step
+    size_t rest_slot, slot_step;
+    if constexpr (BALANCED) {
+        int before = 0, per_head = 0, mine = 0;  // tiles of the sequences before b, of all, of b
+        for (int x0 = 0; x0 < a.batch; x0 += 64) {
+            const int x = x0 + lane;
+            int n = 0;
+            if (x < a.batch) {
+                int L = a.seq_lens[x];
+                L = L < 0 ? 0 : (L > a.max_seq_len ? a.max_seq_len : L);
+                n = ((L + 31) >> 5) + 1;
+            }
+            int nb = x < b ? n : 0, nm = x == b ? n : 0;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                n += __shfl_xor(n, off);
+                nb += __shfl_xor(nb, off);
+                nm += __shfl_xor(nm, off);
+            }
+            per_head += n;
+            before += nb;
+            mine += nm;
+        }
+        const int64_t total = (int64_t)per_head * a.num_kv_heads;
+        const int64_t nwg = total < (int64_t)a.bal_wgs ? total : (int64_t)a.bal_wgs;
+        const int64_t U0 = (int64_t)g * per_head + before, U1 = U0 + mine;
+        // workgroup w starts at tile floor(w * total / nwg): w_lo is the last one that starts at or
+        // before U0, w_hi the last one that starts before U1
+        const int64_t w_lo = ((U0 + 1) * nwg + total - 1) / total - 1;
+        const int64_t w_hi = (U1 * nwg + total - 1) / total - 1;
+        if (w_lo == w_hi) return;  // one workgroup held the whole unit and wrote its rows
+        live = (int)(w_hi - w_lo + 1);
+        first_slot = (size_t)w_lo * 2 + 1;
+        rest_slot = (size_t)w_lo * 2;
+        slot_step = 2;
+    } else {
+        int L = ((const const_i32 *)a.seq_lens)[b];
+        L = L < 0 ? 0 : (L > a.max_seq_len ? a.max_seq_len : L);
+        live = split_cut(L, a.num_splits, 0).live;  // the split kernel's pieces of this sequence
+        first_slot = rest_slot = (size_t)unit * a.num_splits;
+        slot_step = 1;
+    }
     // partial `s` of this unit: (m, l) of the lane's row and the lane's float4 of the accumulator
     auto ml_at = [&](int s) __attribute__((always_inline)) {
-        const size_t slot = (first_slot + s) * W + wave;
+        const size_t slot = (s == 0 ? first_slot : rest_slot + (size_t)s * slot_step) * W + wave;
         return (const float2 *)a.part_ml + slot * 32 + col;
     };
     auto po_at = [&](int s) __attribute__((always_inline)) {
-        const size_t slot = (first_slot + s) * W + wave;
+        const size_t slot = (s == 0 ? first_slot : rest_slot + (size_t)s * slot_step) * W + wave;
         return (const float4 *)a.part_o + slot * (DBLK * 4 * 64) + (size_t)(db * 4 + r4) * 64 + lane;
     };
 
@@ -458,124 +501,6 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const AttnArgs a)
             acc.x += sc * v[u].x; acc.y += sc * v[u].y; acc.z += sc * v[u].z; acc.w += sc * v[u].w;
         }
     }
-    if (ridx >= a.rows) return;
-    const int G = a.group, K = a.block_k;
-    const int i = ridx / G, hl = ridx - i * G;
-    const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
-    uint16_t *op = a.out + (((int64_t)b * K + i) * a.num_q_heads + (int64_t)g * G + hl) * D;
-    uint2 pk;
-    pk.x = pack_bf16(acc.x * inv, acc.y * inv);
-    pk.y = pack_bf16(acc.z * inv, acc.w * inv);
-    *(uint2 *)(op + 32 * db + 8 * r4 + 4 * h) = pk;
-    if (a.lse && db == 0 && r4 == 0 && h == 0)
-        a.lse[((int64_t)b * a.num_q_heads + (int64_t)g * G + hl) * K + i] =
-            (M + __builtin_amdgcn_logf(lsum)) * 0.6931471805599453f;
-}
-
-// The same for the balanced partition.  The pieces of a unit are found from the split kernel's partition arithmetic
-// (NWG is that launch's workgroup count): unit (g, b) covers tiles [U0, U1) of the launch's tile sequence, its pieces
-// belong to workgroups w_lo..w_hi, the first in its slot 2w+1 and the others in slot 2w; a unit held by one workgroup
-// was finished by the split kernel.
-constexpr unsigned kUnitsPerZ = 32768;  // grid (row block x d block, unit modulo this, unit / this)
-template <int D>
-__global__ void __launch_bounds__(256) attn_combine_balanced_kernel(const AttnArgs a)
-{
-    const int PB = (a.rows + 31) >> 5;  // row blocks of a partial
-    constexpr int DBLK = D / 32;
-    const int lane = threadIdx.x & 63, r4 = threadIdx.x >> 6;
-    const int col = lane & 31, h = lane >> 5;
-    const int db = blockIdx.x % DBLK;
-    const int wave = blockIdx.x / DBLK;  // row block
-    const int unit = (int)(blockIdx.z * kUnitsPerZ + blockIdx.y);
-    if (unit >= a.batch * a.num_kv_heads) return;
-    const int b = unit / a.num_kv_heads, g = unit % a.num_kv_heads;
-    const int ridx = wave * 32 + col;
-    int before = 0, per_head = 0, mine = 0;  // tiles of the sequences before b, of all, of b
-    for (int x0 = 0; x0 < a.batch; x0 += 64) {
-        const int x = x0 + lane;
-        int n = 0;
-        if (x < a.batch) {
-            int L = a.seq_lens[x];
-            L = L < 0 ? 0 : (L > a.max_seq_len ? a.max_seq_len : L);
-            n = ((L + 31) >> 5) + 1;
-        }
-        int nb = x < b ? n : 0, nm = x == b ? n : 0;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            n += __shfl_xor(n, off);
-            nb += __shfl_xor(nb, off);
-            nm += __shfl_xor(nm, off);
-        }
-        per_head += n;
-        before += nb;
-        mine += nm;
-    }
-    const int64_t total = (int64_t)per_head * a.num_kv_heads;
-    const int64_t nwg = total < (int64_t)a.bal_wgs ? total : (int64_t)a.bal_wgs;
-    const int64_t U0 = (int64_t)g * per_head + before, U1 = U0 + mine;
-    // workgroup w starts at tile floor(w * total / nwg): w_lo is the last one that starts at or
-    // before U0, w_hi the last one that starts before U1
-    const int64_t w_lo = ((U0 + 1) * nwg + total - 1) / total - 1;
-    const int64_t w_hi = (U1 * nwg + total - 1) / total - 1;
-    if (w_lo == w_hi) return;  // one workgroup held the whole unit and wrote its rows
-    const int live = (int)(w_hi - w_lo + 1);  // pieces of this unit
-    // piece 0 sits in slot 2 w_lo + 1, piece s > 0 in slot 2 (w_lo + s); a slot is PB row blocks
-    // CHUNK partials per round, all of a round's loads issued before anything waits (up to four past the last piece,
-    // which read the last one again), merged in piece order against the running maximum: the result does not depend
-    // on timing.  Attention over 16 sequences of 512..8192 tokens, 28/4 heads, K = 32: 12.0 -> 10.9 us against the
-    // two-pass merge of attn_combine_kernel.
-    constexpr int CHUNK = 8;
-    constexpr uint32_t kBlockO = DBLK * 4 * 64 * 16, kBlockMl = 32 * 8;  // bytes of one row block
-    const uint32_t lane_o = (uint32_t)((db * 4 + r4) * 64 + lane) * 16u, lane_ml = (uint32_t)col * 8u;
-    const uint32_t step = 2u * PB;  // row blocks from piece to piece
-    float M = kNegBig, lsum = 0.f;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    int s0 = 0;
-    do {
-        const size_t block = (size_t)(w_lo + s0) * step + wave;
-        const char *base_o = (const char *)a.part_o + block * kBlockO, *base_ml = (const char *)a.part_ml + block * kBlockMl;
-        float4 v[CHUNK];
-        float2 e[CHUNK];
-#pragma unroll
-        for (int q = 0; q < CHUNK; q += 4) {  // four loads share one test; past the end the last slot is read again
-            if (s0 + q < live) {
-#pragma unroll
-                for (int u = q; u < q + 4; ++u) {
-                    uint32_t at = (uint32_t)min(u, live - 1 - s0) * step;
-                    if (u == 0 && s0 == 0) at = PB;
-                    v[u] = *(const float4 *)(base_o + (lane_o + at * kBlockO));
-                    e[u] = *(const float2 *)(base_ml + (lane_ml + at * kBlockMl));
-                }
-            } else {
-#pragma unroll
-                for (int u = q; u < q + 4; ++u) {
-                    v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-                    e[u] = make_float2(kNegBig, 0.f);
-                }
-            }
-        }
-        float mx = M;
-#pragma unroll
-        for (int u = 0; u < CHUNK; ++u) {
-            const bool ok = s0 + u < live;  // selects, not products: a dropped slot may hold anything
-            e[u].x = ok ? e[u].x : kNegBig;
-            e[u].y = ok ? e[u].y : 0.f;
-            v[u].x = ok ? v[u].x : 0.f; v[u].y = ok ? v[u].y : 0.f;
-            v[u].z = ok ? v[u].z : 0.f; v[u].w = ok ? v[u].w : 0.f;
-            mx = fmaxf(mx, e[u].x);
-        }
-        const float old = __builtin_amdgcn_exp2f(M - mx);
-        M = mx;
-        lsum *= old;
-        acc.x *= old; acc.y *= old; acc.z *= old; acc.w *= old;
-#pragma unroll
-        for (int u = 0; u < CHUNK; ++u) {
-            const float sc = __builtin_amdgcn_exp2f(e[u].x - M);
-            lsum += sc * e[u].y;
-            acc.x += sc * v[u].x; acc.y += sc * v[u].y; acc.z += sc * v[u].z; acc.w += sc * v[u].w;
-        }
-        s0 += CHUNK;
-    } while (s0 < live);
     if (ridx >= a.rows) return;
     const int G = a.group, K = a.block_k;
     const int i = ridx / G, hl = ridx - i * G;
@@ -701,13 +626,15 @@ static hipError_t launch_split(const AttnArgs &a, const AttnPlan &plan, dim3 gri
                         plan.lds_bytes, a, stream, ev, 0);
 }
 
-template <int D, int W>
-static hipError_t launch_combine(const AttnArgs &a, unsigned workgroups, hipStream_t stream, AttnLaunchEvents *ev)
+template <int D, int W, int BALANCED>
+static hipError_t launch_combine(const AttnArgs &a, hipStream_t stream, AttnLaunchEvents *ev)
 {
-    auto comb = a.num_splits > 16 ? attn_combine_kernel<D, W, 32>
-                : a.num_splits > 8 ? attn_combine_kernel<D, W, 16>
-                                   : attn_combine_kernel<D, W, 8>;
-    return launch_timed(comb, dim3(workgroups), dim3(256), 0, a, stream, ev, 1);
+    auto comb = attn_combine_kernel<D, W, BALANCED, 8>;
+    if constexpr (!BALANCED) {
+        if (a.num_splits > 16) comb = attn_combine_kernel<D, W, 0, 32>;
+        else if (a.num_splits > 8) comb = attn_combine_kernel<D, W, 0, 16>;
+    }
+    return launch_timed(comb, dim3((unsigned)(a.batch * a.num_kv_heads) * W * (D / 32)), dim3(256), 0, a, stream, ev, 1);
 }
 
 // One attention call: the split kernel, then the merge when units were cut into pieces.
@@ -732,20 +659,16 @@ static hipError_t launch_attn_d(const AttnArgs &a, const AttnPlan &plan, hipStre
         }
     }
     if (e != hipSuccess) return e;
-    const unsigned units = (unsigned)(a.batch * a.num_kv_heads), blocks = (unsigned)((a.rows + 31) / 32) * (D / 32);
-    if constexpr (BALANCED) {
-        dim3 cgrid(blocks, units < kUnitsPerZ ? units : kUnitsPerZ, (units + kUnitsPerZ - 1) / kUnitsPerZ);
-        e = launch_timed(attn_combine_balanced_kernel<D>, cgrid, dim3(256), 0, a, stream, ev, 1);
-    } else if (plan.num_splits > 1) {
+    if (BALANCED || plan.num_splits > 1) {
         switch (plan.waves) {
-        case 1: e = launch_combine<D, 1>(a, units * blocks, stream, ev); break;
-        case 2: e = launch_combine<D, 2>(a, units * blocks, stream, ev); break;
-        case 3: e = launch_combine<D, 3>(a, units * blocks, stream, ev); break;
-        case 4: e = launch_combine<D, 4>(a, units * blocks, stream, ev); break;
-        case 5: e = launch_combine<D, 5>(a, units * blocks, stream, ev); break;
-        case 6: e = launch_combine<D, 6>(a, units * blocks, stream, ev); break;
-        case 7: e = launch_combine<D, 7>(a, units * blocks, stream, ev); break;
-        case 8: e = launch_combine<D, 8>(a, units * blocks, stream, ev); break;
+        case 1: e = launch_combine<D, 1, BALANCED>(a, stream, ev); break;
+        case 2: e = launch_combine<D, 2, BALANCED>(a, stream, ev); break;
+        case 3: e = launch_combine<D, 3, BALANCED>(a, stream, ev); break;
+        case 4: e = launch_combine<D, 4, BALANCED>(a, stream, ev); break;
+        case 5: e = launch_combine<D, 5, BALANCED>(a, stream, ev); break;
+        case 6: e = launch_combine<D, 6, BALANCED>(a, stream, ev); break;
+        case 7: e = launch_combine<D, 7, BALANCED>(a, stream, ev); break;
+        case 8: e = launch_combine<D, 8, BALANCED>(a, stream, ev); break;
         }
     }
     return e;
