@@ -214,7 +214,7 @@ static orthrus_status consensus_commit_impl(orthrus_ctx *ctx, const orthrus_para
     a.accept_len = accept_len; a.num_committed = num_committed; a.out_tokens = out_tokens; a.next_anchor = next_anchor;
     a.part_val = (float *)workspace;
     a.part_idx = (uint32_t *)((char *)workspace + o1);
-    a.commit_info = (int32_t *)((char *)workspace + o2); a.first_rej = nullptr;
+    a.commit_info = (int32_t *)((char *)workspace + o2); a.decided = a.commit_info + p->batch; a.copy_apart = 0;
     a.err_word = ctx->err_word;
     a.stride_layer = p->pool_stride_layer; a.stride_page = p->pool_stride_page;
     a.stride_head = p->pool_stride_head; a.stride_tok = p->pool_stride_tok; a.num_pages = p->num_pages;
@@ -642,7 +642,7 @@ orthrus_status orthrus_sampling_consensus_commit(orthrus_ctx *ctx, const orthrus
     c.page_table = page_table; c.seq_lens = seq_lens;
     c.accept_len = accept_len; c.num_committed = num_committed; c.out_tokens = out_tokens; c.next_anchor = next_anchor;
     c.part_val = nullptr; c.part_idx = nullptr;
-    c.commit_info = (int32_t *)((char *)workspace + o2); c.first_rej = c.commit_info + p->batch;
+    c.commit_info = (int32_t *)((char *)workspace + o2); c.decided = c.commit_info + p->batch; c.copy_apart = 0;
     c.err_word = ctx->err_word;
     c.stride_layer = p->pool_stride_layer; c.stride_page = p->pool_stride_page;
     c.stride_head = p->pool_stride_head; c.stride_tok = p->pool_stride_tok; c.num_pages = p->num_pages;

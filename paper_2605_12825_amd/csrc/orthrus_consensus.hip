@@ -14,6 +14,8 @@
 //                          workgroup repeats the few microseconds of the decision: a third launch that copies
 //                          by it cost 4 to 7 us.  It reads nothing that layer 0's workgroup writes, drafts
 //                          included: out_tokens may be draft_tokens.)
+//   commit_kernel          grid (sequence, layer): the copy as a launch of its own, for many (sequence, layer)
+//                          pairs (kCopyApart); accept_commit_kernel then has grid (sequence).
 // (A single-launch variant in which the last-arriving workgroup of a sequence finishes the job was
 // measured and dropped: the device-scope release/acquire fences it needs per workgroup cost far
 // more than the two extra launches.)
@@ -215,7 +217,8 @@ __global__ void __launch_bounds__(256) accept_commit_kernel(const ConsensusArgs 
                 a.next_anchor[b] = anchor;
             }
             s_L = probe.L;
-            s_m = a.do_commit ? committed : 0;
+            s_m = a.do_commit && !a.copy_apart ? committed : 0;
+            if (a.copy_apart) a.decided[b] = committed;
         }
     }
     __syncthreads();
@@ -223,14 +226,32 @@ __global__ void __launch_bounds__(256) accept_commit_kernel(const ConsensusArgs 
     if (s_m > 0) append_rows(a, b, layer, s_L, s_m, tid, 256, s_pg);
 }
 
-hipError_t launch_consensus(const ConsensusArgs &a, hipStream_t stream)
+// The same copy as its own launch.
+__global__ void __launch_bounds__(256) commit_kernel(const ConsensusArgs a)
+{
+    const int b = blockIdx.x, layer = blockIdx.y;
+    const int m = a.decided[b];
+    if (m > 0) append_rows(a, b, layer, a.commit_info[b], m, threadIdx.x, 256);
+}
+
+// From this many (sequence, layer) pairs on, repeating the decision in each costs more than a third launch: 64 x 16 rows,
+// 36 layers (2304 pairs) 42 us against 44 with the copy apart; 80 x 16, 36 layers (2880) 47 against 45; 64 x 32, 48 layers
+// 75 against 68; 64 x 32, 64 layers 91 against 77; 512 x 16, 36 layers 216 against 189.  (Several layers to a workgroup,
+// one after the other: 86 us at 64 x 32 x 64, 156 at 256 x 16 x 36 where one launch of a workgroup each takes 123.)
+constexpr int kCopyApart = 2560;
+
+hipError_t launch_consensus(ConsensusArgs a, hipStream_t stream)
 {
     if (a.batch == 0) return hipSuccess;
+    a.copy_apart = a.do_commit && (int64_t)a.batch * a.num_layers >= kCopyApart;
     dim3 g1((unsigned)a.chunks * (unsigned)(a.batch * a.block_k));
     hipLaunchKernelGGL(argmax_partial_kernel, g1, dim3(256), 0, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(accept_commit_kernel, dim3(a.batch, a.do_commit ? a.num_layers : 1), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(accept_commit_kernel, dim3(a.batch, a.do_commit && !a.copy_apart ? a.num_layers : 1), dim3(256), 0, stream, a);
+    e = hipGetLastError();
+    if (e != hipSuccess || !a.copy_apart) return e;
+    hipLaunchKernelGGL(commit_kernel, dim3(a.batch, a.num_layers), dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 

@@ -55,12 +55,13 @@ struct ConsensusArgs {
     float *part_val;     // [B*K][chunks]
     uint32_t *part_idx;  // [B*K][chunks]: index << 1, plus 1 if it is the row's draft
     int32_t *commit_info;  // [B]: length before the step (the scan's snapshot; seq_lens is bumped while others still read)
-    int32_t *first_rej;    // [B]: sampling: first row that is not kept, K if none (the draw kernel's decision)
+    int32_t *decided;      // [B]: greedy: rows to append, where the copy is a launch of its own; sampling: first row not kept
     int32_t *err_word;
     int64_t stride_layer, stride_page, stride_head, stride_tok, num_pages;
     int64_t blk_stride_layer, blk_stride_row, blk_stride_head;  // of k_blk_ar / v_blk_ar
     int batch, block_k, vocab, num_layers, num_kv_heads, head_dim;
     int page_shift, max_pages_per_seq, chunks, chunk_elems, do_commit;
+    int copy_apart;  // greedy: the commit's copy is a launch of its own (set by the launcher)
 };
 
 struct SamplingArgs {
@@ -177,7 +178,7 @@ size_t attn_wide_lds(int waves, int head_dim);
 hipError_t launch_attn_wide(const AttnArgs &a, const AttnPlan &plan, int head_dim, dim3 grid, hipStream_t stream, AttnLaunchEvents *events);
 hipError_t launch_prefill_attn(const AttnArgs &a, int head_dim, int num_cus, hipStream_t stream);
 hipError_t launch_prefill_split(const AttnArgs &a, int head_dim, hipStream_t stream);
-hipError_t launch_consensus(const ConsensusArgs &a, hipStream_t stream);
+hipError_t launch_consensus(ConsensusArgs a, hipStream_t stream);
 hipError_t launch_sampling_consensus(const SamplingArgs &a, hipStream_t stream);
 int consensus_chunk_elems();
 int draw_chunk_elems();

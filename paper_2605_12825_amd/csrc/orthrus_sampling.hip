@@ -189,7 +189,7 @@ __global__ void __launch_bounds__(256) draw_partial_kernel(const SamplingArgs a)
     const int K = a.c.block_k, V = a.c.vocab;
     float lsep, lseq;
     const int j = first_rejected(a, b, tid, lsep, lseq);
-    if (chunk == 0 && tid == 0) a.c.first_rej[b] = j;
+    if (chunk == 0 && tid == 0) a.c.decided[b] = j;
     if (j >= K) return;  // every draft kept: nothing to draw
     const float it = a.inv_temperature;
     const float *pr = a.c.ar_logits + ((int64_t)b * K + j) * V;
@@ -280,7 +280,7 @@ __global__ void __launch_bounds__(256) sample_commit_kernel(const SamplingArgs a
     __shared__ int s_pg[32];
     if (tid < 64) {
         const int lane = tid;
-        const int j = c.first_rej[b];
+        const int j = c.decided[b];
         CommitProbe probe = {0, -1};
         if (c.do_commit) probe = commit_probe(c, b, lane);
         const int m = min(j + 1, K);

@@ -1,6 +1,7 @@
 """Consensus and commit with out_tokens written over draft_tokens, for several layers: every layer's workgroup commits by
 the same decision, whatever the order in which the tokens replace the drafts.  Results are the oracle's, bit for bit.
-Pages run out inside the block of some sequences, so that a layer that counted one more row would append none."""
+Pages run out inside the block of some sequences, so that a layer that counted one more row would append none, and too
+early in others, which are left alone."""
 import numpy as np
 import pytest
 import torch
@@ -13,9 +14,9 @@ from test_gpu_sampling import _clear_case
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("layers", [1, 3, 36])
 @pytest.mark.parametrize("temperature", [0.0, 0.9])
-@pytest.mark.parametrize("batch,K", [(1, 4), (9, 16), (24, 32)])
+@pytest.mark.parametrize("batch,K,layers", [(1, 4, 1), (1, 4, 36), (9, 16, 1), (9, 16, 3), (24, 32, 36),
+                                            (71, 2, 36), (72, 3, 36)])      # either side of the copy as its own launch
 def test_tokens_replace_the_drafts_in_place(batch, K, temperature, layers):
     from paper_2605_12825_amd import runtime as rt
     w = Workload(name="inplace", seed=9700 + K, batch=batch, num_q_heads=4, num_kv_heads=2, head_dim=64, block_k=K,
@@ -36,13 +37,16 @@ def test_tokens_replace_the_drafts_in_place(batch, K, temperature, layers):
                                                     temperature, kb, vb, k, v, table, l)
         return oracle.consensus_commit(c["ar_logits"], c["draft_tokens"], kb, vb, k, v, table, l)
 
-    m = oracle_call(kp.copy(), vp.copy(), lens.copy(), pt)["num_committed"]
+    rk, rv, rl = kp.copy(), vp.copy(), lens.copy()
+    want = oracle_call(rk, rv, rl, pt)
+    m = want["num_committed"].copy()
     table = pt.copy()
     for b in range(0, batch, 2):
         table[b, (lens[b] + m[b] + 15) // 16:] = -1
-    rk, rv, rl = kp.copy(), vp.copy(), lens.copy()
-    want = oracle_call(rk, rv, rl, table)
-    assert (want["num_committed"] == m).all()
+    for b in range(7, batch, 8):
+        table[b, (lens[b] + m[b] - 1) // 16] = -1
+        own = pt[b][pt[b] >= 0]
+        rk[:, own], rv[:, own], rl[b], want["num_committed"][b] = kp[:, own], vp[:, own], lens[b], 0
     step = rt.DecodeStep(batch=batch, num_q_heads=4, num_kv_heads=2, head_dim=64, block_k=K, page_size=16,
                          max_pages_per_seq=pt.shape[1], max_seq_len=16 * pt.shape[1], num_pages=kp.shape[1], vocab=700,
                          num_layers=layers)
@@ -56,7 +60,7 @@ def test_tokens_replace_the_drafts_in_place(batch, K, temperature, layers):
         else:
             step.consensus_commit(D(c["ar_logits"]), tok, *rest)
         torch.cuda.synchronize()
-        assert step.device_error() == 0
+        assert step.device_error() == (-4 if batch > 7 else 0)
         for name, got in (("accept_len", acc), ("num_committed", ncm), ("out_tokens", tok), ("next_anchor", anc)):
             np.testing.assert_array_equal(got.cpu().numpy(), want[name], err_msg=name)
         np.testing.assert_array_equal(dl.cpu().numpy(), rl)
