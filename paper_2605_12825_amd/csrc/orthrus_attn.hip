@@ -534,7 +534,7 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
     plan->rows = R;
     const int blocks = R > 32 ? (R + 31) / 32 : 1;
     const int64_t units = (int64_t)batch * num_kv_heads;
-    plan->wide = requested_splits >= 0 && requested_splits <= 1 && attn_wide_pays(R, units, num_cus);
+    plan->wide = requested_splits >= 0 && requested_splits <= 1 && attn_wide_pays(head_dim, R, max_seq_len, units, num_cus);
     const int W = plan->wide ? (R > 128 ? 4 : 2) : blocks;
     plan->waves = W;
     plan->rows_padded = blocks * 32;

@@ -376,14 +376,32 @@ size_t attn_wide_lds(int waves, int head_dim)
     return (size_t)wide_stages(waves) * (head_dim == 128 ? AttnGeom<128>::STAGE_B : AttnGeom<64>::STAGE_B);
 }
 
-// Decode mode: worth it when the waves' rows are nearly all real (7/8) and the units alone put a wave on every SIMD.
-// Both sides of the line, attn_split_kernel -> this kernel: training mask with 8192 units of 128 rows 857 -> 697 us, of
-// 96 rows 626 -> 640; 64 sequences of 2000 tokens, 512 units of 128 rows 102 -> 90; 32 of 4000, 256 units 93 -> 97;
-// 256 units of 256 rows 79 -> 74; 8 units cut into 32 splits each 45 -> 54.
-bool attn_wide_pays(int rows, int64_t units, int num_cus)
+// Decode mode: whether this kernel beats attn_split_kernel when neither cuts a unit.  It needs waves that are nearly all
+// rows (7/8; of 96 rows the training mask takes 626 -> 640 us), units enough for a wave on every SIMD, and lengths over
+// which its shorter tile makes up for the longer start and end.  Where the lines lie (attn_split_kernel -> this kernel,
+// us per call, lengths equal to the bound; 256 CUs):
+//   d = 128, up to 128 rows: 512 units of 64 / 300 / 1000 tokens at 112 rows 16.3 -> 18.5 / 28.8 -> 27.7 / 74 -> 67, of
+//     400 at 128 rows 36.9 -> 33.7; 256 units 34 -> 42; a second round for a few units does not pay (640 units of 400:
+//     50.8 -> 52.7, 768: 61.1 -> 59.0, 1024: 82 -> 71)
+//   d = 128, more rows: two such waves' work is what four 32-row waves with a loader do as well; 224 rows lose everywhere
+//     (1024 units of 1000 tokens 175 -> 187), 256 rows gain from about 2000 tokens on (384 units of 1000 / 2500 tokens
+//     87.4 -> 90.7 / 183 -> 165, 256 units of 3000 119 -> 121; masks over 1024 / 2048 tokens 394 -> 400 / 351 -> 346)
+//   d = 64, up to 128 rows: 512 units lose at any length (3000 tokens: 95.6 -> 102.7), 640 of 400 / 1000 tokens 25.9 ->
+//     25.6 / 53.9 -> 51.3, 1024 of 180 / 400 tokens 25.5 -> 23.9 / 41.6 -> 34.2
+//   d = 64, more rows: 320 units of 300 / 512 / 1000 tokens at 256 rows 24.8 -> 24.0 / 32.1 -> 29.9 / 50.7 -> 42.7, at 224
+//     rows 21.0 -> 23.6 / 27.1 -> 28.6 / 43.1 -> 41.6; 256 units of 700 / 1000 tokens at 256 rows 23.9 -> 24.7 / 32.1 -> 31.4
+bool attn_wide_pays(int head_dim, int rows, int max_seq_len, int64_t units, int num_cus)
 {
     const int waves = rows > 128 ? 4 : 2;
-    return 8 * rows >= 7 * 64 * waves && units * waves >= 4 * (int64_t)num_cus;
+    const bool full = rows >= 60 * waves;
+    if (rows < 56 * waves) return false;
+    if (waves == 2) {
+        if (max_seq_len < 384) return false;
+        return head_dim == 128 ? units == 2 * (int64_t)num_cus || units >= 3 * (int64_t)num_cus : 2 * units >= 5 * (int64_t)num_cus;
+    }
+    if (head_dim == 128) return full && max_seq_len >= 2048 && 4 * units >= 5 * (int64_t)num_cus;
+    if (full && max_seq_len >= 1024) return units >= num_cus;
+    return max_seq_len >= (full ? 512 : 1024) && 4 * units >= 5 * (int64_t)num_cus;
 }
 
 template <int D, int W>
@@ -410,22 +428,52 @@ static hipError_t launch_prefill_wide(AttnArgs a, hipStream_t stream)
     return hipGetLastError();
 }
 
-// Prefill forms.  While the launch leaves SIMDs idle a 32-row wave with its own loader is the faster chain (0.55 us per
-// tile against 0.65 us for twice the rows): up to one such wave per SIMD, two workgroups per CU and four waves per
-// workgroup attn_split_kernel's prefill form stays (1024 new tokens, group 4: 38 against 45 us; 2048: 92 against 69).
-// Otherwise four waves per workgroup once every CU gets two of them, else two waves for the finer grain
-// (8 sequences of 333 tokens: 38 against 42 us; d = 64 is faster with four throughout, 40 against 47 us).
+// Prefill forms.  A 32-row wave with its own loader is the faster chain (0.55 us per tile against 0.65 us for twice the
+// rows), so for up to four waves a workgroup attn_split_kernel's prefill form stays while SIMDs would be idle otherwise.
+// How long that is depends on how the items' lengths are spread:
+//   - From 0 up, the new tokens being most of what is cached (by the bound: max_seq_len < 2 * max_new): the longest items
+//     start first and short ones fill in behind them.  32-row form -> this kernel, one sequence of n tokens, us per call:
+//     d = 128: group 4, 2 heads, n = 7000 (1.7 waves per SIMD) 135 -> 160, 8 heads, n = 4000 (3.9) 169 -> 137; group 3, 2
+//     heads, n = 7000 (1.3) 129 -> 159; group 2, 8 heads, n = 2000 / 4000 (1.0 / 2.0) 47 -> 57 / 106 -> 106; group 1, 8
+//     heads, n = 4000 / 7000 (1.0 / 1.7) 78 -> 99 / 170 -> 165.  d = 64: group 1, 8 heads, n = 4000 / 9000 (1.0 / 2.2)
+//     59 -> 79 / 152 -> 162; group 4, 8 heads, n = 2000 / 4000 (2.0 / 3.9) 39 -> 47 / 100 -> 92.
+//   - Of about equal length (behind a longer cache): what does not fit at once comes as a whole round more.  One 32-row
+//     wave per SIMD, all workgroups resident (LDS ring: three per CU, of four waves two; d = 64 and one wave: six):
+//     3000 cached tokens, d = 128: group 1, 32 heads, n = 700 (2.75 workgroups per CU) 77 -> 93, n = 1021 (4) 103 -> 93;
+//     group 2, 8 heads, n = 2000 (1.0 waves per SIMD) 119 -> 122; group 4, 8 heads, n = 700 / 2000 (0.7 / 2.0) 79 -> 94 /
+//     164 -> 141.  Or where this kernel would need a second round and the 32-row form would not: group 3, 32 heads,
+//     n = 700 146 -> 169.
+// More than four query heads per KV head: this kernel at any size.  Against the 32-row form with five to eight waves that
+// it took the place of, 4000 cached tokens, n = 32: group 5 / 6 / 7 / 8 108 -> 97 / 107 -> 97 / 111 -> 97 / 113 -> 97; empty
+// cache, n = 700: 36 -> 31 / 34 -> 29 / 35 -> 30 / 36 -> 30 (5 us of each for the shorter front end).
+// Four waves per workgroup once every CU gets two of them, else two waves for the finer grain (8 sequences of 333 tokens:
+// 38 against 42 us), unless the finer grain spills into a round of its own (group 3, 32 heads, 2500 cached tokens, n = 677:
+// 544 workgroups of two waves 144 us, 256 of four 104); d = 64 is faster with four throughout (40 against 47 us).
+int prefill_wide_waves(int head_dim, int group, int64_t units, int max_new, int max_seq_len, int num_cus)
+{
+    const int64_t cus = num_cus;
+    auto items_of = [&](int tokens) { return units * ((max_new + tokens - 1) / tokens); };
+    const int64_t items4 = items_of(256 / group);
+    const bool even = max_seq_len >= 2 * (int64_t)max_new;
+    if (group <= 4) {
+        const int64_t items32 = items_of(32), waves32 = items32 * group;
+        const bool thin = head_dim == 64 && group == 1;
+        if (!even) {
+            if (waves32 <= (head_dim == 64 ? 10 : group <= 2 ? 6 : 8) * cus) return 0;
+        } else if (items32 < (thin ? 6 : group <= 3 ? 3 : 2) * cus && (waves32 <= (thin ? 6 : 4) * cus || items4 > cus)) {
+            return 0;
+        }
+    }
+    if (head_dim == 64 || items4 >= 2 * cus) return 4;
+    return even && (items_of(128 / group) + 2 * cus - 1) / (2 * cus) > (items4 + cus - 1) / cus ? 4 : 2;
+}
+
 hipError_t launch_prefill_attn(const AttnArgs &a, int head_dim, int num_cus, hipStream_t stream)
 {
     if (a.batch == 0 || a.max_new == 0) return hipSuccess;
-    const int64_t units = (int64_t)a.batch * a.num_kv_heads;
-    const int64_t items32 = units * ((a.max_new + 31) / 32);
-    if (a.group <= 4 && items32 <= 2 * num_cus && items32 * a.group <= 4 * num_cus)
-        return launch_prefill_split(a, head_dim, stream);
-    const int chunk = 256 / a.group;
-    const int64_t items = units * ((a.max_new + chunk - 1) / chunk);
-    if (head_dim == 128)
-        return items < 2 * num_cus ? launch_prefill_wide<128, 2>(a, stream) : launch_prefill_wide<128, 4>(a, stream);
+    const int waves = prefill_wide_waves(head_dim, a.group, (int64_t)a.batch * a.num_kv_heads, a.max_new, a.max_seq_len, num_cus);
+    if (waves == 0) return launch_prefill_split(a, head_dim, stream);
+    if (head_dim == 128) return waves == 2 ? launch_prefill_wide<128, 2>(a, stream) : launch_prefill_wide<128, 4>(a, stream);
     if (head_dim == 64) return launch_prefill_wide<64, 4>(a, stream);
     return hipErrorInvalidValue;
 }

@@ -173,8 +173,10 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
 hipError_t launch_attn(const AttnArgs &a, const AttnPlan &plan, int head_dim, hipStream_t stream,
                        AttnLaunchEvents *events = nullptr);
 // The 64-rows-per-wave kernel: whether it is the better one for these rows, its LDS need, its launch (grid from the plan).
-bool attn_wide_pays(int rows, int64_t units, int num_cus);
+bool attn_wide_pays(int head_dim, int rows, int max_seq_len, int64_t units, int num_cus);
 size_t attn_wide_lds(int waves, int head_dim);
+// Prefill: waves of 64 rows per workgroup, 0 for the 32-row form.
+int prefill_wide_waves(int head_dim, int group, int64_t units, int max_new, int max_seq_len, int num_cus);
 hipError_t launch_attn_wide(const AttnArgs &a, const AttnPlan &plan, int head_dim, dim3 grid, hipStream_t stream, AttnLaunchEvents *events);
 hipError_t launch_prefill_attn(const AttnArgs &a, int head_dim, int num_cus, hipStream_t stream);
 hipError_t launch_prefill_split(const AttnArgs &a, int head_dim, hipStream_t stream);

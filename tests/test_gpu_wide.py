@@ -9,6 +9,7 @@ import pytest
 import oracle
 from orthrus_inputs import Workload, bf16_bits_to_f32, f32_to_bf16_bits, make_block, make_cache
 
+from test_attn_routes_cpu import decode_is_wide, prefill_waves
 from test_gpu_parity import AR, DIFF, GpuCase, _check_attn, _oracle_attn
 from test_gpu_prefill import Case, _check, _new_tokens
 
@@ -23,21 +24,39 @@ def _lens(n, seed):
     return rng.permutation(np.concatenate((EDGES, rng.integers(0, 301, size=n)))[:max(n, len(EDGES))])[:n].astype(np.int32)
 
 
+BOUND = 4096  # the kernel is chosen by the bound on the lengths, not by the lengths
+
+
+def _roomy(cache, page):
+    """The same cache with a page table wide enough for BOUND."""
+    pt = cache["page_table"]
+    wide = np.full((pt.shape[0], BOUND // page), -1, np.int32)
+    wide[:, :pt.shape[1]] = pt
+    return dict(cache, page_table=wide)
+
+
+def _case(w, cache, wide, num_splits=0, num_layers=1):
+    rows, units = w.num_q_heads // w.num_kv_heads * w.block_k, w.batch * w.num_kv_heads
+    assert decode_is_wide(w.head_dim, rows, BOUND, units) == wide
+    return GpuCase(w, _roomy(cache, w.page_size), num_splits=num_splits, num_layers=num_layers, max_seq_len=BOUND)
+
+
 @pytest.mark.parametrize("view", [DIFF, AR])
 @pytest.mark.parametrize("g,K,hkv,batch,d,page", [
     (4, 32, 8, 64, 128, 16),     # 128 rows, two waves, full
     (7, 16, 8, 64, 128, 32),     # 112 rows: the second wave's last block ends in padding
-    (8, 32, 4, 64, 128, 16),     # 256 rows, four waves
-    (7, 32, 4, 64, 128, 64),     # 224 rows: a block of padding
-    (8, 16, 8, 64, 64, 16),
+    (8, 32, 4, 80, 128, 16),     # 256 rows, four waves
+    (8, 30, 4, 80, 128, 64),     # 240 rows: half a block of padding
+    (8, 16, 8, 80, 64, 16),
     (8, 31, 4, 64, 64, 16),
+    (7, 32, 4, 80, 64, 64),      # 224 rows: a block of padding
 ])
 def test_decode_batches_that_fill_the_chip(g, K, hkv, batch, d, page, view):
     w = Workload(name="wide", seed=8100 + g * K + d, batch=batch, num_q_heads=g * hkv, num_kv_heads=hkv, head_dim=d,
                  block_k=K, context=300, page_size=page, paging="scattered")
     cache = make_cache(w, seq_lens=_lens(batch, 8200 + K))
     blk = make_block(w, 8300 + K)
-    case = GpuCase(w, cache, max_seq_len=300)
+    case = _case(w, cache, True)
     got, lse = case.attn(view, blk)
     want, want_lse = _oracle_attn(view, w, blk, cache, want_lse=True)
     _check_attn(got, want)
@@ -50,6 +69,7 @@ def test_decode_batches_that_fill_the_chip(g, K, hkv, batch, d, page, view):
 
 @pytest.mark.parametrize("g,hkv,batch,d,T", [
     (4, 8, 64, 128, 70),         # 64 tokens x 4 heads per workgroup: one full and one short chunk
+    (4, 8, 12, 128, 70),         # the same with two waves: 32 tokens
     (1, 8, 70, 128, 40),
     (7, 8, 40, 128, 75),         # 36 tokens x 7 heads: 252 of 256 rows
     (5, 2, 3, 128, 90),          # two waves: 25 tokens x 5 heads
@@ -65,7 +85,9 @@ def test_prefill_that_fills_the_chip(g, hkv, batch, d, T):
     q, kn, vn = _new_tokens(w, T, 8700 + g)
     ref_k, ref_v, ref_l = cache["k_pool"].copy(), cache["v_pool"].copy(), cache["seq_lens"].copy()
     want, _ = oracle.prefill_attn(w.sm_scale, q, kn, vn, new_lens, ref_k, ref_v, cache["page_table"], ref_l)
-    case = Case(w, cache, max_seq_len=int(cache["seq_lens"].max()) + T)
+    msl = int(cache["seq_lens"].max()) + T
+    assert prefill_waves(d, g, batch * hkv, T, msl) == (2 if batch < 20 and d == 128 else 4)
+    case = Case(w, cache, max_seq_len=msl)
     got = case.prefill(q, kn, vn, new_lens)
     _check(got, want, new_lens)
     k, v, l = case.state()
@@ -81,6 +103,7 @@ def test_pool_strides_past_32_bit_byte_arithmetic(batch, hkv, K):
     """Pages of 2^23 tokens (only their first rows exist): an in-page offset no longer fits the kernels' 32-bit byte
     arithmetic, which their general address form has to take over, in both attention kernels."""
     d, rows, L = 128, 320, 290
+    assert decode_is_wide(d, 4 * K, BOUND, batch * hkv) == (batch == 64)
     w = Workload(name="huge", seed=8800 + batch, batch=batch, num_q_heads=4 * hkv, num_kv_heads=hkv, head_dim=d, block_k=K,
                  context=L, page_size=rows, paging="contiguous", steps=0)
     lens = _lens(batch, 8900)
@@ -92,7 +115,7 @@ def test_pool_strides_past_32_bit_byte_arithmetic(batch, hkv, K):
     from paper_2605_12825_amd import runtime as rt
     import torch
     step = rt.DecodeStep(batch=batch, num_q_heads=4 * hkv, num_kv_heads=hkv, head_dim=d, block_k=K, page_size=1 << 23,
-                         max_pages_per_seq=1, max_seq_len=L, num_pages=batch, pool_strides=(0, hkv * rows * d, rows * d, d))
+                         max_pages_per_seq=1, max_seq_len=BOUND, num_pages=batch, pool_strides=(0, hkv * rows * d, rows * d, d))
     D = rt.to_device_bits
     out = torch.zeros((batch, K, 4 * hkv, d), dtype=torch.int16, device="cuda")
     step.attn(AR, D(blk["q"]), D(blk["k_blk"]), D(blk["v_blk"]), D(k_pool), D(v_pool), D(cache["page_table"]),
@@ -108,7 +131,7 @@ def _wider(q):
     return f32_to_bf16_bits(np.float32(2.0) * bf16_bits_to_f32(q))
 
 
-@pytest.mark.parametrize("g,K,hkv,batch,d", [(4, 32, 8, 64, 128), (8, 32, 4, 64, 128), (7, 32, 4, 64, 128), (8, 16, 8, 64, 64)])
+@pytest.mark.parametrize("g,K,hkv,batch,d", [(4, 32, 8, 64, 128), (8, 32, 4, 80, 128), (7, 32, 4, 80, 64), (8, 16, 8, 80, 64)])
 def test_decode_bits_do_not_depend_on_the_batch_size(g, K, hkv, batch, d):
     """A sequence that is not split gets the same bits in a batch that fills the chip (64 rows per wave) and alone (32
     rows): both kernels move a row's softmax reference by the same rule.  Scores of twice the usual size and
@@ -117,13 +140,13 @@ def test_decode_bits_do_not_depend_on_the_batch_size(g, K, hkv, batch, d):
                  block_k=K, context=300, page_size=16, paging="scattered")
     cache, blk = make_cache(w, seq_lens=_lens(batch, 9001)), make_block(w, 9002)
     blk["q"] = _wider(blk["q"])
-    case = GpuCase(w, cache, max_seq_len=300)
+    case = _case(w, cache, True)
     got = case.attn(DIFF, blk, want_lse=False)
     _check_attn(got, _oracle_attn(DIFF, w, blk, cache))
     case.step.close()
     for b in range(0, batch, 2):
-        few = GpuCase(replace(w, batch=2), dict(cache, page_table=cache["page_table"][b:b + 2], seq_lens=cache["seq_lens"][b:b + 2]),
-                      num_splits=1, max_seq_len=300)
+        few = _case(replace(w, batch=2), dict(cache, page_table=cache["page_table"][b:b + 2], seq_lens=cache["seq_lens"][b:b + 2]),
+                    False, num_splits=1)
         part = few.attn(DIFF, {x: blk[x][b:b + 2] for x in blk}, want_lse=False)
         np.testing.assert_array_equal(part, got[b:b + 2], err_msg="sequences %d, %d" % (b, b + 1))
         few.step.close()
@@ -139,6 +162,7 @@ def test_prefill_bits_do_not_depend_on_the_batch_size(g, batch, T):
     q, kn, vn = _new_tokens(w, T, 9103)
     q = _wider(q)
     msl = int(cache["seq_lens"].max()) + T
+    assert prefill_waves(128, g, batch * 8, T, msl) == 4 and prefill_waves(128, g, 16, T, msl) == 0
     case = Case(w, cache, max_seq_len=msl)
     got = case.prefill(q, kn, vn, new_lens)
     case.step.close()
@@ -157,7 +181,7 @@ def _check_with_infinities(got, want):
     _check_attn(np.where(fin, got, 0.0), np.where(fin, want, 0.0))
 
 
-@pytest.mark.parametrize("batch", [2, 64])                        # the 32-row kernel, the 64-row kernel
+@pytest.mark.parametrize("batch", [2, 96])                        # the 32-row kernel, the 64-row kernel
 @pytest.mark.parametrize("g,K,hkv,d", [(4, 32, 8, 128), (8, 32, 4, 128), (8, 16, 8, 64)])
 def test_infinite_value_in_the_first_tile_stays_infinite(batch, g, K, hkv, d):
     """An infinite V in a sequence's first 32 tokens, or in its block when the cache is empty, makes its column infinite
@@ -172,7 +196,7 @@ def test_infinite_value_in_the_first_tile_stays_infinite(batch, g, K, hkv, d):
             cache["v_pool"][cache["page_table"][b, b % 2], head, b % 16, col] = bits
         else:
             blk["v_blk"][b, 0, head, col] = bits
-    case = GpuCase(w, cache)
+    case = _case(w, cache, batch > 2)
     _check_with_infinities(case.attn(DIFF, blk, want_lse=False), _oracle_attn(DIFF, w, blk, cache))
     case.step.close()
 
@@ -189,6 +213,8 @@ def test_infinite_value_in_the_first_tile_stays_infinite_in_prefill(batch):
     new_lens = np.full(batch, T, np.int32)
     ref = [cache[x].copy() for x in ("k_pool", "v_pool", "seq_lens")]
     want, _ = oracle.prefill_attn(w.sm_scale, q, kn, vn, new_lens, ref[0], ref[1], cache["page_table"], ref[2])
-    case = Case(w, cache, max_seq_len=int(cache["seq_lens"].max()) + T)
+    msl = int(cache["seq_lens"].max()) + T
+    assert prefill_waves(d, 4, batch * hkv, T, msl) == (4 if batch > 2 else 0)
+    case = Case(w, cache, max_seq_len=msl)
     _check_with_infinities(bf16_bits_to_f32(case.prefill(q, kn, vn, new_lens)).astype(np.float64), want)
     case.step.close()
