@@ -381,27 +381,32 @@ size_t attn_wide_lds(int waves, int head_dim)
 // which its shorter tile makes up for the longer start and end.  Where the lines lie (attn_split_kernel -> this kernel,
 // us per call, lengths equal to the bound; 256 CUs):
 //   d = 128, up to 128 rows: 512 units of 64 / 300 / 1000 tokens at 112 rows 16.3 -> 18.5 / 28.8 -> 27.7 / 74 -> 67, of
-//     400 at 128 rows 36.9 -> 33.7; 256 units 34 -> 42; a second round for a few units does not pay (640 units of 400:
-//     50.8 -> 52.7, 768: 61.1 -> 59.0, 1024: 82 -> 71)
+//     180 at 128 rows 25.9 -> 24.2, 896 of 180 45.3 -> 42.7; 256 units 34 -> 42; a second round for a few units pays only when it is long or the
+//     lengths are mixed, which a long bound suggests (640 units of 400 tokens 50.8 -> 52.7, 544 of 1000 85 -> 90, 640 of
+//     2000 and of 200..1800 1.02 and 1.00 times as fast, the mask's 544 over 1024 / 2048 tokens 1.05 and 1.15; 768 units
+//     of 400 61.1 -> 59.0)
 //   d = 128, more rows: two such waves' work is what four 32-row waves with a loader do as well; 224 rows lose everywhere
 //     (1024 units of 1000 tokens 175 -> 187), 256 rows gain from about 2000 tokens on (384 units of 1000 / 2500 tokens
 //     87.4 -> 90.7 / 183 -> 165, 256 units of 3000 119 -> 121; masks over 1024 / 2048 tokens 394 -> 400 / 351 -> 346)
 //   d = 64, up to 128 rows: 512 units lose at any length (3000 tokens: 95.6 -> 102.7), 640 of 400 / 1000 tokens 25.9 ->
-//     25.6 / 53.9 -> 51.3, 1024 of 180 / 400 tokens 25.5 -> 23.9 / 41.6 -> 34.2
-//   d = 64, more rows: 320 units of 300 / 512 / 1000 tokens at 256 rows 24.8 -> 24.0 / 32.1 -> 29.9 / 50.7 -> 42.7, at 224
-//     rows 21.0 -> 23.6 / 27.1 -> 28.6 / 43.1 -> 41.6; 256 units of 700 / 1000 tokens at 256 rows 23.9 -> 24.7 / 32.1 -> 31.4
+//     25.6 / 53.9 -> 51.3 but the mask's 640 over 2048 tokens 52 -> 58, its 704 1.03 times as fast; 768 of 180 / 256 tokens 19.3 -> 20.5 / 21.9 -> 21.6, 1024 of 400 41.6 -> 34.2
+//   d = 64, more rows: 320 units of 300 / 512 / 1000 tokens at 256 rows 24.8 -> 24.0 / 32.1 -> 29.9 / 50.7 -> 42.7, 256 of
+//     700 / 1000 23.9 -> 24.7 / 32.1 -> 31.4; at 224 rows 384 units of 700 / 2000 tokens 34.0 -> 33.3 / 89 -> 79, the
+//     mask's 352 over 4096 tokens 0.82 times as fast, its 384 1.23
 bool attn_wide_pays(int head_dim, int rows, int max_seq_len, int64_t units, int num_cus)
 {
     const int waves = rows > 128 ? 4 : 2;
+    const int64_t cus = num_cus;
     const bool full = rows >= 60 * waves;
     if (rows < 56 * waves) return false;
     if (waves == 2) {
-        if (max_seq_len < 384) return false;
-        return head_dim == 128 ? units == 2 * (int64_t)num_cus || units >= 3 * (int64_t)num_cus : 2 * units >= 5 * (int64_t)num_cus;
+        if (head_dim == 64) return max_seq_len >= 256 && 4 * units >= 11 * cus;
+        if (full && max_seq_len >= 128 && (units == 2 * cus || 2 * units >= 7 * cus)) return true;
+        return max_seq_len >= 384 && (units == 2 * cus || units >= 3 * cus || (units > 2 * cus && max_seq_len >= 1024));
     }
-    if (head_dim == 128) return full && max_seq_len >= 2048 && 4 * units >= 5 * (int64_t)num_cus;
-    if (full && max_seq_len >= 1024) return units >= num_cus;
-    return max_seq_len >= (full ? 512 : 1024) && 4 * units >= 5 * (int64_t)num_cus;
+    if (head_dim == 128) return full && max_seq_len >= 1920 && units > cus;
+    if (!full) return max_seq_len >= 1024 && 2 * units >= 3 * cus;
+    return max_seq_len >= 896 ? units >= cus : max_seq_len >= 512 && 4 * units >= 5 * cus;
 }
 
 template <int D, int W>

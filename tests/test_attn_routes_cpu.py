@@ -24,12 +24,13 @@ def prefill_waves(head_dim, group, units, max_new, max_seq_len):
 
 
 @pytest.mark.parametrize("wide,head_dim,rows,max_seq_len,units", [
-    (True, 128, 128, 2048, 8192), (True, 128, 112, 1000, 512), (False, 128, 112, 64, 512), (False, 128, 96, 2048, 8192),
-    (False, 128, 128, 1000, 256), (False, 128, 128, 1000, 640), (True, 128, 128, 1000, 768),
+    (True, 128, 128, 2048, 8192), (True, 128, 112, 1000, 512), (False, 128, 112, 180, 512), (True, 128, 128, 180, 512),
+    (False, 128, 128, 256, 768), (True, 128, 128, 400, 768), (True, 128, 128, 180, 896), (False, 128, 96, 2048, 8192),
+    (False, 128, 128, 1000, 256), (False, 128, 128, 1000, 640), (True, 128, 112, 2035, 568), (True, 128, 128, 1000, 768),
     (False, 128, 224, 4000, 4096), (True, 128, 256, 2500, 384), (False, 128, 256, 1000, 384), (False, 128, 256, 3000, 256),
-    (False, 64, 128, 3000, 512), (True, 64, 128, 400, 1024), (False, 64, 128, 180, 640),
+    (False, 64, 128, 3000, 512), (False, 64, 128, 2048, 640), (True, 64, 128, 2048, 704), (True, 64, 128, 400, 1024), (False, 64, 128, 180, 768), (True, 64, 112, 256, 768),
     (True, 64, 256, 512, 320), (False, 64, 256, 300, 320), (True, 64, 256, 1024, 256), (False, 64, 256, 700, 256),
-    (True, 64, 224, 1024, 320), (False, 64, 224, 700, 320), (False, 64, 224, 2000, 256),
+    (True, 64, 224, 1024, 384), (False, 64, 224, 700, 384), (False, 64, 224, 4000, 352),
 ])
 def test_decode_route(wide, head_dim, rows, max_seq_len, units):
     assert decode_is_wide(head_dim, rows, max_seq_len, units) == wide

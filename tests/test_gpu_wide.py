@@ -47,9 +47,9 @@ def _case(w, cache, wide, num_splits=0, num_layers=1):
     (7, 16, 8, 64, 128, 32),     # 112 rows: the second wave's last block ends in padding
     (8, 32, 4, 80, 128, 16),     # 256 rows, four waves
     (8, 30, 4, 80, 128, 64),     # 240 rows: half a block of padding
-    (8, 16, 8, 80, 64, 16),
+    (8, 16, 8, 96, 64, 16),
     (8, 31, 4, 64, 64, 16),
-    (7, 32, 4, 80, 64, 64),      # 224 rows: a block of padding
+    (7, 32, 4, 96, 64, 64),      # 224 rows: a block of padding
 ])
 def test_decode_batches_that_fill_the_chip(g, K, hkv, batch, d, page, view):
     w = Workload(name="wide", seed=8100 + g * K + d, batch=batch, num_q_heads=g * hkv, num_kv_heads=hkv, head_dim=d,
@@ -131,7 +131,7 @@ def _wider(q):
     return f32_to_bf16_bits(np.float32(2.0) * bf16_bits_to_f32(q))
 
 
-@pytest.mark.parametrize("g,K,hkv,batch,d", [(4, 32, 8, 64, 128), (8, 32, 4, 80, 128), (7, 32, 4, 80, 64), (8, 16, 8, 80, 64)])
+@pytest.mark.parametrize("g,K,hkv,batch,d", [(4, 32, 8, 64, 128), (8, 32, 4, 80, 128), (7, 32, 4, 96, 64), (8, 16, 8, 96, 64)])
 def test_decode_bits_do_not_depend_on_the_batch_size(g, K, hkv, batch, d):
     """A sequence that is not split gets the same bits in a batch that fills the chip (64 rows per wave) and alone (32
     rows): both kernels move a row's softmax reference by the same rule.  Scores of twice the usual size and
