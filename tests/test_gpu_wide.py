@@ -11,7 +11,7 @@ from orthrus_inputs import Workload, bf16_bits_to_f32, f32_to_bf16_bits, make_bl
 
 from test_attn_routes_cpu import decode_is_wide, prefill_waves
 from test_gpu_parity import AR, DIFF, GpuCase, _check_attn, _oracle_attn
-from test_gpu_prefill import Case, _check, _new_tokens
+from test_gpu_prefill import SENTINEL, Case, _check, _new_tokens
 
 pytestmark = pytest.mark.gpu
 
@@ -217,4 +217,102 @@ def test_infinite_value_in_the_first_tile_stays_infinite_in_prefill(batch):
     assert prefill_waves(d, 4, batch * hkv, T, msl) == (4 if batch > 2 else 0)
     case = Case(w, cache, max_seq_len=msl)
     _check_with_infinities(bf16_bits_to_f32(case.prefill(q, kn, vn, new_lens)).astype(np.float64), want)
+    case.step.close()
+
+
+def test_caches_of_their_own_stream_past_the_last_level_cache():
+    """The non-temporal form of the tile loads (a model whose layers' caches together outgrow the last-level cache) gives
+    the same bits, for every width and head size."""
+    for g, K, hkv, batch, d in ((4, 32, 8, 64, 128), (8, 32, 4, 80, 128), (8, 16, 8, 96, 64), (8, 31, 4, 64, 64)):
+        w = Workload(name="nt", seed=9400 + K + d, batch=batch, num_q_heads=g * hkv, num_kv_heads=hkv, head_dim=d, block_k=K,
+                     context=300, page_size=16, paging="scattered")
+        cache, blk = make_cache(w, seq_lens=_lens(batch, 9401)), make_block(w, 9402)
+        layers = 2 + int(1.25 * 2**28) // (4 * cache["k_pool"].size)   # K and V: 4 bytes per element of one pool
+        plain, streamed = _case(w, cache, True), _case(w, cache, True, num_layers=layers)
+        got = plain.attn(AR, blk, want_lse=False)
+        _check_attn(got, _oracle_attn(AR, w, blk, cache))
+        np.testing.assert_array_equal(streamed.attn(AR, blk, want_lse=False), got)
+        plain.step.close()
+        streamed.step.close()
+
+
+@pytest.mark.parametrize("g,K,hkv,batch,d", [(4, 32, 8, 64, 128), (8, 31, 4, 64, 64)])
+def test_block_inputs_read_in_place(g, K, hkv, batch, d):
+    """q, k_blk and v_blk as column ranges of one fused projection output: the bits of dense inputs."""
+    from paper_2605_12825_amd import runtime as rt
+    import torch
+    w = Workload(name="fusedw", seed=9500 + d, batch=batch, num_q_heads=g * hkv, num_kv_heads=hkv, head_dim=d, block_k=K,
+                 context=300, page_size=16, paging="scattered")
+    cache, blk = make_cache(w, seq_lens=_lens(batch, 9501)), make_block(w, 9502)
+    case = _case(w, cache, True)
+    want = case.attn(AR, blk, want_lse=False)
+    fused = np.concatenate([blk[x].reshape(batch * K, -1, d) for x in ("q", "k_blk", "v_blk")], axis=1)
+    row = fused.shape[1] * d
+    step = rt.DecodeStep(batch=batch, num_q_heads=g * hkv, num_kv_heads=hkv, head_dim=d, block_k=K, page_size=16,
+                         max_pages_per_seq=BOUND // 16, max_seq_len=BOUND, num_pages=cache["k_pool"].shape[0],
+                         block_strides=(row, d, row, d, batch * K * row))
+    buf, at = rt.to_device_bits(fused), lambda h: h * d * 2
+    out = torch.zeros((batch, K, g * hkv, d), dtype=torch.int16, device="cuda")
+    base = buf.data_ptr()
+    step.attn(AR, base, base + at(g * hkv), base + at((g + 1) * hkv), case.k_pool, case.v_pool, case.page_table, case.seq_lens, out)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(bf16_bits_to_f32(rt.bits_to_numpy(out)).astype(np.float64), want)
+    step.close()
+    case.step.close()
+
+
+@pytest.mark.parametrize("g,K,hkv,batch,d", [(4, 32, 8, 64, 128), (8, 31, 4, 64, 64)])
+def test_bad_pages_and_lengths_are_flagged_and_stay_with_their_sequence(g, K, hkv, batch, d):
+    """A page id outside the pool in the first, a middle or the last, ragged tile, or a length outside [0, bound]: the error
+    word is set, every other sequence keeps its bits."""
+    w = Workload(name="bad", seed=9600 + d, batch=batch, num_q_heads=g * hkv, num_kv_heads=hkv, head_dim=d, block_k=K,
+                 context=300, page_size=16, paging="scattered")
+    lens = np.full(batch, 290, np.int32)
+    cache, blk = make_cache(w, seq_lens=lens), make_block(w, 9601)
+    case = _case(w, cache, True)
+    want = case.attn(DIFF, blk, want_lse=False)
+    assert case.step.device_error() == 0
+    case.step.close()
+    for b, slot, page, length in ((3, 0, -1, 290), (5, 7, cache["k_pool"].shape[0], 290), (9, 18, 1 << 30, 290), (11, 0, None, -1),
+                                  (batch - 1, 0, None, BOUND + 1)):
+        bad = dict(cache, page_table=cache["page_table"].copy(), seq_lens=lens.copy())
+        if page is not None:
+            bad["page_table"][b, slot] = page
+        bad["seq_lens"][b] = length
+        case = _case(w, bad, True)
+        got = case.attn(DIFF, blk, want_lse=False)
+        assert case.step.device_error() == -4, (b, slot, page, length)
+        rest = np.arange(batch) != b
+        np.testing.assert_array_equal(got[rest], want[rest])
+        case.step.close()
+
+
+def test_prefill_capacity_error_stays_with_its_sequence():
+    """New tokens that fall on an unmapped page leave their sequence alone (cache, length, output); a bad page among the
+    cached ones is flagged; the other sequences are as without either."""
+    g, hkv, batch, d, T = 4, 8, 64, 128, 70
+    w = Workload(name="badp", seed=9700, batch=batch, num_q_heads=g * hkv, num_kv_heads=hkv, head_dim=d, block_k=8, context=300,
+                 page_size=16, paging="shuffled", steps=(T + 7) // 8 + 1)
+    cache = make_cache(w, seq_lens=np.full(batch, 200, np.int32))
+    new_lens = np.full(batch, T, np.int32)
+    q, kn, vn = _new_tokens(w, T, 9701)
+    msl = 200 + T
+    assert prefill_waves(d, g, batch * hkv, T, msl) == 4
+    case = Case(w, cache, max_seq_len=msl)
+    want = case.prefill(q, kn, vn, new_lens)
+    case.step.close()
+    bad = dict(cache, page_table=cache["page_table"].copy())
+    bad["page_table"][4, 16] = -1                              # position 256 of sequence 4: its 57th new token
+    bad["page_table"][6, 3] = cache["k_pool"].shape[0] + 7     # cached positions of sequence 6
+    case = Case(w, bad, max_seq_len=msl)
+    got = case.prefill(q, kn, vn, new_lens)
+    assert case.step.device_error() == -4
+    rest = ~np.isin(np.arange(batch), (4, 6))
+    np.testing.assert_array_equal(got[rest], want[rest])
+    assert (got[4] == SENTINEL).all()
+    k, v, lens = case.state()
+    np.testing.assert_array_equal(lens, np.where(np.arange(batch) == 4, 200, 200 + T))
+    own = cache["page_table"][4][cache["page_table"][4] >= 0]
+    np.testing.assert_array_equal(k[own], cache["k_pool"][own])
+    np.testing.assert_array_equal(v[own], cache["v_pool"][own])
     case.step.close()
