@@ -362,12 +362,13 @@ orthrus_status orthrus_attn_timing_samples(orthrus_ctx *ctx, double *split_us, d
 /*
  * Measurement helper: the K/V stream of one attention call with no arithmetic.  Sections 1, 2.1 and 3.1
  * name the repeated loading of the KV cache as the memory-bandwidth bottleneck of decoding; this call
- * launches the attention kernel of orthrus_dual_view_attn for these params in a form whose compute
- * waves do nothing: same grid, same partition of the sequences, the same loads of the cached K and V
- * rows through the page table, no queries, no arithmetic, nothing written (the block's own K/V tile
- * is not read either).  Its duration is the time this library's access pattern needs for the call's
- * K/V bytes on the machine at hand: a measured ceiling to hold the attention kernels against, next to
- * the published peak.  Asynchronous on `stream`, allocates nothing.  While per-kernel timing is
+ * launches the 32-row attention kernel for these params in a form whose compute waves do nothing: the
+ * call's grid and partition of the sequences, one loader wave per workgroup that loads the cached K and V
+ * rows through the page table as that kernel does, no queries, no arithmetic, nothing written (the block's
+ * own K/V tile is not read either).  Its duration is the time this library's access pattern needs for the
+ * call's K/V bytes on the machine at hand: a measured ceiling to hold the attention kernels against, next to
+ * the published peak.  (Calls with enough rows and units to be bound by arithmetic run another kernel, in
+ * which every wave loads its share into a deeper ring; the probe stays the loader-wave form for them too.)  Asynchronous on `stream`, allocates nothing.  While per-kernel timing is
  * enabled the launch is recorded like an attention call without a combine kernel.
  *   k_pool, v_pool, page_table, seq_lens [dev] as in orthrus_dual_view_attn (read only)
  * Page ids outside [0, num_pages) are read as page 0 and lengths are clamped to [0, max_seq_len], with

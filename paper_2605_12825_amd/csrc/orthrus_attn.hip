@@ -71,8 +71,10 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(const AttnA
     constexpr bool PREFILL = MODE == kItemsPrefill, BALANCED = MODE == kItemsBalanced;
     // With two compute waves on a SIMD the other wave fills a wave's waits, and what counts is instructions: the weights
     // are taken before anything is known of the maximum (row_weights).  One wave alone is a chain, in which that puts
-    // the test behind the exponentials.  64 sequences of 1024..3072 tokens, 256 rows: 194 -> 182 us, 224 rows 91 -> 87;
-    // batch 1 at 64 rows 13.4 -> 14.1, at 256 rows of d = 64 (half the products per exponential) 12.5 -> 13.4.
+    // the test behind the exponentials.  64 sequences of 1024..3072 tokens, 4 KV heads, 160 / 192 / 224 rows: 99.0 ->
+    // 95.5 / 91.7 -> 87.0 / 94.6 -> 92.4 us; 32 of 2000, 256 rows 59.6 -> 57.3; one of 4096 (36-layer graph), 192 / 224 /
+    // 256 rows 20.8 -> 21.0 / 17.9 -> 18.1 / 22.7 -> 22.7.  Four waves and fewer, batch 1 at 64 rows 13.4 -> 14.1; 256
+    // rows of d = 64 (half the products per exponential) 12.5 -> 13.4.
     constexpr bool kWeightsFirst = W > 4 && D == 128 && MODE == kItemsSplit;
     static_assert(!PROBE || (W == 1 && !PREFILL), "the stream probe is a decode-mode kernel with one idle compute wave");
     using Gm = AttnGeom<D>;

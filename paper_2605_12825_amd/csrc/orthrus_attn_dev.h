@@ -68,7 +68,8 @@ __device__ __forceinline__ float sum_with_other_half(float x)
 // that one of them may have outgrown it by more than 2^kLazy (rarely, after a row's first tile) is the maximum taken,
 // and the reference moves to it by the same rule that a maximum in every tile would apply: no maximum on the common
 // path (about 15 of the 75 vector instructions a tile would cost) and the same bits.  A weight above 2^kLazy puts the
-// sum above kLazySum (a little below 2^kLazy, for the exponential's rounding); a sum that is NaN compares false.
+// sum above kLazySum (a little below 2^kLazy, for the exponential's rounding); a sum that is NaN compares false.  (A
+// row whose later tiles all score 4 to 8 octaves above its first one has its maximum taken in every tile.)
 constexpr float kLazySum = 255.0f;
 static_assert(kLazy == 8.0f, "kLazySum follows it");
 __device__ __forceinline__ void row_weights(const f32x16 &s, float c, float m, float (&e)[16], float &sum)

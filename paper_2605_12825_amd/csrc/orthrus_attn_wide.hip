@@ -14,8 +14,9 @@
 //
 // What bounds it: issue.  A slot is 16 MFMA (512 cycles) next to ~60 vector, 8-16 LDS and ~22 scalar instructions of
 // one wave; about 1470 cycles per 64x32 tile against 1024 of matrix work, and at full load the clock drops from 2.3 to
-// 1.95 GHz.  Measured (32/8 heads, d = 128, 8192 new tokens): 666 -> 488 us per call, 1.2 PFLOP/s in this kernel against
-// 1.36 for the library's bf16 matrix product; ragged prefill at 28/4 heads 389 -> 324 us; training mask 844 -> 645 us.
+// 1.95 GHz.  Measured against attn_split_kernel's form (32/8 heads, d = 128, 8192 new tokens): 675 -> 485 us per call, 1.2
+// PFLOP/s in this kernel against 1.36 for the library's bf16 matrix product; ragged prefill at 28/4 heads 400 -> 330 us;
+// training mask 864 -> 647 us.
 // Without any tile load the same loop takes 458 us, and 5, 6 or 9 ring stages make no difference.
 #include "orthrus_attn_dev.h"
 

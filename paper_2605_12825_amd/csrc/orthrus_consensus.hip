@@ -18,7 +18,7 @@
 //                          pairs (kCopyApart); accept_commit_kernel then has grid (sequence).
 // (A single-launch variant in which the last-arriving workgroup of a sequence finishes the job was
 // measured and dropped: the device-scope release/acquire fences it needs per workgroup cost far
-// more than the two extra launches.)
+// more than the second launch.)
 //
 // Order among candidates: a NaN outranks every number, larger values outrank smaller ones, and
 // among equals the smaller index wins; this is a total order, so the result does not depend on

@@ -189,8 +189,8 @@ int draw_chunk_elems();
 hipError_t consensus_scratch_init(int device);
 void *consensus_scratch(int device);
 size_t consensus_scratch_bytes();
-// Measurement helper: the attention call's own K/V stream with idle compute waves (same grid, same
-// partition, same loader, no arithmetic, nothing written).
+// Measurement helper: the attention call's K/V stream with idle compute waves (same grid, same partition, the loader
+// wave and ring of attn_split_kernel also for calls of attn_wide_kernel, no arithmetic, nothing written).
 hipError_t launch_kv_stream_probe(const AttnArgs &a, const AttnPlan &plan, int head_dim, hipStream_t stream,
                                   hipEvent_t start, hipEvent_t stop);
 

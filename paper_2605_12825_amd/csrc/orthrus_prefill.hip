@@ -9,7 +9,8 @@
 //                          while others still read it.
 // (A planning launch in front of the copy cost 5 us of every call, and the copy, one load and store at a time, 16 us
 // for 8192 tokens of 8 heads.)
-// The attention itself is the split kernel of orthrus_attn.hip in its prefill form.
+// The attention itself is the prefill form of attn_wide_kernel, or of attn_split_kernel for small launches
+// (prefill_wide_waves in orthrus_attn_wide.hip).
 #include "orthrus_internal.h"
 
 namespace orthrus {
