@@ -154,6 +154,10 @@ __device__ __forceinline__ const void *uniform_ptr(const void *p)
                           (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)((uint64_t)p >> 32)) << 32);
 }
 
+// A scalar register that a vector instruction (a lane read) has written may be read by a vector-memory instruction five
+// wait states later; the compiler keeps that distance for its own instructions, not for the assembly statements below.
+__device__ __forceinline__ void lane_read_settles() { asm volatile("s_nop 4"); }
+
 // Direct global->LDS load of 64 x 16 bytes: lane's bytes land at lds_addr + lane*16.  Issued through inline assembly so
 // that whole tiles can stay in flight while older ones are computed; completion is awaited explicitly with s_waitcnt
 // vmcnt (loads return in order).  M0 carries the LDS destination and is declared clobbered, so the compiler never

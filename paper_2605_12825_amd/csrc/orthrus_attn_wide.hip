@@ -12,12 +12,15 @@
 // (sched_barrier): the compiler's own order keeps them apart.
 // Every wave issues its own share of the tile loads (a loader wave would halve the registers), NS-1 tiles ahead.
 //
-// What bounds it: issue.  A slot is 16 MFMA (512 cycles) next to ~60 vector, 8-16 LDS and ~22 scalar instructions of
-// one wave; about 1470 cycles per 64x32 tile against 1024 of matrix work, and at full load the clock drops from 2.3 to
-// 1.95 GHz.  Measured against attn_split_kernel's form (32/8 heads, d = 128, 8192 new tokens): 675 -> 485 us per call, 1.2
-// PFLOP/s in this kernel against 1.36 for the library's bf16 matrix product; ragged prefill at 28/4 heads 400 -> 330 us;
-// training mask 864 -> 647 us.
-// Without any tile load the same loop takes 458 us, and 5, 6 or 9 ring stages make no difference.
+// What bounds it: issue, and at full load the power that the products draw.  One wave issues a vector instruction every
+// 6 to 8 cycles, other ones every 4, so whatever is not a product or softmax costs time: a product with its share of the
+// softmax (multiply-add, exponential, sum, half a conversion) takes 35 cycles against the product's own 32, and the rest
+// of a tile's instructions come on top.  The main loop therefore takes a turn of the ring at a time, so that LDS
+// addresses are instruction offsets, waits for LDS twice a tile, and keeps the memory addresses of 64 tiles in vector
+// registers: 188 instructions a 64x32 tile where an address calculation and a wait at each use made it 225.  Measured
+// before and after: one item to a CU (100 new tokens behind 16000, 7 heads a KV head) 351 -> 291 us a call; 8192 new tokens
+// (32/8 heads) 478 -> 456, where the kernel's cycles fall by 12 % and the clock by 6 (1.97 -> 1.85 GHz); ragged prefill at
+// 28/4 heads 325 -> 300; training mask 623 -> 598.  (attn_split_kernel's form: 675, 400 and 864.)
 #include "orthrus_attn_dev.h"
 
 namespace orthrus {
@@ -61,22 +64,42 @@ __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(const AttnArgs a)
     const uint32_t dst_first = smem_lds + my_dst, dst_end = dst_first + NS * STAGE_B;
     const uint16_t *my_operand = (my_v ? a.v_pool : a.k_pool) + w.head_off;
     const char *my_pool = half.lowered(my_operand);
+    uint32_t worst = 0;  // largest page id that this lane has fetched
     const int n_whole = half.usable ? min(w.n_cache, (w.t_end - w.t_begin) >> 5) : 0;  // tiles loaded a half at a time
     uint32_t dst = dst_first;                                     // where the next tile to be issued goes
     uint32_t page_at = (uint32_t)(w.t_begin + my_half * 16);      // token position of this wave's first half of that tile
-    int page[PG];                                                 // page ids of its halves
-    auto load_pages = [&]() __attribute__((always_inline)) {
-#pragma unroll
-        for (int u = 0; u < PG; ++u) page[u] = w.pt_row[(page_at + u * 16u) >> a.page_shift];
-    };
     auto advance = [&]() __attribute__((always_inline)) {
         dst = dst + STAGE_B == dst_end ? dst_first : dst + STAGE_B;
         page_at += 32;
     };
+    // Where the halves of 64 whole tiles start in memory, a tile to a lane: one vector load and a few vector
+    // instructions for 64 tiles, and two lane reads for a half when it is issued.  (A scalar load of the page id and the
+    // address arithmetic on it were 24 of the ~105 instructions that a tile costs next to its products and softmax.)
+    uint32_t at_lo[PG], at_hi[PG];
+    int win = 0;  // tile of lane 0
+    auto open_window = [&](int t) __attribute__((always_inline)) {
+        win = t;
+        const uint32_t tok = (uint32_t)(w.t_begin + min(t + lane, n_whole - 1) * 32 + my_half * 16);
+#pragma unroll
+        for (int u = 0; u < PG; ++u) {
+            const uint32_t id = (uint32_t)((const int32_t *)w.pt_row)[(tok + u * 16u) >> a.page_shift];
+            worst = max(worst, id);
+            const uint64_t at = (uint64_t)(uintptr_t)my_pool + (uint64_t)(id < half.num_pages ? id : 0u) * half.page_bytes +
+                                ((tok + u * 16u) & half.page_mask) * half.tok_bytes;
+            at_lo[u] = (uint32_t)at;
+            at_hi[u] = (uint32_t)(at >> 32);
+        }
+    };
+    auto half_base = [&](int u, int t) __attribute__((always_inline)) {
+        return (const char *)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)at_lo[u], t - win) |
+                              (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)at_hi[u], t - win) << 32);
+    };
     // any tile t, outside the main loop
     auto issue_tile = [&](int t) __attribute__((always_inline)) {
         if (t < n_whole) {
-            load_pages();
+            int page[PG];
+#pragma unroll
+            for (int u = 0; u < PG; ++u) page[u] = w.pt_row[(page_at + u * 16u) >> a.page_shift];
 #pragma unroll
             for (int u = 0; u < PG; ++u)
                 half.issue(NtTag{}, my_pool + half.offset(page[u], page_at + u * 16u), dst + u * half.GPH * GS);
@@ -122,16 +145,15 @@ __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(const AttnArgs a)
     const float c = a.scale_log2e;
     // ---- pipeline fill (the page ids of the whole fill in one round trip)
     if (n_whole >= NS - 1) {
-        int ids[NS - 1][PG];
-#pragma unroll
-        for (int t = 0; t < NS - 1; ++t)
-#pragma unroll
-            for (int u = 0; u < PG; ++u) ids[t][u] = w.pt_row[(page_at + t * 32u + u * 16u) >> a.page_shift];
+        open_window(0);
 #pragma unroll
         for (int t = 0; t < NS - 1; ++t) {
+            const char *base[PG];
 #pragma unroll
-            for (int u = 0; u < PG; ++u)
-                half.issue(NtTag{}, my_pool + half.offset(ids[t][u], page_at + u * 16u), dst + u * half.GPH * GS);
+            for (int u = 0; u < PG; ++u) base[u] = half_base(u, t);
+            lane_read_settles();
+#pragma unroll
+            for (int u = 0; u < PG; ++u) half.issue(NtTag{}, base[u], dst + u * half.GPH * GS);
             advance();
         }
     } else {
@@ -193,23 +215,51 @@ __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(const AttnArgs a)
 #pragma unroll
             for (int r = 0; r < 16; ++r) o[x][db][r] = 0.f;
     }
-    // LDS reads: one add per operand base, the rest are instruction offsets (the empty asm keeps them so)
-    auto read_k = [&](uint32_t st, int kk) __attribute__((always_inline)) {
-        uint32_t ad = st + kb[kk >> 1];
-        asm("" : "+v"(ad));
+    // LDS reads at a stage that is known when the kernel is compiled (S >= 0): the stage is part of the instruction's
+    // 16-bit offset, from one of two bases; at any other stage: an add per base.
+    constexpr int SPB = 3;  // stages behind one base
+    static_assert(NS <= 2 * SPB && SPB * STAGE_B <= 65536, "");
+    uint32_t ka[2][KSTEPS / 2], va[2][DBLK];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+#pragma unroll
+        for (int q = 0; q < KSTEPS / 2; ++q) {
+            ka[u][q] = smem_lds + u * SPB * STAGE_B + kb[q];
+            asm("" : "+v"(ka[u][q]));
+        }
+#pragma unroll
+        for (int db = 0; db < DBLK; ++db) {
+            va[u][db] = smem_lds + u * SPB * STAGE_B + vb[db];
+            asm("" : "+v"(va[u][db]));
+        }
+    }
+    auto read_k = [&](auto stage, uint32_t st, int kk) __attribute__((always_inline)) {
+        constexpr int S = decltype(stage)::value;
+        uint32_t ad;
+        if constexpr (S >= 0) {
+            ad = ka[S / SPB][kk >> 1] + S % SPB * STAGE_B;
+        } else {
+            ad = st + kb[kk >> 1];
+            asm("" : "+v"(ad));
+        }
         kf[kk].n = *(const lds_u32x4 *)(uintptr_t)(ad + ((kk & 1) << 5));
     };
-    auto read_v = [&](uint32_t st, int db, int q2) __attribute__((always_inline)) {
-        uint32_t ad = st + vb[db];
-        asm("" : "+v"(ad));
+    auto read_v = [&](auto stage, uint32_t st, int db, int q2) __attribute__((always_inline)) {
+        constexpr int S = decltype(stage)::value;
+        uint32_t ad;
+        if constexpr (S >= 0) {
+            ad = va[S / SPB][db] + S % SPB * STAGE_B;
+        } else {
+            ad = st + vb[db];
+            asm("" : "+v"(ad));
+        }
 #pragma unroll
         for (int q = 0; q < 2; ++q)
             vf[db][q2].h[q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
                 (lds_s16x4 *)(uintptr_t)(ad + (2 * q2 + q) * (8 / RPI) * GS));
     };
+    using AnyStage = std::integral_constant<int, -1>;
     constexpr int NCH = KSTEPS + 2 * DBLK;  // products of a slot
-    constexpr int JD = NCH == 16 ? 6 : 3;        // the slot's first tile load goes out here
-    static_assert(JD + LPW <= NCH, "");
     constexpr int VPC = 16 / NCH;           // softmax values handled next to each of them
     // One slot: the matrix work of block C (scores of tile i, values of tile i-1) next to the softmax of the other
     // block's last scores, one product and VPC values at a time.  `extra(j)` adds the loads that go next to product j.
@@ -224,13 +274,14 @@ __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(const AttnArgs a)
         const float mref = m[X];
 #pragma unroll
         for (int j = 0; j < NCH; ++j) {
+            extra(j, std::integral_constant<bool, false>{});
             if (j < KSTEPS) {
                 z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[j].v, qf[C][j].v, z, 0, 0, 0);
             } else {
                 const int db = (j - KSTEPS) % DBLK, q2 = (j - KSTEPS) / DBLK;
                 o[C][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db][q2].v, p[C][q2].v, o[C][db], 0, 0, 0);
             }
-            extra(j);
+            extra(j, std::integral_constant<bool, true>{});
 #pragma unroll
             for (int v = 0; v < VPC; ++v) {
                 const int r = j * VPC + v;
@@ -291,50 +342,67 @@ __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(const AttnArgs a)
     uint32_t st = smem_lds, sv = smem_lds + (NS - 1) * STAGE_B;  // stages of tiles i and i-1
     auto next = [&](uint32_t x) __attribute__((always_inline)) { return x + STAGE_B == smem_lds + NS * STAGE_B ? smem_lds : x + STAGE_B; };
 #pragma unroll
-    for (int kk = 0; kk < KSTEPS; ++kk) read_k(st, kk);
-    auto tile = [&](auto fast, auto masked, int i) __attribute__((always_inline)) {
-        slot(std::integral_constant<int, 0>{}, masked, limit(1, i - 1), [&](int j) __attribute__((always_inline)) {
-            if (j < KSTEPS) read_v(sv, j % DBLK, j / DBLK);
-            if constexpr (decltype(fast)::value) {
-                if (j == NCH - 1) load_pages();
+    for (int kk = 0; kk < KSTEPS; ++kk) read_k(std::integral_constant<int, 0>{}, st, kk);
+#pragma unroll
+    for (int db = 0; db < DBLK; ++db) vf[db][0].u = make_uint4(0, 0, 0, 0);
+    // One tile step.  The reads of a step go out well before their products, in two groups with one wait each (a wait in
+    // front of every product costs an issue slot each): next tile's keys as soon as this tile's last product with them is
+    // out, the first half of this tile's values (for the next step) behind them, the second half when the next step
+    // starts.  S >= 0: the ring stage of tile i, and the step issues the whole tile i+NS-1.
+    auto tile = [&](auto stage, auto masked, int i) __attribute__((always_inline)) {
+        constexpr int S = decltype(stage)::value;
+        constexpr bool FAST = S >= 0;
+        using Prev = std::integral_constant<int, FAST ? (S + NS - 1) % NS : -1>;
+        using Next = std::integral_constant<int, FAST ? (S + 1) % NS : -1>;
+        constexpr int JK = NCH == 16 ? 4 : 2;  // the first read of the next tile's keys
+        slot(std::integral_constant<int, 0>{}, masked, limit(1, i - 1), [&](int j, auto after) __attribute__((always_inline)) {
+            if constexpr (!decltype(after)::value) {
+                if (j == 0) __builtin_amdgcn_s_waitcnt(0xc07f | 2 * DBLK << 8);  // lgkmcnt: all but the values behind the keys
+                if (j == KSTEPS) __builtin_amdgcn_s_waitcnt(0xc07f);             // lgkmcnt(0)
+            } else if (j < DBLK) {
+                read_v(Prev{}, sv, j, 1);
             }
         });
-        sv = st;
-        uint64_t off[PG];
-        slot(std::integral_constant<int, 1>{}, masked, limit(0, i), [&](int j) __attribute__((always_inline)) {
-            if constexpr (decltype(fast)::value) {
+        const char *base[PG];
+        slot(std::integral_constant<int, 1>{}, masked, limit(0, i), [&](int j, auto after) __attribute__((always_inline)) {
+            if constexpr (!decltype(after)::value) return;
+            if constexpr (FAST) {
                 if (j == 0) {
                     wait_vmcnt<(NS - 3) * LPW>();
                     wg_barrier();
-                }
-                if (j == 1) st = next(st);
 #pragma unroll
-                for (int u = 0; u < PG; ++u) {
-                    if (j == JD - 1 - u) {
-                        off[u] = half.offset(page[u], page_at + u * 16u);
-                    }
-                    if (j == JD + 2 * u) half.issue(NtTag{}, my_pool + off[u], dst + u * half.GPH * GS);
+                    for (int u = 0; u < PG; ++u) base[u] = half_base(u, i + NS - 1);
                 }
-                if (j == NCH - 1) advance();
-            } else {
-                if (j == 0) {
-                    step_barrier(i);
-                    st = next(st);
-                }
+#pragma unroll
+                for (int u = 0; u < PG; ++u)
+                    if (j == 2 + u) half.issue(NtTag{}, base[u], dst_first + Prev::value * STAGE_B + u * half.GPH * GS);
+            } else if (j == 0) {
+                step_barrier(i);
+                sv = st;
+                st = next(st);
             }
-            if (j >= KSTEPS) read_k(st, j - KSTEPS);
+            if (j >= JK && j < JK + KSTEPS) read_k(Next{}, st, j - JK);
+            if (j >= NCH - DBLK) read_v(stage, sv, j - (NCH - DBLK), 0);
         });
     };
-    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the queries are in registers before the loop starts
+    __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0), lgkmcnt(0): queries and keys are in registers before the loop starts
     int i = 0;
-    const int n_fast = min(n_full, n_whole - (NS - 1));  // tiles whose step issues a whole tile
-    for (; i < n_fast; ++i) tile(std::true_type{}, std::false_type{}, i);
-    for (; i < n_full; ++i) tile(std::false_type{}, std::false_type{}, i);
-    for (; i < n_mine; ++i) tile(std::false_type{}, std::true_type{}, i);
+    // steps that issue a whole tile and whose rows see all of theirs, a turn of the ring at a time
+    const int n_fast = min(n_full, n_whole - (NS - 1)) / NS * NS;
+    while (i < n_fast) {
+        if (i + 2 * NS - 2 - win >= 64) open_window(i + NS - 1);
+        [&]<int... S>(std::integer_sequence<int, S...>) __attribute__((always_inline)) {
+            (tile(std::integral_constant<int, S>{}, std::false_type{}, i + S), ...);
+        }(std::make_integer_sequence<int, NS>{});
+        i += NS;
+        page_at += 32 * NS;
+    }
+    for (; i < n_full; ++i) tile(AnyStage{}, std::false_type{}, i);
+    for (; i < n_mine; ++i) tile(AnyStage{}, std::true_type{}, i);
     // drain: the last tile's value products (its second block's softmax in between)
 #pragma unroll
-    for (int kk = 0; kk < KSTEPS; ++kk) read_v(sv, kk / 2, kk % 2);
-    slot(std::integral_constant<int, 0>{}, std::true_type{}, limit(1, n_mine - 1), [](int) {});
+    for (int db = 0; db < DBLK; ++db) read_v(AnyStage{}, sv, db, 1);
+    slot(std::integral_constant<int, 0>{}, std::true_type{}, limit(1, n_mine - 1), [](int, auto) {});
 #pragma unroll
     for (int q2 = 0; q2 < 2; ++q2)
 #pragma unroll
@@ -363,7 +431,7 @@ __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(const AttnArgs a)
             a.lse[((int64_t)w.b * a.num_q_heads + (int64_t)w.g * G + hl) * K + irow[x]] =
                 (m[x] + __builtin_amdgcn_logf(lt)) * 0.6931471805599453f;
     }
-    if (half.worst >= half.num_pages && lane == 0) atomicExch(a.err_word, -4);
+    if (max(worst, half.worst) >= half.num_pages) atomicExch(a.err_word, -4);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -316,3 +316,61 @@ def test_prefill_capacity_error_stays_with_its_sequence():
     np.testing.assert_array_equal(k[own], cache["k_pool"][own])
     np.testing.assert_array_equal(v[own], cache["v_pool"][own])
     case.step.close()
+
+
+# a wave keeps the addresses of 64 tiles at a time: lengths around one and two such windows, ring turns (4 and 6 tiles) apart
+WINDOWS = [2016, 2047, 2048, 2079, 2112, 2143, 2175, 2240, 4050]
+
+
+@pytest.mark.parametrize("g,K,hkv,batch,d,page", [(4, 32, 8, 64, 128, 16), (8, 32, 4, 80, 128, 64), (8, 31, 4, 64, 64, 32)])
+def test_decode_past_a_window_of_addresses(g, K, hkv, batch, d, page):
+    w = Workload(name="window", seed=9800 + d, batch=batch, num_q_heads=g * hkv, num_kv_heads=hkv, head_dim=d, block_k=K,
+                 context=300, page_size=page, paging="scattered")
+    lens = np.full(batch, 5, np.int32)
+    lens[:len(WINDOWS)] = WINDOWS
+    cache, blk = make_cache(w, seq_lens=lens), make_block(w, 9801)
+    case = _case(w, cache, True)
+    _check_attn(case.attn(AR, blk, want_lse=False), _oracle_attn(AR, w, blk, cache))
+    assert case.step.device_error() == 0
+    case.step.close()
+
+
+@pytest.mark.parametrize("g,d,page", [(7, 128, 16), (5, 128, 64), (8, 64, 32)])
+def test_prefill_past_a_window_of_addresses(g, d, page):
+    """Against the oracle with two waves (four for d = 64); with four of d = 128, which take a batch that fills the chip,
+    the same bits."""
+    T, hkv = 51, 1
+    w = Workload(name="windowp", seed=9900 + g, batch=len(WINDOWS), num_q_heads=g, num_kv_heads=hkv, head_dim=d, block_k=8,
+                 context=300, page_size=page, paging="shuffled", steps=(T + 7) // 8 + 1)
+    cache = make_cache(w, seq_lens=np.array(WINDOWS, np.int32))
+    new_lens = np.array([T, 1, 25, 26, T, 32, 33, T, 50], np.int32)
+    q, kn, vn = _new_tokens(w, T, 9901)
+    ref = [cache[x].copy() for x in ("k_pool", "v_pool", "seq_lens")]
+    want, _ = oracle.prefill_attn(w.sm_scale, q, kn, vn, new_lens, ref[0], ref[1], cache["page_table"], ref[2])
+    msl = max(WINDOWS) + T
+    assert prefill_waves(d, g, w.batch, T, msl) == (2 if d == 128 else 4)
+    case = Case(w, cache, max_seq_len=msl)
+    got = case.prefill(q, kn, vn, new_lens)
+    _check(got, want, new_lens)
+    np.testing.assert_array_equal(case.state()[0], ref[0])
+    case.step.close()
+    if g != 5:
+        return
+    rep = 20                                      # 180 sequences: copies of these nine, which share the cached pages
+    assert prefill_waves(d, g, rep * w.batch, T, msl) == 4
+    tile = lambda x: np.concatenate([x] * rep)
+    pages, slots = cache["page_table"].copy(), cache["page_table"].shape[1]
+    own = [np.arange(L // page, (L + T - 1) // page + 1) for L in WINDOWS]   # pages that the new tokens write
+    pt, k, v = [pages], [cache["k_pool"]], [cache["v_pool"]]
+    at = cache["k_pool"].shape[0]
+    for r in range(1, rep):
+        p = pages.copy()
+        for b, s in enumerate(own):
+            k.append(cache["k_pool"][pages[b, s]]), v.append(cache["v_pool"][pages[b, s]])
+            p[b, s] = np.arange(at, at + len(s))
+            at += len(s)
+        pt.append(p)
+    big = dict(cache, k_pool=np.concatenate(k), v_pool=np.concatenate(v), page_table=np.concatenate(pt), seq_lens=tile(cache["seq_lens"]))
+    case = Case(replace(w, batch=rep * w.batch), big, max_seq_len=msl)
+    np.testing.assert_array_equal(case.prefill(tile(q), tile(kn), tile(vn), tile(new_lens)), tile(got))
+    case.step.close()
