@@ -65,7 +65,11 @@ namespace orthrus {
 // PROBE = 1 is the measurement form behind orthrus_kv_stream_probe: the loader wave streams exactly the
 // tiles of the call, the compute waves only keep the barriers (no queries, no arithmetic, nothing is
 // written), so the launch takes as long as this kernel's K/V stream alone.
-template <int D, int W, int NS, int MODE = kItemsSplit, int PROBE = 0>
+//
+// NT: the non-temporal forms of the tile loads and of the partials' stores.  A form of the kernel and not a test in it:
+// every jump into code that no wave of the launch has fetched yet is a round trip to the L2 or beyond, in the loader's
+// first tile and between the last tile and the write-out alike.
+template <int D, int W, int NS, int MODE, int NT, int PROBE = 0>
 __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(const AttnArgs a)
 {
     constexpr bool PREFILL = MODE == kItemsPrefill, BALANCED = MODE == kItemsBalanced;
@@ -107,87 +111,84 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(const AttnA
         // Before the barrier the loads of tile i are complete; after it every compute wave is done reading the stage
         // of tile i-1, which is refilled with tile i+NS-1 while tile i is computed.
         HalfLoads<D> half(a, lane);
-        auto run = [&](auto nt) __attribute__((always_inline)) {
-            for (;;) {
-                const int n_whole = half.usable ? min(it.n_cache, (it.t_end - it.t_begin) >> 5) : 0;
-                const char *kp = half.lowered(a.k_pool + it.head_off), *vp = half.lowered(a.v_pool + it.head_off);
-                uint32_t dst = smem_lds;  // ring slot of the next tile to be issued
-                int p0 = 0, p1 = 0;       // page ids of its two halves (the second repeats the first past the end)
-                // fetched one tile ahead of their use, so that the scalar load's latency is never in front of a tile's loads
-                auto fetch_pages = [&](int t) __attribute__((always_inline)) {
-                    if (t < it.n_cache) {
-                        const int ts = it.t_begin + t * 32;
-                        p0 = it.pt_row[(uint32_t)ts >> a.page_shift];
-                        p1 = it.pt_row[(uint32_t)(ts + 16 < it.t_end ? ts + 16 : ts) >> a.page_shift];
+        const std::integral_constant<bool, NT != 0> nt;
+        for (;;) {
+            const int n_whole = half.usable ? min(it.n_cache, (it.t_end - it.t_begin) >> 5) : 0;
+            const char *kp = half.lowered(a.k_pool + it.head_off), *vp = half.lowered(a.v_pool + it.head_off);
+            uint32_t dst = smem_lds;  // ring slot of the next tile to be issued
+            int p0 = 0, p1 = 0;       // page ids of its two halves (the second repeats the first past the end)
+            // fetched one tile ahead of their use, so that the scalar load's latency is never in front of a tile's loads
+            auto fetch_pages = [&](int t) __attribute__((always_inline)) {
+                if (t < it.n_cache) {
+                    const int ts = it.t_begin + t * 32;
+                    p0 = it.pt_row[(uint32_t)ts >> a.page_shift];
+                    p1 = it.pt_row[(uint32_t)(ts + 16 < it.t_end ? ts + 16 : ts) >> a.page_shift];
+                }
+            };
+            auto issue_tile = [&](int t) __attribute__((always_inline)) {
+                if (t < n_whole) {
+                    const uint32_t ts = (uint32_t)(it.t_begin + t * 32);
+                    const uint64_t o0 = half.offset(p0, ts), o1 = half.offset(p1, ts + 16);
+                    half.issue(nt, kp + o0, dst);
+                    half.issue(nt, kp + o1, dst + half.GPH * GS);
+                    half.issue(nt, vp + o0, dst + TILE_B);
+                    half.issue(nt, vp + o1, dst + TILE_B + half.GPH * GS);
+                } else if (half.usable && t < it.n_cache) {
+                    // the last, ragged cache tile: rows past the end repeat the last valid row (finite data, masked
+                    // later), so nothing is fetched through an unmapped page and no LDS row is left undefined
+                    const uint64_t o0 = half.offset(p0, 0) >> 1, o1 = half.offset(p1, 0) >> 1;
+                    const uint16_t *const kb[2] = {a.k_pool + it.head_off + o0, a.k_pool + it.head_off + o1};
+                    const uint16_t *const vb[2] = {a.v_pool + it.head_off + o0, a.v_pool + it.head_off + o1};
+                    issue_rows<D>(nt, kb, vb, dst, [&](int u) __attribute__((always_inline)) {
+                        const int tg = min(it.t_begin + t * 32 + u * RPI + ld_tok, it.t_end - 1);
+                        return ((uint32_t)tg & half.page_mask) * half.tok_bytes + ld_swz;
+                    });
+                } else if (t < it.n_cache) {  // strides past 32-bit arithmetic: an address per lane and load
+                    half.worst = max(half.worst, max((uint32_t)p0, (uint32_t)p1));
+                    const int q0 = (uint32_t)p0 < half.num_pages ? p0 : 0, q1 = (uint32_t)p1 < half.num_pages ? p1 : 0;
+#pragma unroll 1
+                    for (int u = 0; u < NI; ++u) {
+                        const int tg = min(it.t_begin + t * 32 + u * RPI + ld_tok, it.t_end - 1);
+                        const int64_t off = (int64_t)(u * RPI < 16 ? q0 : q1) * a.stride_page + it.head_off +
+                                            (int64_t)(tg & (P - 1)) * a.stride_tok + (ld_swz >> 1);
+                        dma16(nt, a.k_pool + off, dst + u * GS);
+                        dma16(nt, a.v_pool + off, dst + TILE_B + u * GS);
                     }
-                };
-                auto issue_tile = [&](int t) __attribute__((always_inline)) {
-                    if (t < n_whole) {
-                        const uint32_t ts = (uint32_t)(it.t_begin + t * 32);
-                        const uint64_t o0 = half.offset(p0, ts), o1 = half.offset(p1, ts + 16);
-                        half.issue(nt, kp + o0, dst);
-                        half.issue(nt, kp + o1, dst + half.GPH * GS);
-                        half.issue(nt, vp + o0, dst + TILE_B);
-                        half.issue(nt, vp + o1, dst + TILE_B + half.GPH * GS);
-                    } else if (half.usable && t < it.n_cache) {
-                        // the last, ragged cache tile: rows past the end repeat the last valid row (finite data, masked
-                        // later), so nothing is fetched through an unmapped page and no LDS row is left undefined
-                        const uint64_t o0 = half.offset(p0, 0) >> 1, o1 = half.offset(p1, 0) >> 1;
-                        const uint16_t *const kb[2] = {a.k_pool + it.head_off + o0, a.k_pool + it.head_off + o1};
-                        const uint16_t *const vb[2] = {a.v_pool + it.head_off + o0, a.v_pool + it.head_off + o1};
+                } else if constexpr (!PROBE && !PREFILL) {  // (the stream probe has no block inputs: its in-block tile stays empty)
+                    // the in-block tile; rows past the block repeat its last row
+                    const int64_t off0 = (int64_t)it.b * K * a.blk_stride_row + (int64_t)it.g * a.blk_stride_head;
+                    if (a.blk_stride_row < (1ll << 25)) {
+                        const uint16_t *const kb[2] = {a.k_blk + off0, a.k_blk + off0}, *const vb[2] = {a.v_blk + off0, a.v_blk + off0};
+                        const uint32_t row_bytes = (uint32_t)a.blk_stride_row * 2u;
                         issue_rows<D>(nt, kb, vb, dst, [&](int u) __attribute__((always_inline)) {
-                            const int tg = min(it.t_begin + t * 32 + u * RPI + ld_tok, it.t_end - 1);
-                            return ((uint32_t)tg & half.page_mask) * half.tok_bytes + ld_swz;
+                            return (uint32_t)min(u * RPI + ld_tok, K - 1) * row_bytes + ld_swz;
                         });
-                    } else if (t < it.n_cache) {  // strides past 32-bit arithmetic: an address per lane and load
-                        half.worst = max(half.worst, max((uint32_t)p0, (uint32_t)p1));
-                        const int q0 = (uint32_t)p0 < half.num_pages ? p0 : 0, q1 = (uint32_t)p1 < half.num_pages ? p1 : 0;
+                    } else {
 #pragma unroll 1
                         for (int u = 0; u < NI; ++u) {
-                            const int tg = min(it.t_begin + t * 32 + u * RPI + ld_tok, it.t_end - 1);
-                            const int64_t off = (int64_t)(u * RPI < 16 ? q0 : q1) * a.stride_page + it.head_off +
-                                                (int64_t)(tg & (P - 1)) * a.stride_tok + (ld_swz >> 1);
-                            dma16(nt, a.k_pool + off, dst + u * GS);
-                            dma16(nt, a.v_pool + off, dst + TILE_B + u * GS);
-                        }
-                    } else if constexpr (!PROBE && !PREFILL) {  // (the stream probe has no block inputs: its in-block tile stays empty)
-                        // the in-block tile; rows past the block repeat its last row
-                        const int64_t off0 = (int64_t)it.b * K * a.blk_stride_row + (int64_t)it.g * a.blk_stride_head;
-                        if (a.blk_stride_row < (1ll << 25)) {
-                            const uint16_t *const kb[2] = {a.k_blk + off0, a.k_blk + off0}, *const vb[2] = {a.v_blk + off0, a.v_blk + off0};
-                            const uint32_t row_bytes = (uint32_t)a.blk_stride_row * 2u;
-                            issue_rows<D>(nt, kb, vb, dst, [&](int u) __attribute__((always_inline)) {
-                                return (uint32_t)min(u * RPI + ld_tok, K - 1) * row_bytes + ld_swz;
-                            });
-                        } else {
-#pragma unroll 1
-                            for (int u = 0; u < NI; ++u) {
-                                const int64_t off = off0 + (int64_t)min(u * RPI + ld_tok, K - 1) * a.blk_stride_row + (ld_swz >> 1);
-                                dma16(nt, a.k_blk + off, dst + u * GS);
-                                dma16(nt, a.v_blk + off, dst + TILE_B + u * GS);
-                            }
+                            const int64_t off = off0 + (int64_t)min(u * RPI + ld_tok, K - 1) * a.blk_stride_row + (ld_swz >> 1);
+                            dma16(nt, a.k_blk + off, dst + u * GS);
+                            dma16(nt, a.v_blk + off, dst + TILE_B + u * GS);
                         }
                     }
-                    dst = dst + STAGE_B == smem_lds + NS * STAGE_B ? smem_lds : dst + STAGE_B;
-                    fetch_pages(t + 1);
-                };
-                int t = 0;  // next tile to be issued
-                fetch_pages(0);
-                for (; t < min(NS - 1, it.n_tiles); ++t) issue_tile(t);
-                for (int i = 0; i < it.n_tiles; ++i) {
-                    const int ahead = min(NS - 2, it.n_tiles - 1 - i);  // tiles issued after tile i so far
-                    if (ahead >= 2) wait_vmcnt<2 * LPT>();
-                    else if (ahead == 1) wait_vmcnt<LPT>();
-                    else wait_vmcnt<0>();
-                    wg_barrier();
-                    if (t < it.n_tiles) issue_tile(t++);
                 }
-                if (!BALANCED || !it.open(a)) break;
-                wg_barrier();  // every compute wave is done with the previous segment's last tile
+                dst = dst + STAGE_B == smem_lds + NS * STAGE_B ? smem_lds : dst + STAGE_B;
+                fetch_pages(t + 1);
+            };
+            int t = 0;  // next tile to be issued
+            fetch_pages(0);
+            for (; t < min(NS - 1, it.n_tiles); ++t) issue_tile(t);
+            for (int i = 0; i < it.n_tiles; ++i) {
+                const int ahead = min(NS - 2, it.n_tiles - 1 - i);  // tiles issued after tile i so far
+                if (ahead >= 2) wait_vmcnt<2 * LPT>();
+                else if (ahead == 1) wait_vmcnt<LPT>();
+                else wait_vmcnt<0>();
+                wg_barrier();
+                if (t < it.n_tiles) issue_tile(t++);
             }
-        };
-        if (a.kv_nt) run(std::true_type{});
-        else run(std::false_type{});
+            if (!BALANCED || !it.open(a)) break;
+            wg_barrier();  // every compute wave is done with the previous segment's last tile
+        }
         if (half.worst >= half.num_pages && lane == 0) atomicExch(a.err_word, -4);
         return;
     }
@@ -381,7 +382,7 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(const AttnA
 #pragma unroll
                 for (int r4 = 0; r4 < 4; ++r4) {
                     const f32x4 v = {o[db][4 * r4], o[db][4 * r4 + 1], o[db][4 * r4 + 2], o[db][4 * r4 + 3]};
-                    if (a.kv_nt) __builtin_nontemporal_store(v, &po[(db * 4 + r4) * 64]);
+                    if constexpr (NT != 0) __builtin_nontemporal_store(v, &po[(db * 4 + r4) * 64]);
                     else po[(db * 4 + r4) * 64] = v;
                 }
             if (h == 0) ((float2 *)a.part_ml)[slot * 32 + col] = make_float2(m_run, l_run);
@@ -403,16 +404,21 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(const AttnA
 // CHUNK = partials merged per round of loads: 8 keeps the registers low for the bandwidth-bound merges
 // of many units with few pieces each; 16 or 32 make the latency-bound merge of few units with many
 // splits a single memory round trip (a second round costs it ~1 us).
-template <int D, int W, int BALANCED, int CHUNK>
-__global__ void __launch_bounds__(256) attn_combine_kernel(const AttnArgs a)
+//
+// WAVES = waves per workgroup: 4, or 1 where the launch would have few workgroups.  A CU pulls in some 50 KB per
+// microsecond, and 64 workgroups of four waves want 100 KB each of 26 pieces (launch_combine).
+template <int D, int W, int BALANCED, int CHUNK, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES) attn_combine_kernel(const AttnArgs a)
 {
+    static_assert(WAVES == 4 || WAVES == 1, "the four waves of a row and d block share a workgroup or have one each");
     constexpr int DBLK = D / 32;
     constexpr int MCHUNK = 32;  // m values fetched per round when there are more than CHUNK partials
-    const int lane = threadIdx.x & 63, r4 = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, r4 = WAVES == 4 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : blockIdx.x & 3;
     const int col = lane & 31, h = lane >> 5;
-    const int db = blockIdx.x % DBLK;
-    const int wave = (blockIdx.x / DBLK) % W;  // row block
-    const int unit = blockIdx.x / (DBLK * W);
+    const int block = WAVES == 4 ? blockIdx.x : blockIdx.x >> 2;
+    const int db = block % DBLK;
+    const int wave = (block / DBLK) % W;  // row block
+    const int unit = block / (DBLK * W);
     const int b = unit / a.num_kv_heads, g = unit % a.num_kv_heads;
     const int ridx = wave * 32 + col;
     int live;           // number of partials of this unit
@@ -452,9 +458,7 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const AttnArgs a)
         rest_slot = (size_t)w_lo * 2;
         slot_step = 2;
     } else {
-        int L = ((const const_i32 *)a.seq_lens)[b];
-        L = L < 0 ? 0 : (L > a.max_seq_len ? a.max_seq_len : L);
-        live = split_cut(L, a.num_splits, 0).live;  // the split kernel's pieces of this sequence
+        live = a.num_splits;  // until the length is there
         first_slot = rest_slot = (size_t)unit * a.num_splits;
         slot_step = 1;
     }
@@ -470,18 +474,37 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const AttnArgs a)
 
     // The loads of the first CHUNK partials go out before anything waits; the reference maximum needs
     // every partial's m, so the remaining m values follow MCHUNK at a time, then the rest of the data.
-    // A merge of up to CHUNK partials is one memory round trip, not one per pass.
+    // A merge of up to CHUNK partials is one memory round trip, not one per pass.  Past the last piece the loads repeat it
+    // (a condition on each would be a jump each) and what they bring is dropped.  Fixed splits: nor do the first loads wait
+    // for the sequence's length, which says how many of the num_splits slots hold a piece.  With a wave per workgroup, 36-layer
+    // graph, 64 rows, per call: 8 / 15 / 26 pieces of 4096 tokens 15.3 -> 15.0 / 13.2 -> 12.5 / 13.7 -> 12.7 us.
     float4 v[CHUNK];
     float2 e[CHUNK];
     auto load_chunk = [&](int s0) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < CHUNK; ++u) {
-            const bool ok = s0 + u < live;
-            v[u] = ok ? *po_at(s0 + u) : make_float4(0.f, 0.f, 0.f, 0.f);
-            e[u] = ok ? *ml_at(s0 + u) : make_float2(kNegBig, 0.f);
+            const int s = min(s0 + u, live - 1);
+            v[u] = *po_at(s);
+            e[u] = *ml_at(s);
+        }
+    };
+    auto drop_past_end = [&](int s0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < CHUNK; ++u) {
+            if (s0 + u >= live) {
+                v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+                e[u] = make_float2(kNegBig, 0.f);
+            }
         }
     };
     load_chunk(0);
+    if constexpr (!BALANCED) {
+        __builtin_amdgcn_sched_barrier(0);
+        int L = ((const const_i32 *)a.seq_lens)[b];
+        L = L < 0 ? 0 : (L > a.max_seq_len ? a.max_seq_len : L);
+        live = split_cut(L, a.num_splits, 0).live;  // the split kernel's pieces of this sequence
+    }
+    drop_past_end(0);
     float M = kNegBig;
 #pragma unroll
     for (int u = 0; u < CHUNK; ++u) M = fmaxf(M, e[u].x);
@@ -495,7 +518,10 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const AttnArgs a)
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     float lsum = 0.f;
     for (int s0 = 0; s0 < live; s0 += CHUNK) {
-        if (s0 > 0) load_chunk(s0);
+        if (s0 > 0) {
+            load_chunk(s0);
+            drop_past_end(s0);
+        }
 #pragma unroll
         for (int u = 0; u < CHUNK; ++u) {  // fixed split order: the result does not depend on timing
             const float sc = __builtin_amdgcn_exp2f(e[u].x - M);
@@ -581,7 +607,7 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
         const double kRate = 7.0e6;      // K/V bytes per microsecond (measured ceiling of the paged stream)
         const double kPartRate = 6.0e6;  // bytes per microsecond for the partials
         const double kTile = W <= 4 ? 0.56 : 1.3;  // more than four 32-row blocks: two per SIMD
-        const double kRound = 5.0, kCombine = 4.0, kSplit = 0.12, kWg = 0.008;
+        const double kRound = 5.0, kCombine = 4.0, kSplit = 0.06, kWg = 0.008;
         const int64_t slots = (int64_t)num_cus * per_cu;
         const double tile_bytes = 32.0 * 2.0 * head_dim * 2.0;  // K + V bytes of one tile of one KV head
         const double part_bytes = 2.0 * plan->rows_padded * head_dim * 4.0;  // written once, read once
@@ -624,19 +650,30 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
 template <int D, int W, int BALANCED>
 static hipError_t launch_split(const AttnArgs &a, const AttnPlan &plan, dim3 grid, hipStream_t stream, AttnLaunchEvents *ev)
 {
-    return launch_timed(attn_split_kernel<D, W, kStages, BALANCED ? kItemsBalanced : kItemsSplit>, grid, dim3(64 * (W + 1)),
-                        plan.lds_bytes, a, stream, ev, 0);
+    constexpr int MODE = BALANCED ? kItemsBalanced : kItemsSplit;
+    return launch_timed(plan.kv_nt ? attn_split_kernel<D, W, kStages, MODE, 1> : attn_split_kernel<D, W, kStages, MODE, 0>, grid,
+                        dim3(64 * (W + 1)), plan.lds_bytes, a, stream, ev, 0);
 }
 
+template <int D, int W, int BALANCED, int WAVES>
+static auto combine_kernel(int num_splits)
+{
+    if constexpr (!BALANCED) {
+        if (num_splits > 16) return attn_combine_kernel<D, W, 0, 32, WAVES>;
+        if (num_splits > 8) return attn_combine_kernel<D, W, 0, 16, WAVES>;
+    }
+    return attn_combine_kernel<D, W, BALANCED, 8, WAVES>;
+}
+
+// One wave per workgroup while four would leave most CUs without any (36-layer graph, 4096 tokens, per call: 64 workgroups
+// of 64 rows, 15 / 26 pieces 12.8 -> 12.6 / 13.8 -> 13.1 us; from 128 on the larger number is what counts: 128 rows, 13 / 15
+// pieces 16.3 -> 16.5 / 16.0 -> 16.3; 256 of 64 rows, 8 pieces 19.7 -> 19.9).
 template <int D, int W, int BALANCED>
 static hipError_t launch_combine(const AttnArgs &a, hipStream_t stream, AttnLaunchEvents *ev)
 {
-    auto comb = attn_combine_kernel<D, W, BALANCED, 8>;
-    if constexpr (!BALANCED) {
-        if (a.num_splits > 16) comb = attn_combine_kernel<D, W, 0, 32>;
-        else if (a.num_splits > 8) comb = attn_combine_kernel<D, W, 0, 16>;
-    }
-    return launch_timed(comb, dim3((unsigned)(a.batch * a.num_kv_heads) * W * (D / 32)), dim3(256), 0, a, stream, ev, 1);
+    const unsigned wgs = (unsigned)(a.batch * a.num_kv_heads) * W * (D / 32);
+    if (wgs < 128) return launch_timed(combine_kernel<D, W, BALANCED, 1>(a.num_splits), dim3(wgs * 4), dim3(64), 0, a, stream, ev, 1);
+    return launch_timed(combine_kernel<D, W, BALANCED, 4>(a.num_splits), dim3(wgs), dim3(256), 0, a, stream, ev, 1);
 }
 
 // One attention call: the split kernel, then the merge when units were cut into pieces.
@@ -683,7 +720,8 @@ static hipError_t launch_probe_d(const AttnArgs &a, const AttnPlan &plan, hipStr
                                  hipEvent_t stop)
 {
     const bool bal = plan.bal_wgs > 0;
-    auto kern = bal ? attn_split_kernel<D, 1, kStages, kItemsBalanced, 1> : attn_split_kernel<D, 1, kStages, kItemsSplit, 1>;
+    auto kern = plan.kv_nt ? (bal ? attn_split_kernel<D, 1, kStages, kItemsBalanced, 1, 1> : attn_split_kernel<D, 1, kStages, kItemsSplit, 1, 1>)
+                           : (bal ? attn_split_kernel<D, 1, kStages, kItemsBalanced, 0, 1> : attn_split_kernel<D, 1, kStages, kItemsSplit, 0, 1>);
     dim3 grid(bal ? (unsigned)plan.bal_wgs : (unsigned)plan.num_splits * (unsigned)a.num_kv_heads * (unsigned)a.batch);
     const size_t lds = lds_need(D);
     if (start && stop) hipExtLaunchKernelGGL(kern, grid, dim3(128), lds, stream, start, stop, 0, a);
@@ -700,7 +738,8 @@ hipError_t launch_kv_stream_probe(const AttnArgs &a, const AttnPlan &plan, int h
     return hipErrorInvalidValue;
 }
 
-// The prefill form with a compute wave per query head of the group (see launch_prefill_attn).
+// The prefill form with a compute wave per query head of the group (see launch_prefill_attn).  Ordinary loads: every chunk
+// of a sequence reads the same cache rows again.
 template <int D>
 static hipError_t launch_prefill_split_d(AttnArgs a, hipStream_t stream)
 {
@@ -708,10 +747,10 @@ static hipError_t launch_prefill_split_d(AttnArgs a, hipStream_t stream)
     a.rows = 32 * a.group;
     a.num_splits = (a.max_new + 31) / 32;
     dim3 grid((unsigned)a.num_splits * (unsigned)a.num_kv_heads * (unsigned)a.batch);
-    auto kern = a.group == 1   ? attn_split_kernel<D, 1, kStages, kItemsPrefill>
-                : a.group == 2 ? attn_split_kernel<D, 2, kStages, kItemsPrefill>
-                : a.group == 3 ? attn_split_kernel<D, 3, kStages, kItemsPrefill>
-                               : attn_split_kernel<D, 4, kStages, kItemsPrefill>;
+    auto kern = a.group == 1   ? attn_split_kernel<D, 1, kStages, kItemsPrefill, 0>
+                : a.group == 2 ? attn_split_kernel<D, 2, kStages, kItemsPrefill, 0>
+                : a.group == 3 ? attn_split_kernel<D, 3, kStages, kItemsPrefill, 0>
+                               : attn_split_kernel<D, 4, kStages, kItemsPrefill, 0>;
     hipLaunchKernelGGL(kern, grid, dim3(64 * (a.group + 1)), lds_need(D), stream, a);
     return hipGetLastError();
 }

@@ -211,6 +211,33 @@ def test_loose_host_bound_on_the_lengths(splits):
         np.testing.assert_allclose(lse, want_lse, rtol=0, atol=2e-3)
 
 
+@pytest.mark.parametrize("batch, kv_heads, block_k, d, splits", [
+    (2, 2, 4, 64, 2),        # one-wave merge workgroups, up to 8 / 16 / 32 pieces and more than one round of them
+    (3, 2, 16, 128, 9),
+    (3, 1, 32, 128, 16),
+    (4, 2, 8, 128, 31),
+    (3, 2, 8, 64, 40),
+    (4, 8, 16, 128, 3),      # 256 four-wave workgroups, the same
+    (4, 8, 16, 128, 12),
+    (4, 4, 32, 128, 20),
+    (5, 8, 16, 128, 35),
+])
+def test_merge_drops_slots_without_a_piece(batch, kv_heads, block_k, d, splits):
+    """The merge reads a sequence's partial slots before it knows how many hold a piece.  Lengths far below the host bound
+    leave most slots unwritten; the workspace is filled with NaN patterns first."""
+    w = Workload(name="drop", seed=4100 + splits, batch=batch, num_q_heads=4 * kv_heads, num_kv_heads=kv_heads, head_dim=d,
+                 block_k=block_k, context=1400, page_size=16, paging="shuffled")
+    lens = np.array([1400, 0, 33, 290, 64][:batch], np.int32)
+    cache = make_cache(w, seq_lens=lens)
+    blk = make_block(w, w.seed + 1)
+    case = GpuCase(w, cache, num_splits=splits, max_seq_len=1400)
+    case.step.attn_ws.fill_(0xFF)
+    got, lse = case.attn(AR, blk)
+    want, want_lse = _oracle_attn(AR, w, blk, cache, want_lse=True)
+    _check_attn(got, want, "drop %d" % splits)
+    np.testing.assert_allclose(lse, want_lse, rtol=0, atol=2e-3)
+
+
 def test_kv_stream_probe_and_timing_samples():
     """The measurement helpers: the stream probe launches, reports no error and writes nothing; timing
     samples come back one per timed call, in launch order, with a combine time only when there was one."""
