@@ -23,6 +23,8 @@ HIPCC_FLAGS = [
     # packed fp32 VALU forms are disabled for every kernel in this library
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wno-unused-value",
+    # leading scalar arguments of a kernel arrive in scalar registers (as many as fit next to the argument pointer)
+    "-mllvm", "-amdgpu-kernarg-preload-count=14",
 ]
 
 # Per-source additions.  attn_wide: the matrix products of that kernel keep scores and accumulators in plain vector

@@ -70,8 +70,9 @@ namespace orthrus {
 // every jump into code that no wave of the launch has fetched yet is a round trip to the L2 or beyond, in the loader's
 // first tile and between the last tile and the write-out alike.
 template <int D, int W, int NS, int MODE, int NT, int PROBE = 0>
-__global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(const AttnArgs a)
+__global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(ATTN_FIRST_PARAMS, const AttnArgs rest)
 {
+    const AttnArgs a = ATTN_WITH_FIRST(rest);
     constexpr bool PREFILL = MODE == kItemsPrefill, BALANCED = MODE == kItemsBalanced;
     // With two compute waves on a SIMD the other wave fills a wave's waits, and what counts is instructions: the weights
     // are taken before anything is known of the maximum (row_weights).  One wave alone is a chain, in which that puts
@@ -408,8 +409,9 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(const AttnA
 // WAVES = waves per workgroup: 4, or 1 where the launch would have few workgroups.  A CU pulls in some 50 KB per
 // microsecond, and 64 workgroups of four waves want 100 KB each of 26 pieces (launch_combine).
 template <int D, int W, int BALANCED, int CHUNK, int WAVES>
-__global__ void __launch_bounds__(64 * WAVES) attn_combine_kernel(const AttnArgs a)
+__global__ void __launch_bounds__(64 * WAVES) attn_combine_kernel(ATTN_FIRST_PARAMS, const AttnArgs rest)
 {
+    const AttnArgs a = ATTN_WITH_FIRST(rest);
     static_assert(WAVES == 4 || WAVES == 1, "the four waves of a row and d block share a workgroup or have one each");
     constexpr int DBLK = D / 32;
     constexpr int MCHUNK = 32;  // m values fetched per round when there are more than CHUNK partials
@@ -607,7 +609,7 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
         const double kRate = 7.0e6;      // K/V bytes per microsecond (measured ceiling of the paged stream)
         const double kPartRate = 6.0e6;  // bytes per microsecond for the partials
         const double kTile = W <= 4 ? 0.56 : 1.3;  // more than four 32-row blocks: two per SIMD
-        const double kRound = 5.0, kCombine = 4.0, kSplit = 0.06, kWg = 0.008;
+        const double kRound = 5.0, kCombine = 4.0, kSplit = 0.06, kManySplits = 1.5, kWg = 0.008;
         const int64_t slots = (int64_t)num_cus * per_cu;
         const double tile_bytes = 32.0 * 2.0 * head_dim * 2.0;  // K + V bytes of one tile of one KV head
         const double part_bytes = 2.0 * plan->rows_padded * head_dim * 4.0;  // written once, read once
@@ -618,7 +620,8 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
         for (int s = 1; s <= max_s; ++s) {
             const int64_t wgs = units * s;
             const double tiles_per_wg = (double)((tiles + s - 1) / s);
-            double t = s > 1 ? kCombine + kSplit * s : 0.0;  // the merge reads one more partial per output and split
+            // the merge reads one more partial per output and split, and past 16 a form with room for 32 (launch_combine)
+            double t = s > 1 ? kCombine + kSplit * s + (s > 16 ? kManySplits : 0.0) : 0.0;
             for (int64_t left = wgs; left > 0; left -= slots) {
                 const int64_t now = left < slots ? left : slots;
                 const double per_tile = tile_bytes * now / kRate;  // all workgroups of the round share the stream
@@ -629,7 +632,7 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
             if (t < best) best = t;
         }
         splits = 1;
-        while (cost[splits] > best * 1.01) ++splits;  // the fewest splits within 1 % of the best estimate
+        while (cost[splits] > best * 1.005) ++splits;  // the fewest splits within half a per cent of the best estimate
     }
     int chunk = (max_seq_len + splits - 1) / splits;
     chunk = ((chunk + 31) / 32) * 32;
@@ -724,8 +727,8 @@ static hipError_t launch_probe_d(const AttnArgs &a, const AttnPlan &plan, hipStr
                            : (bal ? attn_split_kernel<D, 1, kStages, kItemsBalanced, 0, 1> : attn_split_kernel<D, 1, kStages, kItemsSplit, 0, 1>);
     dim3 grid(bal ? (unsigned)plan.bal_wgs : (unsigned)plan.num_splits * (unsigned)a.num_kv_heads * (unsigned)a.batch);
     const size_t lds = lds_need(D);
-    if (start && stop) hipExtLaunchKernelGGL(kern, grid, dim3(128), lds, stream, start, stop, 0, a);
-    else hipLaunchKernelGGL(kern, grid, dim3(128), lds, stream, a);
+    if (start && stop) hipExtLaunchKernelGGL(kern, grid, dim3(128), lds, stream, start, stop, 0, ATTN_FIRST_VALUES(a), a);
+    else hipLaunchKernelGGL(kern, grid, dim3(128), lds, stream, ATTN_FIRST_VALUES(a), a);
     return hipGetLastError();
 }
 
@@ -751,7 +754,7 @@ static hipError_t launch_prefill_split_d(AttnArgs a, hipStream_t stream)
                 : a.group == 2 ? attn_split_kernel<D, 2, kStages, kItemsPrefill, 0>
                 : a.group == 3 ? attn_split_kernel<D, 3, kStages, kItemsPrefill, 0>
                                : attn_split_kernel<D, 4, kStages, kItemsPrefill, 0>;
-    hipLaunchKernelGGL(kern, grid, dim3(64 * (a.group + 1)), lds_need(D), stream, a);
+    hipLaunchKernelGGL(kern, grid, dim3(64 * (a.group + 1)), lds_need(D), stream, ATTN_FIRST_VALUES(a), a);
     return hipGetLastError();
 }
 

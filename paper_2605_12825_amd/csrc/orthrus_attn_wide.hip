@@ -28,8 +28,9 @@ namespace orthrus {
 // D head_dim, W waves of 64 query rows, NS LDS stages, MODE the work items (kItemsSplit or kItemsPrefill), NT the
 // non-temporal form of the tile loads.
 template <int D, int W, int NS, int MODE, int NT = 0>
-__global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(const AttnArgs a)
+__global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(ATTN_FIRST_PARAMS, const AttnArgs rest)
 {
+    const AttnArgs a = ATTN_WITH_FIRST(rest);
     using Gm = AttnGeom<D>;
     constexpr int CH = Gm::CH, ROWB = Gm::ROWB, RPI = Gm::RPI, NI = Gm::NI, GS = Gm::GS;
     constexpr int TILE_B = Gm::TILE_B, STAGE_B = Gm::STAGE_B, KSTEPS = Gm::KSTEPS, DBLK = Gm::DBLK;
@@ -498,7 +499,7 @@ static hipError_t launch_prefill_wide(AttnArgs a, hipStream_t stream)
     a.rows = 64 * W;
     a.num_splits = (a.max_new + a.chunk_tokens - 1) / a.chunk_tokens;
     dim3 grid((unsigned)a.num_splits * (unsigned)a.num_kv_heads * (unsigned)a.batch);
-    hipLaunchKernelGGL((attn_wide_kernel<D, W, wide_stages(W), kItemsPrefill>), grid, dim3(64 * W), attn_wide_lds(W, D), stream, a);
+    hipLaunchKernelGGL((attn_wide_kernel<D, W, wide_stages(W), kItemsPrefill>), grid, dim3(64 * W), attn_wide_lds(W, D), stream, ATTN_FIRST_VALUES(a), a);
     return hipGetLastError();
 }
 
