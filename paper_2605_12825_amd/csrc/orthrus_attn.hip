@@ -361,15 +361,7 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(ATTN_FIRST_
                 const int i = irow, hl = ridx - i * G;
                 const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
                 uint16_t *op = a.out + ((row_base + i) * a.num_q_heads + (int64_t)it.g * G + hl) * D;
-#pragma unroll
-                for (int db = 0; db < DBLK; ++db)
-#pragma unroll
-                    for (int r4 = 0; r4 < 4; ++r4) {
-                        uint2 pk;
-                        pk.x = pack_bf16(o[db][4 * r4] * inv, o[db][4 * r4 + 1] * inv);
-                        pk.y = pack_bf16(o[db][4 * r4 + 2] * inv, o[db][4 * r4 + 3] * inv);
-                        *(uint2 *)(op + 32 * db + 8 * r4 + 4 * h) = pk;
-                    }
+                store_row<DBLK>(op, o, inv, h);
                 if (a.lse && h == 0)
                     a.lse[((int64_t)it.b * a.num_q_heads + (int64_t)it.g * G + hl) * K + i] =
                         (m_run + __builtin_amdgcn_logf(l_run)) * 0.6931471805599453f;

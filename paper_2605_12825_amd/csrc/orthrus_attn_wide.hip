@@ -419,15 +419,7 @@ __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(ATTN_FIRST_PARAMS,
         const int hl = wave * 64 + x * 32 + col - irow[x] * G;
         const float inv = lt > 0.f ? 1.f / lt : 0.f;
         uint16_t *op = a.out + ((row_base + irow[x]) * a.num_q_heads + (int64_t)w.g * G + hl) * D;
-#pragma unroll
-        for (int db = 0; db < DBLK; ++db)
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                uint2 pk;
-                pk.x = pack_bf16(o[x][db][4 * r4] * inv, o[x][db][4 * r4 + 1] * inv);
-                pk.y = pack_bf16(o[x][db][4 * r4 + 2] * inv, o[x][db][4 * r4 + 3] * inv);
-                *(uint2 *)(op + 32 * db + 8 * r4 + 4 * h) = pk;
-            }
+        store_row<DBLK>(op, o[x], inv, h);
         if (!PREFILL && a.lse && h == 0)
             a.lse[((int64_t)w.b * a.num_q_heads + (int64_t)w.g * G + hl) * K + irow[x]] =
                 (m[x] + __builtin_amdgcn_logf(lt)) * 0.6931471805599453f;
