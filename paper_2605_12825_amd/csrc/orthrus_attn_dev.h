@@ -313,6 +313,47 @@ __device__ __forceinline__ void issue_rows(NT nt, const uint16_t *const (&k)[2],
 // which keeps them off the vector-memory counter that paces the tile loads.
 enum { kItemsSplit = 0, kItemsPrefill = 1, kItemsBalanced = 2 };
 
+// Prefill of a few sequences: the order in which a launch's chunks start.  A chunk costs as many tiles as it has tokens
+// before its end, and the launch ends with the last one started, so the longest come first, over all sequences (every
+// sequence's last chunk first, whatever the others' lengths, left a sixth of the CUs' time empty behind them: 6 sequences of
+// 0..6001 cached and 333..1500 new tokens, 28/4 heads).  With E = end / T in whole chunks a sequence's chunks lie on the
+// levels E, E-1, .. E-n+1, one on each; rank r is found by counting the chunks above a level: a lane to a level, 64 levels
+// a round, a few instructions a sequence and round.  Hence the limit: 16 sequences take about half a microsecond of an
+// item's 10 to 100; many sequences fill in behind each other in any order.
+constexpr int kRankedBatch = 16;
+
+// The chunk of rank r (from 0, longest first): sequence and chunk index, false past the last.  Every lane calls it with the
+// same arguments except its own sequence's end level and chunk count (lane < batch).
+__device__ __forceinline__ bool ranked_chunk(int r, int batch, int end_level, int chunks, int *seq, int *chunk)
+{
+    const int lane = threadIdx.x & 63;
+    int top = lane < batch ? end_level : 0;
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) top = max(top, __shfl_xor(top, off));
+    int lo = -1, hi = __builtin_amdgcn_readfirstlane(top), above = 0;  // more than r chunks lie above lo, `above` <= r above hi
+    while (hi - lo > 1) {
+        const int step = (hi - lo + 63) >> 6;
+        const int level = min(lo + (lane + 1) * step, hi);
+        int count = 0;
+        for (int b = 0; b < batch; ++b) {
+            const int e = __builtin_amdgcn_readlane(end_level, b), n = __builtin_amdgcn_readlane(chunks, b);
+            count += min(max(e - level, 0), n);
+        }
+        const int f = __builtin_ctzll(__ballot(count <= r));  // (the last lanes stand at hi)
+        above = __builtin_amdgcn_readlane(count, f);
+        hi = min(lo + (f + 1) * step, hi);
+        lo += f * step;
+    }
+    const int down = end_level - hi;  // how far this sequence's end lies above the level
+    uint64_t mask = __ballot(lane < batch && down >= 0 && down < chunks);
+    for (int k = r - above; k > 0 && mask; --k) mask &= mask - 1;
+    if (!mask) return false;
+    const int b = __builtin_ctzll(mask);
+    *seq = b;
+    *chunk = __builtin_amdgcn_readlane(chunks - 1 - down, b);
+    return true;
+}
+
 template <int MODE>
 struct WorkItems {
     int b, g;
@@ -427,10 +468,18 @@ struct WorkItems {
             // own subset of the HBM channels and the XCDs finish far apart.  (Prefill: the middle index
             // is the chunk, longest first.)
             b = (int)(blockIdx.x % (unsigned)a.batch);
-            int split;
+            int split, chunk = 0;
             if constexpr (MODE == kItemsPrefill) {
                 g = (int)((blockIdx.x / (unsigned)a.batch) % (unsigned)a.num_kv_heads);
                 split = (int)(blockIdx.x / ((unsigned)a.batch * (unsigned)a.num_kv_heads));
+                if (a.batch > 1 && a.batch <= kRankedBatch) {
+                    g = (int)(blockIdx.x % (unsigned)a.num_kv_heads);
+                    const int lane = threadIdx.x & 63, x = min(lane, a.batch - 1);
+                    const int n_new = a.new_lens[x], end = a.old_lens[x] + n_new;
+                    if (!ranked_chunk((int)(blockIdx.x / (unsigned)a.num_kv_heads), a.batch, end / a.chunk_tokens,
+                                      (n_new + a.chunk_tokens - 1) / a.chunk_tokens, &b, &chunk))
+                        return false;
+                }
             } else {
                 split = (int)((blockIdx.x / (unsigned)a.batch) % (unsigned)a.num_splits);
                 g = (int)(blockIdx.x / ((unsigned)a.batch * (unsigned)a.num_splits));
@@ -439,9 +488,11 @@ struct WorkItems {
                 // lengths as the append kernel left them: validated, 0 new tokens on a capacity error
                 const int L0 = __builtin_amdgcn_readfirstlane(((const const_i32 *)a.old_lens)[b]);
                 const int n_new = __builtin_amdgcn_readfirstlane(((const const_i32 *)a.new_lens)[b]);
-                // every sequence's last chunk (the one with the most cache tokens) starts first
-                const int chunk = (n_new + a.chunk_tokens - 1) / a.chunk_tokens - 1 - split;
-                if (chunk < 0) return false;
+                if (a.batch == 1 || a.batch > kRankedBatch) {
+                    // every sequence's last chunk (the one with the most cache tokens) starts first
+                    chunk = (n_new + a.chunk_tokens - 1) / a.chunk_tokens - 1 - split;
+                    if (chunk < 0) return false;
+                }
                 // this launch reads the recorded lengths only, so the sequence's first chunk may bump the live one
                 if (chunk == 0 && g == 0 && threadIdx.x == 0) a.seq_lens_out[b] = L0 + n_new;
                 row0 = chunk * a.chunk_tokens;

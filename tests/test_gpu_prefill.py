@@ -182,3 +182,32 @@ def test_prefill_at_the_8b_layer_shape_sampled_rows():
                                       np.array([n - lo], np.int32), rk, rv, pt, rl)
         err = np.abs(got[0, lo:n] - want[0])
         assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, "prefix %d" % n
+
+
+@pytest.mark.parametrize("batch, heads, kv_heads, d, T", [
+    (2, 7, 1, 128, 150),      # chunks in ranked order: two sequences, the most, one more than that (not ranked)
+    (16, 8, 2, 64, 90),
+    (16, 14, 2, 128, 75),
+    (17, 8, 2, 64, 90),
+    (5, 2, 2, 128, 140),      # the 32-row form's chunks
+])
+def test_prefill_ragged_lengths_in_any_order(batch, heads, kv_heads, d, T):
+    """Cached lengths and new-token counts that rise and fall independently, none and all among them."""
+    rng = np.random.default_rng(3000 + batch * heads)
+    w = Workload(name="pr%d" % batch, seed=3100 + batch, batch=batch, num_q_heads=heads, num_kv_heads=kv_heads, head_dim=d,
+                 block_k=8, context=700, steps=(T + 7) // 8 + 1, page_size=16, paging="shuffled")
+    lens = rng.integers(0, 701, batch).astype(np.int32)
+    lens[0], lens[-1] = 700, 0
+    cache = make_cache(w, seq_lens=lens)
+    new_lens = rng.integers(0, T + 1, batch).astype(np.int32)
+    new_lens[-1], new_lens[batch // 2] = T, 0
+    q, kn, vn = _new_tokens(w, T, 3200)
+    ref_k, ref_v, ref_l = cache["k_pool"].copy(), cache["v_pool"].copy(), cache["seq_lens"].copy()
+    want, _ = oracle.prefill_attn(w.sm_scale, q, kn, vn, new_lens, ref_k, ref_v, cache["page_table"], ref_l)
+    case = Case(w, cache, max_seq_len=700 + T)
+    _check(case.prefill(q, kn, vn, new_lens), want, new_lens)
+    k, v, l = case.state()
+    np.testing.assert_array_equal(l, ref_l)
+    np.testing.assert_array_equal(k, ref_k)
+    np.testing.assert_array_equal(v, ref_v)
+    assert case.step.device_error() == 0
