@@ -72,7 +72,7 @@ namespace orthrus {
 template <int D, int W, int NS, int MODE, int NT, int PROBE = 0>
 __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(ATTN_FIRST_PARAMS, const AttnArgs rest)
 {
-    const AttnArgs a = ATTN_WITH_FIRST(rest);
+    const AttnArgs a = with_first(rest, first_lens, first_batch);
     constexpr bool PREFILL = MODE == kItemsPrefill, BALANCED = MODE == kItemsBalanced;
     // With two compute waves on a SIMD the other wave fills a wave's waits, and what counts is instructions: the weights
     // are taken before anything is known of the maximum (row_weights).  One wave alone is a chain, in which that puts
@@ -403,7 +403,7 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(ATTN_FIRST_
 template <int D, int W, int BALANCED, int CHUNK, int WAVES>
 __global__ void __launch_bounds__(64 * WAVES) attn_combine_kernel(ATTN_FIRST_PARAMS, const AttnArgs rest)
 {
-    const AttnArgs a = ATTN_WITH_FIRST(rest);
+    const AttnArgs a = with_first(rest, first_lens, first_batch);
     static_assert(WAVES == 4 || WAVES == 1, "the four waves of a row and d block share a workgroup or have one each");
     constexpr int DBLK = D / 32;
     constexpr int MCHUNK = 32;  // m values fetched per round when there are more than CHUNK partials

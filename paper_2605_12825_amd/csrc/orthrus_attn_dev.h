@@ -165,29 +165,18 @@ struct AttnGeom {
 };
 
 
-// The arguments that a kernel's first dependent loads hang on (lengths, then page ids, then tiles) stand once more in front
-// of the struct, as plain values: the dispatch puts those into scalar registers before a wave starts (the build's
-// kernarg-preload option), and the chain begins a memory round trip earlier.
-#define ATTN_FIRST_PARAMS                                                                                              \
-    const int32_t *first_lens, const int32_t *first_table, int first_batch, int first_splits, int first_heads,         \
-        int first_bound, int first_pages, int first_shift
-#define ATTN_FIRST_VALUES(a)                                                                                           \
-    (a).seq_lens, (a).page_table, (a).batch, (a).num_splits, (a).num_kv_heads, (a).max_seq_len, (a).max_pages_per_seq, \
-        (a).page_shift
+// What the first dependent load (the length, then page ids, then tiles) hangs on stands once more in front of the struct, as
+// plain values: the dispatch puts those into scalar registers before a wave starts (the build's kernarg-preload option), so
+// that load goes out next to the struct's and not behind it.  No more than that: each argument costs the host some 20 ns a
+// launch (eight of them made a small call of two launches 8.7 -> 9.1 us).
+#define ATTN_FIRST_PARAMS const int32_t *first_lens, int first_batch
+#define ATTN_FIRST_VALUES(a) (a).seq_lens, (a).batch
 __device__ __forceinline__ AttnArgs with_first(AttnArgs a, ATTN_FIRST_PARAMS)
 {
     a.seq_lens = first_lens;
-    a.page_table = first_table;
     a.batch = first_batch;
-    a.num_splits = first_splits;
-    a.num_kv_heads = first_heads;
-    a.max_seq_len = first_bound;
-    a.max_pages_per_seq = first_pages;
-    a.page_shift = first_shift;
     return a;
 }
-#define ATTN_WITH_FIRST(rest) \
-    with_first(rest, first_lens, first_table, first_batch, first_splits, first_heads, first_bound, first_pages, first_shift)
 
 // A pointer that is uniform by construction; readfirstlane keeps the compiler from carrying it in vector registers.
 __device__ __forceinline__ const void *uniform_ptr(const void *p)

@@ -20,7 +20,8 @@
 // registers: 188 instructions a 64x32 tile where an address calculation and a wait at each use made it 225.  Measured
 // before and after: one item to a CU (100 new tokens behind 16000, 7 heads a KV head) 351 -> 291 us a call; 8192 new tokens
 // (32/8 heads) 478 -> 456, where the kernel's cycles fall by 12 % and the clock by 6 (1.97 -> 1.85 GHz); ragged prefill at
-// 28/4 heads 325 -> 300; training mask 623 -> 598.  (attn_split_kernel's form: 675, 400 and 864.)
+// 28/4 heads 325 -> 300; training mask 623 -> 598.  (attn_split_kernel's form: 675, 400 and 864.  With the chunks ranked
+// over all sequences the ragged prefill takes 250 to 272, with 16-byte stores the mask 600.)
 #include "orthrus_attn_dev.h"
 
 namespace orthrus {
@@ -30,7 +31,7 @@ namespace orthrus {
 template <int D, int W, int NS, int MODE, int NT = 0>
 __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(ATTN_FIRST_PARAMS, const AttnArgs rest)
 {
-    const AttnArgs a = ATTN_WITH_FIRST(rest);
+    const AttnArgs a = with_first(rest, first_lens, first_batch);
     using Gm = AttnGeom<D>;
     constexpr int CH = Gm::CH, ROWB = Gm::ROWB, RPI = Gm::RPI, NI = Gm::NI, GS = Gm::GS;
     constexpr int TILE_B = Gm::TILE_B, STAGE_B = Gm::STAGE_B, KSTEPS = Gm::KSTEPS, DBLK = Gm::DBLK;
