@@ -185,10 +185,6 @@ __device__ __forceinline__ const void *uniform_ptr(const void *p)
                           (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)((uint64_t)p >> 32)) << 32);
 }
 
-// A scalar register that a vector instruction (a lane read) has written may be read by a vector-memory instruction five
-// wait states later; the compiler keeps that distance for its own instructions, not for the assembly statements below.
-__device__ __forceinline__ void lane_read_settles() { asm volatile("s_nop 4"); }
-
 // Direct global->LDS load of 64 x 16 bytes: lane's bytes land at lds_addr + lane*16.  Issued through inline assembly so
 // that whole tiles can stay in flight while older ones are computed; completion is awaited explicitly with s_waitcnt
 // vmcnt (loads return in order).  M0 carries the LDS destination and is declared clobbered, so the compiler never
@@ -224,6 +220,10 @@ __device__ __forceinline__ void dma16s(NT, const uint16_t *base, uint32_t voff, 
 // loads into groups GS bytes apart.  The instruction offset e*GS moves the LDS side and the memory side of load e
 // alike, so one M0 value serves the half and the lane offsets take e*GS back (the base is lowered by kBias so that
 // they stay positive).  One load costs the issuing wave two instructions instead of the ~11 of 64-bit arithmetic per load.
+//
+// A vector-memory instruction may read a scalar register five wait states after a vector instruction (the lane read that
+// a base comes from) has written it.  The compiler keeps that distance for its own instructions, not into an assembly
+// statement, so the statement brings it along: the write of M0 is one, s_nop 3 the other four.
 template <int D>
 struct HalfLoads {
     using Gm = AttnGeom<D>;
@@ -260,21 +260,21 @@ struct HalfLoads {
         base = (const char *)uniform_ptr(base);
         static_assert(Gm::GS == 1040 && (GPH == 4 || GPH == 2), "the instruction offsets below");
         if constexpr (GPH == 4 && NT::value)
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\t"
                          "global_load_lds_dwordx4 %2, %1 nt\n\tglobal_load_lds_dwordx4 %3, %1 offset:1040 nt\n\t"
                          "global_load_lds_dwordx4 %4, %1 offset:2080 nt\n\tglobal_load_lds_dwordx4 %5, %1 offset:3120 nt"
                          : : "s"(lds_addr), "s"(base), "v"(voff[0]), "v"(voff[1]), "v"(voff[GPH - 2]), "v"(voff[GPH - 1]) : "memory", "m0");
         else if constexpr (GPH == 4)
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\t"
                          "global_load_lds_dwordx4 %2, %1\n\tglobal_load_lds_dwordx4 %3, %1 offset:1040\n\t"
                          "global_load_lds_dwordx4 %4, %1 offset:2080\n\tglobal_load_lds_dwordx4 %5, %1 offset:3120"
                          : : "s"(lds_addr), "s"(base), "v"(voff[0]), "v"(voff[1]), "v"(voff[GPH - 2]), "v"(voff[GPH - 1]) : "memory", "m0");
         else if constexpr (NT::value)
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\t"
                          "global_load_lds_dwordx4 %2, %1 nt\n\tglobal_load_lds_dwordx4 %3, %1 offset:1040 nt"
                          : : "s"(lds_addr), "s"(base), "v"(voff[0]), "v"(voff[1]) : "memory", "m0");
         else
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\t"
                          "global_load_lds_dwordx4 %2, %1\n\tglobal_load_lds_dwordx4 %3, %1 offset:1040"
                          : : "s"(lds_addr), "s"(base), "v"(voff[0]), "v"(voff[1]) : "memory", "m0");
     }

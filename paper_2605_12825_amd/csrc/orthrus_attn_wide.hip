@@ -150,12 +150,8 @@ __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(ATTN_FIRST_PARAMS,
         open_window(0);
 #pragma unroll
         for (int t = 0; t < NS - 1; ++t) {
-            const char *base[PG];
 #pragma unroll
-            for (int u = 0; u < PG; ++u) base[u] = half_base(u, t);
-            lane_read_settles();
-#pragma unroll
-            for (int u = 0; u < PG; ++u) half.issue(NtTag{}, base[u], dst + u * half.GPH * GS);
+            for (int u = 0; u < PG; ++u) half.issue(NtTag{}, half_base(u, t), dst + u * half.GPH * GS);
             advance();
         }
     } else {

@@ -1,0 +1,159 @@
+"""Wait states around the direct-to-LDS loads, counted in the code that is shipped.
+
+The loads are written in inline assembly, where the compiler does not keep the distances that the hardware asks of
+software: a vector-memory instruction may read a scalar register five wait states after a vector instruction (a lane read,
+a compare) has written it, and a direct-to-LDS load may follow the write of M0 by one.  An instruction is a wait state,
+s_nop N is N + 1.  The library's own gfx950 code is disassembled and every path into such an instruction is followed
+backwards over as many wait states, across branches.
+"""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+import paper_2605_12825_amd as orthrus
+from paper_2605_12825_amd import build
+
+LANE_TO_MEMORY, M0_TO_LDS_LOAD = 5, 1
+_VMEM = ("global_", "buffer_", "flat_", "scratch_")
+_LINE = re.compile(r"^\t(\S+)(?:\s+(.*?))?\s*// ([0-9A-Fa-f]+):(.*)$")
+_TARGET = re.compile(r"<[^>]*?(?:\+0x([0-9a-f]+))?>\s*$")
+
+
+def _tool():
+    return os.path.join(os.path.dirname(os.path.dirname(build.hipcc_path())), "llvm", "bin", "llvm-objdump")
+
+
+def _sgprs(operand):
+    """Numbers of the scalar registers in an operand, M0 and VCC by name."""
+    operand = operand.strip()
+    if operand in ("m0", "vcc"):
+        return {operand}
+    hit = re.fullmatch(r"s\[(\d+):(\d+)\]", operand)
+    if hit:
+        return set(range(int(hit.group(1)), int(hit.group(2)) + 1))
+    hit = re.fullmatch(r"s(\d+)", operand)
+    return {int(hit.group(1))} if hit else set()
+
+
+def _vector_writes(op, args):
+    """Scalar registers that a vector instruction writes: the result of a lane read or compare, or a carry."""
+    if not op.startswith("v_") or not args:
+        return set()
+    out = _sgprs(args[0])
+    if len(args) > 1 and re.match(r"v_(add_co|sub_co|subrev_co|addc_co|subb_co|subbrev_co|div_scale|mad_u64_u32|mad_i64_i32)", op):
+        out |= _sgprs(args[1])
+    return out
+
+
+def _functions(listing):
+    """[(name, [(op, args, index of the branch's target or None)])]"""
+    out, name, body, start = [], None, [], 0
+
+    def close():
+        if name is None:
+            return
+        at = {addr: i for i, (_, _, addr, _) in enumerate(body)}
+        out.append((name, [(op, args, at.get(start + t) if t is not None else None) for op, args, _, t in body]))
+
+    for line in listing.splitlines():
+        head = re.match(r"^(?:[0-9a-f]+ )?<(.+)>:$", line)
+        if head:
+            close()
+            name, body, start = head.group(1), [], None
+            continue
+        hit = _LINE.match(line)
+        if not hit:
+            continue
+        op, rest, addr = hit.group(1), hit.group(2) or "", int(hit.group(3), 16)
+        start = addr if start is None else start
+        target = None
+        if op.startswith("s_branch") or op.startswith("s_cbranch"):
+            t = _TARGET.search(hit.group(4))
+            assert t, "no branch target in: " + line
+            target = int(t.group(1), 16) if t.group(1) else 0
+        args = re.split(r",\s*", rest) if rest else []
+        if args:   # modifiers follow the last operand
+            args[-1] = args[-1].split(" ")[0]
+        body.append((op, args, addr, target))
+    close()
+    return out
+
+
+def close_reads(listing):
+    """([(function, index, text)] of the reads that come too soon, number of reads looked at)"""
+    bad, seen = [], 0
+    for name, code in _functions(listing):
+        into = {}   # index -> indices of the instructions that may run before it
+        for i, (op, _, target) in enumerate(code):
+            if target is not None:
+                into.setdefault(target, []).append(i)
+            if not op.startswith(("s_branch", "s_endpgm", "s_setpc")) and i + 1 < len(code):
+                into.setdefault(i + 1, []).append(i)
+        for i, (op, args, _) in enumerate(code):
+            if not op.startswith(_VMEM):
+                continue
+            wanted = [(r, LANE_TO_MEMORY, _vector_writes) for x in args for r in _sgprs(x)]
+            if "_lds_" in op:
+                wanted.append(("m0", M0_TO_LDS_LOAD, lambda o, a: _sgprs(a[0]) if o.startswith("s_") and a else set()))
+            for reg, need, writes in wanted:
+                seen += 1
+                todo, done = [(j, 0) for j in into.get(i, [])], {}
+                while todo:
+                    j, states = todo.pop()
+                    if states >= need or done.get(j, need) <= states:
+                        continue
+                    done[j] = states
+                    o, a, _ = code[j]
+                    if reg in writes(o, a):
+                        bad.append((name, i, "%s %s: %s written %d wait states before, %d needed"
+                                    % (op, ", ".join(args), reg, states, need)))
+                        break
+                    if a and o.startswith("s_") and reg in _sgprs(a[0]) and not o.startswith(("s_cmp", "s_bitcmp")):
+                        continue   # a scalar instruction has written it since
+                    states += int(a[0], 0) + 1 if o == "s_nop" else 1
+                    todo += [(k, states) for k in into.get(j, [])]
+    return bad, seen
+
+
+def _listings(library, folder):
+    """The disassembly of every gfx950 code object inside `library`."""
+    lib = shutil.copy(library, os.path.join(folder, "lib.so"))
+    subprocess.run([_tool(), "--offloading", "lib.so"], cwd=folder, check=True, stdout=subprocess.DEVNULL)
+    objects = sorted(f for f in os.listdir(folder) if f.endswith("gfx950"))
+    assert os.path.exists(lib) and objects
+    return [subprocess.run([_tool(), "-d", f], cwd=folder, check=True, stdout=subprocess.PIPE, text=True).stdout for f in objects]
+
+
+def test_scan_finds_a_planted_distance():
+    """Two wait states between a lane read and the load, five, and two behind a branch back."""
+    text = """
+<f>:
+\tv_readlane_b32 s3, v1, s4                                  // 000000000000: 00000000
+\ts_mov_b32 m0, s9                                           // 000000000008: 00000000
+\ts_nop %d                                                    // 00000000000C: 00000000
+\tglobal_load_lds_dwordx4 v2, s[2:3] offset:1040 nt          // 000000000010: 00000000
+\tv_readfirstlane_b32 s2, v5                                 // 000000000018: 00000000
+\ts_branch 65530                                             // 00000000001C: 00000000 <f+0x%x>
+\ts_endpgm                                                   // 000000000020: 00000000
+"""
+    assert len(close_reads(text % (0, 8))[0]) == 2
+    assert len(close_reads(text % (1, 8))[0]) == 2
+    assert len(close_reads(text % (3, 8))[0]) == 0
+    assert len(close_reads(text % (3, 0xc))[0]) == 0
+    assert len(close_reads(text % (3, 0x10))[0]) == 2      # straight to the load: the lane read and no nop behind M0
+    assert len(close_reads(text.replace("s_nop %d", "s_mov_b32 s8, 0").replace("s_mov_b32 m0, s9", "v_readlane_b32 s2, v1, s4")
+                           % 8)[0]) >= 2
+
+
+@pytest.mark.skipif(not os.path.exists(_tool()), reason="no llvm-objdump next to the compiler")
+def test_loads_keep_their_distance_from_lane_reads(tmp_path):
+    total = 0
+    for listing in _listings(orthrus.library_path(), str(tmp_path)):
+        bad, seen = close_reads(listing)
+        bad = [x for x in bad if "attn_wide_kernel" in x[0]]
+        total += seen
+        assert not bad, "%d reads too soon, the first ones:\n%s" % (len(bad), "\n".join("%s[%d] %s" % x for x in bad[:8]))
+    assert total > 1000   # the direct-to-LDS loads alone are more
