@@ -143,9 +143,9 @@ def test_scan_finds_a_planted_distance():
     assert len(close_reads(text % (1, 8))[0]) == 2
     assert len(close_reads(text % (3, 8))[0]) == 0
     assert len(close_reads(text % (3, 0xc))[0]) == 0
-    assert len(close_reads(text % (3, 0x10))[0]) == 2      # straight to the load: the lane read and no nop behind M0
-    assert len(close_reads(text.replace("s_nop %d", "s_mov_b32 s8, 0").replace("s_mov_b32 m0, s9", "v_readlane_b32 s2, v1, s4")
-                           % 8)[0]) >= 2
+    assert len(close_reads(text % (3, 0x10))[0]) == 1      # straight to the load
+    assert len(close_reads(text.replace("s_nop %d", "v_mov_b32 v9, 0") % 8)[0]) == 2
+    assert len(close_reads(text.replace("s_mov_b32 m0, s9", "s_nop 3").replace("s_nop %d", "s_mov_b32 m0, s9") % 8)[0]) == 1
 
 
 @pytest.mark.skipif(not os.path.exists(_tool()), reason="no llvm-objdump next to the compiler")
