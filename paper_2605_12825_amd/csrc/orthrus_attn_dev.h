@@ -204,15 +204,18 @@ __device__ __forceinline__ void dma16(NT, const uint16_t *gp, uint32_t lds_addr)
         asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(gp), "s"(lds_addr) : "memory", "m0");
 }
 
-// The same with a wave-uniform base and a 32-bit byte offset per lane.
+// The same with a wave-uniform base and a 32-bit byte offset per lane.  A vector-memory instruction may read a scalar
+// register five wait states after a vector instruction has written it (a lane read, from which a base comes whenever the
+// compiler holds it in vector registers).  The compiler keeps that distance for its own instructions, not into an assembly
+// statement, so the statement brings it along: the write of M0 is one, s_nop 3 the other four.
 template <class NT>
 __device__ __forceinline__ void dma16s(NT, const uint16_t *base, uint32_t voff, uint32_t lds_addr)
 {
     base = (const uint16_t *)uniform_ptr(base);
     if constexpr (NT::value)
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" : : "v"(voff), "s"(base), "s"(lds_addr) : "memory", "m0");
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1 nt" : : "v"(voff), "s"(base), "s"(lds_addr) : "memory", "m0");
     else
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(base), "s"(lds_addr) : "memory", "m0");
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(base), "s"(lds_addr) : "memory", "m0");
 }
 
 // The loads of whole 16-token halves of a K or V tile (a half lies inside one page): a wave-uniform base (page, head,
@@ -220,10 +223,7 @@ __device__ __forceinline__ void dma16s(NT, const uint16_t *base, uint32_t voff, 
 // loads into groups GS bytes apart.  The instruction offset e*GS moves the LDS side and the memory side of load e
 // alike, so one M0 value serves the half and the lane offsets take e*GS back (the base is lowered by kBias so that
 // they stay positive).  One load costs the issuing wave two instructions instead of the ~11 of 64-bit arithmetic per load.
-//
-// A vector-memory instruction may read a scalar register five wait states after a vector instruction (the lane read that
-// a base comes from) has written it.  The compiler keeps that distance for its own instructions, not into an assembly
-// statement, so the statement brings it along: the write of M0 is one, s_nop 3 the other four.
+// The wait inside the statements is that of dma16s.
 template <int D>
 struct HalfLoads {
     using Gm = AttnGeom<D>;
