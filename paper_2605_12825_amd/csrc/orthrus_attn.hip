@@ -597,11 +597,13 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
         // both about that long: what binds when few CUs are busy, e.g. batch 1), and the tiles of all
         // workgroups of a round together stream no faster than kRate.  Every workgroup costs kWg to
         // dispatch; every piece beyond a unit's first is an fp32 partial (rows x d x 4 bytes) written
-        // once and read once, and brings the merge launch with it.
+        // once and read once, and brings the merge launch with it.  The constants are part of the interface: programs
+        // keep the workspace that the split count asks for, and each piece rounds its weights against its own
+        // reference, so that another count gives other bits.
         const double kRate = 7.0e6;      // K/V bytes per microsecond (measured ceiling of the paged stream)
         const double kPartRate = 6.0e6;  // bytes per microsecond for the partials
         const double kTile = W <= 4 ? 0.56 : 1.3;  // more than four 32-row blocks: two per SIMD
-        const double kRound = 5.0, kCombine = 4.0, kSplit = 0.06, kManySplits = 1.5, kWg = 0.008;
+        const double kRound = 5.0, kCombine = 4.0, kSplit = 0.12, kWg = 0.008;
         const int64_t slots = (int64_t)num_cus * per_cu;
         const double tile_bytes = 32.0 * 2.0 * head_dim * 2.0;  // K + V bytes of one tile of one KV head
         const double part_bytes = 2.0 * plan->rows_padded * head_dim * 4.0;  // written once, read once
@@ -612,8 +614,7 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
         for (int s = 1; s <= max_s; ++s) {
             const int64_t wgs = units * s;
             const double tiles_per_wg = (double)((tiles + s - 1) / s);
-            // the merge reads one more partial per output and split, and past 16 a form with room for 32 (launch_combine)
-            double t = s > 1 ? kCombine + kSplit * s + (s > 16 ? kManySplits : 0.0) : 0.0;
+            double t = s > 1 ? kCombine + kSplit * s : 0.0;  // the merge reads one more partial per output and split
             for (int64_t left = wgs; left > 0; left -= slots) {
                 const int64_t now = left < slots ? left : slots;
                 const double per_tile = tile_bytes * now / kRate;  // all workgroups of the round share the stream
@@ -624,7 +625,7 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
             if (t < best) best = t;
         }
         splits = 1;
-        while (cost[splits] > best * 1.005) ++splits;  // the fewest splits within half a per cent of the best estimate
+        while (cost[splits] > best * 1.01) ++splits;  // the fewest splits within 1 % of the best estimate
     }
     int chunk = (max_seq_len + splits - 1) / splits;
     chunk = ((chunk + 31) / 32) * 32;

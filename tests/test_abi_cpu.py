@@ -123,6 +123,20 @@ def test_consensus_workspaces_do_not_grow(batch, K, vocab, greedy, sampling):
     assert orthrus.orthrus_sampling_workspace_bytes(p) == sampling
 
 
+@pytest.mark.parametrize("batch,q_heads,kv_heads,d,K,max_seq_len,splits,workspace", [
+    (1, 32, 8, 128, 16, 4112, 13, 3461120), (1, 32, 8, 128, 16, 8000, 21, 5591040), (1, 32, 8, 128, 1, 2000, 11, 1464320),
+    (1, 32, 8, 128, 32, 40000, 30, 15974400), (4, 32, 8, 128, 16, 32768, 8, 8519680), (4, 32, 8, 128, 8, 1000, 4, 2129920),
+    (1, 28, 4, 128, 8, 12000, 27, 3594240), (1, 8, 8, 128, 4, 6000, 19, 2529280), (1, 4, 2, 64, 16, 400, 1, 0),
+    (4, 4, 2, 64, 16, 32768, 47, 3176448), (8, 16, 2, 64, 32, 2000, 9, 9732096), (64, 32, 8, 128, 16, 3071, 1, 0),
+])
+def test_attention_split_plan_stays(batch, q_heads, kv_heads, d, K, max_seq_len, splits, workspace):
+    """Programs keep these buffers too, and another split count gives other bits."""
+    pages = (max_seq_len + 15) // 16
+    p = orthrus.make_params(batch=batch, num_q_heads=q_heads, num_kv_heads=kv_heads, head_dim=d, block_k=K, page_size=16,
+                            max_pages_per_seq=pages, max_seq_len=max_seq_len, num_pages=batch * pages)
+    assert (orthrus.orthrus_attn_num_splits(p), orthrus.orthrus_attn_workspace_bytes(p)) == (splits, workspace)
+
+
 def test_prefill_workspace_and_argument_checks_on_the_host():
     p = _good()
     assert orthrus.orthrus_prefill_workspace_bytes(p, 4096) >= 2 * 4 * p.batch
