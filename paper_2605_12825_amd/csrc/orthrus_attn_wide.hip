@@ -82,11 +82,16 @@ __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(ATTN_FIRST_PARAMS,
     auto open_window = [&](int t) __attribute__((always_inline)) {
         win = t;
         const uint32_t tok = (uint32_t)(w.t_begin + min(t + lane, n_whole - 1) * 32 + my_half * 16);
+        uint32_t id[PG];
+#pragma unroll
+        for (int u = 0; u < PG; ++u) id[u] = (uint32_t)((const int32_t *)w.pt_row)[(tok + u * 16u) >> a.page_shift];
+        // one wait for all of them: the compiler's wait for an id counts its own loads only, so that one behind a tile
+        // load would wait for the tile as well
+        if constexpr (PG == 2) asm volatile("" : "+v"(id[0]), "+v"(id[PG - 1]));
 #pragma unroll
         for (int u = 0; u < PG; ++u) {
-            const uint32_t id = (uint32_t)((const int32_t *)w.pt_row)[(tok + u * 16u) >> a.page_shift];
-            worst = max(worst, id);
-            const uint64_t at = (uint64_t)(uintptr_t)my_pool + (uint64_t)(id < half.num_pages ? id : 0u) * half.page_bytes +
+            worst = max(worst, id[u]);
+            const uint64_t at = (uint64_t)(uintptr_t)my_pool + (uint64_t)(id[u] < half.num_pages ? id[u] : 0u) * half.page_bytes +
                                 ((tok + u * 16u) & half.page_mask) * half.tok_bytes;
             at_lo[u] = (uint32_t)at;
             at_hi[u] = (uint32_t)(at >> 32);

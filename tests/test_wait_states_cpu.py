@@ -156,3 +156,25 @@ def test_loads_keep_their_distance_from_lane_reads(tmp_path):
         total += seen
         assert not bad, "%d reads too soon, the first ones:\n%s" % (len(bad), "\n".join("%s[%d] %s" % x for x in bad[:8]))
     assert total > 1000   # the direct-to-LDS loads alone are more
+
+
+@pytest.mark.skipif(not os.path.exists(_tool()), reason="no llvm-objdump next to the compiler")
+def test_page_ids_of_the_64_row_kernel_arrive_together(tmp_path):
+    """Its waves fetch the page ids of many tiles with one or two vector loads and go on to tile loads.  A wait for an id
+    behind a tile load would wait for the tile too, and two waits in a row are two round trips."""
+    seen = 0
+    for listing in _listings(orthrus.library_path(), str(tmp_path)):
+        for name, code in _functions(listing):
+            if "attn_wide_kernel" not in name:
+                continue
+            ids = [i for i, (op, _, _) in enumerate(code) if op == "global_load_dword"]
+            while ids:
+                first = ids[0]
+                waits = [i for i in range(first, len(code)) if code[i][0] == "s_waitcnt" and "vmcnt(0)" in code[i][1][0]]
+                tile = next(i for i in range(first, len(code)) if "load_lds" in code[i][0])
+                group = [i for i in ids if i < waits[0]]
+                assert waits[0] < tile and not any(i < tile for i in ids[len(group):]), name
+                assert all(not (tile < x < tile + 16) for x in waits), name
+                ids = ids[len(group):]
+                seen += 1
+    assert seen >= 2 * 11   # the fill and the loop of each instance
