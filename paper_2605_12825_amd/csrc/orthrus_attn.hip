@@ -407,12 +407,12 @@ __global__ void __launch_bounds__(64 * WAVES) attn_combine_kernel(ATTN_FIRST_PAR
     static_assert(WAVES == 4 || WAVES == 1, "the four waves of a row and d block share a workgroup or have one each");
     constexpr int DBLK = D / 32;
     constexpr int MCHUNK = 32;  // m values fetched per round when there are more than CHUNK partials
-    const int lane = threadIdx.x & 63, r4 = WAVES == 4 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : blockIdx.x & 3;
+    const int lane = threadIdx.x & 63, r4 = WAVES == 4 ? threadIdx.x >> 6 : blockIdx.x & 3;
     const int col = lane & 31, h = lane >> 5;
-    const int block = WAVES == 4 ? blockIdx.x : blockIdx.x >> 2;
-    const int db = block % DBLK;
-    const int wave = (block / DBLK) % W;  // row block
-    const int unit = block / (DBLK * W);
+    const unsigned block = WAVES == 4 ? blockIdx.x : blockIdx.x >> 2;
+    const int db = (int)(block % DBLK);
+    const int wave = (int)(block / DBLK % W);  // row block
+    const int unit = (int)(block / (DBLK * W));
     const int b = unit / a.num_kv_heads, g = unit % a.num_kv_heads;
     const int ridx = wave * 32 + col;
     int live;           // number of partials of this unit
@@ -452,7 +452,7 @@ __global__ void __launch_bounds__(64 * WAVES) attn_combine_kernel(ATTN_FIRST_PAR
         rest_slot = (size_t)w_lo * 2;
         slot_step = 2;
     } else {
-        live = a.num_splits;  // until the length is there
+        live = a.num_splits;  // the slots, until the length is there
         first_slot = rest_slot = (size_t)unit * a.num_splits;
         slot_step = 1;
     }
@@ -468,18 +468,40 @@ __global__ void __launch_bounds__(64 * WAVES) attn_combine_kernel(ATTN_FIRST_PAR
 
     // The loads of the first CHUNK partials go out before anything waits; the reference maximum needs
     // every partial's m, so the remaining m values follow MCHUNK at a time, then the rest of the data.
-    // A merge of up to CHUNK partials is one memory round trip, not one per pass.  Past the last piece the loads repeat it
-    // (a condition on each would be a jump each) and what they bring is dropped.  Fixed splits: nor do the first loads wait
-    // for the sequence's length, which says how many of the num_splits slots hold a piece.  With a wave per workgroup, 36-layer
-    // graph, 64 rows, per call: 8 / 15 / 26 pieces of 4096 tokens 15.3 -> 15.0 / 13.2 -> 12.5 / 13.7 -> 12.7 us.
+    // A merge of up to CHUNK partials is one memory round trip, not one per pass.
+    //
+    // Few units (one wave per workgroup): what counts is the chain.  With fixed splits the first loads do not wait for the
+    // sequence's length, which says how many of the num_splits slots hold a piece; what the others bring is dropped.  They go
+    // out in pairs, a jump to a pair.  The balanced partition cuts few units into many pieces: whole chunks without a jump,
+    // the last one repeats its last piece and drops the copies.
+    // Many units (four waves): what counts is the loads, so those of live pieces only, a jump to a load.
+    // Per call, this form for every launch -> all CHUNK loads at once for every launch -> as it is: 16 sequences of 50..300
+    // tokens under a bound of 8000 (2 splits) 11.7 -> 13.5 -> 12.4 us; 2 of 300 under 32768, 128 rows (15) 10.9 -> 11.3 ->
+    // 10.8; one of 2000, 128 rows (9) 12.2 -> 12.5 -> 12.1; balanced, 64 of 500..4000 133 -> 143 -> 138 (133 with the
+    // partials' plain stores); one wave: 36-layer graph, 64 rows, 4112 tokens (13), a cycle 965 -> 941 -> 940; one of 4096, 224
+    // rows (22) 15.3 -> 15.6 -> 15.4; balanced, 3 of 100..4000 (d = 64, some 40 pieces) 26 -> 23.4 -> 23.3, in pairs 25.
+    constexpr bool EARLY = WAVES == 1 && !BALANCED;
+    constexpr int RUN = WAVES == 4 ? 1 : BALANCED ? CHUNK : 2;
+    static_assert(CHUNK % RUN == 0, "");
     float4 v[CHUNK];
     float2 e[CHUNK];
     auto load_chunk = [&](int s0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < CHUNK; ++u) {
-            const int s = min(s0 + u, live - 1);
-            v[u] = *po_at(s);
-            e[u] = *ml_at(s);
+        for (int u0 = 0; u0 < CHUNK; u0 += RUN) {
+            if (s0 + u0 < live) {
+#pragma unroll
+                for (int u = u0; u < u0 + RUN; ++u) {
+                    const int s = RUN == 1 ? s0 + u : min(s0 + u, live - 1);
+                    v[u] = *po_at(s);
+                    e[u] = *ml_at(s);
+                }
+            } else {
+#pragma unroll
+                for (int u = u0; u < u0 + RUN; ++u) {
+                    v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    e[u] = make_float2(kNegBig, 0.f);
+                }
+            }
         }
     };
     auto drop_past_end = [&](int s0) __attribute__((always_inline)) {
@@ -491,14 +513,17 @@ __global__ void __launch_bounds__(64 * WAVES) attn_combine_kernel(ATTN_FIRST_PAR
             }
         }
     };
-    load_chunk(0);
-    if constexpr (!BALANCED) {
+    if constexpr (EARLY) {
+        load_chunk(0);
         __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (!BALANCED) {
         int L = ((const const_i32 *)a.seq_lens)[b];
         L = L < 0 ? 0 : (L > a.max_seq_len ? a.max_seq_len : L);
         live = split_cut(L, a.num_splits, 0).live;  // the split kernel's pieces of this sequence
     }
-    drop_past_end(0);
+    if constexpr (!EARLY) load_chunk(0);
+    if constexpr (RUN > 1) drop_past_end(0);
     float M = kNegBig;
 #pragma unroll
     for (int u = 0; u < CHUNK; ++u) M = fmaxf(M, e[u].x);
@@ -514,7 +539,7 @@ __global__ void __launch_bounds__(64 * WAVES) attn_combine_kernel(ATTN_FIRST_PAR
     for (int s0 = 0; s0 < live; s0 += CHUNK) {
         if (s0 > 0) {
             load_chunk(s0);
-            drop_past_end(s0);
+            if constexpr (RUN > 1) drop_past_end(s0);
         }
 #pragma unroll
         for (int u = 0; u < CHUNK; ++u) {  // fixed split order: the result does not depend on timing

@@ -6,24 +6,13 @@ a compare) has written it, and a direct-to-LDS load may follow the write of M0 b
 s_nop N is N + 1.  The library's own gfx950 code is disassembled and every path into such an instruction is followed
 backwards over as many wait states, across branches.
 """
-import os
 import re
-import shutil
-import subprocess
-
-import pytest
 
 import paper_2605_12825_amd as orthrus
-from paper_2605_12825_amd import build
+from built_code import functions, listings, needs_tool
 
 LANE_TO_MEMORY, M0_TO_LDS_LOAD = 5, 1
 _VMEM = ("global_", "buffer_", "flat_", "scratch_")
-_LINE = re.compile(r"^\t(\S+)(?:\s+(.*?))?\s*// ([0-9A-Fa-f]+):(.*)$")
-_TARGET = re.compile(r"<[^>]*?(?:\+0x([0-9a-f]+))?>\s*$")
-
-
-def _tool():
-    return os.path.join(os.path.dirname(os.path.dirname(build.hipcc_path())), "llvm", "bin", "llvm-objdump")
 
 
 def _sgprs(operand):
@@ -48,44 +37,10 @@ def _vector_writes(op, args):
     return out
 
 
-def _functions(listing):
-    """[(name, [(op, args, index of the branch's target or None)])]"""
-    out, name, body, start = [], None, [], 0
-
-    def close():
-        if name is None:
-            return
-        at = {addr: i for i, (_, _, addr, _) in enumerate(body)}
-        out.append((name, [(op, args, at.get(start + t) if t is not None else None) for op, args, _, t in body]))
-
-    for line in listing.splitlines():
-        head = re.match(r"^(?:[0-9a-f]+ )?<(.+)>:$", line)
-        if head:
-            close()
-            name, body, start = head.group(1), [], None
-            continue
-        hit = _LINE.match(line)
-        if not hit:
-            continue
-        op, rest, addr = hit.group(1), hit.group(2) or "", int(hit.group(3), 16)
-        start = addr if start is None else start
-        target = None
-        if op.startswith("s_branch") or op.startswith("s_cbranch"):
-            t = _TARGET.search(hit.group(4))
-            assert t, "no branch target in: " + line
-            target = int(t.group(1), 16) if t.group(1) else 0
-        args = re.split(r",\s*", rest) if rest else []
-        if args:   # modifiers follow the last operand
-            args[-1] = args[-1].split(" ")[0]
-        body.append((op, args, addr, target))
-    close()
-    return out
-
-
 def close_reads(listing):
     """([(function, index, text)] of the reads that come too soon, number of reads looked at)"""
     bad, seen = [], 0
-    for name, code in _functions(listing):
+    for name, code in functions(listing):
         into = {}   # index -> indices of the instructions that may run before it
         for i, (op, _, target) in enumerate(code):
             if target is not None:
@@ -118,15 +73,6 @@ def close_reads(listing):
     return bad, seen
 
 
-def _listings(library, folder):
-    """The disassembly of every gfx950 code object inside `library`."""
-    lib = shutil.copy(library, os.path.join(folder, "lib.so"))
-    subprocess.run([_tool(), "--offloading", "lib.so"], cwd=folder, check=True, stdout=subprocess.DEVNULL)
-    objects = sorted(f for f in os.listdir(folder) if f.endswith("gfx950"))
-    assert os.path.exists(lib) and objects
-    return [subprocess.run([_tool(), "-d", f], cwd=folder, check=True, stdout=subprocess.PIPE, text=True).stdout for f in objects]
-
-
 def test_scan_finds_a_planted_distance():
     """Two wait states between a lane read and the load, five, and two behind a branch back."""
     text = """
@@ -148,23 +94,23 @@ def test_scan_finds_a_planted_distance():
     assert len(close_reads(text.replace("s_mov_b32 m0, s9", "s_nop 3").replace("s_nop %d", "s_mov_b32 m0, s9") % 8)[0]) == 1
 
 
-@pytest.mark.skipif(not os.path.exists(_tool()), reason="no llvm-objdump next to the compiler")
+@needs_tool
 def test_loads_keep_their_distance_from_lane_reads(tmp_path):
     total = 0
-    for listing in _listings(orthrus.library_path(), str(tmp_path)):
+    for listing in listings(orthrus.library_path(), str(tmp_path)):
         bad, seen = close_reads(listing)
         total += seen
         assert not bad, "%d reads too soon, the first ones:\n%s" % (len(bad), "\n".join("%s[%d] %s" % x for x in bad[:8]))
     assert total > 1000   # the direct-to-LDS loads alone are more
 
 
-@pytest.mark.skipif(not os.path.exists(_tool()), reason="no llvm-objdump next to the compiler")
+@needs_tool
 def test_page_ids_of_the_64_row_kernel_arrive_together(tmp_path):
     """Its waves fetch the page ids of many tiles with one or two vector loads and go on to tile loads.  A wait for an id
     behind a tile load would wait for the tile too, and two waits in a row are two round trips."""
     seen = 0
-    for listing in _listings(orthrus.library_path(), str(tmp_path)):
-        for name, code in _functions(listing):
+    for listing in listings(orthrus.library_path(), str(tmp_path)):
+        for name, code in functions(listing):
             if "attn_wide_kernel" not in name:
                 continue
             ids = [i for i, (op, _, _) in enumerate(code) if op == "global_load_dword"]
