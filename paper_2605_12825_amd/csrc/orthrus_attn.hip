@@ -33,7 +33,7 @@
 //            both are described at the kernel.
 //   caches = K/V tiles are read once per call.  When the model streams more K/V between two passes
 //            over the same cache than the last-level cache holds, the tile loads carry the
-//            non-temporal hint and the fp32 partials leave with non-temporal stores.
+//            non-temporal hint, and with fixed splits the fp32 partials leave with non-temporal stores.
 #include "orthrus_attn_dev.h"
 
 namespace orthrus {
@@ -69,6 +69,10 @@ namespace orthrus {
 // NT: the non-temporal forms of the tile loads and of the partials' stores.  A form of the kernel and not a test in it:
 // every jump into code that no wave of the launch has fetched yet is a round trip to the L2 or beyond, in the loader's
 // first tile and between the last tile and the write-out alike.
+// The stores' hint is for fixed splits only: there the write-back of the partials at the kernel's end is what the merge waits
+// for (cycles over 12 layers of 4096 tokens at batch 4 / 8 496 -> 479 / 731 -> 711 us, 36 layers at batch 1 942 -> 940; a
+// small call under a loose bound 12.1 -> 12.5).  The balanced partition writes partials all along and reads them out of the
+// L2 again (64 sequences of 500..4000 tokens 133 -> 138 us with the hint).
 template <int D, int W, int NS, int MODE, int NT, int PROBE = 0>
 __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(ATTN_FIRST_PARAMS, const AttnArgs rest)
 {
@@ -375,7 +379,7 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(ATTN_FIRST_
 #pragma unroll
                 for (int r4 = 0; r4 < 4; ++r4) {
                     const f32x4 v = {o[db][4 * r4], o[db][4 * r4 + 1], o[db][4 * r4 + 2], o[db][4 * r4 + 3]};
-                    if constexpr (NT != 0) __builtin_nontemporal_store(v, &po[(db * 4 + r4) * 64]);
+                    if constexpr (NT != 0 && !BALANCED) __builtin_nontemporal_store(v, &po[(db * 4 + r4) * 64]);
                     else po[(db * 4 + r4) * 64] = v;
                 }
             if (h == 0) ((float2 *)a.part_ml)[slot * 32 + col] = make_float2(m_run, l_run);

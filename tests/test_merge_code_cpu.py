@@ -28,3 +28,20 @@ def test_merge_of_many_units_loads_live_pieces_only(tmp_path):
                 assert all(gaps) == (waves == 4), (d, w, balanced, chunk, waves)
             seen += 1
     assert seen == 2 * 8 * 4 * 2
+
+
+@needs_tool
+def test_partials_hint_with_fixed_splits_only(tmp_path):
+    """The compiler folds a hinted and a plain store of the same value in two branches into a plain one, so the hint is a
+    form of the kernel: 16 bytes of every accumulator block in the fixed-split form, none in the others."""
+    seen = 0
+    for text in listings(orthrus.library_path(), str(tmp_path)):
+        for block in re.split(r"\n(?=[0-9a-f]* ?<_Z)", text):
+            head = re.search(r"attn_split_kernelI((?:Li\d+E)+)E", block.split("\n")[0])
+            if not head:
+                continue
+            d, _, _, mode, nt, probe = (int(x) for x in re.findall(r"Li(\d+)E", head.group(1)))
+            hinted = len(re.findall(r"\tglobal_store_dwordx4 [^\n]* nt\b", block))
+            assert hinted == (d // 8 if (mode, nt, probe) == (0, 1, 0) else 0), head.group(0)
+            seen += 1
+    assert seen == 2 * (2 * 8 * 2 + 4 + 4)
