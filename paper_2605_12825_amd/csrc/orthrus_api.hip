@@ -167,7 +167,7 @@ orthrus::AttnArgs decode_attn_args(const orthrus_ctx *ctx, const orthrus_params 
     a.group = p->num_q_heads / p->num_kv_heads; a.block_k = p->block_k; a.rows = plan.rows;
     a.page_shift = log2_exact(p->page_size); a.max_pages_per_seq = p->max_pages_per_seq;
     a.max_seq_len = p->max_seq_len; a.chunk_tokens = plan.chunk_tokens; a.num_splits = plan.num_splits;
-    a.bal_wgs = plan.bal_wgs;
+    a.bal_wgs = plan.bal_wgs; a.ranked = 0;
     a.view = view;
     a.scale_log2e = p->sm_scale * 1.4426950408889634f;
     return a;
@@ -408,7 +408,7 @@ orthrus_status orthrus_prefill_attn(orthrus_ctx *ctx, const orthrus_params *p, i
     a.group = group; a.block_k = 32; a.rows = 32 * group;
     a.page_shift = f.page_shift; a.max_pages_per_seq = p->max_pages_per_seq;
     a.max_seq_len = p->max_seq_len; a.chunk_tokens = 0; a.num_splits = 0;  // the launcher picks the chunks
-    a.bal_wgs = 0;
+    a.bal_wgs = 0; a.ranked = 0;
     a.view = (int)ORTHRUS_VIEW_AR_VERIFY;
     a.scale_log2e = p->sm_scale * 1.4426950408889634f;
     e = orthrus::launch_prefill_attn(a, p->head_dim, plan_cus(ctx), (hipStream_t)stream);

@@ -578,6 +578,14 @@ static size_t lds_need(int head_dim)
     return (size_t)kStages * (head_dim == 128 ? AttnGeom<128>::STAGE_B : AttnGeom<64>::STAGE_B);
 }
 
+// Workgroups of W compute waves that are resident on a CU: LDS ring size, and 12 waves (3 per SIMD: the kernel stays
+// below 168 registers) of W compute waves + the loader wave each
+static int resident_per_cu(int head_dim, int W)
+{
+    const int by_lds = (int)(160 * 1024 / lds_need(head_dim)), by_waves = 12 / (W + 1);
+    return by_lds < by_waves ? by_lds : by_waves > 0 ? by_waves : 1;
+}
+
 hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv_heads, int max_seq_len,
                      int requested_splits, int num_cus, int num_layers, double pool_tokens, AttnPlan *plan)
 {
@@ -590,12 +598,7 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
     plan->waves = W;
     plan->rows_padded = blocks * 32;
     plan->lds_bytes = plan->wide ? attn_wide_lds(W, head_dim) : lds_need(head_dim);
-    // workgroups resident per CU: LDS ring size, and 12 waves (3 per SIMD: the kernel stays below 168
-    // registers) of W compute waves + the loader wave each
-    int per_cu = (int)(160 * 1024 / plan->lds_bytes);
-    const int by_waves = plan->wide ? 4 / W : 12 / (W + 1);
-    if (per_cu > by_waves) per_cu = by_waves;
-    if (per_cu < 1) per_cu = 1;
+    const int per_cu = plan->wide ? attn_wide_per_cu(W) : resident_per_cu(head_dim, W);  // resident workgroups
     plan->bal_wgs = 0;
     // K/V bytes the model streams at most between two passes over the same layer's cache (the other
     // layers' caches come in between), against the 256 MB last-level cache (see the kernel's loads).  Sequences
@@ -766,12 +769,13 @@ hipError_t launch_kv_stream_probe(const AttnArgs &a, const AttnPlan &plan, int h
 // The prefill form with a compute wave per query head of the group (see launch_prefill_attn).  Ordinary loads: every chunk
 // of a sequence reads the same cache rows again.
 template <int D>
-static hipError_t launch_prefill_split_d(AttnArgs a, hipStream_t stream)
+static hipError_t launch_prefill_split_d(AttnArgs a, int num_cus, hipStream_t stream)
 {
     a.chunk_tokens = 32;
     a.rows = 32 * a.group;
     a.num_splits = (a.max_new + 31) / 32;
     dim3 grid((unsigned)a.num_splits * (unsigned)a.num_kv_heads * (unsigned)a.batch);
+    a.ranked = prefill_ranked(a.batch, grid.x, resident_per_cu(D, a.group), num_cus);
     auto kern = a.group == 1   ? attn_split_kernel<D, 1, kStages, kItemsPrefill, 0>
                 : a.group == 2 ? attn_split_kernel<D, 2, kStages, kItemsPrefill, 0>
                 : a.group == 3 ? attn_split_kernel<D, 3, kStages, kItemsPrefill, 0>
@@ -780,11 +784,11 @@ static hipError_t launch_prefill_split_d(AttnArgs a, hipStream_t stream)
     return hipGetLastError();
 }
 
-hipError_t launch_prefill_split(const AttnArgs &a, int head_dim, hipStream_t stream)
+hipError_t launch_prefill_split(const AttnArgs &a, int head_dim, int num_cus, hipStream_t stream)
 {
     if (a.group > 4) return hipErrorInvalidValue;
-    if (head_dim == 128) return launch_prefill_split_d<128>(a, stream);
-    if (head_dim == 64) return launch_prefill_split_d<64>(a, stream);
+    if (head_dim == 128) return launch_prefill_split_d<128>(a, num_cus, stream);
+    if (head_dim == 64) return launch_prefill_split_d<64>(a, num_cus, stream);
     return hipErrorInvalidValue;
 }
 

@@ -305,41 +305,60 @@ enum { kItemsSplit = 0, kItemsPrefill = 1, kItemsBalanced = 2 };
 // Prefill of a few sequences: the order in which a launch's chunks start.  A chunk costs as many tiles as it has tokens
 // before its end, and the launch ends with the last one started, so the longest come first, over all sequences (every
 // sequence's last chunk first, whatever the others' lengths, left a sixth of the CUs' time empty behind them: 6 sequences of
-// 0..6001 cached and 333..1500 new tokens, 28/4 heads).  With E = end / T in whole chunks a sequence's chunks lie on the
-// levels E, E-1, .. E-n+1, one on each; rank r is found by counting the chunks above a level: a lane to a level, 64 levels
-// a round, a few instructions a sequence and round.  Hence the limit: 16 sequences take about half a microsecond of an
-// item's 10 to 100; many sequences fill in behind each other in any order.
+// 0..6001 cached and 333..1500 new tokens, 28/4 heads, 315 -> 272 us; 16 of 0..4000 and 64..512, 32/8 heads 338 -> 177).
+// With E = end / T in whole chunks a sequence's chunks lie on the levels E, E-1, .. E-n+1, one on each; rank r is found by
+// counting the chunks above a level, a lane to a sequence and one of four levels a round (a row of 16 lanes each), so that
+// a round cuts the range to a quarter and the counts are sums over a row.  (A lane to a level instead, with a loop over the
+// sequences, was fewer rounds and three times the instructions: 16 sequences of 1000 cached and 450..512 new tokens, 32/8
+// heads, 2.4 % for the search alone where this one costs 0.2 %.)
+// (A row holds 16 sequences, hence the limit.  Larger batches would gain as well: with a limit of 64, 24 / 32 / 48 sequences
+// of 0..4000 tokens at 28/4 heads 269 -> 187 / 477 -> 258 / 276 -> 205 us, 24 of equal lengths 106 -> 114.)
 constexpr int kRankedBatch = 16;
 
-// The chunk of rank r (from 0, longest first): sequence and chunk index, false past the last.  Every lane calls it with the
-// same arguments except its own sequence's end level and chunk count (lane < batch).
-__device__ __forceinline__ bool ranked_chunk(int r, int batch, int end_level, int chunks, int *seq, int *chunk)
-{
-    const int lane = threadIdx.x & 63;
-    int top = lane < batch ? end_level : 0;
-#pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) top = max(top, __shfl_xor(top, off));
-    int lo = -1, hi = __builtin_amdgcn_readfirstlane(top), above = 0;  // more than r chunks lie above lo, `above` <= r above hi
-    while (hi - lo > 1) {
-        const int step = (hi - lo + 63) >> 6;
-        const int level = min(lo + (lane + 1) * step, hi);
-        int count = 0;
-        for (int b = 0; b < batch; ++b) {
-            const int e = __builtin_amdgcn_readlane(end_level, b), n = __builtin_amdgcn_readlane(chunks, b);
-            count += min(max(e - level, 0), n);
-        }
-        const int f = __builtin_ctzll(__ballot(count <= r));  // (the last lanes stand at hi)
-        above = __builtin_amdgcn_readlane(count, f);
-        hi = min(lo + (f + 1) * step, hi);
-        lo += f * step;
+// A wave's lanes as the search sees them; the host has its own, for tests of the order.
+struct WaveLanes {
+    using Int = int;
+    static __device__ __forceinline__ int lane() { return threadIdx.x & 63; }
+    static __device__ __forceinline__ int lesser(int a, int b) { return min(a, b); }
+    static __device__ __forceinline__ int larger(int a, int b) { return max(a, b); }
+    template <class F>
+    static __device__ __forceinline__ int over_row(int x, F f)  // every lane gets the value of its row of 16
+    {
+        x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x128, 0xf, 0xf, false));  // row_ror:8, 4, 2, 1
+        x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x124, 0xf, 0xf, false));
+        x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x122, 0xf, 0xf, false));
+        return f(x, __builtin_amdgcn_update_dpp(0, x, 0x121, 0xf, 0xf, false));
     }
-    const int down = end_level - hi;  // how far this sequence's end lies above the level
-    uint64_t mask = __ballot(lane < batch && down >= 0 && down < chunks);
+    static __device__ __forceinline__ int row_sum(int x) { return over_row(x, [](int a, int b) { return a + b; }); }
+    static __device__ __forceinline__ int row_max(int x) { return over_row(x, [](int a, int b) { return max(a, b); }); }
+    static __device__ __forceinline__ uint64_t less(int a, int b) { return __ballot(a < b); }
+    static __device__ __forceinline__ int read(int x, int lane) { return __builtin_amdgcn_readlane(x, lane); }
+};
+
+// The chunk of rank r (from 0, longest first): sequence and chunk index, false past the last.  Lane x of a row holds the
+// end level and the chunk count of sequence x, both 0 for one without chunks and past the batch.
+template <class Wave>
+__host__ __device__ __forceinline__ bool ranked_chunk(int r, typename Wave::Int end_level, typename Wave::Int chunks, int *seq, int *chunk)
+{
+    using Int = typename Wave::Int;
+    const Int row = Wave::lane() >> 4;
+    int lo = -1, hi = Wave::read(Wave::row_max(end_level), 0), above = 0;  // more than r chunks lie above lo, `above` <= r above hi
+    while (hi - lo > 1) {
+        const int step = (hi - lo + 3) >> 2;
+        const Int level = Wave::lesser((row + 1) * step + lo, hi);  // (the last row stands at hi)
+        const Int count = Wave::row_sum(Wave::lesser(Wave::larger(end_level - level, 0), chunks));
+        const int f = __builtin_ctzll(Wave::less(count, r + 1));
+        if (f > 0) lo = Wave::read(level, f - 1);
+        hi = Wave::read(level, f);
+        above = Wave::read(count, f);
+    }
+    const Int down = end_level - hi;  // how far this sequence's end lies above the level
+    uint64_t mask = Wave::less(down, chunks) & ~Wave::less(down, 0) & 0xffff;
     for (int k = r - above; k > 0 && mask; --k) mask &= mask - 1;
     if (!mask) return false;
     const int b = __builtin_ctzll(mask);
     *seq = b;
-    *chunk = __builtin_amdgcn_readlane(chunks - 1 - down, b);
+    *chunk = Wave::read(chunks - 1 - down, b);
     return true;
 }
 
@@ -451,34 +470,41 @@ struct WorkItems {
             bal_b = __builtin_amdgcn_readfirstlane(nb);
             bal_g = __builtin_amdgcn_readfirstlane(ng);
         } else {
-            // Workgroup id -> (sequence, split, KV head) with the sequence index fastest and the head
-            // slowest.  Consecutive workgroup ids go to different XCDs; a head's rows sit at a fixed
-            // offset inside every page, so an order that ties XCD k to head k makes each XCD hammer its
-            // own subset of the HBM channels and the XCDs finish far apart.  (Prefill: the middle index
-            // is the chunk, longest first.)
+            // Workgroup id -> work item.  Consecutive workgroup ids go to different XCDs.
+            // Decode: the sequence index is fastest and the KV head slowest.  A head's rows sit at a fixed offset
+            // inside every page, so an order that ties XCD k to head k makes each XCD hammer its own subset of the
+            // HBM channels and the XCDs finish far apart.
+            // Prefill: the sequence is fastest, then the head, then the chunk, every sequence's last (the one with the
+            // most cache tokens) first.  Ranked prefill: the head is fastest, then the chunk's rank; a chunk's heads
+            // are alike in length.
             b = (int)(blockIdx.x % (unsigned)a.batch);
-            int split, chunk = 0;
-            if constexpr (MODE == kItemsPrefill) {
-                g = (int)((blockIdx.x / (unsigned)a.batch) % (unsigned)a.num_kv_heads);
-                split = (int)(blockIdx.x / ((unsigned)a.batch * (unsigned)a.num_kv_heads));
-                if (a.batch > 1 && a.batch <= kRankedBatch) {
-                    g = (int)(blockIdx.x % (unsigned)a.num_kv_heads);
-                    const int lane = threadIdx.x & 63, x = min(lane, a.batch - 1);
-                    const int n_new = a.new_lens[x], end = a.old_lens[x] + n_new;
-                    if (!ranked_chunk((int)(blockIdx.x / (unsigned)a.num_kv_heads), a.batch, end / a.chunk_tokens,
-                                      (n_new + a.chunk_tokens - 1) / a.chunk_tokens, &b, &chunk))
-                        return false;
-                }
-            } else {
-                split = (int)((blockIdx.x / (unsigned)a.batch) % (unsigned)a.num_splits);
-                g = (int)(blockIdx.x / ((unsigned)a.batch * (unsigned)a.num_splits));
-            }
+            int split;
             if constexpr (MODE == kItemsPrefill) {
                 // lengths as the append kernel left them: validated, 0 new tokens on a capacity error
-                const int L0 = __builtin_amdgcn_readfirstlane(((const const_i32 *)a.old_lens)[b]);
-                const int n_new = __builtin_amdgcn_readfirstlane(((const const_i32 *)a.new_lens)[b]);
-                if (a.batch == 1 || a.batch > kRankedBatch) {
-                    // every sequence's last chunk (the one with the most cache tokens) starts first
+                g = (int)((blockIdx.x / (unsigned)a.batch) % (unsigned)a.num_kv_heads);
+                int L0, n_new, chunk = -1;
+                bool alike = true;
+                if (a.ranked) {
+                    const int x = threadIdx.x & 15, y = min(x, a.batch - 1);
+                    const int lane_old = a.old_lens[y], lane_new = a.new_lens[y];
+                    L0 = __builtin_amdgcn_readfirstlane(lane_old);
+                    n_new = __builtin_amdgcn_readfirstlane(lane_new);
+                    alike = !__any(lane_old != L0 || lane_new != n_new);  // all of one length: the plain order is the ranked one
+                    if (!alike) {
+                        g = (int)(blockIdx.x % (unsigned)a.num_kv_heads);
+                        const int chunks = x < a.batch ? (lane_new + a.chunk_tokens - 1) / a.chunk_tokens : 0;
+                        const int end_level = chunks > 0 ? (lane_old + lane_new) / a.chunk_tokens : 0;
+                        if (!ranked_chunk<WaveLanes>((int)(blockIdx.x / (unsigned)a.num_kv_heads), end_level, chunks, &b, &chunk))
+                            return false;
+                        L0 = __builtin_amdgcn_readlane(lane_old, b);
+                        n_new = __builtin_amdgcn_readlane(lane_new, b);
+                    }
+                } else {
+                    L0 = __builtin_amdgcn_readfirstlane(((const const_i32 *)a.old_lens)[b]);
+                    n_new = __builtin_amdgcn_readfirstlane(((const const_i32 *)a.new_lens)[b]);
+                }
+                if (alike) {
+                    split = (int)(blockIdx.x / ((unsigned)a.batch * (unsigned)a.num_kv_heads));
                     chunk = (n_new + a.chunk_tokens - 1) / a.chunk_tokens - 1 - split;
                     if (chunk < 0) return false;
                 }
@@ -493,6 +519,8 @@ struct WorkItems {
                 n_tiles = n_cache;
                 final_out = true;
             } else {
+                split = (int)((blockIdx.x / (unsigned)a.batch) % (unsigned)a.num_splits);
+                g = (int)(blockIdx.x / ((unsigned)a.batch * (unsigned)a.num_splits));
                 const int L = seq_len(a, b);
                 // The sequence's own length, not the host's bound on it, is cut into num_splits pieces:
                 // they stay equal however loose the bound is (it only sized the grid), e.g. when a

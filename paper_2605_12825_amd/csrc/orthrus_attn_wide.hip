@@ -435,6 +435,8 @@ __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(ATTN_FIRST_PARAMS,
 // LDS ring stages: four waves have the CU's LDS to themselves, two workgroups of two waves share it
 constexpr int wide_stages(int W) { return W == 4 ? 6 : 4; }
 
+int attn_wide_per_cu(int waves) { return 4 / waves; }  // one wave per SIMD
+
 size_t attn_wide_lds(int waves, int head_dim)
 {
     return (size_t)wide_stages(waves) * (head_dim == 128 ? AttnGeom<128>::STAGE_B : AttnGeom<64>::STAGE_B);
@@ -486,13 +488,72 @@ hipError_t launch_attn_wide(const AttnArgs &a, const AttnPlan &plan, int head_di
     return launch_timed(kern, grid, dim3(64 * plan.waves), plan.lds_bytes, a, stream, ev, 0);
 }
 
+// Ranked order: a few sequences, and more items than are resident at once.  Items that all start together need no order, and
+// finding a rank costs each of them two round trips and the search (plain -> ranked: 16 sequences of 0..2000 cached and up to
+// 33 new tokens, 32/8 heads, 44.7 -> 48.8 us with the former search; 8 of 0..3000 and 100..300, 4/2 heads of 64, 48.2 -> 50.0).
+bool prefill_ranked(int batch, int64_t items, int per_cu, int num_cus)
+{
+    return batch > 1 && batch <= kRankedBatch && items > (int64_t)per_cu * num_cus;
+}
+
+namespace {
+// 64 lanes as arrays: the search above, compiled for the host
+struct HostLanes {
+    struct Int {
+        int v[64];
+        Int(int x = 0) { for (int &y : v) y = x; }
+        template <class F>
+        static Int each(const Int &a, const Int &b, F f) { Int r; for (int i = 0; i < 64; ++i) r.v[i] = f(a.v[i], b.v[i]); return r; }
+        friend Int operator+(const Int &a, const Int &b) { return each(a, b, [](int x, int y) { return x + y; }); }
+        friend Int operator-(const Int &a, const Int &b) { return each(a, b, [](int x, int y) { return x - y; }); }
+        friend Int operator*(const Int &a, const Int &b) { return each(a, b, [](int x, int y) { return x * y; }); }
+        friend Int operator>>(const Int &a, int n) { return each(a, n, [](int x, int y) { return x >> y; }); }
+    };
+    static Int lane() { Int r; for (int i = 0; i < 64; ++i) r.v[i] = i; return r; }
+    static Int lesser(const Int &a, const Int &b) { return Int::each(a, b, [](int x, int y) { return x < y ? x : y; }); }
+    static Int larger(const Int &a, const Int &b) { return Int::each(a, b, [](int x, int y) { return x > y ? x : y; }); }
+    template <class F>
+    static Int over_row(const Int &a, F f)
+    {
+        Int r;
+        for (int i = 0; i < 64; ++i) {
+            int x = a.v[i & 48];
+            for (int j = 1; j < 16; ++j) x = f(x, a.v[(i & 48) + j]);
+            r.v[i] = x;
+        }
+        return r;
+    }
+    static Int row_sum(const Int &a) { return over_row(a, [](int x, int y) { return x + y; }); }
+    static Int row_max(const Int &a) { return over_row(a, [](int x, int y) { return x > y ? x : y; }); }
+    static uint64_t less(const Int &a, const Int &b)
+    {
+        uint64_t m = 0;
+        for (int i = 0; i < 64; ++i) m |= (uint64_t)(a.v[i] < b.v[i]) << i;
+        return m;
+    }
+    static int read(const Int &a, int lane) { return a.v[lane]; }
+};
+}  // namespace
+
+bool ranked_chunk_on_host(int rank, int batch, const int *end_levels, const int *chunks, int *seq, int *chunk)
+{
+    HostLanes::Int e, n;
+    for (int i = 0; i < 64; ++i) {
+        const int x = i & 15;
+        e.v[i] = x < batch ? end_levels[x] : 0;
+        n.v[i] = x < batch ? chunks[x] : 0;
+    }
+    return ranked_chunk<HostLanes>(rank, e, n, seq, chunk);
+}
+
 template <int D, int W>
-static hipError_t launch_prefill_wide(AttnArgs a, hipStream_t stream)
+static hipError_t launch_prefill_wide(AttnArgs a, int num_cus, hipStream_t stream)
 {
     a.chunk_tokens = 64 * W / a.group;
     a.rows = 64 * W;
     a.num_splits = (a.max_new + a.chunk_tokens - 1) / a.chunk_tokens;
     dim3 grid((unsigned)a.num_splits * (unsigned)a.num_kv_heads * (unsigned)a.batch);
+    a.ranked = prefill_ranked(a.batch, grid.x, attn_wide_per_cu(W), num_cus);
     hipLaunchKernelGGL((attn_wide_kernel<D, W, wide_stages(W), kItemsPrefill>), grid, dim3(64 * W), attn_wide_lds(W, D), stream, ATTN_FIRST_VALUES(a), a);
     return hipGetLastError();
 }
@@ -541,9 +602,9 @@ hipError_t launch_prefill_attn(const AttnArgs &a, int head_dim, int num_cus, hip
 {
     if (a.batch == 0 || a.max_new == 0) return hipSuccess;
     const int waves = prefill_wide_waves(head_dim, a.group, (int64_t)a.batch * a.num_kv_heads, a.max_new, a.max_seq_len, num_cus);
-    if (waves == 0) return launch_prefill_split(a, head_dim, stream);
-    if (head_dim == 128) return waves == 2 ? launch_prefill_wide<128, 2>(a, stream) : launch_prefill_wide<128, 4>(a, stream);
-    if (head_dim == 64) return launch_prefill_wide<64, 4>(a, stream);
+    if (waves == 0) return launch_prefill_split(a, head_dim, num_cus, stream);
+    if (head_dim == 128) return waves == 2 ? launch_prefill_wide<128, 2>(a, num_cus, stream) : launch_prefill_wide<128, 4>(a, num_cus, stream);
+    if (head_dim == 64) return launch_prefill_wide<64, 4>(a, num_cus, stream);
     return hipErrorInvalidValue;
 }
 

@@ -41,6 +41,7 @@ struct AttnArgs {
     int batch, num_q_heads, num_kv_heads, group, block_k, rows;
     int page_shift, max_pages_per_seq, max_seq_len, chunk_tokens, num_splits, view;
     int bal_wgs;  // balanced partition: workgroups of the split launch (0 otherwise)
+    int ranked;   // prefill: chunks start longest first over all sequences (prefill_ranked)
     float scale_log2e;  // sm_scale * log2(e)
 };
 
@@ -174,11 +175,16 @@ hipError_t launch_attn(const AttnArgs &a, const AttnPlan &plan, int head_dim, hi
 // The 64-rows-per-wave kernel: whether it is the better one for these rows, its LDS need, its launch (grid from the plan).
 bool attn_wide_pays(int head_dim, int rows, int max_seq_len, int64_t units, int num_cus);
 size_t attn_wide_lds(int waves, int head_dim);
+int attn_wide_per_cu(int waves);
 // Prefill: waves of 64 rows per workgroup, 0 for the 32-row form.
 int prefill_wide_waves(int head_dim, int group, int64_t units, int max_new, int max_seq_len, int num_cus);
+// Whether a prefill launch's chunks start in ranked order; `items` workgroups of which per_cu are resident on a CU at once.
+bool prefill_ranked(int batch, int64_t items, int per_cu, int num_cus);
+// The order itself on the host: ranked_chunk with the end levels and chunk counts of `batch` sequences (at most 16).
+bool ranked_chunk_on_host(int rank, int batch, const int *end_levels, const int *chunks, int *seq, int *chunk);
 hipError_t launch_attn_wide(const AttnArgs &a, const AttnPlan &plan, int head_dim, dim3 grid, hipStream_t stream, AttnLaunchEvents *events);
 hipError_t launch_prefill_attn(const AttnArgs &a, int head_dim, int num_cus, hipStream_t stream);
-hipError_t launch_prefill_split(const AttnArgs &a, int head_dim, hipStream_t stream);
+hipError_t launch_prefill_split(const AttnArgs &a, int head_dim, int num_cus, hipStream_t stream);
 hipError_t launch_consensus(ConsensusArgs a, hipStream_t stream);
 hipError_t launch_sampling_consensus(const SamplingArgs &a, hipStream_t stream);
 int consensus_chunk_elems();
