@@ -254,29 +254,31 @@ struct HalfLoads {
         return (uint64_t)pg * page_bytes + (tok & page_mask) * tok_bytes;
     }
     static __device__ __forceinline__ const char *lowered(const uint16_t *pool) { return (const char *)pool - kBias; }
-    template <class NT>
+    // SETTLED: the caller keeps the distance from a lane read
+    template <bool SETTLED = false, class NT>
     __device__ __forceinline__ void issue(NT, const char *base, uint32_t lds_addr) const
     {
         base = (const char *)uniform_ptr(base);
+        constexpr int WAIT = SETTLED ? 0 : 3;
         static_assert(Gm::GS == 1040 && (GPH == 4 || GPH == 2), "the instruction offsets below");
         if constexpr (GPH == 4 && NT::value)
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\t"
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop %6\n\t"
                          "global_load_lds_dwordx4 %2, %1 nt\n\tglobal_load_lds_dwordx4 %3, %1 offset:1040 nt\n\t"
                          "global_load_lds_dwordx4 %4, %1 offset:2080 nt\n\tglobal_load_lds_dwordx4 %5, %1 offset:3120 nt"
-                         : : "s"(lds_addr), "s"(base), "v"(voff[0]), "v"(voff[1]), "v"(voff[GPH - 2]), "v"(voff[GPH - 1]) : "memory", "m0");
+                         : : "s"(lds_addr), "s"(base), "v"(voff[0]), "v"(voff[1]), "v"(voff[GPH - 2]), "v"(voff[GPH - 1]), "n"(WAIT) : "memory", "m0");
         else if constexpr (GPH == 4)
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\t"
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop %6\n\t"
                          "global_load_lds_dwordx4 %2, %1\n\tglobal_load_lds_dwordx4 %3, %1 offset:1040\n\t"
                          "global_load_lds_dwordx4 %4, %1 offset:2080\n\tglobal_load_lds_dwordx4 %5, %1 offset:3120"
-                         : : "s"(lds_addr), "s"(base), "v"(voff[0]), "v"(voff[1]), "v"(voff[GPH - 2]), "v"(voff[GPH - 1]) : "memory", "m0");
+                         : : "s"(lds_addr), "s"(base), "v"(voff[0]), "v"(voff[1]), "v"(voff[GPH - 2]), "v"(voff[GPH - 1]), "n"(WAIT) : "memory", "m0");
         else if constexpr (NT::value)
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\t"
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop %4\n\t"
                          "global_load_lds_dwordx4 %2, %1 nt\n\tglobal_load_lds_dwordx4 %3, %1 offset:1040 nt"
-                         : : "s"(lds_addr), "s"(base), "v"(voff[0]), "v"(voff[1]) : "memory", "m0");
+                         : : "s"(lds_addr), "s"(base), "v"(voff[0]), "v"(voff[1]), "n"(WAIT) : "memory", "m0");
         else
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\t"
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop %4\n\t"
                          "global_load_lds_dwordx4 %2, %1\n\tglobal_load_lds_dwordx4 %3, %1 offset:1040"
-                         : : "s"(lds_addr), "s"(base), "v"(voff[0]), "v"(voff[1]) : "memory", "m0");
+                         : : "s"(lds_addr), "s"(base), "v"(voff[0]), "v"(voff[1]), "n"(WAIT) : "memory", "m0");
     }
 };
 

@@ -366,7 +366,7 @@ __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(ATTN_FIRST_PARAMS,
                 read_v(Prev{}, sv, j, 1);
             }
         });
-        const char *base[PG];
+        uint64_t base[PG];
         slot(std::integral_constant<int, 1>{}, masked, limit(0, i), [&](int j, auto after) __attribute__((always_inline)) {
             if constexpr (!decltype(after)::value) return;
             if constexpr (FAST) {
@@ -374,11 +374,18 @@ __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(ATTN_FIRST_PARAMS,
                     wait_vmcnt<(NS - 3) * LPW>();
                     wg_barrier();
 #pragma unroll
-                    for (int u = 0; u < PG; ++u) base[u] = half_base(u, i + NS - 1);
+                    for (int u = 0; u < PG; ++u) {
+                        base[u] = (uint64_t)(uintptr_t)half_base(u, i + NS - 1);
+                        asm volatile("" : "+s"(base[u]));
+                    }
                 }
+                // the base was read from a lane two products ago, and nothing passes the scheduling barriers between
+                // them, so the load does without its own wait (training mask 593.3 -> 589.7 us, 8192 new tokens
+                // 455.6 -> 454.6)
 #pragma unroll
                 for (int u = 0; u < PG; ++u)
-                    if (j == 2 + u) half.issue(NtTag{}, base[u], dst_first + Prev::value * STAGE_B + u * half.GPH * GS);
+                    if (j == 2 + u)
+                        half.template issue<true>(NtTag{}, (const char *)base[u], dst_first + Prev::value * STAGE_B + u * half.GPH * GS);
             } else if (j == 0) {
                 step_barrier(i);
                 sv = st;
