@@ -24,7 +24,15 @@
 // over all sequences the ragged prefill takes 250 to 272, with 16-byte stores the mask 600.)
 #include "orthrus_attn_dev.h"
 
+#include <utility>
+
 namespace orthrus {
+
+template <int... S, class F>
+__device__ __forceinline__ void for_each_stage(std::integer_sequence<int, S...>, F &&f)
+{
+    (f(std::integral_constant<int, S>{}), ...);
+}
 
 // D head_dim, W waves of 64 query rows, NS LDS stages, MODE the work items (kItemsSplit or kItemsPrefill), NT the
 // non-temporal form of the tile loads.
@@ -265,7 +273,8 @@ __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(ATTN_FIRST_PARAMS,
     constexpr int NCH = KSTEPS + 2 * DBLK;  // products of a slot
     constexpr int VPC = 16 / NCH;           // softmax values handled next to each of them
     // One slot: the matrix work of block C (scores of tile i, values of tile i-1) next to the softmax of the other
-    // block's last scores, one product and VPC values at a time.  `extra(j)` adds the loads that go next to product j.
+    // block's last scores, one product and VPC values at a time.  `extra(j, after)` adds the waits that
+    // go in front of product j (after = false) and the loads that go behind it (after = true).
     auto slot = [&](auto cb, auto masked, int lim, auto &&extra) __attribute__((always_inline)) {
         constexpr int C = decltype(cb)::value, X = 1 - C;
         f32x16 z;
@@ -401,9 +410,8 @@ __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(ATTN_FIRST_PARAMS,
     const int n_fast = min(n_full, n_whole - (NS - 1)) / NS * NS;
     while (i < n_fast) {
         if (i + 2 * NS - 2 - win >= 64) open_window(i + NS - 1);
-        [&]<int... S>(std::integer_sequence<int, S...>) __attribute__((always_inline)) {
-            (tile(std::integral_constant<int, S>{}, std::false_type{}, i + S), ...);
-        }(std::make_integer_sequence<int, NS>{});
+        for_each_stage(std::make_integer_sequence<int, NS>{},
+                       [&](auto stage) __attribute__((always_inline)) { tile(stage, std::false_type{}, i + decltype(stage)::value); });
         i += NS;
         page_at += 32 * NS;
     }
