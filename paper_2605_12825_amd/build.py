@@ -23,7 +23,8 @@ HIPCC_FLAGS = [
     # packed fp32 VALU forms are disabled for every kernel in this library
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wno-unused-value",
-    # leading scalar arguments of a kernel arrive in scalar registers (as many as fit next to the argument pointer)
+    # leading scalar arguments of a kernel arrive in scalar registers (14 is the most that fit next to the argument pointer;
+    # the attention kernels use three)
     "-mllvm", "-amdgpu-kernarg-preload-count=14",
 ]
 

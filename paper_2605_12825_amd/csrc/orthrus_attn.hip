@@ -586,6 +586,11 @@ static int resident_per_cu(int head_dim, int W)
     return by_lds < by_waves ? by_lds : by_waves > 0 ? by_waves : 1;
 }
 
+// One wave per workgroup while four would leave most CUs without any (256 CUs, 36-layer graph, 4096 tokens, per call: 64
+// workgroups of 64 rows, 15 / 26 pieces 12.8 -> 12.6 / 13.8 -> 13.1 us; from 128 on the larger number is what counts: 128 rows,
+// 13 / 15 pieces 16.3 -> 16.5 / 16.0 -> 16.3; 256 of 64 rows, 8 pieces 19.7 -> 19.9).
+int merge_waves(int64_t wgs, int num_cus) { return 2 * wgs < num_cus ? 1 : 4; }
+
 hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv_heads, int max_seq_len,
                      int requested_splits, int num_cus, int num_layers, double pool_tokens, AttnPlan *plan)
 {
@@ -599,6 +604,7 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
     plan->rows_padded = blocks * 32;
     plan->lds_bytes = plan->wide ? attn_wide_lds(W, head_dim) : lds_need(head_dim);
     const int per_cu = plan->wide ? attn_wide_per_cu(W) : resident_per_cu(head_dim, W);  // resident workgroups
+    plan->merge_waves = merge_waves(units * W * (head_dim / 32), num_cus);
     plan->bal_wgs = 0;
     // K/V bytes the model streams at most between two passes over the same layer's cache (the other
     // layers' caches come in between), against the 256 MB last-level cache (see the kernel's loads).  Sequences
@@ -693,14 +699,11 @@ static auto combine_kernel(int num_splits)
     return attn_combine_kernel<D, W, BALANCED, 8, WAVES>;
 }
 
-// One wave per workgroup while four would leave most CUs without any (36-layer graph, 4096 tokens, per call: 64 workgroups
-// of 64 rows, 15 / 26 pieces 12.8 -> 12.6 / 13.8 -> 13.1 us; from 128 on the larger number is what counts: 128 rows, 13 / 15
-// pieces 16.3 -> 16.5 / 16.0 -> 16.3; 256 of 64 rows, 8 pieces 19.7 -> 19.9).
 template <int D, int W, int BALANCED>
-static hipError_t launch_combine(const AttnArgs &a, hipStream_t stream, AttnLaunchEvents *ev)
+static hipError_t launch_combine(const AttnArgs &a, const AttnPlan &plan, hipStream_t stream, AttnLaunchEvents *ev)
 {
     const unsigned wgs = (unsigned)(a.batch * a.num_kv_heads) * W * (D / 32);
-    if (wgs < 128) return launch_timed(combine_kernel<D, W, BALANCED, 1>(a.num_splits), dim3(wgs * 4), dim3(64), 0, a, stream, ev, 1);
+    if (plan.merge_waves == 1) return launch_timed(combine_kernel<D, W, BALANCED, 1>(a.num_splits), dim3(wgs * 4), dim3(64), 0, a, stream, ev, 1);
     return launch_timed(combine_kernel<D, W, BALANCED, 4>(a.num_splits), dim3(wgs), dim3(256), 0, a, stream, ev, 1);
 }
 
@@ -728,14 +731,14 @@ static hipError_t launch_attn_d(const AttnArgs &a, const AttnPlan &plan, hipStre
     if (e != hipSuccess) return e;
     if (BALANCED || plan.num_splits > 1) {
         switch (plan.waves) {
-        case 1: e = launch_combine<D, 1, BALANCED>(a, stream, ev); break;
-        case 2: e = launch_combine<D, 2, BALANCED>(a, stream, ev); break;
-        case 3: e = launch_combine<D, 3, BALANCED>(a, stream, ev); break;
-        case 4: e = launch_combine<D, 4, BALANCED>(a, stream, ev); break;
-        case 5: e = launch_combine<D, 5, BALANCED>(a, stream, ev); break;
-        case 6: e = launch_combine<D, 6, BALANCED>(a, stream, ev); break;
-        case 7: e = launch_combine<D, 7, BALANCED>(a, stream, ev); break;
-        case 8: e = launch_combine<D, 8, BALANCED>(a, stream, ev); break;
+        case 1: e = launch_combine<D, 1, BALANCED>(a, plan, stream, ev); break;
+        case 2: e = launch_combine<D, 2, BALANCED>(a, plan, stream, ev); break;
+        case 3: e = launch_combine<D, 3, BALANCED>(a, plan, stream, ev); break;
+        case 4: e = launch_combine<D, 4, BALANCED>(a, plan, stream, ev); break;
+        case 5: e = launch_combine<D, 5, BALANCED>(a, plan, stream, ev); break;
+        case 6: e = launch_combine<D, 6, BALANCED>(a, plan, stream, ev); break;
+        case 7: e = launch_combine<D, 7, BALANCED>(a, plan, stream, ev); break;
+        case 8: e = launch_combine<D, 8, BALANCED>(a, plan, stream, ev); break;
         }
     }
     return e;

@@ -11,6 +11,8 @@ _decode = getattr(_lib, "_ZN7orthrus14attn_wide_paysEiiili")
 _decode.restype, _decode.argtypes = ctypes.c_bool, [ctypes.c_int] * 3 + [ctypes.c_int64, ctypes.c_int]
 _prefill = getattr(_lib, "_ZN7orthrus18prefill_wide_wavesEiiliii")
 _prefill.restype, _prefill.argtypes = ctypes.c_int, [ctypes.c_int] * 2 + [ctypes.c_int64] + [ctypes.c_int] * 3
+_merge = getattr(_lib, "_ZN7orthrus11merge_wavesEli")
+_merge.restype, _merge.argtypes = ctypes.c_int, [ctypes.c_int64, ctypes.c_int]
 
 
 def decode_is_wide(head_dim, rows, max_seq_len, units):
@@ -50,3 +52,9 @@ def test_decode_route(wide, head_dim, rows, max_seq_len, units):
 ])
 def test_prefill_route(waves, head_dim, group, units, max_new, max_seq_len):
     assert prefill_waves(head_dim, group, units, max_new, max_seq_len) == waves
+
+
+@pytest.mark.parametrize("waves,wgs,num_cus", [(1, 64, 256), (1, 127, 256), (4, 128, 256), (4, 64, 32), (1, 15, 32)])
+def test_merge_form(waves, wgs, num_cus):
+    """A workgroup per wave while half the CUs of this device, whatever part of the chip it is, would have none."""
+    assert _merge(wgs, num_cus) == waves
