@@ -211,3 +211,60 @@ def test_prefill_ragged_lengths_in_any_order(batch, heads, kv_heads, d, T):
     np.testing.assert_array_equal(k, ref_k)
     np.testing.assert_array_equal(v, ref_v)
     assert case.step.device_error() == 0
+
+
+def _ranked(batch, heads, kv_heads, d, T, max_seq_len):
+    """Whether the launch of these sizes starts its chunks in ranked order, from the library's own rules."""
+    from test_attn_routes_cpu import prefill_waves
+    from test_prefill_order_math import _rule
+    group = heads // kv_heads
+    waves = prefill_waves(d, group, batch * kv_heads, T, max_seq_len)
+    tokens, per_cu = (64 * waves // group, 4 // waves) if waves else (32, min(3 if d == 128 else 6, 12 // (group + 1)))
+    return _rule(batch, -(-T // tokens) * batch * kv_heads, per_cu, 256)
+
+
+@pytest.mark.parametrize("batch, heads, kv_heads, d, T, alike", [
+    (16, 14, 2, 128, 306, False),     # two waves of 64 rows
+    (16, 14, 2, 128, 306, True),      # the same, sequences of one length: the plain order
+    (6, 32, 4, 64, 400, False),       # four waves
+    (4, 8, 8, 128, 900, False),       # the 32-row form
+    (15, 28, 4, 128, 290, False),
+])
+def test_prefill_of_a_few_sequences_is_that_of_each(batch, heads, kv_heads, d, T, alike):
+    """A launch with more items than are resident starts them longest first over all sequences; which chunk starts when
+    changes no bit.  One sequence has no new tokens, one has more than the call can hold (an error of its own)."""
+    from dataclasses import replace
+    rng = np.random.default_rng(5000 + batch + T)
+    context = 300
+    w = Workload(name="rk%d" % batch, seed=5100 + batch, batch=batch, num_q_heads=heads, num_kv_heads=kv_heads, head_dim=d,
+                 block_k=8, context=context, steps=(T + 7) // 8 + 1, page_size=16, paging="shuffled")
+    lens = np.full(batch, 77, np.int32) if alike else rng.integers(0, context + 1, batch).astype(np.int32)
+    new_lens = np.full(batch, T - 3, np.int32) if alike else rng.integers(1, T + 1, batch).astype(np.int32)
+    bad = None
+    if not alike:
+        new_lens[0], new_lens[1], new_lens[2], bad = T, 0, T + 1, 2
+    cache = make_cache(w, seq_lens=lens)
+    q, kn, vn = _new_tokens(w, T, 5200)
+    assert _ranked(batch, heads, kv_heads, d, T, context + T)
+    case = Case(w, cache, max_seq_len=context + T)
+    got = case.prefill(q, kn, vn, new_lens)
+    k, v, l = case.state()
+    if bad is not None:
+        assert case.step.device_error() == -4
+        assert (got[bad] == SENTINEL).all()
+        new_lens[bad] = 0
+    assert case.step.device_error() == 0
+    np.testing.assert_array_equal(l, lens + new_lens)
+    case.step.close()
+    one = Case(replace(w, batch=1), dict(cache, page_table=cache["page_table"][:1], seq_lens=lens[:1]), max_seq_len=context + T)
+    for b in range(batch):
+        if new_lens[b] == 0:
+            assert (got[b] == SENTINEL).all()
+            continue
+        one.page_table.copy_(torch.from_numpy(cache["page_table"][b:b + 1].copy()))
+        one.seq_lens.fill_(int(lens[b]))
+        np.testing.assert_array_equal(one.prefill(q[b:b + 1], kn[b:b + 1], vn[b:b + 1], new_lens[b:b + 1]), got[b:b + 1])
+    own, ones = one.state()[:2], (k, v)
+    for x, y in zip(own, ones):
+        np.testing.assert_array_equal(x, y)
+    one.step.close()
