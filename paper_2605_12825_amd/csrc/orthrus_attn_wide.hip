@@ -17,11 +17,13 @@
 // softmax (multiply-add, exponential, sum, half a conversion) takes 35 cycles against the product's own 32, and the rest
 // of a tile's instructions come on top.  The main loop therefore takes a turn of the ring at a time, so that LDS
 // addresses are instruction offsets, waits for LDS twice a tile, and keeps the memory addresses of 64 tiles in vector
-// registers: 188 instructions a 64x32 tile where an address calculation and a wait at each use made it 225.  Measured
-// before and after: one item to a CU (100 new tokens behind 16000, 7 heads a KV head) 351 -> 291 us a call; 8192 new tokens
-// (32/8 heads) 478 -> 456, where the kernel's cycles fall by 12 % and the clock by 6 (1.97 -> 1.85 GHz); ragged prefill at
-// 28/4 heads 325 -> 300; training mask 623 -> 598.  (attn_split_kernel's form: 675, 400 and 864.  With the chunks ranked
-// over all sequences the ragged prefill takes 250 to 272, with 16-byte stores the mask 600.)
+// registers: 190 instructions a 64x32 tile (counters: 157 vector ones with the products, 24 LDS, 5 scalar, 4 loads) where an
+// address calculation and a wait at each use made it 225.  Measured before and after: one item to a CU (100 new tokens
+// behind 16000, 7 heads a KV head) 351 -> 291 us a call; 16384 new tokens (32/8 heads) 1763 -> 1670, where the kernel's cycles
+// fall by 13 %, the products' share of them rises from 0.61 to 0.70 and the clock falls from 1.97 to 1.81 GHz; 8192 new tokens
+// 478 -> 456; ragged prefill at 28/4 heads 325 -> 300; training mask 623 -> 598.  (attn_split_kernel's form: 675, 400 and 864
+// for the last three.  With the chunks ranked over all sequences the ragged prefill takes 250 to 280 by the order of the
+// lengths, with 16-byte stores the mask 570 to 596 by the box.)
 #include "orthrus_attn_dev.h"
 
 #include <utility>
@@ -459,21 +461,26 @@ size_t attn_wide_lds(int waves, int head_dim)
 
 // Decode mode: whether this kernel beats attn_split_kernel when neither cuts a unit.  It needs waves that are nearly all
 // rows (7/8; of 96 rows the training mask takes 626 -> 640 us), units enough for a wave on every SIMD, and lengths over
-// which its shorter tile makes up for the longer start and end.  Where the lines lie (attn_split_kernel -> this kernel,
-// us per call, lengths equal to the bound; 256 CUs):
-//   d = 128, up to 128 rows: 512 units of 64 / 300 / 1000 tokens at 112 rows 16.3 -> 18.5 / 28.8 -> 27.7 / 74 -> 67, of
-//     180 at 128 rows 25.9 -> 24.2, 896 of 180 45.3 -> 42.7; 256 units 34 -> 42; a second round for a few units pays only when it is long or the
-//     lengths are mixed, which a long bound suggests (640 units of 400 tokens 50.8 -> 52.7, 544 of 1000 85 -> 90, 640 of
-//     2000 and of 200..1800 1.02 and 1.00 times as fast, the mask's 544 over 1024 / 2048 tokens 1.05 and 1.15; 768 units
-//     of 400 61.1 -> 59.0)
+// which its shorter tile makes up for the longer start and end.  The lines were drawn with the former main loop; both sides
+// with today's (attn_split_kernel -> this kernel, us per call, lengths equal to the bound; 256 CUs):
+//   d = 128, up to 128 rows: 512 units of 64 / 300 / 1000 tokens at 112 rows 13.6 -> 14.9 / 27.6 -> 27.3 / 64.4 -> 60.8, of
+//     180 at 128 rows 21.1 -> 20.6, 896 of 180 40.5 -> 40.9; 256 units of 1000 32.9 -> 36.7; a second round for a few units
+//     pays only when it is long or the lengths are mixed, which a long bound suggests (640 units of 400 tokens 45.0 -> 49.8,
+//     544 of 1000 79.8 -> 81.5, 640 of 2000 and of 200..1800 1.01 and 1.02 times as fast, the mask's 544 over 1024 / 2048
+//     tokens 1.11 and 1.25; 768 units of 400 52.2 -> 54.4)
 //   d = 128, more rows: two such waves' work is what four 32-row waves with a loader do as well; 224 rows lose everywhere
-//     (1024 units of 1000 tokens 175 -> 187), 256 rows gain from about 2000 tokens on (384 units of 1000 / 2500 tokens
-//     87.4 -> 90.7 / 183 -> 165, 256 units of 3000 119 -> 121; masks over 1024 / 2048 tokens 394 -> 400 / 351 -> 346)
-//   d = 64, up to 128 rows: 512 units lose at any length (3000 tokens: 95.6 -> 102.7), 640 of 400 / 1000 tokens 25.9 ->
-//     25.6 / 53.9 -> 51.3 but the mask's 640 over 2048 tokens 52 -> 58, its 704 1.03 times as fast; 768 of 180 / 256 tokens 19.3 -> 20.5 / 21.9 -> 21.6, 1024 of 400 41.6 -> 34.2
-//   d = 64, more rows: 320 units of 300 / 512 / 1000 tokens at 256 rows 24.8 -> 24.0 / 32.1 -> 29.9 / 50.7 -> 42.7, 256 of
-//     700 / 1000 23.9 -> 24.7 / 32.1 -> 31.4; at 224 rows 384 units of 700 / 2000 tokens 34.0 -> 33.3 / 89 -> 79, the
-//     mask's 352 over 4096 tokens 0.82 times as fast, its 384 1.23
+//     (1024 units of 1000 tokens 160 -> 164), 256 rows gain from about 2000 tokens on (384 units of 1000 / 2500 tokens
+//     76.0 -> 72.2 / 176 -> 144, 256 units of 3000 110 -> 102; masks of 384 over 1024 and of 512 over 2048 tokens 52.4 -> 52.1
+//     and 105 -> 97)
+//   d = 64, up to 128 rows: 512 units lose at any length (3000 tokens: 83.5 -> 90.1), 640 of 400 / 1000 tokens 22.5 ->
+//     22.4 / 48.2 -> 44.6 but the mask's 640 and 704 over 2048 tokens 47.7 -> 52.6 and 52.2 -> 54.7; 768 of 180 / 256 tokens
+//     16.1 -> 17.5 / 17.5 -> 18.2, 1024 of 400 38.8 -> 34.3
+//   d = 64, more rows: 320 units of 300 / 512 / 1000 tokens at 256 rows 22.1 -> 20.7 / 28.7 -> 25.1 / 48.2 -> 39.0, 256 of
+//     700 / 1000 19.9 -> 20.8 / 26.6 -> 25.2; at 224 rows 384 units of 700 / 2000 tokens 29.2 -> 30.5 / 81.6 -> 71.3, the
+//     mask's 352 over 4096 tokens 0.96 times as fast, its 384 1.12
+// So a few calls now lie on the wrong side: the 32-row kernel keeps 256 rows of d = 128 at 256 units of 3000 (7 %) and 384 of
+// 1000 (5 %), and of d = 64 640 units of 1000 at 128 rows (8 %) and 320 of 300 at 256 (6 %); this kernel takes 768 units of
+// 400 (4 %), and of d = 64 704 of the mask's (5 %) and 768 of 256 tokens (4 %).
 bool attn_wide_pays(int head_dim, int rows, int max_seq_len, int64_t units, int num_cus)
 {
     const int waves = rows > 128 ? 4 : 2;
@@ -573,27 +580,30 @@ static hipError_t launch_prefill_wide(AttnArgs a, int num_cus, hipStream_t strea
     return hipGetLastError();
 }
 
-// Prefill forms.  A 32-row wave with its own loader is the faster chain (0.55 us per tile against 0.65 us for twice the
-// rows), so for up to four waves a workgroup attn_split_kernel's prefill form stays while SIMDs would be idle otherwise.
-// How long that is depends on how the items' lengths are spread:
+// Prefill forms.  A 32-row wave with its own loader is the shorter chain, so for up to four waves a workgroup
+// attn_split_kernel's prefill form stays while SIMDs would be idle otherwise.  How long that is depends on how the items'
+// lengths are spread (32-row form -> this kernel, us per call):
 //   - From 0 up, the new tokens being most of what is cached (by the bound: max_seq_len < 2 * max_new): the longest items
-//     start first and short ones fill in behind them.  32-row form -> this kernel, one sequence of n tokens, us per call:
-//     d = 128: group 4, 2 heads, n = 7000 (1.7 waves per SIMD) 135 -> 160, 8 heads, n = 4000 (3.9) 169 -> 137; group 3, 2
-//     heads, n = 7000 (1.3) 129 -> 159; group 2, 8 heads, n = 2000 / 4000 (1.0 / 2.0) 47 -> 57 / 106 -> 106; group 1, 8
-//     heads, n = 4000 / 7000 (1.0 / 1.7) 78 -> 99 / 170 -> 165.  d = 64: group 1, 8 heads, n = 4000 / 9000 (1.0 / 2.2)
-//     59 -> 79 / 152 -> 162; group 4, 8 heads, n = 2000 / 4000 (2.0 / 3.9) 39 -> 47 / 100 -> 92.
+//     start first and short ones fill in behind them.  One sequence of n tokens:
+//     d = 128: group 4, 2 heads, n = 7000 (1.7 waves per SIMD) 131 -> 141, 8 heads, n = 4000 (3.9) 164 -> 127; group 3, 2
+//     heads, n = 7000 (1.3) 128 -> 135; group 2, 8 heads, n = 2000 / 4000 (1.0 / 2.0) 45 -> 50 / 105 -> 92; group 1, 8
+//     heads, n = 4000 / 7000 (1.0 / 1.7) 75 -> 85 / 170 -> 150.  d = 64: group 1, 8 heads, n = 4000 / 9000 (1.0 / 2.2)
+//     57 -> 67 / 151 -> 144; group 4, 8 heads, n = 2000 / 4000 (2.0 / 3.9) 36 -> 41 / 96 -> 89.
 //   - Of about equal length (behind a longer cache): what does not fit at once comes as a whole round more.  One 32-row
 //     wave per SIMD, all workgroups resident (LDS ring: three per CU, of four waves two; d = 64 and one wave: six):
-//     3000 cached tokens, d = 128: group 1, 32 heads, n = 700 (2.75 workgroups per CU) 77 -> 93, n = 1021 (4) 103 -> 93;
-//     group 2, 8 heads, n = 2000 (1.0 waves per SIMD) 119 -> 122; group 4, 8 heads, n = 700 / 2000 (0.7 / 2.0) 79 -> 94 /
-//     164 -> 141.  Or where this kernel would need a second round and the 32-row form would not: group 3, 32 heads,
-//     n = 700 146 -> 169.
-// More than four query heads per KV head: this kernel at any size.  Against the 32-row form with five to eight waves that
-// it took the place of, 4000 cached tokens, n = 32: group 5 / 6 / 7 / 8 108 -> 97 / 107 -> 97 / 111 -> 97 / 113 -> 97; empty
-// cache, n = 700: 36 -> 31 / 34 -> 29 / 35 -> 30 / 36 -> 30 (5 us of each for the shorter front end).
+//     3000 cached tokens, d = 128: group 1, 32 heads, n = 700 (2.75 workgroups per CU) 77 -> 89, n = 1021 (4) 132 -> 100;
+//     group 2, 8 heads, n = 2000 (1.0 waves per SIMD) 118 -> 102; group 4, 8 heads, n = 700 / 2000 (0.7 / 2.0) 74 -> 79 /
+//     155 -> 130.  Or where this kernel would need a second round and the 32-row form would not: group 3, 32 heads,
+//     n = 700 152 -> 166.
+// The lines were drawn with the former main loop (which took 57, 159, 122 and 94 us where 50, 135, 102 and 79 stand now), so
+// the 32-row form keeps a little too much: group 2, 8 heads, n = 2000 behind 3000 (15 %) and d = 64, group 1, n = 9000 (5 %).
+// More than four query heads per KV head: this kernel at any size.  Its former main loop against the 32-row form with five to
+// eight waves that it took the place of, 4000 cached tokens, n = 32: group 5 / 6 / 7 / 8 108 -> 97 / 107 -> 97 / 111 -> 97 /
+// 113 -> 97; empty cache, n = 700: 36 -> 31 / 34 -> 29 / 35 -> 30 / 36 -> 30 (5 us of each for the shorter front end).
 // Four waves per workgroup once every CU gets two of them, else two waves for the finer grain (8 sequences of 333 tokens:
-// 38 against 42 us), unless the finer grain spills into a round of its own (group 3, 32 heads, 2500 cached tokens, n = 677:
-// 544 workgroups of two waves 144 us, 256 of four 104); d = 64 is faster with four throughout (40 against 47 us).
+// 29 against 31 us), unless the finer grain spills into a round of its own (group 3, 32 heads, 2500 cached tokens, n = 677:
+// 544 workgroups of two waves 141 us, 256 of four 105); d = 64 is faster with four throughout (40 against 47 us with the
+// former loop).
 int prefill_wide_waves(int head_dim, int group, int64_t units, int max_new, int max_seq_len, int num_cus)
 {
     const int64_t cus = num_cus;
