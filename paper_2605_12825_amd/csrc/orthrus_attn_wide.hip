@@ -23,7 +23,7 @@
 // fall by 13 %, the products' share of them rises from 0.61 to 0.70 and the clock falls from 1.97 to 1.81 GHz; 8192 new tokens
 // 478 -> 456; ragged prefill at 28/4 heads 325 -> 300; training mask 623 -> 598.  (attn_split_kernel's form: 675, 400 and 864
 // for the last three.  With the chunks ranked over all sequences the ragged prefill takes 250 to 280 by the order of the
-// lengths, with 16-byte stores the mask 570 to 596 by the box.)
+// lengths, with 16-byte stores the mask 570 to 602 from one card to another.)
 #include "orthrus_attn_dev.h"
 
 #include <utility>
