@@ -167,7 +167,7 @@ orthrus::AttnArgs decode_attn_args(const orthrus_ctx *ctx, const orthrus_params 
     a.group = p->num_q_heads / p->num_kv_heads; a.block_k = p->block_k; a.rows = plan.rows;
     a.page_shift = log2_exact(p->page_size); a.max_pages_per_seq = p->max_pages_per_seq;
     a.max_seq_len = p->max_seq_len; a.chunk_tokens = plan.chunk_tokens; a.num_splits = plan.num_splits;
-    a.bal_wgs = plan.bal_wgs; a.ranked = 0;
+    a.bal_wgs = plan.bal_wgs; a.kv_nt = plan.kv_nt;
     a.view = view;
     a.scale_log2e = p->sm_scale * 1.4426950408889634f;
     return a;

@@ -68,11 +68,15 @@ namespace orthrus {
 //
 // NT: the non-temporal forms of the tile loads and of the partials' stores.  A form of the kernel and not a test in it:
 // every jump into code that no wave of the launch has fetched yet is a round trip to the L2 or beyond, in the loader's
-// first tile and between the last tile and the write-out alike.
+// first tile and between the last tile and the write-out alike.  The balanced partition's one form (kNtAsked) has both copies
+// of the loader's loop and a test: as two forms the compiler spills more of what lives across its segments (35 scalar
+// registers where it is 28 at 64 rows), 15 sequences of 71..1147 tokens, 16 rows 19.5 -> 20.3 us, 4 of 300..4000, 64 rows 25.1
+// -> 25.6.
 // The stores' hint is for fixed splits only: there the write-back of the partials at the kernel's end is what the merge waits
 // for (cycles over 12 layers of 4096 tokens at batch 4 / 8 496 -> 479 / 731 -> 711 us, 36 layers at batch 1 942 -> 940; a
 // small call under a loose bound 12.1 -> 12.5).  The balanced partition writes partials all along and reads them out of the
 // L2 again (64 sequences of 500..4000 tokens 133 -> 138 us with the hint).
+constexpr int kNtAsked = 2;
 template <int D, int W, int NS, int MODE, int NT, int PROBE = 0>
 __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(ATTN_FIRST_PARAMS, const AttnArgs rest)
 {
@@ -85,6 +89,7 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(ATTN_FIRST_
     // 256 rows 20.8 -> 21.0 / 17.9 -> 18.1 / 22.7 -> 22.7.  Four waves and fewer, batch 1 at 64 rows 13.4 -> 14.1; 256
     // rows of d = 64 (half the products per exponential) 12.5 -> 13.4.
     constexpr bool kWeightsFirst = W > 4 && D == 128 && MODE == kItemsSplit;
+    static_assert(BALANCED && !PROBE ? NT == kNtAsked : NT < kNtAsked, "");
     static_assert(!PROBE || (W == 1 && !PREFILL), "the stream probe is a decode-mode kernel with one idle compute wave");
     using Gm = AttnGeom<D>;
     constexpr int CH = Gm::CH, ROWB = Gm::ROWB, RPI = Gm::RPI, NI = Gm::NI, GS = Gm::GS;
@@ -116,83 +121,90 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(ATTN_FIRST_
         // Before the barrier the loads of tile i are complete; after it every compute wave is done reading the stage
         // of tile i-1, which is refilled with tile i+NS-1 while tile i is computed.
         HalfLoads<D> half(a, lane);
-        const std::integral_constant<bool, NT != 0> nt;
-        for (;;) {
-            const int n_whole = half.usable ? min(it.n_cache, (it.t_end - it.t_begin) >> 5) : 0;
-            const char *kp = half.lowered(a.k_pool + it.head_off), *vp = half.lowered(a.v_pool + it.head_off);
-            uint32_t dst = smem_lds;  // ring slot of the next tile to be issued
-            int p0 = 0, p1 = 0;       // page ids of its two halves (the second repeats the first past the end)
-            // fetched one tile ahead of their use, so that the scalar load's latency is never in front of a tile's loads
-            auto fetch_pages = [&](int t) __attribute__((always_inline)) {
-                if (t < it.n_cache) {
-                    const int ts = it.t_begin + t * 32;
-                    p0 = it.pt_row[(uint32_t)ts >> a.page_shift];
-                    p1 = it.pt_row[(uint32_t)(ts + 16 < it.t_end ? ts + 16 : ts) >> a.page_shift];
-                }
-            };
-            auto issue_tile = [&](int t) __attribute__((always_inline)) {
-                if (t < n_whole) {
-                    const uint32_t ts = (uint32_t)(it.t_begin + t * 32);
-                    const uint64_t o0 = half.offset(p0, ts), o1 = half.offset(p1, ts + 16);
-                    half.issue(nt, kp + o0, dst);
-                    half.issue(nt, kp + o1, dst + half.GPH * GS);
-                    half.issue(nt, vp + o0, dst + TILE_B);
-                    half.issue(nt, vp + o1, dst + TILE_B + half.GPH * GS);
-                } else if (half.usable && t < it.n_cache) {
-                    // the last, ragged cache tile: rows past the end repeat the last valid row (finite data, masked
-                    // later), so nothing is fetched through an unmapped page and no LDS row is left undefined
-                    const uint64_t o0 = half.offset(p0, 0) >> 1, o1 = half.offset(p1, 0) >> 1;
-                    const uint16_t *const kb[2] = {a.k_pool + it.head_off + o0, a.k_pool + it.head_off + o1};
-                    const uint16_t *const vb[2] = {a.v_pool + it.head_off + o0, a.v_pool + it.head_off + o1};
-                    issue_rows<D>(nt, kb, vb, dst, [&](int u) __attribute__((always_inline)) {
-                        const int tg = min(it.t_begin + t * 32 + u * RPI + ld_tok, it.t_end - 1);
-                        return ((uint32_t)tg & half.page_mask) * half.tok_bytes + ld_swz;
-                    });
-                } else if (t < it.n_cache) {  // strides past 32-bit arithmetic: an address per lane and load
-                    half.worst = max(half.worst, max((uint32_t)p0, (uint32_t)p1));
-                    const int q0 = (uint32_t)p0 < half.num_pages ? p0 : 0, q1 = (uint32_t)p1 < half.num_pages ? p1 : 0;
-#pragma unroll 1
-                    for (int u = 0; u < NI; ++u) {
-                        const int tg = min(it.t_begin + t * 32 + u * RPI + ld_tok, it.t_end - 1);
-                        const int64_t off = (int64_t)(u * RPI < 16 ? q0 : q1) * a.stride_page + it.head_off +
-                                            (int64_t)(tg & (P - 1)) * a.stride_tok + (ld_swz >> 1);
-                        dma16(nt, a.k_pool + off, dst + u * GS);
-                        dma16(nt, a.v_pool + off, dst + TILE_B + u * GS);
+        auto run = [&](auto nt) __attribute__((always_inline)) {
+            for (;;) {
+                const int n_whole = half.usable ? min(it.n_cache, (it.t_end - it.t_begin) >> 5) : 0;
+                const char *kp = half.lowered(a.k_pool + it.head_off), *vp = half.lowered(a.v_pool + it.head_off);
+                uint32_t dst = smem_lds;  // ring slot of the next tile to be issued
+                int p0 = 0, p1 = 0;       // page ids of its two halves (the second repeats the first past the end)
+                // fetched one tile ahead of their use, so that the scalar load's latency is never in front of a tile's loads
+                auto fetch_pages = [&](int t) __attribute__((always_inline)) {
+                    if (t < it.n_cache) {
+                        const int ts = it.t_begin + t * 32;
+                        p0 = it.pt_row[(uint32_t)ts >> a.page_shift];
+                        p1 = it.pt_row[(uint32_t)(ts + 16 < it.t_end ? ts + 16 : ts) >> a.page_shift];
                     }
-                } else if constexpr (!PROBE && !PREFILL) {  // (the stream probe has no block inputs: its in-block tile stays empty)
-                    // the in-block tile; rows past the block repeat its last row
-                    const int64_t off0 = (int64_t)it.b * K * a.blk_stride_row + (int64_t)it.g * a.blk_stride_head;
-                    if (a.blk_stride_row < (1ll << 25)) {
-                        const uint16_t *const kb[2] = {a.k_blk + off0, a.k_blk + off0}, *const vb[2] = {a.v_blk + off0, a.v_blk + off0};
-                        const uint32_t row_bytes = (uint32_t)a.blk_stride_row * 2u;
+                };
+                auto issue_tile = [&](int t) __attribute__((always_inline)) {
+                    if (t < n_whole) {
+                        const uint32_t ts = (uint32_t)(it.t_begin + t * 32);
+                        const uint64_t o0 = half.offset(p0, ts), o1 = half.offset(p1, ts + 16);
+                        half.issue(nt, kp + o0, dst);
+                        half.issue(nt, kp + o1, dst + half.GPH * GS);
+                        half.issue(nt, vp + o0, dst + TILE_B);
+                        half.issue(nt, vp + o1, dst + TILE_B + half.GPH * GS);
+                    } else if (half.usable && t < it.n_cache) {
+                        // the last, ragged cache tile: rows past the end repeat the last valid row (finite data, masked
+                        // later), so nothing is fetched through an unmapped page and no LDS row is left undefined
+                        const uint64_t o0 = half.offset(p0, 0) >> 1, o1 = half.offset(p1, 0) >> 1;
+                        const uint16_t *const kb[2] = {a.k_pool + it.head_off + o0, a.k_pool + it.head_off + o1};
+                        const uint16_t *const vb[2] = {a.v_pool + it.head_off + o0, a.v_pool + it.head_off + o1};
                         issue_rows<D>(nt, kb, vb, dst, [&](int u) __attribute__((always_inline)) {
-                            return (uint32_t)min(u * RPI + ld_tok, K - 1) * row_bytes + ld_swz;
+                            const int tg = min(it.t_begin + t * 32 + u * RPI + ld_tok, it.t_end - 1);
+                            return ((uint32_t)tg & half.page_mask) * half.tok_bytes + ld_swz;
                         });
-                    } else {
+                    } else if (t < it.n_cache) {  // strides past 32-bit arithmetic: an address per lane and load
+                        half.worst = max(half.worst, max((uint32_t)p0, (uint32_t)p1));
+                        const int q0 = (uint32_t)p0 < half.num_pages ? p0 : 0, q1 = (uint32_t)p1 < half.num_pages ? p1 : 0;
 #pragma unroll 1
                         for (int u = 0; u < NI; ++u) {
-                            const int64_t off = off0 + (int64_t)min(u * RPI + ld_tok, K - 1) * a.blk_stride_row + (ld_swz >> 1);
-                            dma16(nt, a.k_blk + off, dst + u * GS);
-                            dma16(nt, a.v_blk + off, dst + TILE_B + u * GS);
+                            const int tg = min(it.t_begin + t * 32 + u * RPI + ld_tok, it.t_end - 1);
+                            const int64_t off = (int64_t)(u * RPI < 16 ? q0 : q1) * a.stride_page + it.head_off +
+                                                (int64_t)(tg & (P - 1)) * a.stride_tok + (ld_swz >> 1);
+                            dma16(nt, a.k_pool + off, dst + u * GS);
+                            dma16(nt, a.v_pool + off, dst + TILE_B + u * GS);
+                        }
+                    } else if constexpr (!PROBE && !PREFILL) {  // (the stream probe has no block inputs: its in-block tile stays empty)
+                        // the in-block tile; rows past the block repeat its last row
+                        const int64_t off0 = (int64_t)it.b * K * a.blk_stride_row + (int64_t)it.g * a.blk_stride_head;
+                        if (a.blk_stride_row < (1ll << 25)) {
+                            const uint16_t *const kb[2] = {a.k_blk + off0, a.k_blk + off0}, *const vb[2] = {a.v_blk + off0, a.v_blk + off0};
+                            const uint32_t row_bytes = (uint32_t)a.blk_stride_row * 2u;
+                            issue_rows<D>(nt, kb, vb, dst, [&](int u) __attribute__((always_inline)) {
+                                return (uint32_t)min(u * RPI + ld_tok, K - 1) * row_bytes + ld_swz;
+                            });
+                        } else {
+#pragma unroll 1
+                            for (int u = 0; u < NI; ++u) {
+                                const int64_t off = off0 + (int64_t)min(u * RPI + ld_tok, K - 1) * a.blk_stride_row + (ld_swz >> 1);
+                                dma16(nt, a.k_blk + off, dst + u * GS);
+                                dma16(nt, a.v_blk + off, dst + TILE_B + u * GS);
+                            }
                         }
                     }
+                    dst = dst + STAGE_B == smem_lds + NS * STAGE_B ? smem_lds : dst + STAGE_B;
+                    fetch_pages(t + 1);
+                };
+                int t = 0;  // next tile to be issued
+                fetch_pages(0);
+                for (; t < min(NS - 1, it.n_tiles); ++t) issue_tile(t);
+                for (int i = 0; i < it.n_tiles; ++i) {
+                    const int ahead = min(NS - 2, it.n_tiles - 1 - i);  // tiles issued after tile i so far
+                    if (ahead >= 2) wait_vmcnt<2 * LPT>();
+                    else if (ahead == 1) wait_vmcnt<LPT>();
+                    else wait_vmcnt<0>();
+                    wg_barrier();
+                    if (t < it.n_tiles) issue_tile(t++);
                 }
-                dst = dst + STAGE_B == smem_lds + NS * STAGE_B ? smem_lds : dst + STAGE_B;
-                fetch_pages(t + 1);
-            };
-            int t = 0;  // next tile to be issued
-            fetch_pages(0);
-            for (; t < min(NS - 1, it.n_tiles); ++t) issue_tile(t);
-            for (int i = 0; i < it.n_tiles; ++i) {
-                const int ahead = min(NS - 2, it.n_tiles - 1 - i);  // tiles issued after tile i so far
-                if (ahead >= 2) wait_vmcnt<2 * LPT>();
-                else if (ahead == 1) wait_vmcnt<LPT>();
-                else wait_vmcnt<0>();
-                wg_barrier();
-                if (t < it.n_tiles) issue_tile(t++);
+                if (!BALANCED || !it.open(a)) break;
+                wg_barrier();  // every compute wave is done with the previous segment's last tile
             }
-            if (!BALANCED || !it.open(a)) break;
-            wg_barrier();  // every compute wave is done with the previous segment's last tile
+        };
+        if constexpr (NT == kNtAsked) {
+            if (a.kv_nt) run(std::true_type{});
+            else run(std::false_type{});
+        } else {
+            run(std::integral_constant<bool, NT != 0>{});
         }
         if (half.worst >= half.num_pages && lane == 0) atomicExch(a.err_word, -4);
         return;
@@ -684,9 +696,11 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
 template <int D, int W, int BALANCED>
 static hipError_t launch_split(const AttnArgs &a, const AttnPlan &plan, dim3 grid, hipStream_t stream, AttnLaunchEvents *ev)
 {
-    constexpr int MODE = BALANCED ? kItemsBalanced : kItemsSplit;
-    return launch_timed(plan.kv_nt ? attn_split_kernel<D, W, kStages, MODE, 1> : attn_split_kernel<D, W, kStages, MODE, 0>, grid,
-                        dim3(64 * (W + 1)), plan.lds_bytes, a, stream, ev, 0);
+    auto kern = [&] {
+        if constexpr (BALANCED) return attn_split_kernel<D, W, kStages, kItemsBalanced, kNtAsked>;
+        else return plan.kv_nt ? attn_split_kernel<D, W, kStages, kItemsSplit, 1> : attn_split_kernel<D, W, kStages, kItemsSplit, 0>;
+    }();
+    return launch_timed(kern, grid, dim3(64 * (W + 1)), plan.lds_bytes, a, stream, ev, 0);
 }
 
 template <int D, int W, int BALANCED, int WAVES>

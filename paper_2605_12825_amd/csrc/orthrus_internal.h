@@ -42,7 +42,10 @@ struct AttnArgs {
     int batch, num_q_heads, num_kv_heads, group, block_k, rows;
     int page_shift, max_pages_per_seq, max_seq_len, chunk_tokens, num_splits, view;
     int bal_wgs;  // balanced partition: workgroups of the split launch (0 otherwise)
-    int ranked;   // prefill: chunks start longest first over all sequences (prefill_ranked)
+    union {
+        int ranked;  // prefill: chunks start longest first over all sequences (prefill_ranked)
+        int kv_nt;   // balanced partition: non-temporal tile loads (see AttnPlan)
+    };
     float scale_log2e;  // sm_scale * log2(e)
 };
 

@@ -44,4 +44,4 @@ def test_partials_hint_with_fixed_splits_only(tmp_path):
             hinted = len(re.findall(r"\tglobal_store_dwordx4 [^\n]* nt\b", block))
             assert hinted == (d // 8 if (mode, nt, probe) == (0, 1, 0) else 0), head.group(0)
             seen += 1
-    assert seen == 2 * (2 * 8 * 2 + 4 + 4)
+    assert seen == 2 * (8 * 3 + 4 + 4)
