@@ -77,10 +77,9 @@ namespace orthrus {
 // small call under a loose bound 12.1 -> 12.5).  The balanced partition writes partials all along and reads them out of the
 // L2 again (64 sequences of 500..4000 tokens 133 -> 138 us with the hint).
 constexpr int kNtAsked = 2;
-template <int D, int W, int NS, int MODE, int NT, int PROBE = 0>
-__global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(ATTN_FIRST_PARAMS, const AttnArgs rest)
+template <int D, int W, int NS, int MODE, int NT, int PROBE>
+__device__ __forceinline__ void split_items(const AttnArgs &a)
 {
-    const AttnArgs a = with_first(rest, first_lens, first_batch);
     constexpr bool PREFILL = MODE == kItemsPrefill, BALANCED = MODE == kItemsBalanced;
     // With two compute waves on a SIMD the other wave fills a wave's waits, and what counts is instructions: the weights
     // are taken before anything is known of the maximum (row_weights).  One wave alone is a chain, in which that puts
@@ -88,7 +87,7 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(ATTN_FIRST_
     // 95.5 / 91.7 -> 87.0 / 94.6 -> 92.4 us; 32 of 2000, 256 rows 59.6 -> 57.3; one of 4096 (36-layer graph), 192 / 224 /
     // 256 rows 20.8 -> 21.0 / 17.9 -> 18.1 / 22.7 -> 22.7.  Four waves and fewer, batch 1 at 64 rows 13.4 -> 14.1; 256
     // rows of d = 64 (half the products per exponential) 12.5 -> 13.4.
-    constexpr bool kWeightsFirst = W > 4 && D == 128 && MODE == kItemsSplit;
+    constexpr bool kWeightsFirst = W > 4 && D == 128 && (MODE == kItemsSplit || MODE == kItemsBySize);
     static_assert(BALANCED && !PROBE ? NT == kNtAsked : NT < kNtAsked, "");
     static_assert(!PROBE || (W == 1 && !PREFILL), "the stream probe is a decode-mode kernel with one idle compute wave");
     using Gm = AttnGeom<D>;
@@ -401,6 +400,20 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(ATTN_FIRST_
     }
 }
 
+template <int D, int W, int NS, int MODE, int NT, int PROBE = 0>
+__global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(ATTN_FIRST_PARAMS, const AttnArgs rest)
+{
+    split_items<D, W, NS, MODE, NT, PROBE>(with_first(rest, first_lens, first_batch));
+}
+
+// Fixed splits, the long items first.  A kernel of its own: the search for a workgroup's item in front of a batch-1 call's
+// code cost that call 0.3 % (36-layer graph 940 -> 943 us), though it never ran.
+template <int D, int W, int NS, int NT>
+__global__ void __launch_bounds__(64 * (W + 1), 3) attn_by_size_kernel(ATTN_FIRST_PARAMS, const AttnArgs rest)
+{
+    split_items<D, W, NS, kItemsBySize, NT, 0>(with_first(rest, first_lens, first_batch));
+}
+
 // Merge the per-split partials in split order and write bf16 rows.  One workgroup per (sequence,
 // KV head, 32-row block, 32-wide d block), one wave per group of 4 d values: a lane reads exactly the
 // float4 it would hold in the split kernel's accumulator, so every load is a contiguous 1 KB per wave
@@ -603,6 +616,8 @@ static int resident_per_cu(int head_dim, int W)
 // 13 / 15 pieces 16.3 -> 16.5 / 16.0 -> 16.3; 256 of 64 rows, 8 pieces 19.7 -> 19.9).
 int merge_waves(int64_t wgs, int num_cus) { return 2 * wgs < num_cus ? 1 : 4; }
 
+bool decode_by_size(int batch, int64_t items, int per_cu, int num_cus) { return batch > 1 && items > (int64_t)per_cu * num_cus; }
+
 hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv_heads, int max_seq_len,
                      int requested_splits, int num_cus, int num_layers, double pool_tokens, AttnPlan *plan)
 {
@@ -618,6 +633,7 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
     const int per_cu = plan->wide ? attn_wide_per_cu(W) : resident_per_cu(head_dim, W);  // resident workgroups
     plan->merge_waves = merge_waves(units * W * (head_dim / 32), num_cus);
     plan->bal_wgs = 0;
+    plan->by_size = 0;
     // K/V bytes the model streams at most between two passes over the same layer's cache (the other
     // layers' caches come in between), against the 256 MB last-level cache (see the kernel's loads).  Sequences
     // may share pages: a layer holds no more tokens than its pool (the training mask's 1024 blocks read 32 MB
@@ -684,6 +700,7 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
     if (splits < 1) splits = 1;
     plan->chunk_tokens = chunk;
     plan->num_splits = splits;
+    plan->by_size = decode_by_size(batch, units * splits, per_cu, num_cus) ? 1 : 0;
     if (splits > 1) {
         plan->part_o_bytes = (size_t)units * splits * plan->rows_padded * head_dim * sizeof(float);
         plan->part_ml_bytes = (size_t)units * splits * plan->rows_padded * 2 * sizeof(float);
@@ -698,6 +715,7 @@ static hipError_t launch_split(const AttnArgs &a, const AttnPlan &plan, dim3 gri
 {
     auto kern = [&] {
         if constexpr (BALANCED) return attn_split_kernel<D, W, kStages, kItemsBalanced, kNtAsked>;
+        else if (plan.by_size) return plan.kv_nt ? attn_by_size_kernel<D, W, kStages, 1> : attn_by_size_kernel<D, W, kStages, 0>;
         else return plan.kv_nt ? attn_split_kernel<D, W, kStages, kItemsSplit, 1> : attn_split_kernel<D, W, kStages, kItemsSplit, 0>;
     }();
     return launch_timed(kern, grid, dim3(64 * (W + 1)), plan.lds_bytes, a, stream, ev, 0);

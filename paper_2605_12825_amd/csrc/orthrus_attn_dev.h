@@ -302,7 +302,7 @@ __device__ __forceinline__ void issue_rows(NT nt, const uint16_t *const (&k)[2],
 // attn_split_kernel.  Lengths and the page table are read-only for the whole launch and every index used here
 // is wave-uniform: reading them through the constant address space makes these scalar loads (s_load_dword),
 // which keeps them off the vector-memory counter that paces the tile loads.
-enum { kItemsSplit = 0, kItemsPrefill = 1, kItemsBalanced = 2 };
+enum { kItemsSplit = 0, kItemsPrefill = 1, kItemsBalanced = 2, kItemsBySize = 3 };  // (by size: kItemsSplit, the long items first)
 
 // Prefill of a few sequences: the order in which a launch's chunks start.  A chunk costs as many tiles as it has tokens
 // before its end, and the launch ends with the last one started, so the longest come first, over all sequences (every
@@ -364,6 +364,92 @@ __host__ __device__ __forceinline__ bool ranked_chunk(int r, typename Wave::Int 
     return true;
 }
 
+// Decode-mode items of different lengths: the long ones start first (decode_by_size).  A batch whose lengths only rise or only
+// fall (the training mask's anchors, a queue kept sorted) shows that in a few samples, which cost a round trip of scalar
+// loads; then the order is the batch's own, from its long end.  Otherwise, up to kRankedLens sequences are ranked; a larger
+// batch starts from the end whose sequence is the longer one.
+// Measured (plain -> from the long end / ranked, us per call): mask of one sequence of 4096 tokens, 256 blocks of 16, 237 -> 164 / 178
+// (a ranked item waits for a vector load in front of its first tile); of 4 packed ones of 2048 (1024 items a head, a
+// sawtooth) 622 -> 595 / -; of 3 of 2048, 64 blocks of 32 at 28/4 heads 154 -> 116 / 109; 128 sequences of 300..2500 in any order, 128
+// rows, 180 -> 163 / 142; 100 of 100..2500, 224 rows, 113 -> 109 / 84; 200 of 50..900, 32 rows, 82 -> 78 / 71; 128 of 1000
+// each 113.4 -> 113.8.  A sequence's heads moved on by one from rank to rank, so that no XCD keeps to one head: no gain where
+// K/V stream from memory, 1 to 5 % lost where the items of a sequence share them (mask of 4 x 2048, 60 blocks 142 -> 151).
+constexpr int kOrderSamples = 6;
+enum Direction { kDirUnknown, kDirAlike, kDirUp, kDirDown };
+
+// The lengths of a batch of up to kRankedLens sequences, a lane to a sequence (64 sequences a register), and the sequence of a
+// rank by length in whole tiles, longest first, lower index first among equals.
+constexpr int kRankedLens = 256;
+__host__ __device__ __forceinline__ Direction direction_of(const int (&sample)[kOrderSamples], int batch)
+{
+    const int first = sample[0], last = sample[kOrderSamples - 1];
+    bool up = first < last, down = first > last;
+    if (batch > kRankedLens) return up ? kDirUp : down ? kDirDown : kDirAlike;
+#pragma unroll
+    for (int k = 1; k < kOrderSamples; ++k) {
+        up = up && sample[k - 1] <= sample[k];
+        down = down && sample[k - 1] >= sample[k];
+    }
+    return up ? kDirUp : down ? kDirDown : kDirUnknown;
+}
+struct RankedLens {
+    static constexpr int REGS = kRankedLens / 64;
+    int raw[REGS], tiles[REGS];
+    int top;  // more than the largest number of tiles there may be
+
+    // false when all lengths come to the same number of tiles
+    __device__ __forceinline__ bool load(const AttnArgs &a)
+    {
+        const int lane = threadIdx.x & 63;
+        // loads past the batch give 0
+        const auto lens = __builtin_amdgcn_make_buffer_rsrc((void *)uniform_ptr(a.seq_lens), 0, a.batch * 4, 0x00020000);
+        top = ((a.max_seq_len + 31) >> 5) + 1;
+        bool differ = false;
+#pragma unroll
+        for (int k = 0; k < REGS; ++k) raw[k] = __builtin_amdgcn_raw_buffer_load_b32(lens, (k * 64 + lane) * 4, 0, 0);
+        const int first = (min(max(__builtin_amdgcn_readfirstlane(raw[0]), 0), a.max_seq_len) + 31) >> 5;
+#pragma unroll
+        for (int k = 0; k < REGS; ++k) {
+            const int n = (min(max(raw[k], 0), a.max_seq_len) + 31) >> 5;
+            const bool there = k * 64 + lane < a.batch;
+            differ |= there && n != first;
+            tiles[k] = there ? n : -1;
+        }
+        return __any(differ);
+    }
+    __device__ __forceinline__ int at_rank(int r, int *len) const
+    {
+        int lo = 0, hi = top, above = 0;  // more than r sequences have lo tiles or more, `above` <= r have hi or more
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            int count = 0;
+#pragma unroll
+            for (int k = 0; k < REGS; ++k) count += __popcll(__ballot(tiles[k] >= mid));
+            if (count > r) {
+                lo = mid;
+            } else {
+                hi = mid;
+                above = count;
+            }
+        }
+        int left = r - above, b = 0;
+        *len = 0;
+#pragma unroll
+        for (int k = 0; k < REGS; ++k) {
+            uint64_t mask = __ballot(tiles[k] == lo);
+            const int n = __popcll(mask);
+            if (left >= 0 && left < n) {
+                for (int x = left; x > 0; --x) mask &= mask - 1;
+                const int lane = __builtin_ctzll(mask);
+                b = k * 64 + lane;
+                *len = __builtin_amdgcn_readlane(raw[k], lane);
+            }
+            left -= n;
+        }
+        return b;
+    }
+};
+
 template <int MODE>
 struct WorkItems {
     int b, g;
@@ -377,9 +463,9 @@ struct WorkItems {
     int bal_b, bal_g, bal_o, bal_left;  // balanced form: position in the launch's tile sequence
 
     // validated length of sequence x (scalar)
-    __device__ __forceinline__ int seq_len(const AttnArgs &a, int x)
+    __device__ __forceinline__ int seq_len(const AttnArgs &a, int x) { return checked_len(a, ((const const_i32 *)a.seq_lens)[x]); }
+    __device__ __forceinline__ int checked_len(const AttnArgs &a, int L)
     {
-        int L = ((const const_i32 *)a.seq_lens)[x];
         if (L < 0 || L > a.max_seq_len) {
             if (threadIdx.x == 0) atomicExch(a.err_word, -4);
             L = L < 0 ? 0 : a.max_seq_len;
@@ -442,6 +528,34 @@ struct WorkItems {
             bal_b = __builtin_amdgcn_readfirstlane(bal_b);
             bal_o = __builtin_amdgcn_readfirstlane(bal_o);
         }
+    }
+
+    // Fixed splits, the items that are long first (decode_by_size): finds b, g, the split and the length.  The items of a sequence
+    // follow each other, its heads fastest; with all lengths alike, the plain order.
+    __device__ __forceinline__ void find_by_size(const AttnArgs &a, int *split, int *len)
+    {
+        const unsigned heads = (unsigned)a.num_kv_heads, splits = (unsigned)a.num_splits;
+        const int rank = (int)(blockIdx.x / (heads * splits)), item = (int)(blockIdx.x % (heads * splits)), last = a.batch - 1;
+        // every scalar load in one round trip: samples of the batch, and the lengths that the answer may be
+        const const_i32 *lens = (const const_i32 *)a.seq_lens;
+        int sample[kOrderSamples];
+#pragma unroll
+        for (int k = 0; k < kOrderSamples; ++k) sample[k] = lens[(uint32_t)last * (uint32_t)k / (kOrderSamples - 1)];
+        const int front = lens[rank], back = lens[last - rank], plain = lens[b];
+        const Direction dir = direction_of(sample, a.batch);
+        bool in_turn = dir != kDirAlike;
+        if (dir == kDirUp || dir == kDirDown) {
+            b = dir == kDirUp ? last - rank : rank;
+            *len = dir == kDirUp ? back : front;
+        } else if (dir == kDirUnknown) {
+            RankedLens ranked;
+            in_turn = ranked.load(a);
+            if (in_turn) b = ranked.at_rank(rank, len);
+        }
+        if (!in_turn) *len = plain;
+        g = in_turn ? item % (int)heads : (int)(blockIdx.x / ((unsigned)a.batch * splits));
+        *split = in_turn ? item / (int)heads : (int)(blockIdx.x / (unsigned)a.batch % splits);
+        *len = checked_len(a, *len);
     }
 
     // Opens the next work item; false when the workgroup has none (left).
@@ -521,25 +635,43 @@ struct WorkItems {
                 n_tiles = n_cache;
                 final_out = true;
             } else {
-                split = (int)((blockIdx.x / (unsigned)a.batch) % (unsigned)a.num_splits);
-                g = (int)(blockIdx.x / ((unsigned)a.batch * (unsigned)a.num_splits));
-                const int L = seq_len(a, b);
-                // The sequence's own length, not the host's bound on it, is cut into num_splits pieces:
-                // they stay equal however loose the bound is (it only sized the grid), e.g. when a
-                // decode loop bumps it by K per step without reading back.
-                const SplitCut cut = split_cut(L, a.num_splits, split);
-                if (cut.count == 0) return false;  // fewer tiles than splits: nothing falls in this one
-                n_tiles = __builtin_amdgcn_readfirstlane(cut.count);
-                n_cache = split == cut.live - 1 ? n_tiles - 1 : n_tiles;  // the last piece ends with the in-block tile
-                t_begin = __builtin_amdgcn_readfirstlane(cut.first * 32);
-                t_end = min(L, t_begin + n_cache * 32);
-                final_out = a.num_splits == 1;
-                part_slot = ((size_t)b * a.num_kv_heads + g) * a.num_splits + split;
+                int L;
+                if constexpr (MODE == kItemsBySize) {
+                    find_by_size(a, &split, &L);
+                } else {
+                    split = (int)((blockIdx.x / (unsigned)a.batch) % (unsigned)a.num_splits);
+                    g = (int)(blockIdx.x / ((unsigned)a.batch * (unsigned)a.num_splits));
+                    L = seq_len(a, b);
+                }
+                return take(a, split, L);
             }
         }
+        point(a);
+        return true;
+    }
+
+    // Piece `split` of unit (b, g), whose length is L; false when nothing falls in it.
+    __device__ __forceinline__ bool take(const AttnArgs &a, int split, int L)
+    {
+        // The sequence's own length, not the host's bound on it, is cut into num_splits pieces:
+        // they stay equal however loose the bound is (it only sized the grid), e.g. when a
+        // decode loop bumps it by K per step without reading back.
+        const SplitCut cut = split_cut(L, a.num_splits, split);
+        if (cut.count == 0) return false;  // fewer tiles than splits: nothing falls in this one
+        n_tiles = __builtin_amdgcn_readfirstlane(cut.count);
+        n_cache = split == cut.live - 1 ? n_tiles - 1 : n_tiles;  // the last piece ends with the in-block tile
+        t_begin = __builtin_amdgcn_readfirstlane(cut.first * 32);
+        t_end = min(L, t_begin + n_cache * 32);
+        final_out = a.num_splits == 1;
+        part_slot = ((size_t)b * a.num_kv_heads + g) * a.num_splits + split;
+        point(a);
+        return true;
+    }
+
+    __device__ __forceinline__ void point(const AttnArgs &a)
+    {
         pt_row = (const const_i32 *)(a.page_table + (int64_t)b * a.max_pages_per_seq);
         head_off = (int64_t)g * a.stride_head;
-        return true;
     }
 };
 

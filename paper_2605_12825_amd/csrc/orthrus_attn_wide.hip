@@ -36,7 +36,7 @@ __device__ __forceinline__ void for_each_stage(std::integer_sequence<int, S...>,
     (f(std::integral_constant<int, S>{}), ...);
 }
 
-// D head_dim, W waves of 64 query rows, NS LDS stages, MODE the work items (kItemsSplit or kItemsPrefill), NT the
+// D head_dim, W waves of 64 query rows, NS LDS stages, MODE the work items (not kItemsBalanced), NT the
 // non-temporal form of the tile loads.
 template <int D, int W, int NS, int MODE, int NT = 0>
 __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(ATTN_FIRST_PARAMS, const AttnArgs rest)
@@ -50,7 +50,7 @@ __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(ATTN_FIRST_PARAMS,
     constexpr int PG = 4 / W;  // of a tile's four 16-token halves (K, K, V, V), how many a wave loads
     static_assert(W == 2 || W == 4, "a wave's halves stay within one operand");
     static_assert(NS >= 4 && (NS - 3) * LPW < 64, "stage count");
-    static_assert(MODE == kItemsSplit || MODE == kItemsPrefill, "one work item per workgroup");
+    static_assert(MODE != kItemsBalanced, "one work item per workgroup");
     constexpr bool PREFILL = MODE == kItemsPrefill;
     using NtTag = std::integral_constant<bool, NT != 0>;
 
@@ -498,15 +498,16 @@ bool attn_wide_pays(int head_dim, int rows, int max_seq_len, int64_t units, int 
 }
 
 template <int D, int W>
-static auto wide_decode_kernel(int nt)
+static auto wide_decode_kernel(const AttnPlan &plan)
 {
-    return nt ? attn_wide_kernel<D, W, wide_stages(W), kItemsSplit, 1> : attn_wide_kernel<D, W, wide_stages(W), kItemsSplit, 0>;
+    if (plan.by_size) return plan.kv_nt ? attn_wide_kernel<D, W, wide_stages(W), kItemsBySize, 1> : attn_wide_kernel<D, W, wide_stages(W), kItemsBySize, 0>;
+    return plan.kv_nt ? attn_wide_kernel<D, W, wide_stages(W), kItemsSplit, 1> : attn_wide_kernel<D, W, wide_stages(W), kItemsSplit, 0>;
 }
 
 hipError_t launch_attn_wide(const AttnArgs &a, const AttnPlan &plan, int head_dim, dim3 grid, hipStream_t stream, AttnLaunchEvents *ev)
 {
-    auto kern = head_dim == 128 ? (plan.waves == 4 ? wide_decode_kernel<128, 4>(plan.kv_nt) : wide_decode_kernel<128, 2>(plan.kv_nt))
-                                : (plan.waves == 4 ? wide_decode_kernel<64, 4>(plan.kv_nt) : wide_decode_kernel<64, 2>(plan.kv_nt));
+    auto kern = head_dim == 128 ? (plan.waves == 4 ? wide_decode_kernel<128, 4>(plan) : wide_decode_kernel<128, 2>(plan))
+                                : (plan.waves == 4 ? wide_decode_kernel<64, 4>(plan) : wide_decode_kernel<64, 2>(plan));
     return launch_timed(kern, grid, dim3(64 * plan.waves), plan.lds_bytes, a, stream, ev, 0);
 }
 

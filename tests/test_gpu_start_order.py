@@ -1,0 +1,69 @@
+"""The order in which the items of a fixed-split decode launch start: batches whose items do not all fit the chip at once,
+with lengths that rise, fall, repeat a rise, come in any order or are alike, against the oracle."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import paper_2605_12825_amd as orthrus
+from orthrus_inputs import Workload, make_block, make_cache
+
+from test_attn_routes_cpu import decode_is_wide
+from test_gpu_parity import AR, DIFF, GpuCase, _check_attn, _oracle_attn
+
+_rule = getattr(ctypes.CDLL(orthrus.library_path()), "_ZN7orthrus14decode_by_sizeEilii")
+_rule.restype, _rule.argtypes = ctypes.c_bool, [ctypes.c_int, ctypes.c_int64, ctypes.c_int, ctypes.c_int]
+
+
+def _lens(kind, n, hi, seed):
+    rng = np.random.default_rng(seed)
+    x = rng.integers(0, hi + 1, size=n)
+    x[:4] = (0, hi, hi // 2, 0)[:n]
+    if kind == "rising":
+        x = np.sort(x)
+    elif kind == "falling":
+        x = np.sort(x)[::-1]
+    elif kind == "packed":       # a rise for each packed sequence
+        x = np.concatenate([np.sort(p) for p in np.array_split(x, 3)])
+    elif kind == "nearly":       # every sample in order, a few lengths not
+        x = np.sort(x)
+        x[[3, n // 2 + 1, n - 3]] = (hi, 0, 1)
+    elif kind == "alike":        # one number of tiles, different lengths
+        x = 33 + x % 32
+    elif kind == "one":          # a single sequence that differs
+        x[:] = 40
+        x[n - 2] = 97
+    return np.ascontiguousarray(x.astype(np.int32))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind,batch,splits,g,hkv,d,K,per_cu", [
+    ("any", 200, 1, 2, 8, 64, 4, 6), ("any", 65, 3, 2, 8, 64, 4, 6), ("any", 256, 1, 1, 7, 64, 3, 6), ("any", 64, 4, 2, 8, 64, 4, 6),
+    ("rising", 257, 1, 2, 6, 64, 4, 6), ("falling", 300, 1, 2, 6, 64, 4, 6), ("packed", 300, 1, 2, 6, 64, 4, 6),
+    ("packed", 129, 2, 2, 8, 64, 4, 6), ("nearly", 200, 1, 2, 8, 64, 4, 6), ("nearly", 260, 1, 2, 6, 64, 4, 6),
+    ("alike", 193, 1, 2, 8, 64, 4, 6), ("alike", 385, 1, 2, 4, 64, 4, 6), ("one", 192, 1, 2, 9, 64, 4, 6),
+    ("rising", 130, 2, 6, 4, 128, 31, 1), ("any", 2, 1, 1, 1025, 64, 1, 6),
+    ("any", 112, 1, 4, 8, 128, 32, 2), ("rising", 112, 1, 4, 8, 128, 32, 2),   # the 64-row kernel
+])
+def test_items_that_start_by_size(kind, batch, splits, g, hkv, d, K, per_cu):
+    assert _rule(batch, batch * hkv * splits, per_cu, 256)
+    hi = 130
+    assert decode_is_wide(d, g * K, hi, batch * hkv) == (batch == 112)
+    w = Workload(name="order", seed=9300 + batch, batch=batch, num_q_heads=g * hkv, num_kv_heads=hkv, head_dim=d, block_k=K,
+                 context=hi, page_size=16, paging="scattered")
+    lens = _lens(kind, batch, hi, 9400 + batch)
+    cache = make_cache(w, seq_lens=lens)
+    blk = make_block(w, 9500 + K)
+    case = GpuCase(w, cache, num_splits=splits)
+    for view in (DIFF, AR):
+        got, lse = case.attn(view, blk)
+        want, want_lse = _oracle_attn(view, w, blk, cache, want_lse=True)
+        _check_attn(got, want)
+        np.testing.assert_allclose(lse, want_lse, rtol=0, atol=2e-3)
+    assert case.step.device_error() == 0
+    case.step.close()
+
+
+@pytest.mark.parametrize("by_size,batch,items,per_cu", [(False, 1, 4096, 1), (False, 2, 512, 2), (True, 2, 513, 2), (True, 60000, 257, 1)])
+def test_by_size_where_items_wait_for_others(by_size, batch, items, per_cu):
+    assert _rule(batch, items, per_cu, 256) == by_size
