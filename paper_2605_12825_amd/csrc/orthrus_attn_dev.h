@@ -81,6 +81,18 @@ __device__ __forceinline__ float sum_with_other_half(float x)
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// The same with lane ^ 16.
+__device__ __forceinline__ float max_with_other_row(float x)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float sum_with_other_row(float x)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // Online softmax of one lane's 16 scores (half of a row; lane ^ 32 holds the rest) against a lazily updated
 // reference m in the log2 domain.  The weights are taken against the old reference first.  Only when their sum says
 // that one of them may have outgrown it by more than 2^kLazy (rarely, after a row's first tile) is the maximum taken,
