@@ -77,75 +77,6 @@ namespace orthrus {
 // small call under a loose bound 12.1 -> 12.5).  The balanced partition writes partials all along and reads them out of the
 // L2 again (64 sequences of 500..4000 tokens 133 -> 138 us with the hint).
 constexpr int kNtAsked = 2;
-constexpr int kPairedStages = 6;
-
-// Two waves to a row block (PAR = 2), fixed splits only: they take a piece's even and odd tiles, one barrier to two tiles, and
-// trade halves of the output columns at its end.  For launches that leave most of the chip's SIMDs idle, where a workgroup
-// lasts as long as its chain of tiles (split_pays_pairs).  Two loader waves, one an operand: at 370 cycles to issue a
-// tile one of them would be the longer chain (d = 64, 4 x 12000, 64 rows 12.9 -> 12.5 us, one of 40000 16.4 -> 15.7).
-// The pipeline is that of the single loader below, two tiles a step, in a ring of three steps.
-template <int D, int NS, int PAR, int NT>
-__device__ __forceinline__ void load_operand(const AttnArgs &a, const WorkItems<kItemsSplit> &it, uint32_t smem_lds, bool values)
-{
-    using Gm = AttnGeom<D>;
-    constexpr int CH = Gm::CH, RPI = Gm::RPI, NI = Gm::NI, GS = Gm::GS, TILE_B = Gm::TILE_B, STAGE_B = Gm::STAGE_B;
-    const int lane = threadIdx.x & 63;
-    const int ld_tok = lane / CH;  // this lane's row inside one wave-wide load, and the byte offset of its chunk in that row
-    const uint32_t ld_swz = (uint32_t)(((lane % CH) ^ xm<CH>(ld_tok)) << 4);
-    using NtTag = std::integral_constant<bool, NT != 0>;
-    HalfLoads<D> half(a, lane);
-    const uint16_t *pool = (const uint16_t *)uniform_ptr((values ? a.v_pool : a.k_pool) + it.head_off);
-    const char *low = half.lowered(pool);
-    const int n_whole = half.usable ? min(it.n_cache, (it.t_end - it.t_begin) >> 5) : 0;
-    const uint32_t first = smem_lds + (values ? TILE_B : 0);
-    uint32_t dst = first;
-    int p0 = 0, p1 = 0;
-    auto fetch_pages = [&](int t) __attribute__((always_inline)) {
-        if (t < it.n_cache) {
-            const int ts = it.t_begin + t * 32;
-            p0 = it.pt_row[(uint32_t)ts >> a.page_shift];
-            p1 = it.pt_row[(uint32_t)(ts + 16 < it.t_end ? ts + 16 : ts) >> a.page_shift];
-        }
-    };
-    auto issue_tile = [&](int t) __attribute__((always_inline)) {
-        if (t < n_whole) {
-            const uint32_t ts = (uint32_t)(it.t_begin + t * 32);
-            const uint64_t o0 = half.offset(p0, ts), o1 = half.offset(p1, ts + 16);
-            half.issue(NtTag{}, low + o0, dst);
-            half.issue(NtTag{}, low + o1, dst + half.GPH * GS);
-        } else {
-            // the ragged last cache tile and the in-block tile, row by row: rows past the end repeat the last one
-            const bool blk = t >= it.n_cache;
-            const uint16_t *src = blk ? (values ? a.v_blk : a.k_blk) + (int64_t)it.b * a.block_k * a.blk_stride_row + (int64_t)it.g * a.blk_stride_head : pool;
-            half.worst = max(half.worst, blk ? 0u : max((uint32_t)p0, (uint32_t)p1));
-            const int64_t q0 = (uint32_t)p0 < half.num_pages ? p0 : 0, q1 = (uint32_t)p1 < half.num_pages ? p1 : 0;
-            const int P = 1 << a.page_shift;
-#pragma unroll 1
-            for (int u = 0; u < NI; ++u) {
-                const int row = u * RPI + ld_tok, tg = min(it.t_begin + t * 32 + row, it.t_end - 1);
-                const int64_t off = blk ? (int64_t)min(row, a.block_k - 1) * a.blk_stride_row
-                                        : (u * RPI < 16 ? q0 : q1) * a.stride_page + (int64_t)(tg & (P - 1)) * a.stride_tok;
-                dma16(NtTag{}, src + off + (ld_swz >> 1), dst + u * GS);
-            }
-        }
-        dst = dst + STAGE_B == first + NS * STAGE_B ? first : dst + STAGE_B;
-        fetch_pages(t + 1);
-    };
-    int t = 0;
-    fetch_pages(0);
-    for (; t < min(NS - PAR, it.n_tiles); ++t) issue_tile(t);
-    for (int i = 0; i < it.n_tiles; i += PAR) {
-        const int ahead = t - min(i + PAR, it.n_tiles);  // tiles issued after this step's
-        if (ahead >= 2) wait_vmcnt<2 * NI>();
-        else if (ahead == 1) wait_vmcnt<NI>();
-        else wait_vmcnt<0>();
-        wg_barrier();
-        for (const int end = min(t + PAR, it.n_tiles); t < end;) issue_tile(t++);
-    }
-    wg_barrier();
-    wg_barrier();
-    if (half.worst >= half.num_pages && lane == 0) atomicExch(a.err_word, -4);
-}
 
 // The compute wave of a call with at most 16 query rows per KV head (a short block, few query heads a KV head, one token at a
 // time): v_mfma_f32_16x16x32_bf16 instead of a 32-row block that is half padding.  Same problem, tile layout, masks and
@@ -280,8 +211,8 @@ __device__ __forceinline__ void thin_rows(const AttnArgs &a, WorkItems<MODE> it,
     }
 }
 
-template <int D, int W, int NS, int MODE, int NT, int PROBE, int ROWS = 32, int PAR = 1>
-__device__ __forceinline__ void split_items(const AttnArgs a)
+template <int D, int W, int NS, int MODE, int NT, int PROBE, int ROWS = 32>
+__device__ __forceinline__ void split_items(const AttnArgs &a)
 {
     constexpr bool PREFILL = MODE == kItemsPrefill, BALANCED = MODE == kItemsBalanced;
     // With two compute waves on a SIMD the other wave fills a wave's waits, and what counts is instructions: the weights
@@ -297,15 +228,15 @@ __device__ __forceinline__ void split_items(const AttnArgs a)
     constexpr int CH = Gm::CH, ROWB = Gm::ROWB, RPI = Gm::RPI, NI = Gm::NI, GS = Gm::GS;
     constexpr int TILE_B = Gm::TILE_B, STAGE_B = Gm::STAGE_B, KSTEPS = Gm::KSTEPS, DBLK = Gm::DBLK;
     constexpr int LPT = 2 * NI;  // load instructions per tile (K groups then V groups), all by the loader wave
-    static_assert(PAR == 1 ? NS >= 2 && NS <= 4 : NS == 3 * PAR, "stage count");
-    static_assert((NS - 2) * LPT < 64 || PAR > 1, "outstanding loads must fit the vmcnt field");
+    static_assert(NS >= 2 && NS <= 4, "stage count");
+    static_assert((NS - 2) * LPT < 64, "outstanding loads must fit the vmcnt field");
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6), wave = PAR == 1 ? wave_id : wave_id % W, par = PAR == 1 ? 0 : wave_id / W;
-    const bool loader = PAR == 1 ? wave_id == W : wave_id >= W * PAR;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool loader = wave == W;
     const int col = lane & 31, h = lane >> 5;
     const int K = a.block_k, G = a.group;
     const int P = 1 << a.page_shift;
@@ -318,12 +249,6 @@ __device__ __forceinline__ void split_items(const AttnArgs a)
     const int ld_tok = lane / CH;  // this lane's row inside one wave-wide load, and the byte offset of its chunk in that row
     const uint32_t ld_swz = (uint32_t)(((lane % CH) ^ xm<CH>(ld_tok)) << 4);
 
-    if constexpr (PAR > 1) {
-        if (loader) {
-            load_operand<D, NS, PAR, NT>(a, it, smem_lds, wave_id > W * PAR);
-            return;
-        }
-    }
     if (loader) {
         // The loader wave: nothing but the load pipeline, one step per tile around the tile's workgroup barrier.
         // Before the barrier the loads of tile i are complete; after it every compute wave is done reading the stage
@@ -483,14 +408,13 @@ __device__ __forceinline__ void split_items(const AttnArgs a)
         float m_run = kNegBig, l_run = 0.f;
 
         // ---- main loop: one barrier per tile
-        int stage = par;  // ring slot of tile i (= i % NS)
-        for (int i = par; PAR == 1 ? i < it.n_tiles : i - par < it.n_tiles; i += PAR) {
+        int stage = 0;  // ring slot of tile i (= i % NS)
+        for (int i = 0; i < it.n_tiles; ++i) {
             wg_barrier();
-            if (PAR > 1 && i >= it.n_tiles) break;
 
             // LDS addresses of this tile's operands: one add per base, the rest are instruction offsets
             const uint32_t st_addr = smem_lds + (uint32_t)stage * STAGE_B;
-            stage = stage + PAR >= NS ? stage + PAR - NS : stage + PAR;
+            stage = stage + 1 == NS ? 0 : stage + 1;
             uint32_t ka[KSTEPS / 2], va_[DBLK];
 #pragma unroll
             for (int q = 0; q < KSTEPS / 2; ++q) ka[q] = st_addr + kb[q];
@@ -586,47 +510,6 @@ __device__ __forceinline__ void split_items(const AttnArgs a)
 
         // ---- write-out: this wave's 32 rows
         l_run = sum_with_other_half(l_run);
-        if constexpr (PAR == 2) {
-            // the two waves of a row block trade halves of the output columns
-            constexpr int HB = DBLK / 2, AREA = HB * 4 * 1024 + 512;
-            typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
-            typedef __attribute__((address_space(3))) f32x2 lds_f32x2;
-            wg_barrier();
-            const uint32_t mine = smem_lds + wave_id * AREA, theirs = smem_lds + (par ? wave_id - W : wave_id + W) * AREA;
-            auto send = [&](auto first) __attribute__((always_inline)) {
-#pragma unroll
-                for (int x = 0; x < HB * 4; ++x) {
-                    const int db = decltype(first)::value + x / 4, r = x % 4 * 4;
-                    *(lds_f32x4 *)(uintptr_t)(mine + x * 1024 + lane * 16) = f32x4{o[db][r], o[db][r + 1], o[db][r + 2], o[db][r + 3]};
-                }
-            };
-            if (par == 0) send(std::integral_constant<int, HB>{});
-            else send(std::integral_constant<int, 0>{});
-            *(lds_f32x2 *)(uintptr_t)(mine + HB * 4 * 1024 + lane * 8) = f32x2{m_run, l_run};
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            wg_barrier();
-            if (par) {
-#pragma unroll
-                for (int db = 0; db < HB; ++db) o[db] = o[db + HB];
-            }
-            const f32x2 ml = *(const lds_f32x2 *)(uintptr_t)(theirs + HB * 4 * 1024 + lane * 8);
-            const float M = fmaxf(m_run, ml[0]), own = __builtin_amdgcn_exp2f(m_run - M), other = __builtin_amdgcn_exp2f(ml[0] - M);
-            m_run = M;
-            l_run = par ? ml[1] * other + l_run * own : l_run * own + ml[1] * other;
-            const size_t slot = it.part_slot * W + wave;
-            f32x4 *po = (f32x4 *)a.part_o + slot * (DBLK * 4 * 64) + par * (HB * 4 * 64) + lane;
-#pragma unroll
-            for (int x = 0; x < HB * 4; ++x) {
-                const f32x4 v = *(const lds_f32x4 *)(uintptr_t)(theirs + x * 1024 + lane * 16);
-                f32x4 y;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) y[e] = o[x / 4][x % 4 * 4 + e] * own + v[e] * other;
-                if constexpr (NT != 0) __builtin_nontemporal_store(y, &po[x * 64]);
-                else po[x * 64] = y;
-            }
-            if (par == 0 && h == 0) ((float2 *)a.part_ml)[slot * 32 + col] = make_float2(m_run, l_run);
-            return;
-        }
         if (it.final_out) {
             if (row_ok) {
                 const int i = irow, hl = ridx - i * G;
@@ -675,13 +558,6 @@ template <int D, int NS, int MODE, int NT>
 __global__ void __launch_bounds__(128, 3) attn_thin_kernel(ATTN_FIRST_PARAMS, const AttnArgs rest)
 {
     split_items<D, 1, NS, MODE, NT, 0, 16>(with_first(rest, first_lens, first_batch));
-}
-
-// Two waves to a row block (load_operand, split_items).
-template <int D, int W, int NT>
-__global__ void __launch_bounds__(64 * (2 * W + 2), W > 2 ? 3 : 2) attn_paired_kernel(ATTN_FIRST_PARAMS, const AttnArgs rest)
-{
-    split_items<D, W, kPairedStages, kItemsSplit, NT, 0, 32, 2>(with_first(rest, first_lens, first_batch));
 }
 
 // Merge the per-split partials in split order and write bf16 rows.  One workgroup per (sequence,
@@ -889,28 +765,6 @@ static int resident_per_cu(int head_dim, int W)
 // 13 / 15 pieces 16.3 -> 16.5 / 16.0 -> 16.3; 256 of 64 rows, 8 pieces 19.7 -> 19.9).
 int merge_waves(int64_t wgs, int num_cus) { return 2 * wgs < num_cus ? 1 : 4; }
 
-// Two waves to a row block halve a workgroup's chain of tiles and add the trade at its end, so pieces have to be long enough
-// (`tiles` of the longest one at the host bound); a launch that fills the chip waits for the stream and not for the chain
-// (one wave to a row block -> two, us per call; 256 CUs):
-//   d = 128, 17..32 rows: 84 pieces of 9 tiles 11.8 -> 11.0, 144 of 14 16.8 -> 14.3, 192 of 8 11.2 -> 10.1; 80 of 5 8.6 -> 8.8, a
-//     16-layer graph, 88 of 6 317 -> 320; 224 of 14 13.8 -> 13.8, 240 of 42 29.4 -> 30.5
-//   d = 128, 33..64 rows: 76 of 10 12.9 -> 12.4, 136 of 15 17.8 -> 16.3, 36-layer graph, 104 of 10 940 -> 911; 96 of 8 10.8 ->
-//     11.0, 152 of 10 13.1 -> 13.3, 64 of 6 9.4 -> 10.0, 112 of 7 11.1 -> 11.4, 176 of 9 12.9 -> 13.5, 240 of 33 25.3 -> 26.9
-//   d = 128, 65..96 rows: never (128 of 12 15.3 -> 15.7, 240 of 42 32.1 -> 34.4); 97..128, two waves on every SIMD: where the
-//     stream outgrows the last-level cache (kv_nt), 240 of 83 70.8 -> 65.6, 256 of 128 107 -> 98; 240 of 42, 164 MB, 36.3 -> 35.0
-//     out of that cache and 43.1 -> 44.9 from memory; 192 of 21 21.6 -> 22.1, 16-layer graph, 112 of 9 546 -> 578
-//   d = 64, up to 32 rows: 32 of 6 8.2 -> 8.0, 114 of 22 17.9 -> 15.0; 33..64: 112 of 7 9.4 -> 9.1, 256 of 16 14.5 -> 12.4, 64 of 6
-//     8.4 -> 9.3; 97..128: 72 of 14 16.2 -> 15.8, 200 of 25 21.6 -> 20.1, 76 of 10 12.2 -> 12.3
-bool split_pays_pairs(int head_dim, int rows, int64_t items, int splits, int max_seq_len, bool kv_nt, int num_cus)
-{
-    const int tiles = ((max_seq_len + 31) / 32 + splits) / splits;  // of 1 + ceil(bound / 32), rounded up
-    if (splits < 2 || rows <= 16 || rows > 128 || items > num_cus) return false;
-    if (rows > 96) return head_dim == 64 ? tiles >= 14 : kv_nt && tiles >= 40;
-    if (rows > 64) return false;
-    if (head_dim == 64) return tiles >= 7;
-    return rows <= 32 ? tiles >= 7 && 4 * items <= 3 * num_cus : tiles >= 10 && 16 * items <= 9 * num_cus;
-}
-
 bool decode_by_size(int batch, int64_t items, int per_cu, int num_cus) { return batch > 1 && items > (int64_t)per_cu * num_cus; }
 
 hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv_heads, int max_seq_len,
@@ -928,7 +782,7 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
     const int per_cu = plan->wide ? attn_wide_per_cu(W) : resident_per_cu(head_dim, W);  // resident workgroups
     plan->merge_waves = merge_waves(units * W * (head_dim / 32), num_cus);
     plan->bal_wgs = 0;
-    plan->by_size = plan->paired = 0;
+    plan->by_size = 0;
     // K/V bytes the model streams at most between two passes over the same layer's cache (the other
     // layers' caches come in between), against the 256 MB last-level cache (see the kernel's loads).  Sequences
     // may share pages: a layer holds no more tokens than its pool (the training mask's 1024 blocks read 32 MB
@@ -995,7 +849,6 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
     if (splits < 1) splits = 1;
     plan->chunk_tokens = chunk;
     plan->num_splits = splits;
-    plan->paired = !plan->wide && split_pays_pairs(head_dim, R, units * splits, splits, max_seq_len, plan->kv_nt != 0, num_cus) ? 1 : 0;
     plan->by_size = decode_by_size(batch, units * splits, per_cu, num_cus) ? 1 : 0;
     if (splits > 1) {
         plan->part_o_bytes = (size_t)units * splits * plan->rows_padded * head_dim * sizeof(float);
@@ -1009,11 +862,6 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
 template <int D, int W, int BALANCED>
 static hipError_t launch_split(const AttnArgs &a, const AttnPlan &plan, dim3 grid, hipStream_t stream, AttnLaunchEvents *ev)
 {
-    if constexpr (!BALANCED && W <= 4 && W != 3) {
-        if (plan.paired)
-            return launch_timed(plan.kv_nt ? attn_paired_kernel<D, W, 1> : attn_paired_kernel<D, W, 0>, grid, dim3(64 * (2 * W + 2)),
-                                kPairedStages * (size_t)AttnGeom<D>::STAGE_B, a, stream, ev, 0);
-    }
     auto kern = [&] {
         if constexpr (W == 1) {
             if (a.rows <= 16) {

@@ -17,7 +17,6 @@ struct AttnPlan {
     int num_splits;    // splits per (sequence, KV head)
     int bal_wgs;       // > 0: balanced partition over this many workgroups instead of fixed splits
     int merge_waves;   // waves per workgroup of the merge (merge_waves)
-    int paired;        // 1: two waves to a row block (split_pays_pairs)
     int by_size;       // 1: fixed splits, long items start first (decode_by_size)
     int kv_nt;         // 1: the call streams more K/V than the last-level cache holds: non-temporal tile loads
     size_t lds_bytes;  // dynamic LDS per workgroup
@@ -178,8 +177,6 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
                      int requested_splits, int num_cus, int num_layers, double pool_tokens, AttnPlan *plan);
 // Whether the items of a fixed-split launch start longest first; `items` workgroups of which per_cu are resident on a CU at once.
 bool decode_by_size(int batch, int64_t items, int per_cu, int num_cus);
-// Whether a launch of `items` pieces of units cut into `splits` is faster with two waves to a row block.
-bool split_pays_pairs(int head_dim, int rows, int64_t items, int splits, int max_seq_len, bool kv_nt, int num_cus);
 // Waves per workgroup of a merge that has `wgs` workgroups of four.
 int merge_waves(int64_t wgs, int num_cus);
 hipError_t launch_attn(const AttnArgs &a, const AttnPlan &plan, int head_dim, hipStream_t stream,
