@@ -45,7 +45,7 @@ namespace orthrus {
 // (streaming 2 MB per CU costs the issuing wave about as long as the arithmetic on it costs a compute
 // wave), so when compute waves issue their own loads the two costs add up; with a dedicated loader
 // wave they overlap.  The register budget is 168 (three waves per SIMD), so W + 1 <= 9 waves fit a CU;
-// the balanced form spills a dozen values that live across segments, outside the tile loop.
+// the balanced form at d = 128 spills five vector registers that live across segments, outside the tile loop, the others none.
 //
 // MODE kItemsPrefill turns the same kernel into the AR view's causal prefill attention (Section 3.1): the new
 // tokens' K/V rows are already in the cache, a work item is (sequence, chunk of 32 new tokens, KV head),
@@ -211,338 +211,11 @@ __device__ __forceinline__ void thin_rows(const AttnArgs &a, WorkItems<MODE> it,
     }
 }
 
-template <int D, int W, int NS, int MODE, int NT, int PROBE, int ROWS = 32>
-__device__ __forceinline__ void split_items(const AttnArgs &a)
-{
-    constexpr bool PREFILL = MODE == kItemsPrefill, BALANCED = MODE == kItemsBalanced;
-    // With two compute waves on a SIMD the other wave fills a wave's waits, and what counts is instructions: the weights
-    // are taken before anything is known of the maximum (row_weights).  One wave alone is a chain, in which that puts
-    // the test behind the exponentials.  64 sequences of 1024..3072 tokens, 4 KV heads, 160 / 192 / 224 rows: 99.0 ->
-    // 95.5 / 91.7 -> 87.0 / 94.6 -> 92.4 us; 32 of 2000, 256 rows 59.6 -> 57.3; one of 4096 (36-layer graph), 192 / 224 /
-    // 256 rows 20.8 -> 21.0 / 17.9 -> 18.1 / 22.7 -> 22.7.  Four waves and fewer, batch 1 at 64 rows 13.4 -> 14.1; 256
-    // rows of d = 64 (half the products per exponential) 12.5 -> 13.4.
-    constexpr bool kWeightsFirst = W > 4 && D == 128 && (MODE == kItemsSplit || MODE == kItemsBySize);
-    static_assert(BALANCED && !PROBE ? NT == kNtAsked : NT < kNtAsked, "");
-    static_assert(!PROBE || (W == 1 && !PREFILL), "the stream probe is a decode-mode kernel with one idle compute wave");
-    using Gm = AttnGeom<D>;
-    constexpr int CH = Gm::CH, ROWB = Gm::ROWB, RPI = Gm::RPI, NI = Gm::NI, GS = Gm::GS;
-    constexpr int TILE_B = Gm::TILE_B, STAGE_B = Gm::STAGE_B, KSTEPS = Gm::KSTEPS, DBLK = Gm::DBLK;
-    constexpr int LPT = 2 * NI;  // load instructions per tile (K groups then V groups), all by the loader wave
-    static_assert(NS >= 2 && NS <= 4, "stage count");
-    static_assert((NS - 2) * LPT < 64, "outstanding loads must fit the vmcnt field");
-
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const bool loader = wave == W;
-    const int col = lane & 31, h = lane >> 5;
-    const int K = a.block_k, G = a.group;
-    const int P = 1 << a.page_shift;
-
-    WorkItems<MODE> it;
-    it.start(a);
-    if (!it.open(a)) return;
-
-    const uint32_t smem_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)smem;
-    const int ld_tok = lane / CH;  // this lane's row inside one wave-wide load, and the byte offset of its chunk in that row
-    const uint32_t ld_swz = (uint32_t)(((lane % CH) ^ xm<CH>(ld_tok)) << 4);
-
-    if (loader) {
-        // The loader wave: nothing but the load pipeline, one step per tile around the tile's workgroup barrier.
-        // Before the barrier the loads of tile i are complete; after it every compute wave is done reading the stage
-        // of tile i-1, which is refilled with tile i+NS-1 while tile i is computed.
-        HalfLoads<D> half(a, lane);
-        auto run = [&](auto nt) __attribute__((always_inline)) {
-            for (;;) {
-                const int n_whole = half.usable ? min(it.n_cache, (it.t_end - it.t_begin) >> 5) : 0;
-                const char *kp = half.lowered(a.k_pool + it.head_off), *vp = half.lowered(a.v_pool + it.head_off);
-                uint32_t dst = smem_lds;  // ring slot of the next tile to be issued
-                int p0 = 0, p1 = 0;       // page ids of its two halves (the second repeats the first past the end)
-                // fetched one tile ahead of their use, so that the scalar load's latency is never in front of a tile's loads
-                auto fetch_pages = [&](int t) __attribute__((always_inline)) {
-                    if (t < it.n_cache) {
-                        const int ts = it.t_begin + t * 32;
-                        p0 = it.pt_row[(uint32_t)ts >> a.page_shift];
-                        p1 = it.pt_row[(uint32_t)(ts + 16 < it.t_end ? ts + 16 : ts) >> a.page_shift];
-                    }
-                };
-                auto issue_tile = [&](int t) __attribute__((always_inline)) {
-                    if (t < n_whole) {
-                        const uint32_t ts = (uint32_t)(it.t_begin + t * 32);
-                        const uint64_t o0 = half.offset(p0, ts), o1 = half.offset(p1, ts + 16);
-                        half.issue(nt, kp + o0, dst);
-                        half.issue(nt, kp + o1, dst + half.GPH * GS);
-                        half.issue(nt, vp + o0, dst + TILE_B);
-                        half.issue(nt, vp + o1, dst + TILE_B + half.GPH * GS);
-                    } else if (half.usable && t < it.n_cache) {
-                        // the last, ragged cache tile: rows past the end repeat the last valid row (finite data, masked
-                        // later), so nothing is fetched through an unmapped page and no LDS row is left undefined
-                        const uint64_t o0 = half.offset(p0, 0) >> 1, o1 = half.offset(p1, 0) >> 1;
-                        const uint16_t *const kb[2] = {a.k_pool + it.head_off + o0, a.k_pool + it.head_off + o1};
-                        const uint16_t *const vb[2] = {a.v_pool + it.head_off + o0, a.v_pool + it.head_off + o1};
-                        issue_rows<D>(nt, kb, vb, dst, [&](int u) __attribute__((always_inline)) {
-                            const int tg = min(it.t_begin + t * 32 + u * RPI + ld_tok, it.t_end - 1);
-                            return ((uint32_t)tg & half.page_mask) * half.tok_bytes + ld_swz;
-                        });
-                    } else if (t < it.n_cache) {  // strides past 32-bit arithmetic: an address per lane and load
-                        half.worst = max(half.worst, max((uint32_t)p0, (uint32_t)p1));
-                        const int q0 = (uint32_t)p0 < half.num_pages ? p0 : 0, q1 = (uint32_t)p1 < half.num_pages ? p1 : 0;
-#pragma unroll 1
-                        for (int u = 0; u < NI; ++u) {
-                            const int tg = min(it.t_begin + t * 32 + u * RPI + ld_tok, it.t_end - 1);
-                            const int64_t off = (int64_t)(u * RPI < 16 ? q0 : q1) * a.stride_page + it.head_off +
-                                                (int64_t)(tg & (P - 1)) * a.stride_tok + (ld_swz >> 1);
-                            dma16(nt, a.k_pool + off, dst + u * GS);
-                            dma16(nt, a.v_pool + off, dst + TILE_B + u * GS);
-                        }
-                    } else if constexpr (!PROBE && !PREFILL) {  // (the stream probe has no block inputs: its in-block tile stays empty)
-                        // the in-block tile; rows past the block repeat its last row
-                        const int64_t off0 = (int64_t)it.b * K * a.blk_stride_row + (int64_t)it.g * a.blk_stride_head;
-                        if (a.blk_stride_row < (1ll << 25)) {
-                            const uint16_t *const kb[2] = {a.k_blk + off0, a.k_blk + off0}, *const vb[2] = {a.v_blk + off0, a.v_blk + off0};
-                            const uint32_t row_bytes = (uint32_t)a.blk_stride_row * 2u;
-                            issue_rows<D>(nt, kb, vb, dst, [&](int u) __attribute__((always_inline)) {
-                                return (uint32_t)min(u * RPI + ld_tok, K - 1) * row_bytes + ld_swz;
-                            });
-                        } else {
-#pragma unroll 1
-                            for (int u = 0; u < NI; ++u) {
-                                const int64_t off = off0 + (int64_t)min(u * RPI + ld_tok, K - 1) * a.blk_stride_row + (ld_swz >> 1);
-                                dma16(nt, a.k_blk + off, dst + u * GS);
-                                dma16(nt, a.v_blk + off, dst + TILE_B + u * GS);
-                            }
-                        }
-                    }
-                    dst = dst + STAGE_B == smem_lds + NS * STAGE_B ? smem_lds : dst + STAGE_B;
-                    fetch_pages(t + 1);
-                };
-                int t = 0;  // next tile to be issued
-                fetch_pages(0);
-                for (; t < min(NS - 1, it.n_tiles); ++t) issue_tile(t);
-                for (int i = 0; i < it.n_tiles; ++i) {
-                    const int ahead = min(NS - 2, it.n_tiles - 1 - i);  // tiles issued after tile i so far
-                    if (ahead >= 2) wait_vmcnt<2 * LPT>();
-                    else if (ahead == 1) wait_vmcnt<LPT>();
-                    else wait_vmcnt<0>();
-                    wg_barrier();
-                    if (t < it.n_tiles) issue_tile(t++);
-                }
-                if (!BALANCED || !it.open(a)) break;
-                wg_barrier();  // every compute wave is done with the previous segment's last tile
-            }
-        };
-        if constexpr (NT == kNtAsked) {
-            if (a.kv_nt) run(std::true_type{});
-            else run(std::false_type{});
-        } else {
-            run(std::integral_constant<bool, NT != 0>{});
-        }
-        if (half.worst >= half.num_pages && lane == 0) atomicExch(a.err_word, -4);
-        return;
-    }
-
-    // ---- compute waves
-    if constexpr (PROBE) {
-        for (;;) {
-            for (int i = 0; i < it.n_tiles; ++i) wg_barrier();
-            if (!BALANCED || !it.open(a)) break;
-            wg_barrier();
-        }
-        return;
-    }
-    if constexpr (ROWS == 16) {
-        static_assert(W == 1 && !PREFILL, "");
-        thin_rows<D, NS, MODE, NT>(a, it, smem_lds);
-        return;
-    }
-    // lane-invariant LDS read offsets inside one stage
-    int kb[KSTEPS / 2];  // K operand: row `col`, chunks 4q'..4q'+3 where q' = q ^ (xm >> 2)
-    {
-        const int r = col % RPI;
-#pragma unroll
-        for (int q = 0; q < KSTEPS / 2; ++q)
-            kb[q] = (col / RPI) * GS + r * ROWB + ((q ^ (xm<CH>(r) >> 2)) << 6) + (h << 4);
-    }
-    int vb[DBLK];  // V operand through the transpose read: lane supplies row 4*h + (lane%16)/4 (+8 per step)
-    {
-        const int tok0 = 4 * h + ((lane & 15) >> 2);
-        const int r = tok0 % RPI;
-        const int tr_ch = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);  // chunk inside the 32-wide d block
-#pragma unroll
-        for (int db = 0; db < DBLK; ++db)
-            vb[db] = TILE_B + (tok0 / RPI) * GS + r * ROWB + ((db ^ (xm<CH>(r) >> 2)) << 6) + (tr_ch << 4) +
-                     ((lane & 1) << 3);
-    }
-
-    const float c = a.scale_log2e;
-    for (;;) {  // one pass per work item (balanced mode: per segment)
-        // Queries: B operand of S^T = K.Q^T, lane holds row `col` of this wave's block,
-        // d = 16*kk + 8*h .. +7 (fetched while the loader's first tiles are in flight)
-        Frag qf[KSTEPS];
-        int irow;
-        const int ridx = wave * 32 + col;
-        // the lane's row exists: inside the R rows and, for prefill, inside the chunk's live tokens
-        const bool row_ok = ridx < a.rows && (!PREFILL || ridx / G < it.rows_live);
-        // row of q / out that holds block row (or new token) i of this sequence
-        const int64_t row_base = PREFILL ? (int64_t)it.b * a.max_new + it.row0 : (int64_t)it.b * K;
-        if (row_ok) {
-            const int i = ridx / G, hl = ridx - i * G;
-            irow = i;
-            const uint16_t *qp = a.q + (row_base + i) * a.q_stride_row + ((int64_t)it.g * G + hl) * a.q_stride_head;
-#pragma unroll
-            for (int kk = 0; kk < KSTEPS; ++kk) qf[kk].u = *(const uint4 *)(qp + kk * 16 + h * 8);
-        } else {
-            irow = 31;  // padding rows see every in-block key; their output is never stored
-#pragma unroll
-            for (int kk = 0; kk < KSTEPS; ++kk) qf[kk].u = make_uint4(0, 0, 0, 0);
-        }
-        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the queries are in registers before the loop starts
-
-        f32x16 o[DBLK];
-#pragma unroll
-        for (int db = 0; db < DBLK; ++db)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
-        float m_run = kNegBig, l_run = 0.f;
-
-        // ---- main loop: one barrier per tile
-        int stage = 0;  // ring slot of tile i (= i % NS)
-        for (int i = 0; i < it.n_tiles; ++i) {
-            wg_barrier();
-
-            // LDS addresses of this tile's operands: one add per base, the rest are instruction offsets
-            const uint32_t st_addr = smem_lds + (uint32_t)stage * STAGE_B;
-            stage = stage + 1 == NS ? 0 : stage + 1;
-            uint32_t ka[KSTEPS / 2], va_[DBLK];
-#pragma unroll
-            for (int q = 0; q < KSTEPS / 2; ++q) ka[q] = st_addr + kb[q];
-#pragma unroll
-            for (int db = 0; db < DBLK; ++db) va_[db] = st_addr + vb[db];
-            // lim = number of leading tile tokens this lane's row may see
-            int lim = 32;
-            if (i < it.n_cache) lim = it.t_end - (it.t_begin + i * 32);
-            else lim = a.view == 0 ? K : min(K, irow + 1);  // in-block tile: K rows, causal for the AR view
-            if constexpr (PREFILL) lim = min(lim, it.pos0 + irow + 1 - i * 32);  // causal: tokens up to the row's own
-
-            f32x16 s;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) s[r] = 0.f;
-            Frag kf[KSTEPS];  // all K operand reads are issued before the first product needs one
-#pragma unroll
-            for (int kk = 0; kk < KSTEPS; ++kk) kf[kk].n = *(const lds_u32x4 *)(uintptr_t)(ka[kk >> 1] + ((kk & 1) << 5));
-            __builtin_amdgcn_sched_barrier(0);  // keep the reads ahead of the products (the scheduler would pair them up)
-#pragma unroll
-            for (int kk = 0; kk < KSTEPS; ++kk) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk].v, qf[kk].v, s, 0, 0, 0);
-            // first half of the V operand reads goes out now, so that their latency hides behind the softmax
-            constexpr int VPRE = DBLK / 2;
-            Frag vf[DBLK][2];
-#pragma unroll
-            for (int db = 0; db < VPRE; ++db)
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4)
-                    vf[db][q4 >> 1].h[q4 & 1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                        (lds_s16x4 *)(uintptr_t)(va_[db] + q4 * (8 / RPI) * GS));
-            __builtin_amdgcn_sched_barrier(0);
-            if (lim < 32) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int tok = 8 * (r >> 2) + 4 * h + (r & 3);  // S^T register r of this lane
-                    if (tok >= lim) s[r] = -INFINITY;
-                }
-            }
-            // Online softmax with a lazily updated reference maximum (log2 domain): the reference only
-            // moves when the running maximum has grown by more than kLazy, so exponentials stay below
-            // 2^kLazy and the rescale of the accumulator is skipped for almost every tile.  The result
-            // is unchanged: numerator and denominator always share the same reference.
-            float p[16], sum;
-            float alpha = 1.f;
-            bool moved;
-            if constexpr (kWeightsFirst) {
-                row_weights(s, c, m_run, p, sum);
-                moved = __builtin_expect(may_outgrow(sum), 0) && move_reference(s, c, m_run, p, sum, alpha);
-            } else {
-                float mx = s[0];
-#pragma unroll
-                for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
-                const float m_cand = fmaxf(m_run, max_with_other_half(mx) * c);
-                moved = __any(m_cand - m_run > kLazy);
-                if (moved) {
-                    alpha = __builtin_amdgcn_exp2f(m_run - m_cand);
-                    m_run = m_cand;
-                }
-            }
-            if (moved) {
-                l_run *= alpha;
-#pragma unroll
-                for (int db = 0; db < DBLK; ++db)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
-            }
-            if constexpr (!kWeightsFirst) {
-                sum = 0.f;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c, -m_run));
-                    sum += p[r];
-                }
-            }
-            l_run += sum;
-            Frag p1, p2;
-            p1.u = make_uint4(pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3]), pack_bf16(p[4], p[5]), pack_bf16(p[6], p[7]));
-            p2.u = make_uint4(pack_bf16(p[8], p[9]), pack_bf16(p[10], p[11]), pack_bf16(p[12], p[13]),
-                              pack_bf16(p[14], p[15]));
-            // O^T += V^T P^T.  MFMA k-slot (h, j) of the first product is token 8*(j/4) + 4*h + j%4 (what
-            // registers 0..7 of S^T hold); the second product is 16 tokens further.
-#pragma unroll
-            for (int db = VPRE; db < DBLK; ++db)
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4)
-                    vf[db][q4 >> 1].h[q4 & 1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                        (lds_s16x4 *)(uintptr_t)(va_[db] + q4 * (8 / RPI) * GS));
-#pragma unroll
-            for (int db = 0; db < DBLK; ++db) {
-                o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db][0].v, p1.v, o[db], 0, 0, 0);
-                o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db][1].v, p2.v, o[db], 0, 0, 0);
-            }
-        }
-
-        // ---- write-out: this wave's 32 rows
-        l_run = sum_with_other_half(l_run);
-        if (it.final_out) {
-            if (row_ok) {
-                const int i = irow, hl = ridx - i * G;
-                const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
-                uint16_t *op = a.out + ((row_base + i) * a.num_q_heads + (int64_t)it.g * G + hl) * D;
-                store_row<DBLK>(op, o, inv, h);
-                if (a.lse && h == 0)
-                    a.lse[((int64_t)it.b * a.num_q_heads + (int64_t)it.g * G + hl) * K + i] =
-                        (m_run + __builtin_amdgcn_logf(l_run)) * 0.6931471805599453f;
-            }
-        } else {
-            // partial in register order: [partial][wave][db][r4][lane] float4, then (m, l) per row
-            const size_t slot = it.part_slot * W + wave;
-            f32x4 *po = (f32x4 *)a.part_o + slot * (DBLK * 4 * 64) + lane;
-#pragma unroll
-            for (int db = 0; db < DBLK; ++db)
-#pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    const f32x4 v = {o[db][4 * r4], o[db][4 * r4 + 1], o[db][4 * r4 + 2], o[db][4 * r4 + 3]};
-                    if constexpr (NT != 0 && !BALANCED) __builtin_nontemporal_store(v, &po[(db * 4 + r4) * 64]);
-                    else po[(db * 4 + r4) * 64] = v;
-                }
-            if (h == 0) ((float2 *)a.part_ml)[slot * 32 + col] = make_float2(m_run, l_run);
-        }
-        if (!BALANCED || !it.open(a)) break;
-        wg_barrier();  // matches the loader's barrier between segments
-    }
-}
-
 template <int D, int W, int NS, int MODE, int NT, int PROBE = 0>
 __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(ATTN_FIRST_PARAMS, const AttnArgs rest)
 {
-    split_items<D, W, NS, MODE, NT, PROBE>(with_first(rest, first_lens, first_batch));
+    constexpr int ROWS = 32;
+#include "orthrus_attn_split.inc"
 }
 
 // Fixed splits, the long items first.  A kernel of its own: the search for a workgroup's item in front of a batch-1 call's
@@ -550,14 +223,16 @@ __global__ void __launch_bounds__(64 * (W + 1), 3) attn_split_kernel(ATTN_FIRST_
 template <int D, int W, int NS, int NT>
 __global__ void __launch_bounds__(64 * (W + 1), 3) attn_by_size_kernel(ATTN_FIRST_PARAMS, const AttnArgs rest)
 {
-    split_items<D, W, NS, kItemsBySize, NT, 0>(with_first(rest, first_lens, first_batch));
+    constexpr int MODE = kItemsBySize, PROBE = 0, ROWS = 32;
+#include "orthrus_attn_split.inc"
 }
 
 // At most 16 query rows per KV head (thin_rows).
 template <int D, int NS, int MODE, int NT>
 __global__ void __launch_bounds__(128, 3) attn_thin_kernel(ATTN_FIRST_PARAMS, const AttnArgs rest)
 {
-    split_items<D, 1, NS, MODE, NT, 0, 16>(with_first(rest, first_lens, first_batch));
+    constexpr int W = 1, PROBE = 0, ROWS = 16;
+#include "orthrus_attn_split.inc"
 }
 
 // Merge the per-split partials in split order and write bf16 rows.  One workgroup per (sequence,
