@@ -442,6 +442,13 @@ int merge_waves(int64_t wgs, int num_cus) { return 2 * wgs < num_cus ? 1 : 4; }
 
 bool decode_by_size(int batch, int64_t items, int per_cu, int num_cus) { return batch > 1 && items > (int64_t)per_cu * num_cus; }
 
+int decode_direction_on_host(const int *lens, int batch, bool small_counts)
+{
+    int sample[kOrderSamples];
+    for (int k = 0; k < kOrderSamples; ++k) sample[k] = lens[order_sample(k, batch)];
+    return direction_of(sample, batch, small_counts);
+}
+
 hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv_heads, int max_seq_len,
                      int requested_splits, int num_cus, int num_layers, double pool_tokens, AttnPlan *plan)
 {

@@ -377,33 +377,50 @@ __host__ __device__ __forceinline__ bool ranked_chunk(int r, typename Wave::Int 
 }
 
 // Decode-mode items of different lengths: the long ones start first (decode_by_size).  A batch whose lengths only rise or only
-// fall (the training mask's anchors, a queue kept sorted) shows that in a few samples, which cost a round trip of scalar
-// loads; then the order is the batch's own, from its long end.  Otherwise, up to kRankedLens sequences are ranked; a larger
-// batch starts from the end whose sequence is the longer one.
+// fall (the training mask's anchors, a queue kept sorted) shows that in a few samples, which the scalar loads of the other
+// arguments' round trip bring; then the order is the batch's own, from its long end.  Otherwise, up to kRankedLens sequences
+// are ranked; a larger batch starts from the end whose sequence is the longer one.  The plain order stays where the samples
+// are alike: of one count of whole tiles for the 64-row kernel, within an eighth for the 32- and 16-row ones, where up to there
+// the order gave nothing and its loads cost up to 2 %.
 // Measured (plain -> from the long end / ranked, us per call): mask of one sequence of 4096 tokens, 256 blocks of 16, 237 -> 164 / 178
 // (a ranked item waits for a vector load in front of its first tile); of 4 packed ones of 2048 (1024 items a head, a
 // sawtooth) 622 -> 595 / -; of 3 of 2048, 64 blocks of 32 at 28/4 heads 154 -> 116 / 109; 128 sequences of 300..2500 in any order, 128
-// rows, 180 -> 163 / 142; 100 of 100..2500, 224 rows, 113 -> 109 / 84; 200 of 50..900, 32 rows, 82 -> 78 / 71; 128 of 1000
-// each 113.4 -> 113.8.  A sequence's heads moved on by one from rank to rank, so that no XCD keeps to one head: no gain where
+// rows, 180 -> 163 / 142; 100 of 100..2500, 224 rows, 113 -> 109 / 84; 200 of 50..900, 32 rows, 82 -> 78 / 71.  Above kRankedLens, 400
+// sequences of 100..1500 in any order (three of them), 16 rows 245 -> 233, 239 -> 231, 235 -> 234; 64 rows 273 -> 259, 270 -> 263, 266
+// -> 265; 128 rows 319 -> 290, 308 -> 296, 303 -> 293.
+// Lengths nearly alike (plain -> in order -> as it is): 128 sequences at 64 rows, 1000 each 108.7 -> 109.9 -> 109.2, 1000..1031
+// 108.6 -> 110.7 rising, 110.6 in any order -> 108.9, 1000..1249 in any order 121.7 -> 120.6 -> 120.3; 128 rows, 1000..1031 rising 115.4 ->
+// 111.7 -> 111.2, 1000..1249 in any order 125.8 -> 122.1 -> 121.6; 16 rows, 256 of 1000..1031 in any order 182.9 -> 184.4 -> 181.4.
+// A sequence's heads moved on by one from rank to rank, so that no XCD keeps to one head: no gain where
 // K/V stream from memory, 1 to 5 % lost where the items of a sequence share them (mask of 4 x 2048, 60 blocks 142 -> 151).
 constexpr int kOrderSamples = 6;
+__host__ __device__ __forceinline__ uint32_t order_sample(int k, int batch) { return (uint32_t)(batch - 1) * (uint32_t)k / (kOrderSamples - 1); }
 enum Direction { kDirUnknown, kDirAlike, kDirUp, kDirDown };
+constexpr int kRankedLens = 256;
+
+// What the samples say.  `small_counts`: a tile more or less is an order worth keeping; else a spread of an eighth.
+__host__ __device__ __forceinline__ Direction direction_of(const int (&sample)[kOrderSamples], int batch, bool small_counts)
+{
+    int tiles[kOrderSamples];  // whole ones (bad lengths, which are checked later, only come out of order)
+#pragma unroll
+    for (int k = 0; k < kOrderSamples; ++k) tiles[k] = sample[k] >> 5;
+    int low = tiles[0], high = tiles[0];
+    bool up = true, down = true;
+#pragma unroll
+    for (int k = 1; k < kOrderSamples; ++k) {
+        low = tiles[k] < low ? tiles[k] : low;
+        high = tiles[k] > high ? tiles[k] : high;
+        up = up && tiles[k - 1] <= tiles[k];
+        down = down && tiles[k - 1] >= tiles[k];
+    }
+    if (high == low || (!small_counts && (high - low) * 8 <= high)) return kDirAlike;
+    const int first = tiles[0], last = tiles[kOrderSamples - 1];
+    if (batch > kRankedLens) return first < last ? kDirUp : first > last ? kDirDown : kDirAlike;
+    return up ? kDirUp : down ? kDirDown : kDirUnknown;
+}
 
 // The lengths of a batch of up to kRankedLens sequences, a lane to a sequence (64 sequences a register), and the sequence of a
 // rank by length in whole tiles, longest first, lower index first among equals.
-constexpr int kRankedLens = 256;
-__host__ __device__ __forceinline__ Direction direction_of(const int (&sample)[kOrderSamples], int batch)
-{
-    const int first = sample[0], last = sample[kOrderSamples - 1];
-    bool up = first < last, down = first > last;
-    if (batch > kRankedLens) return up ? kDirUp : down ? kDirDown : kDirAlike;
-#pragma unroll
-    for (int k = 1; k < kOrderSamples; ++k) {
-        up = up && sample[k - 1] <= sample[k];
-        down = down && sample[k - 1] >= sample[k];
-    }
-    return up ? kDirUp : down ? kDirDown : kDirUnknown;
-}
 struct RankedLens {
     static constexpr int REGS = kRankedLens / 64;
     int raw[REGS], tiles[REGS];
@@ -543,35 +560,42 @@ struct WorkItems {
     }
 
     // Fixed splits, the items that are long first (decode_by_size): finds b, g, the split and the length.  The items of a sequence
-    // follow each other, its heads fastest; with all lengths alike, the plain order.
-    __device__ __forceinline__ void find_by_size(const AttnArgs &a, int *split, int *len)
+    // follow each other, its heads fastest; with lengths alike, the plain order.
+    __device__ __forceinline__ void find_by_size(const AttnArgs &a, bool small_counts, int *split, int *len)
     {
-        const unsigned heads = (unsigned)a.num_kv_heads, splits = (unsigned)a.num_splits;
-        const int rank = (int)(blockIdx.x / (heads * splits)), item = (int)(blockIdx.x % (heads * splits)), last = a.batch - 1;
-        // every scalar load in one round trip: samples of the batch, and the lengths that the answer may be
+        // what the batch's address and size alone lead to, in the round trip that the other arguments take: samples of the
+        // batch, and the length that the plain order names
         const const_i32 *lens = (const const_i32 *)a.seq_lens;
+        const int last = a.batch - 1;
         int sample[kOrderSamples];
 #pragma unroll
-        for (int k = 0; k < kOrderSamples; ++k) sample[k] = lens[(uint32_t)last * (uint32_t)k / (kOrderSamples - 1)];
-        const int front = lens[rank], back = lens[last - rank], plain = lens[b];
-        const Direction dir = direction_of(sample, a.batch);
-        bool in_turn = dir != kDirAlike;
-        if (dir == kDirUp || dir == kDirDown) {
-            b = dir == kDirUp ? last - rank : rank;
-            *len = dir == kDirUp ? back : front;
-        } else if (dir == kDirUnknown) {
+        for (int k = 0; k < kOrderSamples; ++k) sample[k] = lens[order_sample(k, a.batch)];
+        *len = lens[b];
+        const Direction dir = direction_of(sample, a.batch, small_counts);
+        const unsigned heads = (unsigned)a.num_kv_heads, splits = (unsigned)a.num_splits;
+        g = (int)(blockIdx.x / ((unsigned)a.batch * splits));
+        *split = (int)(blockIdx.x / (unsigned)a.batch % splits);
+        if (dir != kDirAlike) {
+            const int rank = (int)(blockIdx.x / (heads * splits)), item = (int)(blockIdx.x % (heads * splits));
             RankedLens ranked;
-            in_turn = ranked.load(a);
-            if (in_turn) b = ranked.at_rank(rank, len);
+            bool in_turn = true;
+            if (dir == kDirUnknown) {
+                in_turn = ranked.load(a);
+                if (in_turn) b = ranked.at_rank(rank, len);
+            } else {
+                b = dir == kDirUp ? last - rank : rank;
+                *len = lens[b];
+            }
+            if (in_turn) {
+                g = item % (int)heads;
+                *split = item / (int)heads;
+            }
         }
-        if (!in_turn) *len = plain;
-        g = in_turn ? item % (int)heads : (int)(blockIdx.x / ((unsigned)a.batch * splits));
-        *split = in_turn ? item / (int)heads : (int)(blockIdx.x / (unsigned)a.batch % splits);
         *len = checked_len(a, *len);
     }
 
     // Opens the next work item; false when the workgroup has none (left).
-    __device__ __forceinline__ bool open(const AttnArgs &a)
+    __device__ __forceinline__ bool open(const AttnArgs &a, bool small_counts = false)
     {
         if constexpr (MODE == kItemsBalanced) {
             if (bal_left <= 0) return false;
@@ -601,7 +625,8 @@ struct WorkItems {
             // Workgroup id -> work item.  Consecutive workgroup ids go to different XCDs.
             // Decode: the sequence index is fastest and the KV head slowest.  A head's rows sit at a fixed offset
             // inside every page, so an order that ties XCD k to head k makes each XCD hammer its own subset of the
-            // HBM channels and the XCDs finish far apart.
+            // HBM channels and the XCDs finish far apart.  (By size the heads are fastest all the same: with lengths that differ,
+            // what the order gives is more, and sequences of the 64-row kernel gain 4 % even where they hardly differ.)
             // Prefill: the sequence is fastest, then the head, then the chunk, every sequence's last (the one with the
             // most cache tokens) first.  Ranked prefill: the head is fastest, then the chunk's rank; a chunk's heads
             // are alike in length.
@@ -649,7 +674,7 @@ struct WorkItems {
             } else {
                 int L;
                 if constexpr (MODE == kItemsBySize) {
-                    find_by_size(a, &split, &L);
+                    find_by_size(a, small_counts, &split, &L);
                 } else {
                     split = (int)((blockIdx.x / (unsigned)a.batch) % (unsigned)a.num_splits);
                     g = (int)(blockIdx.x / ((unsigned)a.batch * (unsigned)a.num_splits));

@@ -64,7 +64,7 @@ __global__ void __launch_bounds__(64 * W, 1) attn_wide_kernel(ATTN_FIRST_PARAMS,
 
     WorkItems<MODE> w;
     w.start(a);
-    if (!w.open(a)) return;
+    if (!w.open(a, true)) return;
 
     // ---- tile loads: a tile is four 16-token halves (K, K, V, V) and a wave loads PG of them, both of one operand
     const int ld_tok = lane / CH;  // this lane's row inside one wave-wide load, and the byte offset of its chunk in that row

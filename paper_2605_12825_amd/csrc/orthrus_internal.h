@@ -177,6 +177,8 @@ hipError_t plan_attn(int head_dim, int group, int block_k, int batch, int num_kv
                      int requested_splits, int num_cus, int num_layers, double pool_tokens, AttnPlan *plan);
 // Whether the items of a fixed-split launch start longest first; `items` workgroups of which per_cu are resident on a CU at once.
 bool decode_by_size(int batch, int64_t items, int per_cu, int num_cus);
+// What the kernels make of a batch's lengths: 0 to be ranked, 1 alike, 2 rising, 3 falling.  `small_counts`: the 64-row kernel.
+int decode_direction_on_host(const int *lens, int batch, bool small_counts);
 // Waves per workgroup of a merge that has `wgs` workgroups of four.
 int merge_waves(int64_t wgs, int num_cus);
 hipError_t launch_attn(const AttnArgs &a, const AttnPlan &plan, int head_dim, hipStream_t stream,

@@ -67,3 +67,22 @@ def test_items_that_start_by_size(kind, batch, splits, g, hkv, d, K, per_cu):
 @pytest.mark.parametrize("by_size,batch,items,per_cu", [(False, 1, 4096, 1), (False, 2, 512, 2), (True, 2, 513, 2), (True, 60000, 257, 1)])
 def test_by_size_where_items_wait_for_others(by_size, batch, items, per_cu):
     assert _rule(batch, items, per_cu, 256) == by_size
+
+
+_direction = getattr(ctypes.CDLL(orthrus.library_path()), "_ZN7orthrus24decode_direction_on_hostEPKiib")
+_direction.restype, _direction.argtypes = ctypes.c_int, [ctypes.POINTER(ctypes.c_int), ctypes.c_int, ctypes.c_bool]
+RANKED, ALIKE, RISING, FALLING = range(4)
+
+
+@pytest.mark.parametrize("lens,wide,others", [
+    ([1000] * 128, ALIKE, ALIKE), ([0] * 3, ALIKE, ALIKE), ([7] * 400, ALIKE, ALIKE),
+    (list(range(992, 1023)), ALIKE, ALIKE),                  # a token or two apart, one count of whole tiles
+    (list(range(1000, 1064, 2)), RISING, ALIKE), (list(range(1063, 1000, -2)), FALLING, ALIKE),
+    (list(range(1000, 1240, 2)), RISING, RISING), ([20] * 50 + [40] * 50, RISING, RISING),
+    (list(range(1000, 1200)) * 2, RISING, RISING),           # a repeated rise above what is ranked: its two ends
+    (list(range(1000, 1128)) * 2, RANKED, ALIKE), ([500, 100, 100] * 67, RANKED, RANKED), ([100] + [500] * 299, RISING, RISING),
+    ([-(2 ** 31)] + [5] * 99 + [2 ** 31 - 1], RISING, RISING), ([2 ** 31 - 1, -(2 ** 31)] * 150, FALLING, FALLING),
+])
+def test_lengths_that_are_nearly_alike_keep_the_plain_order(lens, wide, others):
+    got = [_direction((ctypes.c_int * len(lens))(*lens), len(lens), small) for small in (True, False)]
+    assert got == [wide, others]
