@@ -155,9 +155,6 @@ def _ptr(t) -> Optional[int]:
     return t if t is None or isinstance(t, int) else t.data_ptr()
 
 
-# The calls of a decode step name the tensors' addresses in one expression and go through _ptr only when that fails, because
-# one of them is an address or None: a Python call for each of a dozen arguments cost the host 0.4 us a call or more (an
-# attention call's binding 3.2 -> 2.8 us; a toy step of three calls, bound by the host, 24.7 -> 23.9).
 def _nbytes(t) -> int:
     return 0 if t is None else t.nbytes
 
@@ -258,15 +255,9 @@ def orthrus_kv_stream_probe(ctx, p: orthrus_params, k_pool, v_pool, page_table, 
 
 def orthrus_dual_view_attn(ctx, p: orthrus_params, view: int, q, k_blk, v_blk, k_pool, v_pool, page_table,
                            seq_lens, out, lse=None, workspace=None, stream=None, check: bool = True) -> int:
-    try:
-        st = _lib.orthrus_dual_view_attn(ctx, ctypes.byref(p), int(view), q.data_ptr(), k_blk.data_ptr(), v_blk.data_ptr(),
-                                         k_pool.data_ptr(), v_pool.data_ptr(), page_table.data_ptr(),
-                                         seq_lens.data_ptr(), out.data_ptr(), _ptr(lse), _ptr(workspace),
-                                         _nbytes(workspace), _stream_handle(stream))
-    except AttributeError:
-        st = _lib.orthrus_dual_view_attn(ctx, ctypes.byref(p), int(view), _ptr(q), _ptr(k_blk), _ptr(v_blk),
-                                         _ptr(k_pool), _ptr(v_pool), _ptr(page_table), _ptr(seq_lens), _ptr(out),
-                                         _ptr(lse), _ptr(workspace), _nbytes(workspace), _stream_handle(stream))
+    st = _lib.orthrus_dual_view_attn(ctx, ctypes.byref(p), int(view), _ptr(q), _ptr(k_blk), _ptr(v_blk),
+                                     _ptr(k_pool), _ptr(v_pool), _ptr(page_table), _ptr(seq_lens), _ptr(out),
+                                     _ptr(lse), _ptr(workspace), _nbytes(workspace), _stream_handle(stream))
     if check and st != ORTHRUS_OK:
         raise OrthrusError(st, "orthrus_dual_view_attn")
     return st
@@ -275,19 +266,11 @@ def orthrus_dual_view_attn(ctx, p: orthrus_params, view: int, q, k_blk, v_blk, k
 def orthrus_consensus_commit(ctx, p: orthrus_params, ar_logits, draft_tokens, k_blk_ar, v_blk_ar, k_pool, v_pool,
                              page_table, seq_lens, accept_len, num_committed, out_tokens, next_anchor,
                              workspace=None, stream=None, check: bool = True) -> int:
-    try:
-        st = _lib.orthrus_consensus_commit(ctx, ctypes.byref(p), ar_logits.data_ptr(), draft_tokens.data_ptr(),
-                                           k_blk_ar.data_ptr(), v_blk_ar.data_ptr(), k_pool.data_ptr(),
-                                           v_pool.data_ptr(), page_table.data_ptr(), seq_lens.data_ptr(),
-                                           accept_len.data_ptr(), num_committed.data_ptr(), out_tokens.data_ptr(),
-                                           next_anchor.data_ptr(), _ptr(workspace), _nbytes(workspace),
-                                           _stream_handle(stream))
-    except AttributeError:
-        st = _lib.orthrus_consensus_commit(ctx, ctypes.byref(p), _ptr(ar_logits), _ptr(draft_tokens), _ptr(k_blk_ar),
-                                           _ptr(v_blk_ar), _ptr(k_pool), _ptr(v_pool), _ptr(page_table),
-                                           _ptr(seq_lens), _ptr(accept_len), _ptr(num_committed), _ptr(out_tokens),
-                                           _ptr(next_anchor), _ptr(workspace), _nbytes(workspace),
-                                           _stream_handle(stream))
+    st = _lib.orthrus_consensus_commit(ctx, ctypes.byref(p), _ptr(ar_logits), _ptr(draft_tokens), _ptr(k_blk_ar),
+                                       _ptr(v_blk_ar), _ptr(k_pool), _ptr(v_pool), _ptr(page_table),
+                                       _ptr(seq_lens), _ptr(accept_len), _ptr(num_committed), _ptr(out_tokens),
+                                       _ptr(next_anchor), _ptr(workspace), _nbytes(workspace),
+                                       _stream_handle(stream))
     if check and st != ORTHRUS_OK:
         raise OrthrusError(st, "orthrus_consensus_commit")
     return st
@@ -321,19 +304,11 @@ def orthrus_sampling_consensus_commit(ctx, p: orthrus_params, temperature: float
                                       draft_tokens, accept_u, gumbel, k_blk_ar, v_blk_ar, k_pool, v_pool,
                                       page_table, seq_lens, accept_len, num_committed, out_tokens, next_anchor,
                                       workspace=None, stream=None, check: bool = True) -> int:
-    try:
-        st = _lib.orthrus_sampling_consensus_commit(
-            ctx, ctypes.byref(p), float(temperature), ar_logits.data_ptr(), diff_logits.data_ptr(),
-            draft_tokens.data_ptr(), accept_u.data_ptr(), gumbel.data_ptr(), k_blk_ar.data_ptr(), v_blk_ar.data_ptr(),
-            k_pool.data_ptr(), v_pool.data_ptr(), page_table.data_ptr(), seq_lens.data_ptr(), accept_len.data_ptr(),
-            num_committed.data_ptr(), out_tokens.data_ptr(), next_anchor.data_ptr(), _ptr(workspace),
-            _nbytes(workspace), _stream_handle(stream))
-    except AttributeError:
-        st = _lib.orthrus_sampling_consensus_commit(
-            ctx, ctypes.byref(p), float(temperature), _ptr(ar_logits), _ptr(diff_logits), _ptr(draft_tokens),
-            _ptr(accept_u), _ptr(gumbel), _ptr(k_blk_ar), _ptr(v_blk_ar), _ptr(k_pool), _ptr(v_pool),
-            _ptr(page_table), _ptr(seq_lens), _ptr(accept_len), _ptr(num_committed), _ptr(out_tokens),
-            _ptr(next_anchor), _ptr(workspace), _nbytes(workspace), _stream_handle(stream))
+    st = _lib.orthrus_sampling_consensus_commit(
+        ctx, ctypes.byref(p), float(temperature), _ptr(ar_logits), _ptr(diff_logits), _ptr(draft_tokens),
+        _ptr(accept_u), _ptr(gumbel), _ptr(k_blk_ar), _ptr(v_blk_ar), _ptr(k_pool), _ptr(v_pool), _ptr(page_table),
+        _ptr(seq_lens), _ptr(accept_len), _ptr(num_committed), _ptr(out_tokens), _ptr(next_anchor),
+        _ptr(workspace), _nbytes(workspace), _stream_handle(stream))
     if check and st != ORTHRUS_OK:
         raise OrthrusError(st, "orthrus_sampling_consensus_commit")
     return st

@@ -194,3 +194,33 @@ def test_compute_entry_points_reject_null_context_before_any_launch():
     code = ctypes.c_int32(0)
     assert lib.orthrus_last_device_error(None, None, ctypes.byref(code)) == B.ORTHRUS_EINVAL
     assert lib.orthrus_destroy(None) == B.ORTHRUS_EINVAL
+
+
+class _Device:
+    """Stands for a tensor: counts how often its address is asked for."""
+    nbytes = 64
+
+    def __init__(self):
+        self.asked = 0
+
+    def data_ptr(self):
+        self.asked += 1
+        return 4096
+
+
+@pytest.mark.parametrize("call,operands,before", [
+    (orthrus.orthrus_dual_view_attn, 8, (0,)), (orthrus.orthrus_consensus_commit, 12, ()),
+    (orthrus.orthrus_sampling_consensus_commit, 15, (1.0,)),
+])
+@pytest.mark.parametrize("plain", [4096, None])
+def test_a_call_takes_each_operand_once_whatever_mix_of_tensors_and_addresses(call, operands, before, plain):
+    for at in range(operands):
+        args = [_Device() for _ in range(operands)]
+        args[at] = plain
+        ws = _Device()
+        assert call(None, _good(), *before, *args, workspace=ws, stream=0, check=False) == B.ORTHRUS_EINVAL   # no context
+        assert [x.asked for x in args if x is not plain] == [1] * (operands - 1) and ws.asked == 1
+    args, ws = [_Device() for _ in range(operands)], object()   # an operand that is neither: its error, raised once
+    with pytest.raises(AttributeError):
+        call(None, _good(), *before, *args, workspace=ws, stream=0, check=False)
+    assert [x.asked for x in args] == [1] * operands
