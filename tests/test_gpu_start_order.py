@@ -1,5 +1,6 @@
 """The order in which the items of a fixed-split decode launch start: batches whose items do not all fit the chip at once,
-with lengths that rise, fall, repeat a rise, come in any order or are alike, against the oracle."""
+with lengths that rise, fall, repeat a rise, come in any order or are alike, against the oracle (most of them at few rows, so in
+the 16-row form); every kernel and number of row blocks in two of these orders; and the rules on the CPU."""
 import ctypes
 
 import numpy as np
@@ -13,6 +14,10 @@ from test_gpu_parity import AR, DIFF, GpuCase, _check_attn, _oracle_attn
 
 _rule = getattr(ctypes.CDLL(orthrus.library_path()), "_ZN7orthrus14decode_by_sizeEilii")
 _rule.restype, _rule.argtypes = ctypes.c_bool, [ctypes.c_int, ctypes.c_int64, ctypes.c_int, ctypes.c_int]
+
+_direction = getattr(ctypes.CDLL(orthrus.library_path()), "_ZN7orthrus24decode_direction_on_hostEPKiib")
+_direction.restype, _direction.argtypes = ctypes.c_int, [ctypes.POINTER(ctypes.c_int), ctypes.c_int, ctypes.c_bool]
+RANKED, ALIKE, RISING, FALLING = range(4)
 
 
 def _lens(kind, n, hi, seed):
@@ -64,14 +69,61 @@ def test_items_that_start_by_size(kind, batch, splits, g, hkv, d, K, per_cu):
     case.step.close()
 
 
+def _check(case, view, w, blk, cache, lens):
+    got, lse = case.attn(view, blk)
+    want, want_lse = _oracle_attn(view, w, blk, cache, want_lse=True, seq_lens=lens)
+    _check_attn(got, want)
+    np.testing.assert_allclose(lse, want_lse, rtol=0, atol=2e-3)
+    return got, lse
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layers", [1, 1000])   # 1000 layers of the pool: the non-temporal form
+@pytest.mark.parametrize("kind", ["any", "rising"])
+@pytest.mark.parametrize("g,K,d,splits,batch,per_cu,bound", [
+    (2, 4, 64, 1, 200, 6, 130), (1, 16, 128, 2, 50, 3, 130),                                     # up to 16 rows
+    (2, 10, 128, 2, 50, 3, 130), (1, 17, 64, 1, 200, 6, 130), (4, 16, 128, 1, 105, 3, 130),      # one to eight row blocks
+    (5, 16, 128, 2, 50, 3, 130), (3, 25, 64, 1, 110, 3, 130), (4, 32, 128, 2, 34, 2, 130), (8, 17, 128, 2, 34, 2, 130),
+    (6, 31, 128, 2, 18, 1, 130), (7, 32, 128, 2, 18, 1, 130), (7, 29, 64, 1, 34, 1, 130), (8, 32, 128, 2, 18, 1, 130),
+    (4, 32, 128, 1, 112, 2, 130), (8, 16, 64, 1, 96, 2, 4096), (8, 32, 128, 1, 40, 1, 4096),      # the 64-row kernel
+])
+def test_every_kernel_that_starts_its_items_by_size(g, K, d, splits, batch, per_cu, bound, kind, layers):
+    """16-row, 32-row and 64-row forms, with lengths in order, in any order, and outside the bound where the samples look."""
+    hkv, hi, rows = 8, 130, g * K
+    assert _rule(batch, batch * hkv * splits, per_cu, 256)
+    assert (splits == 1 and decode_is_wide(d, rows, bound, batch * hkv)) == ((g, K, batch) in ((4, 32, 112), (8, 16, 96), (8, 32, 40)))
+    w = Workload(name="by", seed=9600 + rows + d, batch=batch, num_q_heads=g * hkv, num_kv_heads=hkv, head_dim=d, block_k=K,
+                 context=hi, page_size=16, paging="scattered")
+    lens = _lens(kind, batch, hi, 9700 + batch)
+    assert _direction((ctypes.c_int * batch)(*lens), batch, False) == (RISING if kind == "rising" else RANKED)
+    cache, blk = make_cache(w, seq_lens=lens), make_block(w, 9800 + K)
+    table = np.zeros((batch, max(-(-bound // 16), cache["page_table"].shape[1])), np.int32)
+    table[:, :cache["page_table"].shape[1]] = cache["page_table"]
+    roomy = dict(cache, page_table=table)
+    case = GpuCase(w, roomy, num_splits=splits, num_layers=layers, max_seq_len=bound)
+    assert case.step.num_splits == splits
+    good = _check(case, AR, w, blk, cache, lens)
+    assert case.step.device_error() == 0
+    case.step.close()
+    # outside the bound on either side, where a sample is taken (or near it): read as 0, and as the bound
+    bad = lens.copy()
+    bad[[0, batch // 2]] = (-(2 ** 31), -1)
+    many = bound == hi
+    if many:
+        full = int(np.flatnonzero(lens == hi)[-1])
+        bad[full] = 2 ** 31 - 1
+    case = GpuCase(w, dict(roomy, seq_lens=bad), num_splits=splits, num_layers=layers, max_seq_len=bound)
+    got = _check(case, AR, w, blk, cache, np.clip(bad, 0, hi))
+    assert case.step.device_error() == -4
+    same = bad == lens
+    np.testing.assert_array_equal(got[0][same], good[0][same])
+    np.testing.assert_array_equal(got[1][same], good[1][same])
+    case.step.close()
+
+
 @pytest.mark.parametrize("by_size,batch,items,per_cu", [(False, 1, 4096, 1), (False, 2, 512, 2), (True, 2, 513, 2), (True, 60000, 257, 1)])
 def test_by_size_where_items_wait_for_others(by_size, batch, items, per_cu):
     assert _rule(batch, items, per_cu, 256) == by_size
-
-
-_direction = getattr(ctypes.CDLL(orthrus.library_path()), "_ZN7orthrus24decode_direction_on_hostEPKiib")
-_direction.restype, _direction.argtypes = ctypes.c_int, [ctypes.POINTER(ctypes.c_int), ctypes.c_int, ctypes.c_bool]
-RANKED, ALIKE, RISING, FALLING = range(4)
 
 
 @pytest.mark.parametrize("lens,wide,others", [
