@@ -15,8 +15,8 @@ LIB = os.path.join(_HERE, "liborthrus.so")
 LIB_HOST_UBSAN = os.path.join(_HERE, "liborthrus_hostubsan.so")
 HOST_UBSAN_FLAGS = ["-Xarch_host", "-fsanitize=undefined", "-Xarch_host", "-fsanitize-trap=undefined",
                     "-Xarch_host", "-fno-omit-frame-pointer"]
-SOURCES = ["orthrus_api.hip", "orthrus_attn.hip", "orthrus_attn_wide.hip", "orthrus_consensus.hip", "orthrus_sampling.hip",
-           "orthrus_prefill.hip"]
+SOURCES = ["orthrus_api.hip", "orthrus_attn.hip", "orthrus_attn_forms.hip", "orthrus_attn_wide.hip", "orthrus_consensus.hip",
+           "orthrus_sampling.hip", "orthrus_prefill.hip"]
 
 HIPCC_FLAGS = [
     "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",

@@ -479,6 +479,14 @@ struct RankedLens {
     }
 };
 
+// The NT argument of the 32-row and 16-row kernels' balanced form, which asks the call (attn_split_kernel).
+constexpr int kNtAsked = 2;
+
+#ifndef ORTHRUS_ATTN_STAGES
+#define ORTHRUS_ATTN_STAGES 3
+#endif
+constexpr int kStages = ORTHRUS_ATTN_STAGES;  // LDS ring depth of these kernels (2..4)
+
 template <int MODE>
 struct WorkItems {
     int b, g;
@@ -725,5 +733,9 @@ inline hipError_t launch_timed(Kern kern, dim3 grid, dim3 block, size_t lds, con
     }
     return hipGetLastError();
 }
+
+// The compute wave of a call of at most 16 rows (orthrus_attn_forms.hip; named by the body that the kernels share).
+template <int D, int NS, int MODE, int NT>
+__device__ void thin_rows(const AttnArgs &a, WorkItems<MODE> it, uint32_t smem_lds);
 
 }  // namespace orthrus

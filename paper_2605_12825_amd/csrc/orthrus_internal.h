@@ -194,6 +194,8 @@ bool prefill_ranked(int batch, int64_t items, int per_cu, int num_cus);
 // The order itself on the host: ranked_chunk with the end levels and chunk counts of `batch` sequences (at most 16).
 bool ranked_chunk_on_host(int rank, int batch, const int *end_levels, const int *chunks, int *seq, int *chunk);
 hipError_t launch_attn_wide(const AttnArgs &a, const AttnPlan &plan, int head_dim, dim3 grid, hipStream_t stream, AttnLaunchEvents *events);
+hipError_t launch_attn_thin(const AttnArgs &a, const AttnPlan &plan, int head_dim, dim3 grid, hipStream_t stream, AttnLaunchEvents *events);
+hipError_t launch_attn_by_size(const AttnArgs &a, const AttnPlan &plan, int head_dim, dim3 grid, hipStream_t stream, AttnLaunchEvents *events);
 hipError_t launch_prefill_attn(const AttnArgs &a, int head_dim, int num_cus, hipStream_t stream);
 hipError_t launch_prefill_split(const AttnArgs &a, int head_dim, int num_cus, hipStream_t stream);
 hipError_t launch_consensus(ConsensusArgs a, hipStream_t stream);

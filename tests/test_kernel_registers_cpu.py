@@ -1,11 +1,11 @@
-"""What the compiler put into scratch memory, read from the metadata of the library's own gfx950 code."""
+"""What the compiler put into scratch memory, read from the metadata of the library's own gfx950 code, and which kernels lie together."""
 import os
 import re
 import subprocess
 
 import paper_2605_12825_amd as orthrus
 
-from built_code import listings, needs_tool, tool
+from built_code import functions, listings, needs_tool, tool
 
 BALANCED = 2   # the MODE argument of attn_split_kernel<D, W, NS, MODE, NT, PROBE>
 
@@ -36,3 +36,11 @@ def test_only_the_balanced_kernel_spills(tmp_path):
             assert registers <= 5 and scratch <= 24, name
         else:
             assert registers == 0 and scratch == 0, name
+
+
+@needs_tool
+def test_the_forms_of_the_attention_kernel_lie_apart_from_its_split_and_merge(tmp_path):
+    """A batch-1 step runs these two and the consensus; other kernels between them cost it time."""
+    for listing in listings(orthrus.library_path(), str(tmp_path)):
+        kinds = {hit.group(1) for name, _ in functions(listing) for hit in [re.search(r"attn_(split|combine|by_size|thin|wide)_kernel", name)] if hit}
+        assert not ({"split", "combine"} & kinds and {"by_size", "thin", "wide"} & kinds), kinds
