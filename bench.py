@@ -618,7 +618,8 @@ def main():
         tf = kv_bytes_post * R / (call.mean() * 1e-6) / 1e12     # R flop per K/V byte: 4 R d flop per 4 d bytes
         roofline = {"bound": "hbm", "achieved": r_call["achieved"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": r_call["frac"],
-                    "kernel": "one orthrus_dual_view_attn call = attn_split_kernel" +
+                    "kernel": "one orthrus_dual_view_attn call = " +
+                              ("attn_thin_kernel" if R <= 16 else "attn_split_kernel, or the by-size or 64-row form its plan takes") +
                               (" + attn_combine_kernel" if cb.max() > 0 else "") +
                               " (the call, not the split kernel alone, is what the fraction is of)",
                     "launches": int(len(samples)),

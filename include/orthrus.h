@@ -368,7 +368,9 @@ orthrus_status orthrus_attn_timing_samples(orthrus_ctx *ctx, double *split_us, d
  * own K/V tile is not read either).  Its duration is the time this library's access pattern needs for the
  * call's K/V bytes on the machine at hand: a measured ceiling to hold the attention kernels against, next to
  * the published peak.  (Calls with enough rows and units to be bound by arithmetic run another kernel, in
- * which every wave loads its share into a deeper ring; the probe stays the loader-wave form for them too.)  Asynchronous on `stream`, allocates nothing.  While per-kernel timing is
+ * which every wave loads its share into a deeper ring; the probe stays the loader-wave form for them too.
+ * Where a call starts its long items first, the probe keeps the batch's order.)
+ * Asynchronous on `stream`, allocates nothing.  While per-kernel timing is
  * enabled the launch is recorded like an attention call without a combine kernel.
  *   k_pool, v_pool, page_table, seq_lens [dev] as in orthrus_dual_view_attn (read only)
  * Page ids outside [0, num_pages) are read as page 0 and lengths are clamped to [0, max_seq_len], with

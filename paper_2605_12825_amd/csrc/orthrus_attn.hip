@@ -453,7 +453,7 @@ static hipError_t launch_attn_d(const AttnArgs &a, const AttnPlan &plan, hipStre
 }
 
 // The stream probe: the same grid, partition and loader as the attention call planned by `plan`, with one
-// idle compute wave per workgroup.
+// idle compute wave per workgroup and the items in the plain order.
 template <int D>
 static hipError_t launch_probe_d(const AttnArgs &a, const AttnPlan &plan, hipStream_t stream, hipEvent_t start,
                                  hipEvent_t stop)

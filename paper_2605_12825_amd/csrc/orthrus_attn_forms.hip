@@ -11,13 +11,14 @@ namespace orthrus {
 // The compute wave of a call with at most 16 query rows per KV head (a short block, few query heads a KV head, one token at a
 // time): v_mfma_f32_16x16x32_bf16 instead of a 32-row block that is half padding.  Same problem, tile layout, masks and
 // softmax order; a lane owns row lane % 16, and the four lanes of a row hold a quarter of a tile's scores each.
-// What it saves is a wave's chain (8 exponentials a tile for 16, products of 16 cycles for 32: 955 cycles a tile where a
-// 32-row block takes 1200), power, and half of every partial: written in the same register order, rows 16..31 of a block left
-// out.  32-row block -> this form, us per call (32/8 heads, 4 rows a head, unless said otherwise): one sequence of 4096 / 12000 /
-// 40000 tokens 10.3 -> 9.3 / 14.9 -> 13.8 / 29.9 -> 29.5, 24-layer graph of 4000 tokens 524 -> 488; 64 of 100 tokens 6.8 -> 6.0;
-// balanced, 17 of 797..12753 92 -> 82; 4 x 40000 100.4 -> 99.5; d = 64, 4 of 12000, 16 rows 12.4 -> 11.3; masks of 2 x 2000, 256
-// blocks of 8 (16/8 heads) 137 -> 92, half of it by their order.  In blocks of 16 for more rows (two waves for 32 rows, four
-// for 64) it reads the tiles twice: 10.3 -> 10.0 and 12.0 -> 12.3 at 4096 tokens, a 12-layer graph at batch 2 377 -> 385.
+// What it saves is a wave's chain (8 exponentials a tile for 16, products of 16 cycles for 32: a workgroup with a CU to itself
+// takes 0.36 us a tile where a 32-row block takes 0.45), power, and half of every partial: written in the same register order,
+// rows 16..31 of a block left out.  32-row block -> this form, us per call (32/8 heads, K = 4, unless said otherwise): one
+// sequence of 4096 / 12000 / 40000 tokens 10.5 -> 9.4 / 15.2 -> 14.0 / 28.9 -> 28.5, 36-layer graph of 4096 tokens 835 -> 778
+// (the kernel alone 7.85 -> 6.92); 64 of 100 tokens 6.8 -> 6.1; balanced, 17 of 797..12753 91.8 -> 82.0, 64 of 300..3000 92.3 ->
+// 82.2; 4 x 40000 103.8 -> 103.0; d = 64, 4 of 12000, 16 rows 12.5 -> 11.4; masks of 2 x 2000, 256 blocks of 8 (16/8 heads) 145 ->
+// 102, half of it by their order.  In blocks of 16 for more rows (two waves for 32 rows, four for 64) it reads the tiles
+// twice: 10.3 -> 10.0 and 12.0 -> 12.3 at 4096 tokens, a 12-layer graph at batch 2 377 -> 385.
 template <int D, int NS, int MODE, int NT>
 __device__ __forceinline__ void thin_rows(const AttnArgs &a, WorkItems<MODE> it, uint32_t smem_lds)
 {
