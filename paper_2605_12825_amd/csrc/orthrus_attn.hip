@@ -30,7 +30,8 @@
 //            attn_combine_kernel merges in a fixed split order (deterministic).
 //   other forms of the same kernel: the balanced partition of a ragged batch's tiles over the
 //            resident workgroups (MODE kItemsBalanced) and the AR view's causal prefill (kItemsPrefill);
-//            both are described at the kernel.
+//            both are described at the kernel.  Calls of at most 16 rows, and launches whose long items
+//            start first, are in orthrus_attn_forms.hip.
 //   caches = K/V tiles are read once per call.  When the model streams more K/V between two passes
 //            over the same cache than the last-level cache holds, the tile loads carry the
 //            non-temporal hint, and with fixed splits the fp32 partials leave with non-temporal stores.
